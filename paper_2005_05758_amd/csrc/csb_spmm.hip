@@ -487,19 +487,29 @@ __global__ __launch_bounds__(NW * 64) void spmm_bf16_kernel(const DevMat m, cons
 // parts a block does not have repeat a valid address and are not multiplied), so the loads of
 // the NEXT pass are in flight while this pass multiplies and the compiler's counted waits hold.
 // Same records, same value layout, same merge of the wavefronts' tiles as the general kernel.
-template <int NH>
+//
+// NQ: how many times 64 right-hand sides a workgroup takes.  What a pass costs besides its
+// products -- opening the block, the map, the column list, the kernel values -- is the same for 64
+// and for 128 right-hand sides, and so are a workgroup's records, its barriers and its place in
+// the launch, so the wide form (NQ = 2; 8 wavefronts, whose registers hold the 32 x 128 results)
+// does half of all that.  The wavefronts' tiles are merged 64 columns at a time, so the LDS does
+// not grow.
+// Measured on the 8192 x 8192 matrix at 12x (32 x 32 blocks), 64 -> 128 right-hand sides per
+// workgroup: float32, batch 128, 71.2 -> 63.4 us (22.7 TFLOP/s; there the chip is filled by
+// one turn of 256 workgroups instead of two of 512); bfloat16, batch 512, 169.7 -> 121.1 us.
+template <int NH, int NQ>
 struct RegOps {
     float av[NH][4];
-    float4 bv[4];
+    float4 bv[4][NQ];
     uint32_t parts;              // bit h: the block has rows in part h (uniform)
 };
 // ... with 16-bit right-hand sides (X16): a pass is ONE 16-column MFMA step per part and tile; a
 // lane's four columns of its tile row are two words of the value stream, its four right-hand
 // sides of a column eight bytes of X.
-template <int NH>
+template <int NH, int NQ>
 struct RegOps16 {
     uint32_t aw[NH][2];
-    uint2 xv[4];
+    uint2 xv[4][NQ];
     uint32_t parts;
 };
 struct RegPass {
@@ -509,18 +519,18 @@ struct RegPass {
     bool valid;
 };
 
-template <bool TWO, int NW, int NH, int VF, bool X16 = false>
+template <bool TWO, int NW, int NH, int VF, int NQ, bool X16 = false>
 __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, float *__restrict__ Y, const int64_t ldy,
                                               const uint32_t batch, const uint32_t block_x, const uint32_t block_y) {
     extern __shared__ float4 smem4[];
-    constexpr uint32_t NB = 64, NTHR = NW * 64;
+    constexpr uint32_t NB = 64, NTHR = NW * 64;                    // right-hand sides per merge
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = uni_(tid >> 6);
-    const uint32_t bt0 = block_y * NB;
+    const uint32_t bt0 = block_y * (NB * NQ);
     const uint32_t br = m.br;                                      // == 16 NH
     if (block_x >= m.n_nz_tiles) {                 // a row tile without work: zeros
         const uint32_t tile = m.zero_tiles[block_x - m.n_nz_tiles];
-        for (uint32_t e = tid; e < br * NB; e += NTHR) {
-            const uint32_t row = tile * br + e / NB, n = bt0 + e % NB;
+        for (uint32_t e = tid; e < br * NB * NQ; e += NTHR) {
+            const uint32_t row = tile * br + e / (NB * NQ), n = bt0 + e % (NB * NQ);
             if (row < m.rows_out && n < batch) Y[(size_t)row * ldy + n] = 0.0f;
         }
         return;
@@ -531,15 +541,20 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
     uint8_t *inv = (uint8_t *)(acc + (size_t)NW * br * NB) + wave * 64u;   // tile row -> kernel row of the current block, 0xff: none
     const uint32_t rank = block_x, tile = m.nz_tiles[rank];
     const uint32_t mrow = lane & 15u, kq = lane >> 4;              // A: tile row in its part, column-in-4; B: right-hand sides 4 mrow .. + 3, row-in-4
-    const uint32_t ncol = bt0 + 4u * mrow;
-    const uint32_t nbyte = (ncol < batch ? ncol : 0u) * (X16 ? 2u : 4u);   // (batch is a multiple of 4: the four are in or out together)
-    const uint8_t *const x0 = (const uint8_t *)X.p0 + nbyte, *const x1 = (const uint8_t *)X.p1 + nbyte;
+    uint32_t nbyte[NQ];                            // this lane's right-hand sides: bt0 + 64 q + 4 mrow .. + 3
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const uint32_t ncol = bt0 + 64u * q + 4u * mrow;
+        nbyte[q] = (ncol < batch ? ncol : 0u) * (X16 ? 2u : 4u);   // (batch is a multiple of 4: the four are in or out together)
+    }
     const uint32_t split4 = 4u * X.n0;
-    floatx4 D[NH][4];
+    floatx4 D[NH][NQ][4];
 #pragma unroll
     for (int h = 0; h < NH; ++h)
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) D[h][nt] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) D[h][q][nt] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
 
     for (uint32_t sg = m.tile_seg0[rank]; sg < m.tile_seg0[rank + 1]; ++sg) {
         // ---- stage the segment's records ------------------------------------------------
@@ -605,8 +620,8 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
             q.valid = same || more;
             return q;
         };
-        // 4 NH + 4 loads, always.  (Uses irow4 / parts of the block opened last: p's.)
-        auto issue = [&](const RegPass &p, RegOps<NH> &o) {
+        // 4 NH + 4 NQ loads, always.  (Uses irow4 / parts of the block opened last: p's.)
+        auto issue = [&](const RegPass &p, RegOps<NH, NQ> &o) {
             uint32_t cb[4], ja[4];
             o.parts = parts;
 #pragma unroll
@@ -626,14 +641,17 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
                     }
                 if constexpr (TWO) {
                     const bool first = cb[s4] < split4;
-                    const uint8_t *src = first ? x0 + __umul24(cb[s4], X.sj0) : x1 + __umul24(cb[s4] - split4, X.sj1);
-                    o.bv[s4] = *(const float4 *)src;
+                    const uint8_t *src = first ? (const uint8_t *)X.p0 + __umul24(cb[s4], X.sj0) : (const uint8_t *)X.p1 + __umul24(cb[s4] - split4, X.sj1);
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) o.bv[s4][q] = *(const float4 *)(src + nbyte[q]);
                 } else {
-                    o.bv[s4] = *(const float4 *)((const uint8_t *)X.p0 + (size_t)(__umul24(cb[s4], X.sj0) + nbyte));
+                    const uint32_t joff = __umul24(cb[s4], X.sj0);
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) o.bv[s4][q] = *(const float4 *)((const uint8_t *)X.p0 + (size_t)(joff + nbyte[q]));
                 }
             }
         };
-        auto multiply = [&](const RegPass &p, const RegOps<NH> &o) {
+        auto multiply = [&](const RegPass &p, const RegOps<NH, NQ> &o) {
             const uint32_t nk = min(4u, (p.c - p.kc + 3u) >> 2);      // k-steps the block has in this pass (uniform)
 #pragma unroll
             for (int h = 0; h < NH; ++h) {
@@ -647,16 +665,19 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
                         if constexpr (VF == CSB_VAL_BF16) a = __uint_as_float((kq & 1u) ? w & 0xffff0000u : w << 16);
                         else a = (float)__builtin_bit_cast(_Float16, (uint16_t)((kq & 1u) ? w >> 16 : w & 0xffffu));
                     }
-                    D[h][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, o.bv[s4].x, D[h][0], 0, 0, 0);
-                    D[h][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, o.bv[s4].y, D[h][1], 0, 0, 0);
-                    D[h][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, o.bv[s4].z, D[h][2], 0, 0, 0);
-                    D[h][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, o.bv[s4].w, D[h][3], 0, 0, 0);
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) {
+                        D[h][q][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, o.bv[s4][q].x, D[h][q][0], 0, 0, 0);
+                        D[h][q][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, o.bv[s4][q].y, D[h][q][1], 0, 0, 0);
+                        D[h][q][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, o.bv[s4][q].z, D[h][q][2], 0, 0, 0);
+                        D[h][q][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, o.bv[s4][q].w, D[h][q][3], 0, 0, 0);
+                    }
                 }
             }
         };
         // The same two steps with 16-bit right-hand sides (X.p0: their rows, X.sj0: elements per row):
-        // 2 NH + 4 loads, always, and one 16-column MFMA per part and tile.
-        auto issue16 = [&](const RegPass &p, RegOps16<NH> &o) {
+        // 2 NH + 4 NQ loads, always, and one 16-column MFMA per part and tile.
+        auto issue16 = [&](const RegPass &p, RegOps16<NH, NQ> &o) {
             o.parts = parts;
             const uint32_t j0 = p.kc + 4u * kq;                                  // this lane's four columns
             const uint32_t w0 = j0 < p.c ? (j0 >> 1) * 256u : 0x3fffff00u;       // words of the pairs (j0, j0 + 1), (j0 + 2, j0 + 3);
@@ -671,26 +692,32 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i)      // (a column the block lacks reads its last one: finite, times a zero)
-                o.xv[i] = *(const uint2 *)((const uint8_t *)X.p0 + (size_t)((__umul24(cb[i], X.sj0) >> 1) + nbyte));
-        };
-        auto multiply16 = [&](const RegOps16<NH> &o) {
-            // xv[i] = right-hand sides 0..3 at column i; tile t wants columns 0..3 at right-hand side t
-            const uint2 b0 = make_uint2((o.xv[0].x & 0xffffu) | (o.xv[1].x << 16), (o.xv[2].x & 0xffffu) | (o.xv[3].x << 16));
-            const uint2 b1 = make_uint2((o.xv[0].x >> 16) | (o.xv[1].x & 0xffff0000u), (o.xv[2].x >> 16) | (o.xv[3].x & 0xffff0000u));
-            const uint2 b2 = make_uint2((o.xv[0].y & 0xffffu) | (o.xv[1].y << 16), (o.xv[2].y & 0xffffu) | (o.xv[3].y << 16));
-            const uint2 b3 = make_uint2((o.xv[0].y >> 16) | (o.xv[1].y & 0xffff0000u), (o.xv[2].y >> 16) | (o.xv[3].y & 0xffff0000u));
 #pragma unroll
-            for (int h = 0; h < NH; ++h) {
-                if (!((o.parts >> h) & 1u)) continue;              // (uniform) no row of the block in this part
-                const uint2 a = make_uint2(o.aw[h][0], o.aw[h][1]);
-                D[h][0] = mfma_16bit<VF == CSB_VAL_F16>(a, b0, D[h][0]);
-                D[h][1] = mfma_16bit<VF == CSB_VAL_F16>(a, b1, D[h][1]);
-                D[h][2] = mfma_16bit<VF == CSB_VAL_F16>(a, b2, D[h][2]);
-                D[h][3] = mfma_16bit<VF == CSB_VAL_F16>(a, b3, D[h][3]);
+                for (int q = 0; q < NQ; ++q)
+                    o.xv[i][q] = *(const uint2 *)((const uint8_t *)X.p0 + (size_t)((__umul24(cb[i], X.sj0) >> 1) + nbyte[q]));
+        };
+        auto multiply16 = [&](const RegOps16<NH, NQ> &o) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                // xv[i] = right-hand sides 0..3 at column i; tile t wants columns 0..3 at right-hand side t
+                const uint2 x0 = o.xv[0][q], x1 = o.xv[1][q], x2 = o.xv[2][q], x3 = o.xv[3][q];
+                const uint2 b0 = make_uint2((x0.x & 0xffffu) | (x1.x << 16), (x2.x & 0xffffu) | (x3.x << 16));
+                const uint2 b1 = make_uint2((x0.x >> 16) | (x1.x & 0xffff0000u), (x2.x >> 16) | (x3.x & 0xffff0000u));
+                const uint2 b2 = make_uint2((x0.y & 0xffffu) | (x1.y << 16), (x2.y & 0xffffu) | (x3.y << 16));
+                const uint2 b3 = make_uint2((x0.y >> 16) | (x1.y & 0xffff0000u), (x2.y >> 16) | (x3.y & 0xffff0000u));
+#pragma unroll
+                for (int h = 0; h < NH; ++h) {
+                    if (!((o.parts >> h) & 1u)) continue;          // (uniform) no row of the block in this part
+                    const uint2 a = make_uint2(o.aw[h][0], o.aw[h][1]);
+                    D[h][q][0] = mfma_16bit<VF == CSB_VAL_F16>(a, b0, D[h][q][0]);
+                    D[h][q][1] = mfma_16bit<VF == CSB_VAL_F16>(a, b1, D[h][q][1]);
+                    D[h][q][2] = mfma_16bit<VF == CSB_VAL_F16>(a, b2, D[h][q][2]);
+                    D[h][q][3] = mfma_16bit<VF == CSB_VAL_F16>(a, b3, D[h][q][3]);
+                }
             }
         };
         if constexpr (X16) {
-            RegOps16<NH> oa, ob;
+            RegOps16<NH, NQ> oa, ob;
             RegPass pa, pb;
             open_vb(wave, pa);
             issue16(pa, oa);
@@ -706,7 +733,7 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
             }
             continue;                                              // (the next segment)
         }
-        RegOps<NH> oa, ob;
+        RegOps<NH, NQ> oa, ob;
         RegPass pa, pb;
         open_vb(wave, pa);
         issue(pa, oa);
@@ -721,34 +748,38 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
             if (!pa.valid) break;
         }
     }
-    // the wavefront's tile: lane holds rows 16 h + 4 kq + i, right-hand sides 4 mrow + t (tile t)
+    // the wavefront's tile, 64 columns at a time: lane holds rows 16 h + 4 kq + i, right-hand sides 4 mrow + t (tile t)
 #pragma unroll
-    for (int h = 0; h < NH; ++h)
+    for (int q = 0; q < NQ; ++q) {
+        if (q > 0) __syncthreads();                                // the columns before are summed
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            *(float4 *)(myacc + (16u * h + 4u * kq + i) * NB + 4u * mrow) = make_float4(D[h][0][i], D[h][1][i], D[h][2][i], D[h][3][i]);
-    __syncthreads();
-    for (uint32_t e = tid; e < br * NB; e += NTHR) {
-        float s = 0.0f;
+        for (int h = 0; h < NH; ++h)
 #pragma unroll
-        for (int w = 0; w < NW; ++w) s += acc[(size_t)w * br * NB + e];
-        const uint32_t row = tile * br + e / NB, n = bt0 + e % NB;
-        if (row < m.rows_out && n < batch) Y[(size_t)row * ldy + n] = s;
+            for (int i = 0; i < 4; ++i)
+                *(float4 *)(myacc + (16u * h + 4u * kq + i) * NB + 4u * mrow) = make_float4(D[h][q][0][i], D[h][q][1][i], D[h][q][2][i], D[h][q][3][i]);
+        __syncthreads();
+        for (uint32_t e = tid; e < br * NB; e += NTHR) {
+            float s = 0.0f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) s += acc[(size_t)w * br * NB + e];
+            const uint32_t row = tile * br + e / NB, n = bt0 + 64u * q + e % NB;
+            if (row < m.rows_out && n < batch) Y[(size_t)row * ldy + n] = s;
+        }
     }
 }
 
-template <bool TWO, int NW, int NH, int VF>
+template <bool TWO, int NW, int NH, int VF, int NQ>
 __global__ __launch_bounds__(NW * 64) void spmm_reg_kernel(const DevMat m, const XSrc X, float *__restrict__ Y,
                                                            const int64_t ldy, const uint32_t batch) {
-    spmm_reg_body<TWO, NW, NH, VF>(m, X, Y, ldy, batch, blockIdx.x, blockIdx.y);
+    spmm_reg_body<TWO, NW, NH, VF, NQ>(m, X, Y, ldy, batch, blockIdx.x, blockIdx.y);
 }
 
 // 16-bit kernel values times 16-bit right-hand sides (X.p0: the rows of X, X.sj0: elements per row).
-template <int NW, int NH, int VF>
+template <int NW, int NH, int VF, int NQ>
 __global__ __launch_bounds__(NW * 64) void spmm_reg16_kernel(const DevMat m, const XSrc X, float *__restrict__ Y,
                                                              const int64_t ldy, const uint32_t batch) {
     static_assert(VF == CSB_VAL_F16 || VF == CSB_VAL_BF16, "16-bit formats only");
-    spmm_reg_body<false, NW, NH, VF, true>(m, X, Y, ldy, batch, blockIdx.x, blockIdx.y);
+    spmm_reg_body<false, NW, NH, VF, NQ, true>(m, X, Y, ldy, batch, blockIdx.x, blockIdx.y);
 }
 
 // Several independent products in one launch (blockIdx.z picks the product): the per-step
@@ -766,11 +797,11 @@ __global__ __launch_bounds__(NW * 64) void spmm_multi_kernel(const SpmmJobs J, c
     spmm_body<NT, TWO, NW, WIDE>(J.m[j], J.X[j], J.Y[j], J.ldy[j], batch, blockIdx.x, blockIdx.y);
 }
 
-template <bool TWO, int NW, int NH, int VF>
+template <bool TWO, int NW, int NH, int VF, int NQ>
 __global__ __launch_bounds__(NW * 64) void spmm_reg_multi_kernel(const SpmmJobs J, const uint32_t batch) {
     const uint32_t j = blockIdx.z;
     if (blockIdx.x >= J.m[j].n_nz_tiles + J.m[j].n_zero_tiles) return;      // the grid is as wide as the widest product
-    spmm_reg_body<TWO, NW, NH, VF>(J.m[j], J.X[j], J.Y[j], J.ldy[j], batch, blockIdx.x, blockIdx.y);
+    spmm_reg_body<TWO, NW, NH, VF, NQ>(J.m[j], J.X[j], J.Y[j], J.ldy[j], batch, blockIdx.x, blockIdx.y);
 }
 
 // Launch shape of one product: batch columns per workgroup (16 nt), wavefronts per workgroup.
@@ -780,10 +811,16 @@ struct SpmmShape {
     int reg_parts;          // wide form, row tiles of 16 or 32 rows: the kernel that keeps the results in
                             // registers, with this many 16-row parts (else 0; four parts do not fit the
                             // registers of a 16-wavefront workgroup)
+    int nq;                 // ... and this many times 64 right-hand sides per workgroup
     int vf;                 // storage format of the kernel values
     size_t lds;
     unsigned tiles, batch_tiles;
 };
+
+// How many times 64 right-hand sides a workgroup of the register-accumulating kernels takes: 128 when
+// the batch has them and every one of the 256 CUs still gets a workgroup (`wgs128`: workgroups of
+// the launch at 128 columns each).
+static int reg_columns(size_t wgs128, int32_t batch) { return batch > 64 && wgs128 >= 256 ? 2 : 1; }
 
 // Checks one product's operands and chooses its launch shape; `launch_wgs_factor` products of
 // this size share the launch, which counts when the launch is sized against the GPU's 256 CUs.
@@ -821,8 +858,10 @@ static int spmm_shape(const SpmmCall &c, int32_t batch, size_t launch_wgs_factor
     // (its 32-bit byte offsets into the value stream must stay below the out-of-range marker)
     const int reg_parts = (wide && (h.br == 16 || h.br == 32) && h.n_vals * 4 < 0x7fffff00ull &&
                            (size_t)h.seg_meta + (size_t)nw * acc_per_wave + (size_t)nw * 64 <= (size_t)160 * 1024) ? (int)h.br / 16 : 0;
-    *out = SpmmShape{nt, nw, two, wide, reg_parts, (int)h.val_fmt, (size_t)h.seg_meta + (size_t)nw * acc_per_wave + (reg_parts ? (size_t)nw * 64 : 0), (unsigned)tiles,
-                     (unsigned)((batch + 16 * nt - 1) / (16 * nt))};
+    const int nq = reg_parts ? reg_columns(wgs(8) * launch_wgs_factor, batch) : 1;
+    const int nwr = nq > 1 ? 8 : nw;
+    *out = SpmmShape{nt, nwr, two, wide, reg_parts, nq, (int)h.val_fmt, (size_t)h.seg_meta + (size_t)nwr * acc_per_wave + (reg_parts ? (size_t)nwr * 64 : 0), (unsigned)tiles,
+                     (unsigned)((batch + 16 * nt * nq - 1) / (16 * nt * nq))};
     return CSB_OK;
 }
 
@@ -832,11 +871,12 @@ static const void *spmm_kernel_for(const SpmmShape &sh) {
 #define CSB_SPMM_K(NT, TWO, NW, WIDE) \
     (MULTI ? (const void *)spmm_multi_kernel<NT, TWO, NW, WIDE> : (const void *)spmm_kernel<NT, TWO, NW, WIDE>)
     if (sh.reg_parts) {
-#define CSB_SPMM_RV(TWO, NW, NH, VF) (MULTI ? (const void *)spmm_reg_multi_kernel<TWO, NW, NH, VF> : (const void *)spmm_reg_kernel<TWO, NW, NH, VF>)
-#define CSB_SPMM_R(TWO, NW, NH) (sh.vf == CSB_VAL_F16 ? CSB_SPMM_RV(TWO, NW, NH, CSB_VAL_F16) : sh.vf == CSB_VAL_BF16 ? CSB_SPMM_RV(TWO, NW, NH, CSB_VAL_BF16) : CSB_SPMM_RV(TWO, NW, NH, CSB_VAL_F32))
+#define CSB_SPMM_RV(TWO, NW, NH, VF, NQ) (MULTI ? (const void *)spmm_reg_multi_kernel<TWO, NW, NH, VF, NQ> : (const void *)spmm_reg_kernel<TWO, NW, NH, VF, NQ>)
+#define CSB_SPMM_R(TWO, NW, NH, NQ) (sh.vf == CSB_VAL_F16 ? CSB_SPMM_RV(TWO, NW, NH, CSB_VAL_F16, NQ) : sh.vf == CSB_VAL_BF16 ? CSB_SPMM_RV(TWO, NW, NH, CSB_VAL_BF16, NQ) : CSB_SPMM_RV(TWO, NW, NH, CSB_VAL_F32, NQ))
 #define CSB_SPMM_RN(NH) \
-        if (sh.nw == 16) return sh.two ? CSB_SPMM_R(true, 16, NH) : CSB_SPMM_R(false, 16, NH); \
-        return sh.two ? CSB_SPMM_R(true, 8, NH) : CSB_SPMM_R(false, 8, NH);
+        if (sh.nq == 2) return sh.two ? CSB_SPMM_R(true, 8, NH, 2) : CSB_SPMM_R(false, 8, NH, 2); \
+        if (sh.nw == 16) return sh.two ? CSB_SPMM_R(true, 16, NH, 1) : CSB_SPMM_R(false, 16, NH, 1); \
+        return sh.two ? CSB_SPMM_R(true, 8, NH, 1) : CSB_SPMM_R(false, 8, NH, 1);
         if (sh.reg_parts == 1) { CSB_SPMM_RN(1) }
         CSB_SPMM_RN(2)
 #undef CSB_SPMM_RN
@@ -888,7 +928,7 @@ int spmm_strided_multi(const SpmmCall *calls, int n, int32_t batch, void *stream
         for (int i = 0; i < n; ++i) {
             int rc = spmm_shape(calls[i], batch, (size_t)n, &sh[i], &J.X[i]);
             if (rc != CSB_OK) return rc;
-            same = same && sh[i].nt == sh[0].nt && sh[i].nw == sh[0].nw && sh[i].two == sh[0].two && sh[i].wide == sh[0].wide && sh[i].reg_parts == sh[0].reg_parts && sh[i].vf == sh[0].vf;
+            same = same && sh[i].nt == sh[0].nt && sh[i].nw == sh[0].nw && sh[i].two == sh[0].two && sh[i].wide == sh[0].wide && sh[i].reg_parts == sh[0].reg_parts && sh[i].nq == sh[0].nq && sh[i].vf == sh[0].vf;
             lds = std::max(lds, sh[i].lds);
             tiles = std::max(tiles, sh[i].tiles);
             J.m[i] = dev_mat(calls[i].mat);
@@ -948,18 +988,21 @@ static int spmm_16bit(const char *who, int fmt, const csb_matrix *m, const uint1
     int64_t ldy_ = ldy;
     const bool half = fmt == CSB_VAL_F16;
     // row tiles of 16 or 32 rows: the kernel that keeps its results in registers
-    const size_t lds_reg = (size_t)h.seg_meta + (size_t)nw * acc_per_wave + (size_t)nw * 64;
+    const size_t tiles = (size_t)h.n_nz_tiles + h.n_zero_tiles;
+    const int nq = reg_columns(tiles * (size_t)((batch + 127) / 128), batch), nwr = nq > 1 ? 8 : nw;
+    const size_t lds_reg = (size_t)h.seg_meta + (size_t)nwr * acc_per_wave + (size_t)nwr * 64;
     if ((h.br == 16 || h.br == 32) && h.n_vals * 4 < 0x7fffff00ull && lds_reg <= (size_t)160 * 1024) {
         XSrc X{(const float *)d_X, (uint32_t)h.cols, ld, 1u, (const float *)d_X, ld, 1u};
         void *rargs[] = {&dm, &X, &d_Y, &ldy_, &b};
         const void *kern;
-#define CSB_R16(NW, NH) (half ? (const void *)spmm_reg16_kernel<NW, NH, CSB_VAL_F16> : (const void *)spmm_reg16_kernel<NW, NH, CSB_VAL_BF16>)
-        if (nw == 16) kern = h.br == 16 ? CSB_R16(16, 1) : CSB_R16(16, 2);
-        else kern = h.br == 16 ? CSB_R16(8, 1) : CSB_R16(8, 2);
+#define CSB_R16(NW, NH, NQ) (half ? (const void *)spmm_reg16_kernel<NW, NH, CSB_VAL_F16, NQ> : (const void *)spmm_reg16_kernel<NW, NH, CSB_VAL_BF16, NQ>)
+        if (nq == 2) kern = h.br == 16 ? CSB_R16(8, 1, 2) : CSB_R16(8, 2, 2);
+        else if (nw == 16) kern = h.br == 16 ? CSB_R16(16, 1, 1) : CSB_R16(16, 2, 1);
+        else kern = h.br == 16 ? CSB_R16(8, 1, 1) : CSB_R16(8, 2, 1);
 #undef CSB_R16
         hipError_t e = ensure_dynamic_lds(kern, lds_reg);
         if (e == hipSuccess)
-            e = hipLaunchKernel(kern, dim3((unsigned)(h.n_nz_tiles + h.n_zero_tiles), (unsigned)((batch + 63) / 64)), dim3(nw * 64), rargs, lds_reg,
+            e = hipLaunchKernel(kern, dim3((unsigned)tiles, (unsigned)((batch + 64 * nq - 1) / (64 * nq))), dim3(nwr * 64), rargs, lds_reg,
                                 (hipStream_t)stream);
         if (e != hipSuccess) { set_error(w + ": " + hipGetErrorString(e)); return CSB_EDEVICE; }
         return CSB_OK;
