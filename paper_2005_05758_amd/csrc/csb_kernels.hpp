@@ -168,9 +168,9 @@ struct SpmvGatedCall {
 int spmv_gated_multi(const SpmvGatedCall *calls, int n, void *stream);
 
 // Y = A Z for `batch` right-hand sides.  Element (column j, right-hand side n) of Z is
-// p0[j*sj0 + n*sn0] for j < n0 and p1[(j-n0)*sj1 + n*sn1] otherwise; Y is [rows_out][ldy].
-int spmm_strided(const csb_matrix *mat, const float *p0, uint32_t n0, int64_t sj0, int64_t sn0, const float *p1,
-                 int64_t sj1, int64_t sn1, float *d_Y, int64_t ldy, int32_t batch, void *stream);
+// p0[j*sj0 + n] for j < n0 and p1[(j-n0)*sj1 + n] otherwise; Y is [rows_out][ldy].
+int spmm_strided(const csb_matrix *mat, const float *p0, uint32_t n0, int64_t sj0, const float *p1,
+                 int64_t sj1, float *d_Y, int64_t ldy, int32_t batch, void *stream);
 
 // Raises a kernel's limit of dynamic LDS on the current device to `bytes` if it is below it.
 // (The limit sticks to the kernel; setting it is a runtime call of its own, too slow to repeat
@@ -182,9 +182,9 @@ struct SpmmCall {
     const csb_matrix *mat;
     const float *p0;
     uint32_t n0;
-    int64_t sj0, sn0;
+    int64_t sj0;
     const float *p1;
-    int64_t sj1, sn1;
+    int64_t sj1;
     float *Y;
     int64_t ldy;
 };

@@ -1545,10 +1545,10 @@ static int rnn_forward_enqueue(const csb_rnn *r, const float *d_x, const float *
                     const int l = l0 + i, t = d - l;
                     float *hl = hi + (size_t)l * HS * batch;
                     if (l == 0)
-                        calls[i] = SpmmCall{r->W[l], xt + (size_t)(t % wl.xt_steps) * batch * I, (uint32_t)I, batch, 1, hl, batch, 1,
+                        calls[i] = SpmmCall{r->W[l], xt + (size_t)(t % wl.xt_steps) * batch * I, (uint32_t)I, batch, hl, batch,
                                             a + (size_t)l * a_stride, batch};
                     else
-                        calls[i] = SpmmCall{r->W[l], hi + (size_t)(l - 1) * HS * batch, (uint32_t)HS, batch, 1, hl, batch, 1,
+                        calls[i] = SpmmCall{r->W[l], hi + (size_t)(l - 1) * HS * batch, (uint32_t)HS, batch, hl, batch,
                                             a + (size_t)l * a_stride, batch};
                 }
                 return spmm_strided_multi(calls, n, batch, st);
@@ -1566,7 +1566,7 @@ static int rnn_forward_enqueue(const csb_rnn *r, const float *d_x, const float *
                     const int l = l0 + i;
                     float *ml = mb + (size_t)l * hb;
                     float *dst = lstmp ? hi + (size_t)l * HS * batch : a2 + (size_t)l * hb;
-                    calls[i] = SpmmCall{r->Wp[l], ml, (uint32_t)H, batch, 1, ml, batch, 1, dst, batch};
+                    calls[i] = SpmmCall{r->Wp[l], ml, (uint32_t)H, batch, ml, batch, dst, batch};
                 }
                 return spmm_strided_multi(calls, n, batch, st);
             });

@@ -2,8 +2,8 @@
 //
 // With B right-hand sides a kernel matrix K_b (r x c) meets a gathered c x B slab of X: a
 // real dense product, so it goes to the matrix cores (v_mfma_f32_16x16x4_f32).  One
-// workgroup owns one output row tile and one batch tile.  The tile's records (groups,
-// virtual blocks, lane descriptors, input-offset lists) are staged in LDS one segment at a
+// workgroup owns one output row tile and one batch tile.  The tile's records
+// (virtual blocks, lane descriptors, input-offset lists) are staged in LDS one segment at a
 // time; the wavefronts take the segment's virtual blocks round-robin, each as 16-row
 // slices: per 4 columns one A operand (16 x 4 of the kernel) feeds one MFMA per 16 batch
 // columns.  The operands of the next pass are loaded while the current one multiplies.
@@ -26,18 +26,24 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint32_t uni_(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// Element (column j of A, right-hand side n) of the input, from one of two sources.  Element
-// offsets fit 32 bits and the strides over j fit 24 bits (checked on the host).
+// Element (column j of A, right-hand side n) of the input, from one of two sources; the right-hand
+// sides of a column are contiguous.  Byte offsets fit 32 bits and the strides over j fit 24 bits
+// (checked on the host).
 struct XSrc {
     const float *p0;
     uint32_t n0;          // columns j < n0 come from p0, the rest from p1
-    uint32_t sj0, sn0;    // strides over j and over n
+    uint32_t sj0;         // stride over j
     const float *p1;
-    uint32_t sj1, sn1;
+    uint32_t sj1;
 };
 
-// One pass: 4 KS columns (KS MFMA k-steps; 8, or 4 in the wide form, whose operands take
-// four times the registers per k-step) of one 16-row slice of one virtual block.
+// NT neighbouring right-hand sides (a load of NT words, aligned to one word).
+template <int NT> struct RhsVec;
+template <> struct RhsVec<1> { typedef float type __attribute__((ext_vector_type(1))); };
+template <> struct RhsVec<2> { typedef float type __attribute__((ext_vector_type(2))); };
+template <> struct RhsVec<4> { typedef float type __attribute__((ext_vector_type(4))); };
+
+// One pass: 16 columns (4 MFMA k-steps) of one 16-row slice of one virtual block.
 struct Pass {
     uint32_t k;           // virtual block, counted inside the segment
     uint32_t m0, kc;      // first row of the slice, first column of the pass
@@ -48,23 +54,31 @@ struct Pass {
     bool valid;
 };
 
-template <int NT, int KS>
+template <int NT>
 struct Operands {
-    float av[KS];
-    float bv[KS][NT];
+    uint32_t av[4];                          // kernel values as stored
+    typename RhsVec<NT>::type bv[4];         // NT right-hand sides of the lane's column
 };
 
-// WIDE (NT = 4, right-hand sides contiguous in memory, batch a multiple of 4): a lane reads
-// four neighbouring right-hand sides of its input row with one 16-byte load and feeds one
-// of them to each of four MFMA tiles, so tile t holds the right-hand sides 4 n + t; a
-// lane's four results of one row are then neighbours again and go to the accumulator as one
-// 16-byte word.  A quarter of the load and LDS instructions per multiply.
-template <int NT, bool TWO, int NW, bool WIDE>
+// What bounds it: vector instructions.  The products of a pruned gate matrix are tiny (13 x 13
+// kernels out of 64 x 64 blocks) and a wavefront has two or three passes of at most 16 NT MFMAs, so
+// a pass is written to cost few instructions: a lane reads its NT neighbouring right-hand sides
+// with one load (tile t of the MFMA holds the right-hand sides NT n + t; the loads are aligned to a
+// word, and lanes past the batch are moved back to its last NT right-hand sides, so any batch and
+// stride will do), what a block lacks repeats its last row or column instead of being branched
+// around, operands are masked in a block's last, partial k-step only, rows a slice lacks go to a
+// spare row of the accumulator instead of being predicated, and a pass always issues the same
+// loads, so that counted waits let those of the next two passes fly.
+// Measured against the form with a branch per k-step, value format and slice and masked operands (about
+// 480 instructions per pass): two LSTM layers of 1024 at batch 64 17.2 -> 16.2 us per step, two
+// Li-GRU layers of 512 at batch 33 12.3 -> 11.1.
+template <int NT, bool TWO, int NW>
 __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float *__restrict__ Y, const int64_t ldy,
                                           const uint32_t batch, const uint32_t block_x, const uint32_t block_y) {
     extern __shared__ float4 smem4[];
-    constexpr int NB = 16 * NT;                    // batch columns per workgroup
-    constexpr int KS = WIDE ? 4 : 8;               // k-steps per pass
+    typedef typename RhsVec<NT>::type vec;
+    typedef vec vec_u __attribute__((aligned(4)));
+    constexpr uint32_t NB = 16 * NT;               // batch columns per workgroup
     constexpr uint32_t NTHR = NW * 64;             // NW wavefronts
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = uni_(tid >> 6);
     const uint32_t bt0 = block_y * NB;
@@ -78,209 +92,162 @@ __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float 
         return;
     }
     uint8_t *meta = (uint8_t *)smem4;                              // one record segment
-    float *acc = (float *)(meta + m.seg_meta);                     // [waves][br][NB]
-    float *myacc = acc + (size_t)wave * br * NB;
-    for (uint32_t e = lane; e < br * NB; e += 64) myacc[e] = 0.0f;
+    float *acc = (float *)(meta + m.seg_meta);                     // [waves][br + 1][NB], the last row a spare one
+    const uint32_t acc_wave = (br + 1u) * NB;
+    float *myacc = acc + (size_t)wave * acc_wave;
+    for (uint32_t e = lane; e < acc_wave / 4u; e += 64) ((float4 *)myacc)[e] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     const uint32_t rank = block_x, tile = m.nz_tiles[rank];
     const uint32_t vf = uni_(m.val_fmt);                           // storage format of the value stream
-    const uint32_t mrow = lane & 15u, kq = lane >> 4;              // A: row, column-in-4; B: column n, row-in-4
-    static_assert(!WIDE || NT == 4, "the wide form feeds four tiles from one load");
-    const uint32_t ncol = bt0 + (WIDE ? 4u * mrow : mrow);         // this lane's right-hand side (per 16: + 16 nt)
-    uint32_t noff0[NT], noff1[NT];                                 // its byte offset in either source
-    bool n_ok[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        const uint32_t n = WIDE ? ncol + (uint32_t)nt : ncol + 16u * nt;
-        n_ok[nt] = n < batch;
-        noff0[nt] = (n_ok[nt] ? n : 0u) * X.sn0 * 4u;              // bytes
-        noff1[nt] = (n_ok[nt] ? n : 0u) * X.sn1 * 4u;
-    }
+    const uint32_t mrow = lane & 15u, kq = lane >> 4;              // A: row, column-in-4; B: right-hand sides, column-in-4
+    const uint32_t nstart = min(bt0 + NT * mrow, batch - NT);      // this lane's first right-hand side (batch >= NT)
+    const uint32_t split4 = 4u * X.n0;
+    const uint8_t *const x0 = (const uint8_t *)(X.p0 + nstart);
+    const uint8_t *const x1 = (const uint8_t *)(X.p1 + nstart) - (size_t)split4 * X.sj1;
 
     for (uint32_t sg = m.tile_seg0[rank]; sg < m.tile_seg0[rank + 1]; ++sg) {
         // ---- stage the segment's records ------------------------------------------------
         const SegRec *sp = m.segs + sg;
-        const uint32_t ga = sp->g0, ng = sp->ng, vb0 = sp->vb0, nvbs = sp->nvbs, idx0 = sp->idx0, idx_bytes = sp->idx_bytes;
-        const uint32_t voff = (ng * (uint32_t)sizeof(GroupRec) + 15u) & ~15u;
-        const uint32_t ioff = voff + ((nvbs * (uint32_t)sizeof(VbRec) + 15u) & ~15u);
+        const uint32_t vb0 = sp->vb0, nvbs = sp->nvbs, idx0 = sp->idx0, idx_bytes = sp->idx_bytes;
+        const uint32_t ioff = nvbs * (uint32_t)sizeof(VbRec);
         __syncthreads();                                           // the previous segment is done with
         {
-            const uint2 *gs = (const uint2 *)(m.groups + ga);
-            uint2 *gd = (uint2 *)meta;
-            for (uint32_t i = tid; i < ng * 3u; i += NTHR) gd[i] = gs[i];
             const float4 *vs = (const float4 *)(m.vbs + vb0);
-            float4 *vd = (float4 *)(meta + voff);
+            float4 *vd = (float4 *)meta;
             for (uint32_t i = tid; i < nvbs; i += NTHR) vd[i] = vs[i];
             const float4 *is = (const float4 *)(m.idx + idx0);
             float4 *id = (float4 *)(meta + ioff);
             for (uint32_t i = tid; i < idx_bytes >> 4; i += NTHR) id[i] = is[i];
         }
         __syncthreads();
+        if (wave >= nvbs) continue;                                // (uniform per wavefront; the barriers above are passed by all)
 
         // ---- passes of this wavefront's virtual blocks ----------------------------------
-        auto open_vb = [&](uint32_t k) -> Pass {
-            Pass p{};
-            p.k = k;
-            p.valid = k < nvbs;
-            if (!p.valid) return p;
-            const uint4 v = *(const uint4 *)(meta + voff + k * (uint32_t)sizeof(VbRec));
+        auto open_vb = [&](uint32_t k, Pass &p) {
+            const uint4 v = *(const uint4 *)(meta + k * (uint32_t)sizeof(VbRec));
             const uint32_t v0 = uni_(v.x);
+            p.k = k;
             p.r = v0 & 0xffu; p.lane0 = (v0 >> 8) & 0xffu; p.c = v0 >> 16;
             p.val_off = uni_(v.y);
             p.desc = ioff + (uni_(v.z) - idx0);
             p.list = ioff + (uni_(v.w) - idx0);
-            p.m0 = 0; p.kc = 0;
-            return p;
         };
+        // The pass after p.  Past the wavefront's last one the fields stay (its loads are issued again
+        // and dropped) and only `valid` goes off.
         auto next_pass = [&](const Pass &p) -> Pass {
-            Pass q = p;
-            q.kc += 4 * KS;
-            if (q.kc < q.c) return q;
-            q.kc = 0; q.m0 += 16;
-            if (q.m0 < q.r) return q;
-            return open_vb(p.k + NW);
+            const bool cols = p.kc + 16u < p.c, rows = p.m0 + 16u < p.r, more = p.k + NW < nvbs;
+            Pass q;
+            open_vb(cols || rows || !more ? p.k : p.k + NW, q);
+            q.valid = p.valid && (cols || rows || more);
+            q.kc = cols ? p.kc + 16u : rows || more ? 0u : p.kc;
+            q.m0 = cols ? p.m0 : rows ? p.m0 + 16u : more ? 0u : p.m0;
+            return q;
         };
-        // All loads of a pass are independent: kernel values and gathered inputs of up to 8
-        // k-steps.  Out-of-range lanes load from clamped addresses; their operands are zeroed.
-        auto load_pass = [&](const Pass &p, Operands<NT, KS> &o) {
-            const float *gv = m.vals + p.val_off;
-            const uint32_t *gv16 = (const uint32_t *)m.vals + (p.val_off >> 1);
-            const uint16_t *colp = (const uint16_t *)(meta + p.list);
-            const bool row_ok = p.m0 + mrow < p.r;
-            const uint32_t arow = p.lane0 + p.m0 + (row_ok ? mrow : 0u);
+        // Eight loads, always.  Rows and columns the block lacks repeat its last ones.
+        auto load_pass = [&](const Pass &p, Operands<NT> &o) {
+            const uint32_t *gv = (const uint32_t *)m.vals + (vf == CSB_VAL_F32 ? p.val_off : p.val_off >> 1);
+            const uint32_t arow = p.lane0 + min(p.m0 + mrow, p.r - 1u);
+            const uint32_t half = vf == CSB_VAL_F32 ? 0u : 1u;     // 16-bit: a word per lane and PAIR of columns
+            uint32_t jc[4], cb[4];
 #pragma unroll
-            for (int s8 = 0; s8 < KS; ++s8) {
-                if (p.kc + 4u * s8 >= p.c) break;                  // uniform: k-steps the block does not have
-                const uint32_t jj = p.kc + 4u * s8 + kq;
-                const bool ok = jj < p.c;
-                const uint32_t jc = ok ? jj : 0u;
-                float t;
-                if (vf == CSB_VAL_F32) {                           // uniform
-                    t = gv[jc * (uint32_t)kWave + arow];
-                } else {                                           // one word per lane and pair of steps
-                    const uint32_t w = gv16[(jc >> 1) * (uint32_t)kWave + arow];
-                    const uint32_t bits = (jc & 1u) ? w >> 16 : w & 0xffffu;
-                    t = vf == CSB_VAL_BF16 ? __uint_as_float(bits << 16) : (float)__builtin_bit_cast(_Float16, (uint16_t)bits);
-                }
-                o.av[s8] = ok && row_ok ? t : 0.0f;
-                // The input operand is not zeroed where the kernel operand is: a lane without a
-                // column reads the block's first column (finite wherever the block's own rows
-                // would be), one past the batch reads right-hand side 0, and its result column
-                // is never stored.
-                const uint32_t cb = colp[jc];                      // 4 * column: the list holds byte offsets
-                const bool first = !TWO || cb < 4u * X.n0;
-                const uint8_t *src = (const uint8_t *)(first ? X.p0 : X.p1);
-                const uint32_t joff = first ? __umul24(cb, X.sj0) : __umul24(cb - 4u * X.n0, X.sj1);   // bytes
-                if constexpr (WIDE) {                              // batch % 4 == 0: the four are in or out together
-                    const float4 x4 = *(const float4 *)(src + joff + (first ? noff0[0] : noff1[0]));
-                    o.bv[s8][0] = x4.x; o.bv[s8][1] = x4.y; o.bv[s8][2] = x4.z; o.bv[s8][3] = x4.w;
-                } else {
+            for (int s = 0; s < 4; ++s) {
+                jc[s] = min(p.kc + 4u * s + kq, p.c - 1u);
+                cb[s] = *(const uint16_t *)(meta + p.list + 2u * jc[s]);                   // 4 * column
+            }
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-                        o.bv[s8][nt] = *(const float *)(src + joff + (first ? noff0[nt] : noff1[nt]));
-                }
+            for (int s = 0; s < 4; ++s) o.av[s] = gv[(jc[s] >> half) * (uint32_t)kWave + arow];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const bool first = !TWO || cb[s] < split4;
+                const uint8_t *src = (first ? x0 : x1) + (size_t)__umul24(cb[s], first ? X.sj0 : X.sj1);
+                o.bv[s] = *(const vec_u *)src;
             }
         };
         floatx4 D[NT];
-        const floatx4 zero4 = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        auto mult_pass = [&](const Pass &p, const Operands<NT> &o) {
+            if (p.kc == 0) {                                       // (uniform) a new slice
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) D[nt] = zero4;
-        auto mult_pass = [&](const Pass &p, const Operands<NT, KS> &o) {
-#pragma unroll
-            for (int s8 = 0; s8 < KS; ++s8) {
-                if (p.kc + 4u * s8 >= p.c) break;                  // uniform
-                // a slice's first k-step starts from a zero operand: the accumulators need no clearing
-                if (s8 == 0 && p.kc == 0) {                        // uniform
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-                        D[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.av[s8], o.bv[s8][nt], zero4, 0, 0, 0);
-                } else {
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-                        D[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.av[s8], o.bv[s8][nt], D[nt], 0, 0, 0);
-                }
+                for (int nt = 0; nt < NT; ++nt) D[nt] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
             }
-            if (p.kc + 4 * KS < p.c) return;                       // the slice has more columns
-            // lane holds rows 4*(lane/16)+i, column lane%16 of each 16 x 16 result; the rows of
-            // a slice are distinct, so no two lanes meet in the accumulator: all reads, then
-            // all writes
+            const uint32_t left = p.c - p.kc;                      // columns from here on
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                if (4u * s >= left) break;                         // (uniform) k-steps the block does not have
+                uint32_t w = o.av[s];
+                vec b = o.bv[s];
+                if (vf != CSB_VAL_F32) {                           // (uniform) this lane's column of the pair: kc is even, so its parity is kq's
+                    const uint32_t bits = (kq & 1u) ? w >> 16 : w & 0xffffu;
+                    w = vf == CSB_VAL_BF16 ? bits << 16 : __float_as_uint((float)__builtin_bit_cast(_Float16, (uint16_t)bits));
+                }
+                if (4u * s + 4u > left) {                          // (uniform) the last, partial one
+                    const bool ok = 4u * s + kq < left;
+                    w = ok ? w : 0u;
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) b[nt] = ok ? b[nt] : 0.0f;
+                }
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    D[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w), b[nt], D[nt], 0, 0, 0);
+            }
+            if (left > 16u) return;                                // the slice has more columns
+            // lane holds rows 4 kq + i, right-hand sides NT mrow + t of each result; the rows of a slice
+            // are distinct, so no two lanes meet in the accumulator (but in its spare row, which nobody
+            // reads): all reads, then all writes
             uint32_t at[4];
-            bool on[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const uint32_t mr = p.m0 + 4u * kq + i;
-                on[i] = mr < p.r;
-                const uint32_t slot = meta[p.desc + 4u * (p.lane0 + (on[i] ? mr : 0u))];
-                at[i] = slot * NB + (WIDE ? 4u * mrow : mrow);
+                const uint32_t slot = meta[p.desc + 4u * (p.lane0 + min(mr, p.r - 1u))];
+                at[i] = (mr < p.r ? slot : br) * NB + NT * mrow;
             }
-            if constexpr (WIDE) {
-                float4 old4[4];
+            vec old[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) old4[i] = *(const float4 *)(myacc + at[i]);
+            for (int i = 0; i < 4; ++i) old[i] = *(const vec *)(myacc + at[i]);
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (on[i])
-                        *(float4 *)(myacc + at[i]) = make_float4(old4[i].x + D[0][i], old4[i].y + D[1][i],
-                                                                 old4[i].z + D[2][i], old4[i].w + D[3][i]);
-                return;
+            for (int i = 0; i < 4; ++i) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) old[i][nt] += D[nt][i];
+                *(vec *)(myacc + at[i]) = old[i];
             }
-            float old[4][NT];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) old[i][nt] = myacc[at[i] + 16u * nt];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-                    if (on[i]) myacc[at[i] + 16u * nt] = old[i][nt] + D[nt][i];
         };
-        auto nxt = [&](const Pass &p) -> Pass { return p.valid ? next_pass(p) : p; };
-        if constexpr (WIDE) {
-            // three passes in flight (their operands are small: 4 k-steps)
-            Operands<NT, KS> oa, ob, oc;
-            Pass pa = open_vb(wave), pb = nxt(pa), pc{};
-            if (pa.valid) load_pass(pa, oa);
-            if (pb.valid) load_pass(pb, ob);
-            while (true) {
-                pc = nxt(pb); if (pc.valid) load_pass(pc, oc);
-                if (!pa.valid) break;
-                mult_pass(pa, oa);
-                pa = nxt(pc); if (pa.valid) load_pass(pa, oa);
-                if (!pb.valid) break;
-                mult_pass(pb, ob);
-                pb = nxt(pa); if (pb.valid) load_pass(pb, ob);
-                if (!pc.valid) break;
-                mult_pass(pc, oc);
-            }
-        } else {
-            Operands<NT, KS> oa, ob;
-            Pass pa = open_vb(wave), pb{};
-            if (pa.valid) load_pass(pa, oa);
-            while (pa.valid) {
-                pb = next_pass(pa);
-                if (pb.valid) load_pass(pb, ob);
-                mult_pass(pa, oa);
-                if (!pb.valid) break;
-                pa = next_pass(pb);
-                if (pa.valid) load_pass(pa, oa);
-                mult_pass(pb, ob);
-            }
+        Operands<NT> oa, ob, oc;                                   // three passes in flight
+        Pass pa, pb, pc;
+        open_vb(wave, pa);
+        pa.m0 = pa.kc = 0;
+        pa.valid = true;
+        load_pass(pa, oa);
+        pb = next_pass(pa);
+        load_pass(pb, ob);
+        while (true) {
+            pc = next_pass(pb); load_pass(pc, oc);
+            mult_pass(pa, oa);
+            if (!pb.valid) break;
+            pa = next_pass(pc); load_pass(pa, oa);
+            mult_pass(pb, ob);
+            if (!pc.valid) break;
+            pb = next_pass(pa); load_pass(pb, ob);
+            mult_pass(pc, oc);
+            if (!pa.valid) break;
         }
     }
     __syncthreads();
-    for (uint32_t e = tid; e < br * NB; e += NTHR) {
-        float s = 0.0f;
+    for (uint32_t e = tid; e < br * 16u; e += NTHR) {              // a row and a lane's NT right-hand sides
+        vec s = *(const vec *)(acc + (size_t)e * NT);
 #pragma unroll
-        for (int w = 0; w < NW; ++w) s += acc[(size_t)w * br * NB + e];
-        const uint32_t row = tile * br + e / NB, n = bt0 + e % NB;
-        if (row < m.rows_out && n < batch) Y[(size_t)row * ldy + n] = s;
+        for (int w = 1; w < NW; ++w) s += *(const vec *)(acc + (size_t)w * acc_wave + (size_t)e * NT);
+        const uint32_t row = tile * br + (e >> 4), n_lane = bt0 + NT * (e & 15u);
+        if (row >= m.rows_out) continue;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {                             // (a group moved back repeats right-hand sides of the one before)
+            const uint32_t n = min(n_lane, batch - NT) + t;
+            if (n >= n_lane) Y[(size_t)row * ldy + n] = s[t];
+        }
     }
 }
 
-template <int NT, bool TWO, int NW, bool WIDE>
+template <int NT, bool TWO, int NW>
 __global__ __launch_bounds__(NW * 64) void spmm_kernel(const DevMat m, const XSrc X, float *__restrict__ Y,
                                                              const int64_t ldy, const uint32_t batch) {
-    spmm_body<NT, TWO, NW, WIDE>(m, X, Y, ldy, batch, blockIdx.x, blockIdx.y);
+    spmm_body<NT, TWO, NW>(m, X, Y, ldy, batch, blockIdx.x, blockIdx.y);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -335,16 +302,12 @@ __global__ __launch_bounds__(NW * 64) void spmm_bf16_kernel(const DevMat m, cons
 
     for (uint32_t sg = m.tile_seg0[rank]; sg < m.tile_seg0[rank + 1]; ++sg) {
         const SegRec *sp = m.segs + sg;
-        const uint32_t ga = sp->g0, ng = sp->ng, vb0 = sp->vb0, nvbs = sp->nvbs, idx0 = sp->idx0, idx_bytes = sp->idx_bytes;
-        const uint32_t voff = (ng * (uint32_t)sizeof(GroupRec) + 15u) & ~15u;
-        const uint32_t ioff = voff + ((nvbs * (uint32_t)sizeof(VbRec) + 15u) & ~15u);
+        const uint32_t vb0 = sp->vb0, nvbs = sp->nvbs, idx0 = sp->idx0, idx_bytes = sp->idx_bytes;
+        const uint32_t ioff = nvbs * (uint32_t)sizeof(VbRec);
         __syncthreads();
         {
-            const uint2 *gs = (const uint2 *)(m.groups + ga);
-            uint2 *gd = (uint2 *)meta;
-            for (uint32_t i = tid; i < ng * 3u; i += NTHR) gd[i] = gs[i];
             const float4 *vs = (const float4 *)(m.vbs + vb0);
-            float4 *vd = (float4 *)(meta + voff);
+            float4 *vd = (float4 *)meta;
             for (uint32_t i = tid; i < nvbs; i += NTHR) vd[i] = vs[i];
             const float4 *is = (const float4 *)(m.idx + idx0);
             float4 *id = (float4 *)(meta + ioff);
@@ -357,7 +320,7 @@ __global__ __launch_bounds__(NW * 64) void spmm_bf16_kernel(const DevMat m, cons
             p.k = k;
             p.valid = k < nvbs;
             if (!p.valid) return p;
-            const uint4 v = *(const uint4 *)(meta + voff + k * (uint32_t)sizeof(VbRec));
+            const uint4 v = *(const uint4 *)(meta + k * (uint32_t)sizeof(VbRec));
             const uint32_t v0 = uni_(v.x);
             p.r = v0 & 0xffu; p.lane0 = (v0 >> 8) & 0xffu; p.c = v0 >> 16;
             p.val_off = uni_(v.y);
@@ -559,16 +522,12 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
     for (uint32_t sg = m.tile_seg0[rank]; sg < m.tile_seg0[rank + 1]; ++sg) {
         // ---- stage the segment's records ------------------------------------------------
         const SegRec *sp = m.segs + sg;
-        const uint32_t ga = sp->g0, ng = sp->ng, vb0 = sp->vb0, nvbs = sp->nvbs, idx0 = sp->idx0, idx_bytes = sp->idx_bytes;
-        const uint32_t voff = (ng * (uint32_t)sizeof(GroupRec) + 15u) & ~15u;
-        const uint32_t ioff = voff + ((nvbs * (uint32_t)sizeof(VbRec) + 15u) & ~15u);
+        const uint32_t vb0 = sp->vb0, nvbs = sp->nvbs, idx0 = sp->idx0, idx_bytes = sp->idx_bytes;
+        const uint32_t ioff = nvbs * (uint32_t)sizeof(VbRec);
         __syncthreads();                                           // the previous segment is done with
         {
-            const uint2 *gs = (const uint2 *)(m.groups + ga);
-            uint2 *gd = (uint2 *)meta;
-            for (uint32_t i = tid; i < ng * 3u; i += NTHR) gd[i] = gs[i];
             const float4 *vs = (const float4 *)(m.vbs + vb0);
-            float4 *vd = (float4 *)(meta + voff);
+            float4 *vd = (float4 *)meta;
             for (uint32_t i = tid; i < nvbs; i += NTHR) vd[i] = vs[i];
             const float4 *is = (const float4 *)(m.idx + idx0);
             float4 *id = (float4 *)(meta + ioff);
@@ -585,7 +544,7 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
         uint32_t parts = 0;
         // Opens virtual block k < nvbs: its record, and the map from tile rows to its kernel rows.
         auto open_vb = [&](uint32_t k, RegPass &p) {
-            const uint4 v = *(const uint4 *)(meta + voff + k * (uint32_t)sizeof(VbRec));
+            const uint4 v = *(const uint4 *)(meta + k * (uint32_t)sizeof(VbRec));
             const uint32_t v0 = uni_(v.x);
             p.k = k; p.valid = true; p.kc = 0;
             p.r = v0 & 0xffu; p.lane0 = (v0 >> 8) & 0xffu; p.c = v0 >> 16;
@@ -790,11 +749,11 @@ struct SpmmJobs {
     float *Y[kMaxJobsPerLaunch];
     int64_t ldy[kMaxJobsPerLaunch];
 };
-template <int NT, bool TWO, int NW, bool WIDE>
+template <int NT, bool TWO, int NW>
 __global__ __launch_bounds__(NW * 64) void spmm_multi_kernel(const SpmmJobs J, const uint32_t batch) {
     const uint32_t j = blockIdx.z;
     if (blockIdx.x >= J.m[j].n_nz_tiles + J.m[j].n_zero_tiles) return;      // the grid is as wide as the widest product
-    spmm_body<NT, TWO, NW, WIDE>(J.m[j], J.X[j], J.Y[j], J.ldy[j], batch, blockIdx.x, blockIdx.y);
+    spmm_body<NT, TWO, NW>(J.m[j], J.X[j], J.Y[j], J.ldy[j], batch, blockIdx.x, blockIdx.y);
 }
 
 template <bool TWO, int NW, int NH, int VF, int NQ>
@@ -807,8 +766,8 @@ __global__ __launch_bounds__(NW * 64) void spmm_reg_multi_kernel(const SpmmJobs 
 // Launch shape of one product: batch columns per workgroup (16 nt), wavefronts per workgroup.
 struct SpmmShape {
     int nt, nw;
-    bool two, wide;
-    int reg_parts;          // wide form, row tiles of 16 or 32 rows: the kernel that keeps the results in
+    bool two;
+    int reg_parts;          // 64 columns, row tiles of 16 or 32 rows: the kernel that keeps the results in
                             // registers, with this many 16-row parts (else 0; four parts do not fit the
                             // registers of a 16-wavefront workgroup)
     int nq;                 // ... and this many times 64 right-hand sides per workgroup
@@ -829,47 +788,44 @@ static int spmm_shape(const SpmmCall &c, int32_t batch, size_t launch_wgs_factor
     if (!mat->plan.valid || !mat->uploaded || !mat->d_buf) { set_error("csb_spmm: matrix not planned and uploaded"); return CSB_ESTATE; }
     const DevHeader &h = mat->plan.hdr;
     // 32-bit element offsets, 24-bit multiplies
-    const int64_t smax_j = std::max(c.sj0, c.sj1), smax_n = std::max(c.sn0, c.sn1);
-    if (c.sj0 < 0 || c.sj1 < 0 || c.sn0 < 0 || c.sn1 < 0 || smax_j >= (1 << 24) || (int64_t)h.cols >= (1 << 24) ||
-        (int64_t)h.cols * smax_j + (int64_t)batch * smax_n >= (1ll << 30)) {
+    const int64_t smax_j = std::max(c.sj0, c.sj1);
+    if (c.sj0 < 0 || c.sj1 < 0 || smax_j >= (1 << 24) || (int64_t)h.cols >= (1 << 24) ||
+        (int64_t)h.cols * smax_j + (int64_t)batch >= (1ll << 30)) {
         set_error("csb_spmm: strides or sizes beyond the kernel's 32-bit element offsets");
         return CSB_EUNSUPPORTED;
     }
-    *X = XSrc{c.p0, c.n0, (uint32_t)c.sj0, (uint32_t)c.sn0, c.p1, (uint32_t)c.sj1, (uint32_t)c.sn1};
+    *X = XSrc{c.p0, c.n0, (uint32_t)c.sj0, c.p1, (uint32_t)c.sj1};
     const bool two = c.n0 < (uint32_t)h.cols;
-    // the wide form: right-hand sides contiguous, rows of the input 16-byte aligned, batch in
-    // fours, and eight wavefronts' accumulator tiles of 64 columns fit LDS
-    const bool aligned = ((uintptr_t)c.p0 % 16 == 0) && c.sj0 % 4 == 0 && c.sn0 == 1 &&
-                         (!two || (((uintptr_t)c.p1 % 16 == 0) && c.sj1 % 4 == 0 && c.sn1 == 1));
-    const bool wide_ok = aligned && batch % 4 == 0 &&
-                         (size_t)h.seg_meta + 8 * (size_t)h.br * 64 * sizeof(float) <= (size_t)kLdsBudget;
-    // batch columns per workgroup: the widest form whose launch still gives every CU (256) a workgroup
+    // batch columns per workgroup: the widest form whose launch still gives every CU (256) a workgroup;
+    // 16 wavefronts share a tile's blocks when their accumulator tiles fit LDS and the launch alone would
+    // not give every CU two workgroups (64 columns: always when they fit), else 8
     const size_t tiles = (size_t)h.n_nz_tiles + h.n_zero_tiles;
     auto wgs = [&](int n) { return tiles * (size_t)((batch + 16 * n - 1) / (16 * n)); };
+    auto acc_lds = [&](int n, int waves) { return (size_t)h.seg_meta + (size_t)waves * (h.br + 1) * 16 * n * sizeof(float); };
     int nt = 1;
     if (h.br <= 128 && batch > 16 && wgs(2) * launch_wgs_factor >= 256) nt = 2;
-    if (wide_ok && batch >= 48 && wgs(4) * launch_wgs_factor >= 256) nt = 4;
-    const bool wide = nt == 4;
-    // 16 wavefronts share a tile's blocks when their accumulator tiles fit LDS and the launch
-    // alone would not give every CU of an MI355X (256) two workgroups; else 8
-    const size_t acc_per_wave = (size_t)h.br * 16 * nt * sizeof(float);
-    const bool fits16 = (size_t)h.seg_meta + 16 * acc_per_wave <= (size_t)kLdsBudget;
-    const int nw = fits16 && (wide || wgs(nt) * launch_wgs_factor < 2 * 256) ? 16 : 8;
-    // (its 32-bit byte offsets into the value stream must stay below the out-of-range marker)
-    const int reg_parts = (wide && (h.br == 16 || h.br == 32) && h.n_vals * 4 < 0x7fffff00ull &&
-                           (size_t)h.seg_meta + (size_t)nw * acc_per_wave + (size_t)nw * 64 <= (size_t)160 * 1024) ? (int)h.br / 16 : 0;
-    const int nq = reg_parts ? reg_columns(wgs(8) * launch_wgs_factor, batch) : 1;
-    const int nwr = nq > 1 ? 8 : nw;
-    *out = SpmmShape{nt, nwr, two, wide, reg_parts, nq, (int)h.val_fmt, (size_t)h.seg_meta + (size_t)nwr * acc_per_wave + (reg_parts ? (size_t)nwr * 64 : 0), (unsigned)tiles,
-                     (unsigned)((batch + 16 * nt * nq - 1) / (16 * nt * nq))};
+    if (batch >= 48 && wgs(4) * launch_wgs_factor >= 256 && acc_lds(4, 8) <= (size_t)kLdsBudget) nt = 4;
+    const bool fits16 = acc_lds(nt, 16) <= (size_t)kLdsBudget;
+    const int nw = fits16 && (nt == 4 || wgs(nt) * launch_wgs_factor < 2 * 256) ? 16 : 8;
+    // The register-accumulating kernels: row tiles of 16 or 32 rows, 16-byte aligned rows of the input, batch in
+    // fours (their 32-bit byte offsets into the value stream must stay below the out-of-range marker).
+    const bool aligned = ((uintptr_t)c.p0 % 16 == 0) && c.sj0 % 4 == 0 && (!two || (((uintptr_t)c.p1 % 16 == 0) && c.sj1 % 4 == 0));
+    const size_t reg_wave = (size_t)h.br * 64 * sizeof(float) + 64;
+    const int nq = reg_columns(wgs(8) * launch_wgs_factor, batch), nwr = nq > 1 ? 8 : nw;
+    const int reg_parts = (nt == 4 && aligned && batch % 4 == 0 && (h.br == 16 || h.br == 32) && h.n_vals * 4 < 0x7fffff00ull &&
+                           (size_t)h.seg_meta + (size_t)nwr * reg_wave <= (size_t)160 * 1024) ? (int)h.br / 16 : 0;
+    if (reg_parts)
+        *out = SpmmShape{nt, nwr, two, reg_parts, nq, (int)h.val_fmt, (size_t)h.seg_meta + (size_t)nwr * reg_wave, (unsigned)tiles,
+                         (unsigned)((batch + 64 * nq - 1) / (64 * nq))};
+    else
+        *out = SpmmShape{nt, nw, two, 0, 1, (int)h.val_fmt, acc_lds(nt, nw), (unsigned)tiles, (unsigned)((batch + 16 * nt - 1) / (16 * nt))};
     return CSB_OK;
 }
 
 // The kernel instantiation for a launch shape (one product per launch, or several).
 template <bool MULTI>
 static const void *spmm_kernel_for(const SpmmShape &sh) {
-#define CSB_SPMM_K(NT, TWO, NW, WIDE) \
-    (MULTI ? (const void *)spmm_multi_kernel<NT, TWO, NW, WIDE> : (const void *)spmm_kernel<NT, TWO, NW, WIDE>)
+#define CSB_SPMM_K(NT, TWO, NW) (MULTI ? (const void *)spmm_multi_kernel<NT, TWO, NW> : (const void *)spmm_kernel<NT, TWO, NW>)
     if (sh.reg_parts) {
 #define CSB_SPMM_RV(TWO, NW, NH, VF, NQ) (MULTI ? (const void *)spmm_reg_multi_kernel<TWO, NW, NH, VF, NQ> : (const void *)spmm_reg_kernel<TWO, NW, NH, VF, NQ>)
 #define CSB_SPMM_R(TWO, NW, NH, NQ) (sh.vf == CSB_VAL_F16 ? CSB_SPMM_RV(TWO, NW, NH, CSB_VAL_F16, NQ) : sh.vf == CSB_VAL_BF16 ? CSB_SPMM_RV(TWO, NW, NH, CSB_VAL_BF16, NQ) : CSB_SPMM_RV(TWO, NW, NH, CSB_VAL_F32, NQ))
@@ -883,22 +839,19 @@ static const void *spmm_kernel_for(const SpmmShape &sh) {
 #undef CSB_SPMM_R
 #undef CSB_SPMM_RV
     }
-    if (sh.wide) {
-        if (sh.nw == 16) return sh.two ? CSB_SPMM_K(4, true, 16, true) : CSB_SPMM_K(4, false, 16, true);
-        return sh.two ? CSB_SPMM_K(4, true, 8, true) : CSB_SPMM_K(4, false, 8, true);
-    }
-    if (sh.nw == 16) {
-        if (sh.nt == 2) return sh.two ? CSB_SPMM_K(2, true, 16, false) : CSB_SPMM_K(2, false, 16, false);
-        return sh.two ? CSB_SPMM_K(1, true, 16, false) : CSB_SPMM_K(1, false, 16, false);
-    }
-    if (sh.nt == 2) return sh.two ? CSB_SPMM_K(2, true, 8, false) : CSB_SPMM_K(2, false, 8, false);
-    return sh.two ? CSB_SPMM_K(1, true, 8, false) : CSB_SPMM_K(1, false, 8, false);
+#define CSB_SPMM_KN(NT) \
+    if (sh.nw == 16) return sh.two ? CSB_SPMM_K(NT, true, 16) : CSB_SPMM_K(NT, false, 16); \
+    return sh.two ? CSB_SPMM_K(NT, true, 8) : CSB_SPMM_K(NT, false, 8);
+    if (sh.nt == 4) { CSB_SPMM_KN(4) }
+    if (sh.nt == 2) { CSB_SPMM_KN(2) }
+    CSB_SPMM_KN(1)
+#undef CSB_SPMM_KN
 #undef CSB_SPMM_K
 }
 
-int spmm_strided(const csb_matrix *mat, const float *p0, uint32_t n0, int64_t sj0, int64_t sn0, const float *p1,
-                 int64_t sj1, int64_t sn1, float *d_Y, int64_t ldy, int32_t batch, void *stream) {
-    const SpmmCall c{mat, p0, n0, sj0, sn0, p1, sj1, sn1, d_Y, ldy};
+int spmm_strided(const csb_matrix *mat, const float *p0, uint32_t n0, int64_t sj0, const float *p1,
+                 int64_t sj1, float *d_Y, int64_t ldy, int32_t batch, void *stream) {
+    const SpmmCall c{mat, p0, n0, sj0, p1, sj1, d_Y, ldy};
     SpmmShape sh;
     XSrc X;
     int rc = spmm_shape(c, batch, 1, &sh, &X);
@@ -928,7 +881,7 @@ int spmm_strided_multi(const SpmmCall *calls, int n, int32_t batch, void *stream
         for (int i = 0; i < n; ++i) {
             int rc = spmm_shape(calls[i], batch, (size_t)n, &sh[i], &J.X[i]);
             if (rc != CSB_OK) return rc;
-            same = same && sh[i].nt == sh[0].nt && sh[i].nw == sh[0].nw && sh[i].two == sh[0].two && sh[i].wide == sh[0].wide && sh[i].reg_parts == sh[0].reg_parts && sh[i].nq == sh[0].nq && sh[i].vf == sh[0].vf;
+            same = same && sh[i].nt == sh[0].nt && sh[i].nw == sh[0].nw && sh[i].two == sh[0].two && sh[i].reg_parts == sh[0].reg_parts && sh[i].nq == sh[0].nq && sh[i].vf == sh[0].vf;
             lds = std::max(lds, sh[i].lds);
             tiles = std::max(tiles, sh[i].tiles);
             J.m[i] = dev_mat(calls[i].mat);
@@ -948,7 +901,7 @@ int spmm_strided_multi(const SpmmCall *calls, int n, int32_t batch, void *stream
     }
     for (int i = 0; i < n; ++i) {
         const SpmmCall &c = calls[i];
-        int rc = spmm_strided(c.mat, c.p0, c.n0, c.sj0, c.sn0, c.p1, c.sj1, c.sn1, c.Y, c.ldy, batch, stream);
+        int rc = spmm_strided(c.mat, c.p0, c.n0, c.sj0, c.p1, c.sj1, c.Y, c.ldy, batch, stream);
         if (rc != CSB_OK) return rc;
     }
     return CSB_OK;
@@ -992,7 +945,7 @@ static int spmm_16bit(const char *who, int fmt, const csb_matrix *m, const uint1
     const int nq = reg_columns(tiles * (size_t)((batch + 127) / 128), batch), nwr = nq > 1 ? 8 : nw;
     const size_t lds_reg = (size_t)h.seg_meta + (size_t)nwr * acc_per_wave + (size_t)nwr * 64;
     if ((h.br == 16 || h.br == 32) && h.n_vals * 4 < 0x7fffff00ull && lds_reg <= (size_t)160 * 1024) {
-        XSrc X{(const float *)d_X, (uint32_t)h.cols, ld, 1u, (const float *)d_X, ld, 1u};
+        XSrc X{(const float *)d_X, (uint32_t)h.cols, ld, (const float *)d_X, ld};
         void *rargs[] = {&dm, &X, &d_Y, &ldy_, &b};
         const void *kern;
 #define CSB_R16(NW, NH, NQ) (half ? (const void *)spmm_reg16_kernel<NW, NH, CSB_VAL_F16, NQ> : (const void *)spmm_reg16_kernel<NW, NH, CSB_VAL_BF16, NQ>)
@@ -1036,5 +989,5 @@ extern "C" int csb_spmm(const csb_matrix *m, const float *d_X, int64_t ldx, floa
     if (!m || !d_X || !d_Y) { csb::set_error("csb_spmm: NULL pointer"); return CSB_EINVAL; }
     if (batch <= 0 || ldx < batch || ldy < batch) { csb::set_error("csb_spmm: batch <= 0 or a leading dimension below batch"); return CSB_EINVAL; }
     if (m->plan.valid && m->plan.split.active()) { csb::set_error("csb_spmm: matrix is planned for a GRU step"); return CSB_ESTATE; }
-    return csb::spmm_strided(m, d_X, (uint32_t)m->cols, ldx, 1, d_X, ldx, 1, d_Y, ldy, batch, stream);
+    return csb::spmm_strided(m, d_X, (uint32_t)m->cols, ldx, d_X, ldx, d_Y, ldy, batch, stream);
 }

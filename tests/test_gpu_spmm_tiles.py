@@ -7,6 +7,8 @@ import pytest
 import csb_inputs
 import oracle
 
+from paper_2005_05758_amd import CsbMatrix
+
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
@@ -37,3 +39,40 @@ def test_spmm_16bit_128_columns(fmt, name, R, C, br, bc, batch):
         torch.cuda.synchronize()
         got = Y.cpu().numpy().astype(np.float64)
         assert np.all(np.abs(got - ref) <= 2.0 * np.maximum(k, 1) * 2.0 ** -24 * absr + 1e-30)
+
+
+# The general form: any batch, any alignment.  Batches around 16, 32 and 64 columns per workgroup (the last
+# lanes move back to the batch's last right-hand sides), block sizes with partial 16-row slices and 16-column
+# passes, and tiles taller than 32 rows.
+@pytest.mark.parametrize("R,C,br,bc", [(70, 50, 16, 16), (200, 90, 64, 64), (150, 77, 33, 40), (8200, 41, 32, 32), (16400, 40, 64, 8)])
+@pytest.mark.parametrize("batch", [2, 15, 17, 31, 49, 63, 66])
+def test_spmm_any_batch(R, C, br, bc, batch):
+    m = csb_inputs.small_matrix(R + C + batch, R, C, br, bc, rate=3.0)
+    X = csb_inputs.make_vectors(batch, C, batch).reshape(C, batch)
+    M, Y = check_spmm(m.A, br, bc, X, tag="any-batch")
+    wide = torch.zeros((C, batch + 5), device="cuda")               # rows at odd word offsets
+    wide[:, 3:3 + batch] = torch.from_numpy(X).cuda()
+    wide[:, batch + 3:] = float("nan")                              # what lies beside the batch is never used
+    out = torch.full((R, batch + 3), 7.0, device="cuda")
+    M.spmm(wide[:, 3:3 + batch], out[:, 1:1 + batch])
+    torch.cuda.synchronize()
+    assert torch.all(out[:, 0] == 7.0) and torch.all(out[:, batch + 1:] == 7.0)
+    ref = oracle.matmat(m.A, X)
+    bound = 2.0 * np.maximum(np.count_nonzero(m.A, axis=1)[:, None], 1) * 2.0 ** -24 * oracle.matmat(np.abs(m.A), np.abs(X)) + 1e-30
+    assert np.all(np.abs(out[:, 1:1 + batch].cpu().numpy().astype(np.float64) - ref) <= bound)
+
+
+@pytest.mark.parametrize("batch", [5, 33, 70])
+def test_spmm_infinite_input(batch):
+    """An infinite input reaches the rows that hold an entry of its column, and no others."""
+    m = csb_inputs.small_matrix(5, 96, 64, 32, 32, rate=6.0)
+    col = int(np.flatnonzero(np.count_nonzero(m.A, axis=0))[-1])
+    X = csb_inputs.make_vectors(batch, 64, batch).reshape(64, batch)
+    X[col] = np.inf
+    M = CsbMatrix(m.A, 32, 32)
+    M.plan()
+    M.upload()
+    got = M.spmm(torch.from_numpy(X).cuda()).cpu().numpy()
+    hit = m.A[:, col] != 0
+    assert np.all(np.isinf(got[hit])) and np.all(np.sign(got[hit]) == np.sign(m.A[hit, col])[:, None])
+    assert np.all(np.isfinite(got[~hit]))
