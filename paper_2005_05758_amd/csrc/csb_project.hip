@@ -194,52 +194,57 @@ __global__ __launch_bounds__(256) void col_segment_keys_vec_kernel(const float *
 
 // One workgroup ranks the n <= 16384 segments of one block-column (block-row) and marks the k
 // weakest as pruned, "weaker" being the order of (key, position).  No sort: every thread keeps
-// 16 consecutive keys in registers; the key T of the k-th weakest is found eight bits at a time
+// P consecutive keys in registers; the key T of the k-th weakest is found eight bits at a time
 // from the highest bit on which the keys differ at all (a histogram of the digit over the keys
 // that still match, by LDS atomics -- sums of squares of one block-column agree on their top
 // exponent bits, and counting those would put every key into one bin -- then the digit whose
 // bin holds the k-th); then a segment is pruned if its key is below T, or equal to T and fewer
 // than (k - #below) equal keys lie at earlier positions.
-constexpr int kSelPer = 16;          // keys per thread
+// What bounds it: latency -- one workgroup per block-column, 256 of them on the 8192 x 8192 matrix,
+// and a chain of rounds.  So P is the smallest of 4, 8, 16 that covers n (a thread's atomics follow
+// one another), and every wavefront scans a round's 256 bins for itself, four to a lane: one
+// barrier per round.
+// Measured on 8192 x 8192, the whole projection: 135.3 -> 129.9 us (16 keys a thread, so half of the
+// threads idle, and three barriers a round before).
+template <int P>
 __global__ __launch_bounds__(1024) void select_kernel(const uint32_t *__restrict__ keys, uint8_t *__restrict__ keep,
                                                        const uint32_t n, const uint32_t k) {
     __shared__ uint32_t wsum[3][16];
-    __shared__ uint32_t hist[4][256];            // one histogram per digit
-    __shared__ uint32_t pick[2];                 // the digit that holds the k-th, and k inside its bin
+    __shared__ uint4 hist[4][64];                // one histogram of 256 bins per digit
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const size_t base = (size_t)blockIdx.x * n;
-    const uint32_t i0 = tid * kSelPer;
+    const uint32_t i0 = tid * P;
     if (k == 0 || k >= n) {                      // nothing / everything pruned
-        for (uint32_t q = 0; q < kSelPer; ++q)
+        for (uint32_t q = 0; q < P; ++q)
             if (i0 + q < n) keep[base + i0 + q] = k == 0 ? 1 : 0;
         return;
     }
-    uint32_t key[kSelPer];
-    bool valid[kSelPer];
-    const bool vec = (n & 15u) == 0;             // 16-byte accesses: every thread's run is whole and aligned
+    uint32_t key[P];
+    bool valid[P];
+    const bool vec = n % P == 0;                 // accesses of P keys (flags): every thread's run is whole and aligned
 #pragma unroll
-    for (int q = 0; q < kSelPer; ++q) valid[q] = i0 + q < n;
+    for (int q = 0; q < P; ++q) valid[q] = i0 + q < n;
     if (vec) {
         if (valid[0]) {
             const uint4 *src = (const uint4 *)(keys + base + i0);
 #pragma unroll
-            for (int v = 0; v < kSelPer / 4; ++v) {
+            for (int v = 0; v < P / 4; ++v) {
                 const uint4 w = src[v];
                 key[4 * v] = w.x; key[4 * v + 1] = w.y; key[4 * v + 2] = w.z; key[4 * v + 3] = w.w;
             }
         } else {
 #pragma unroll
-            for (int q = 0; q < kSelPer; ++q) key[q] = 0u;
+            for (int q = 0; q < P; ++q) key[q] = 0u;
         }
     } else {
 #pragma unroll
-        for (int q = 0; q < kSelPer; ++q) key[q] = valid[q] ? keys[base + i0 + q] : 0u;
+        for (int q = 0; q < P; ++q) key[q] = valid[q] ? keys[base + i0 + q] : 0u;
     }
     ((uint32_t *)hist)[tid] = 0u;                // 4 x 256 words, 1024 threads
     // bits on which every key agrees need no counting
     uint32_t all_and = 0xffffffffu, all_or = 0u;
 #pragma unroll
-    for (int q = 0; q < kSelPer; ++q)
+    for (int q = 0; q < P; ++q)
         if (valid[q]) { all_and &= key[q]; all_or |= key[q]; }
     for (int d = 32; d > 0; d >>= 1) {
         all_and &= (uint32_t)__shfl_xor((int)all_and, d, 64);
@@ -257,53 +262,62 @@ __global__ __launch_bounds__(1024) void select_kernel(const uint32_t *__restrict
         const int lo = hi >= 7 ? hi - 7 : 0;
         const uint32_t dmask = (2u << (hi - lo)) - 1u;
 #pragma unroll
-        for (int q = 0; q < kSelPer; ++q)
-            if (valid[q] && (key[q] & mask) == prefix) atomicAdd(&hist[round][(key[q] >> lo) & dmask], 1u);
+        for (int q = 0; q < P; ++q)
+            if (valid[q] && (key[q] & mask) == prefix) atomicAdd((uint32_t *)hist[round] + ((key[q] >> lo) & dmask), 1u);
         __syncthreads();
-        uint32_t h = 0, incl = 0;
-        if (tid < 256) {                         // inclusive scan of the 256 bins
-            h = hist[round][tid];
-            incl = h;
-            for (int d = 1; d < 64; d <<= 1) {
-                const uint32_t up = (uint32_t)__shfl_up((int)incl, d, 64);
-                if (lane >= (uint32_t)d) incl += up;
+        const uint4 h = hist[round][lane];       // bins 4 lane .. + 3
+        const uint32_t sum = h.x + h.y + h.z + h.w;
+        uint32_t incl = sum;
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t up = (uint32_t)__shfl_up((int)incl, d, 64);
+            if (lane >= (uint32_t)d) incl += up;
+        }
+        uint32_t below = incl - sum, digit = 4u * lane;
+        const unsigned long long hit = __ballot(below < kk && kk <= incl);      // the lane whose bins hold the k-th
+        if (kk > below + h.x) {
+            below += h.x; ++digit;
+            if (kk > below + h.y) {
+                below += h.y; ++digit;
+                if (kk > below + h.z) { below += h.z; ++digit; }
             }
-            if (lane == 63) wsum[0][wave] = incl;
         }
-        __syncthreads();
-        if (tid < 256) {
-            for (uint32_t w = 0; w < wave; ++w) incl += wsum[0][w];
-            const uint32_t excl = incl - h;
-            if (excl < kk && kk <= incl) { pick[0] = tid; pick[1] = kk - excl; }
-        }
-        __syncthreads();                         // (pick and wsum[0] are next written behind two more barriers)
-        prefix |= pick[0] << lo;
+        const int src = __builtin_ctzll(hit);
+        prefix |= (uint32_t)__builtin_amdgcn_readlane((int)digit, src) << lo;
         mask |= dmask << lo;
-        kk = pick[1];
+        kk = (uint32_t)__builtin_amdgcn_readlane((int)(kk - below), src);
     }
     // prefix is T; kk of the keys equal to T are pruned: the first ones by position
     uint32_t eq_wave = 0, eq_lower = 0;          // equal keys in the wavefront / in its lower lanes
 #pragma unroll
-    for (int q = 0; q < kSelPer; ++q) {
+    for (int q = 0; q < P; ++q) {
         const unsigned long long m = __ballot(valid[q] && key[q] == prefix);
         eq_wave += (uint32_t)__popcll(m);
         eq_lower += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
     }
-    __syncthreads();                             // (wsum[0] is free: the scans' readers are behind their rounds' last barrier)
     if (lane == 0) wsum[0][wave] = eq_wave;
     __syncthreads();
     uint32_t rank = eq_lower;
     for (uint32_t w = 0; w < wave; ++w) rank += wsum[0][w];
-    uint32_t flags[kSelPer / 4] = {};            // keep flags, one byte each
+    uint32_t flags[P / 4] = {};            // keep flags, one byte each
 #pragma unroll
-    for (int q = 0; q < kSelPer; ++q) {
+    for (int q = 0; q < P; ++q) {
         const bool eq = valid[q] && key[q] == prefix;
         const bool pruned = key[q] < prefix || (eq && rank < kk);
         rank += eq ? 1u : 0u;
         flags[q >> 2] |= (pruned ? 0u : 1u) << (8 * (q & 3));
         if (!vec && valid[q]) keep[base + i0 + q] = pruned ? 0 : 1;
     }
-    if (vec && valid[0]) *(uint4 *)(keep + base + i0) = make_uint4(flags[0], flags[1], flags[2], flags[3]);
+    if (vec && valid[0]) {
+        if constexpr (P == 4) *(uint32_t *)(keep + base + i0) = flags[0];
+        else if constexpr (P == 8) *(uint2 *)(keep + base + i0) = make_uint2(flags[0], flags[1]);
+        else *(uint4 *)(keep + base + i0) = make_uint4(flags[0], flags[1], flags[2], flags[3]);
+    }
+}
+
+static void launch_select(uint32_t groups, hipStream_t st, const uint32_t *keys, uint8_t *keep, uint32_t n, uint32_t k) {
+    if (n <= 4096) hipLaunchKernelGGL(select_kernel<4>, dim3(groups), dim3(1024), 0, st, keys, keep, n, k);
+    else if (n <= 8192) hipLaunchKernelGGL(select_kernel<8>, dim3(groups), dim3(1024), 0, st, keys, keep, n, k);
+    else hipLaunchKernelGGL(select_kernel<16>, dim3(groups), dim3(1024), 0, st, keys, keep, n, k);
 }
 
 // Z = W where both its row segment and its column segment survive, else +0.  A thread takes
@@ -455,12 +469,12 @@ extern "C" int csb_project(const float *d_W, int64_t rows, int64_t cols, int64_t
                 default: hipLaunchKernelGGL(row_segment_keys_kernel<-1>, grid_r, dim3(256), lds_rows, st, d_W, ld, R, C, BC, NBC, TR, TS, keys_r); break;
             }
         }
-        hipLaunchKernelGGL(select_kernel, dim3(NBC), dim3(1024), 0, st, keys_r, keep_r, R, prune_count(rows, rate));
+        launch_select(NBC, st, keys_r, keep_r, R, prune_count(rows, rate));
         if (rows8)
             hipLaunchKernelGGL(col_segment_keys_vec_kernel, dim3((C + 255) / 256, NBR), dim3(256), 0, st, d_W, ld, R, C, BR, BC, keep_r, keys_c);
         else
             hipLaunchKernelGGL(col_segment_keys_kernel, dim3((C + 255) / 256, NBR), dim3(256), 0, st, d_W, ld, R, C, BR, BC, keep_r, keys_c);
-        hipLaunchKernelGGL(select_kernel, dim3(NBR), dim3(1024), 0, st, keys_c, keep_c, C, prune_count(cols, rate));
+        launch_select(NBR, st, keys_c, keep_c, C, prune_count(cols, rate));
         if (vec4 && rows8 && BC % 4 == 0)
             hipLaunchKernelGGL(masked_copy_vec_kernel, dim3((C + 1023) / 1024, R / 8), dim3(256), 0, st,
                                d_W, ld, d_Z, ldz, R, C, BR, BC, keep_r, keep_c);
