@@ -26,6 +26,10 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint32_t uni_(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
+// First record segment of the rank-th row tile.  Where every tile's records fit one segment it is the rank
+// itself: one dependent trip to memory less before a launch of a few microseconds has any work.
+__device__ __forceinline__ uint32_t first_segment(const DevMat &m, uint32_t rank) { return m.one_seg ? rank : m.tile_seg0[rank]; }
+
 // Element (column j of A, right-hand side n) of the input, from one of two sources; the right-hand
 // sides of a column are contiguous.  Byte offsets fit 32 bits and the strides over j fit 24 bits
 // (checked on the host).
@@ -104,7 +108,8 @@ __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float 
     const uint8_t *const x0 = (const uint8_t *)(X.p0 + nstart);
     const uint8_t *const x1 = (const uint8_t *)(X.p1 + nstart) - (size_t)split4 * X.sj1;
 
-    for (uint32_t sg = m.tile_seg0[rank]; sg < m.tile_seg0[rank + 1]; ++sg) {
+    const uint32_t sg0 = first_segment(m, rank), sg1 = first_segment(m, rank + 1u);
+    for (uint32_t sg = sg0; sg < sg1; ++sg) {
         // ---- stage the segment's records ------------------------------------------------
         const SegRec *sp = m.segs + sg;
         const uint32_t vb0 = sp->vb0, nvbs = sp->nvbs, idx0 = sp->idx0, idx_bytes = sp->idx_bytes;
@@ -300,7 +305,8 @@ __global__ __launch_bounds__(NW * 64) void spmm_bf16_kernel(const DevMat m, cons
     const uint32_t ncol = bt0 + 4u * mrow;         // first of this lane's four right-hand sides (batch % 4 == 0)
     const uint32_t noff = (ncol < batch ? ncol : 0u) * 2u;   // bytes; one past the batch reads 0..3, never stored
 
-    for (uint32_t sg = m.tile_seg0[rank]; sg < m.tile_seg0[rank + 1]; ++sg) {
+    const uint32_t sg0 = first_segment(m, rank), sg1 = first_segment(m, rank + 1u);
+    for (uint32_t sg = sg0; sg < sg1; ++sg) {
         const SegRec *sp = m.segs + sg;
         const uint32_t vb0 = sp->vb0, nvbs = sp->nvbs, idx0 = sp->idx0, idx_bytes = sp->idx_bytes;
         const uint32_t ioff = nvbs * (uint32_t)sizeof(VbRec);
@@ -519,7 +525,8 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
 #pragma unroll
             for (int nt = 0; nt < 4; ++nt) D[h][q][nt] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
 
-    for (uint32_t sg = m.tile_seg0[rank]; sg < m.tile_seg0[rank + 1]; ++sg) {
+    const uint32_t sg0 = first_segment(m, rank), sg1 = first_segment(m, rank + 1u);
+    for (uint32_t sg = sg0; sg < sg1; ++sg) {
         // ---- stage the segment's records ------------------------------------------------
         const SegRec *sp = m.segs + sg;
         const uint32_t vb0 = sp->vb0, nvbs = sp->nvbs, idx0 = sp->idx0, idx_bytes = sp->idx_bytes;

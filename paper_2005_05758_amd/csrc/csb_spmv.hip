@@ -48,6 +48,7 @@ DevMat dev_mat(const csb_matrix *m) {
     d.tile_g0 = (const uint32_t *)(b + h.off_tile_g0);
     d.tile_seg0 = (const uint32_t *)(b + h.off_tile_seg0);
     d.segs = (const SegRec *)(b + h.off_segs);
+    d.one_seg = h.n_segs == h.n_nz_tiles;
     return d;
 }
 
