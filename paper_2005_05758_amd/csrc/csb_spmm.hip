@@ -552,6 +552,9 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
         // A block's data in LDS is four dependent reads deep (record, row slots, map, input offsets), as long as
         // its products; so records are read two blocks ahead and row slots one, and a block opens with
         // one wait: the map's.  (8192 x 8192 x 128 float32 63.4 -> 62.7 us, x 512 bfloat16 121.1 -> 118.6.)
+        // One source only: the two-source kernels have not the registers for it (16 wavefronts, 32 rows and 16-bit
+        // values went to scratch), and a recurrent step's wavefronts open too few blocks to gain by it.
+        constexpr bool kAhead = !TWO;
         auto read_rec = [&](uint32_t k) { return *(const uint4 *)(meta + min(k, nvbs - 1u) * (uint32_t)sizeof(VbRec)); };
         auto decode = [&](const uint4 v, uint32_t k) -> RegPass {
             RegPass p;
@@ -586,15 +589,23 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
             }
         };
         RegPass ahead = decode(read_rec(wave), wave);              // the next block ...
-        uint32_t ahead_slot = read_slot(ahead);                    // ... its rows' places
-        uint4 after = read_rec(wave + NW);                         // the record of the one after it
+        uint32_t ahead_slot = 0;                                   // ... its rows' places
+        uint4 after = make_uint4(0u, 0u, 0u, 0u);                  // the record of the one after it
+        if constexpr (kAhead) {
+            ahead_slot = read_slot(ahead);
+            after = read_rec(wave + NW);
+        }
         auto open_next = [&]() -> RegPass {
             const RegPass p = ahead;
-            const uint32_t slot = ahead_slot;
+            const uint32_t slot = kAhead ? ahead_slot : read_slot(p);
             read_cols(p);
-            ahead = decode(after, p.k + NW);
-            ahead_slot = read_slot(ahead);
-            after = read_rec(p.k + 2u * NW);
+            if constexpr (kAhead) {
+                ahead = decode(after, p.k + NW);
+                ahead_slot = read_slot(ahead);
+                after = read_rec(p.k + 2u * NW);
+            } else {
+                ahead = decode(read_rec(p.k + NW), p.k + NW);
+            }
             map_rows(p, slot);
             return p;
         };

@@ -1,0 +1,65 @@
+"""What the compiler made of the kernels: the gfx950 code in the built library, read with the
+toolchain's own tools.  No GPU."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_2005_05758_amd import build
+
+LLVM = "/opt/rocm/llvm/bin/"
+pytestmark = pytest.mark.skipif(not os.path.exists(LLVM + "llvm-readelf"), reason="no LLVM tools")
+
+
+@pytest.fixture(scope="module")
+def code_objects(tmp_path_factory):
+    """Paths of the gfx950 code objects bundled in the library, one per source file."""
+    if not os.path.exists(build.LIB):
+        build.build()
+    d = tmp_path_factory.mktemp("code")
+    fat = str(d / "fat.bin")
+    subprocess.run(["objcopy", "--dump-section", ".hip_fatbin=" + fat, build.LIB, str(d / "copy.so")], check=True)
+    data = open(fat, "rb").read()
+    magic, paths = b"__CLANG_OFFLOAD_BUNDLE__", []
+    for at in (m.start() for m in re.finditer(magic, data)):
+        pos = at + len(magic)
+        n, = struct.unpack_from("<Q", data, pos)
+        pos += 8
+        for _ in range(n):
+            off, size, length = struct.unpack_from("<QQQ", data, pos)
+            triple = data[pos + 24:pos + 24 + length].decode()
+            pos += 24 + length
+            if triple.startswith("hip") and size:
+                assert "gfx950" in triple
+                paths.append(str(d / f"{len(paths)}.co"))
+                with open(paths[-1], "wb") as f:
+                    f.write(data[at + off:at + off + size])
+    assert paths
+    return paths
+
+
+def _demangled(names):
+    out = subprocess.run(["c++filt"], input="\n".join(names), text=True, stdout=subprocess.PIPE, check=True).stdout.split("\n")
+    return [re.sub(r"\(.*", "", o).replace("void csb::", "") for o in out[:len(names)]]
+
+
+def _notes(paths):
+    """{kernel: bytes of scratch per lane}"""
+    found = []
+    for p in paths:
+        text = subprocess.run([LLVM + "llvm-readelf", "--notes", p], text=True, stdout=subprocess.PIPE, check=True).stdout
+        for entry in re.split(r"\n  - \.", text)[1:]:
+            name = re.search(r"\.?name: +(_Z\S+)", entry)
+            scratch = re.search(r"\.private_segment_fixed_size: +(\d+)", entry)
+            if name and scratch:
+                found.append((name.group(1), int(scratch.group(1))))
+    return dict(zip(_demangled([n for n, _ in found]), [s for _, s in found]))
+
+
+def test_batched_products_use_no_scratch(code_objects):
+    """The loops of the batched products count the loads in flight: a spilled register is one more."""
+    scratch = {k: s for k, s in _notes(code_objects).items() if k.startswith("spmm_")}
+    assert sum(k.startswith("spmm_reg_multi_kernel<true, 16, 2") for k in scratch) == 3      # the widest two-source forms
+    assert {k: s for k, s in scratch.items() if s} == {}
