@@ -24,6 +24,11 @@ namespace csb {
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 
+// A value that is the same in every lane, in a scalar register.  Two kernel arguments between which a lane
+// chooses (the strides of two sources) go through it: the compiler turns a choice between two arguments
+// into a per-lane load of the chosen one, a trip to memory in front of every load that needs it.
+// (24 of those per pair of passes in the kernels that take several products; without them, batch 64, us
+// per step: two GRU layers of 1024 in 16-row blocks 32.6 -> 25.4, two LSTM layers in 32-row blocks 23.0 -> 20.0.)
 __device__ __forceinline__ uint32_t uni_(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // First record segment of the rank-th row tile.  Where every tile's records fit one segment it is the rank
@@ -104,9 +109,9 @@ __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float 
     const uint32_t vf = uni_(m.val_fmt);                           // storage format of the value stream
     const uint32_t mrow = lane & 15u, kq = lane >> 4;              // A: row, column-in-4; B: right-hand sides, column-in-4
     const uint32_t nstart = min(bt0 + NT * mrow, batch - NT);      // this lane's first right-hand side (batch >= NT)
-    const uint32_t split4 = 4u * X.n0;
+    const uint32_t split4 = 4u * X.n0, sj0 = uni_(X.sj0), sj1 = uni_(X.sj1);   // (see uni_)
     const uint8_t *const x0 = (const uint8_t *)(X.p0 + nstart);
-    const uint8_t *const x1 = (const uint8_t *)(X.p1 + nstart) - (size_t)split4 * X.sj1;
+    const uint8_t *const x1 = (const uint8_t *)(X.p1 + nstart) - (size_t)split4 * sj1;
 
     const uint32_t sg0 = first_segment(m, rank), sg1 = first_segment(m, rank + 1u);
     for (uint32_t sg = sg0; sg < sg1; ++sg) {
@@ -163,7 +168,7 @@ __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float 
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 const bool first = !TWO || cb[s] < split4;
-                const uint8_t *src = (first ? x0 : x1) + (size_t)__umul24(cb[s], first ? X.sj0 : X.sj1);
+                const uint8_t *src = (first ? x0 : x1) + (size_t)__umul24(cb[s], first ? sj0 : sj1);
                 o.bv[s] = *(const vec_u *)src;
             }
         };
@@ -516,7 +521,9 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
         const uint32_t ncol = bt0 + 64u * q + 4u * mrow;
         nbyte[q] = (ncol < batch ? ncol : 0u) * (X16 ? 2u : 4u);   // (batch is a multiple of 4: the four are in or out together)
     }
-    const uint32_t split4 = 4u * X.n0;
+    const uint32_t split4 = 4u * X.n0, sj0 = uni_(X.sj0), sj1 = uni_(X.sj1);   // (see uni_)
+    // (the lane's own pointers: choosing one of them is a choice between registers)
+    const uint8_t *const x0 = (const uint8_t *)X.p0 + nbyte[0], *const x1 = (const uint8_t *)X.p1 + nbyte[0];
     floatx4 D[NH][NQ][4];
 #pragma unroll
     for (int h = 0; h < NH; ++h)
@@ -639,11 +646,11 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
                     }
                 if constexpr (TWO) {
                     const bool first = cb[s4] < split4;
-                    const uint8_t *src = first ? (const uint8_t *)X.p0 + __umul24(cb[s4], X.sj0) : (const uint8_t *)X.p1 + __umul24(cb[s4] - split4, X.sj1);
+                    const uint8_t *src = first ? x0 + __umul24(cb[s4], sj0) : x1 + __umul24(cb[s4] - split4, sj1);
 #pragma unroll
-                    for (int q = 0; q < NQ; ++q) o.bv[s4][q] = *(const float4 *)(src + nbyte[q]);
+                    for (int q = 0; q < NQ; ++q) o.bv[s4][q] = *(const float4 *)(src + (int)(nbyte[q] - nbyte[0]));
                 } else {
-                    const uint32_t joff = __umul24(cb[s4], X.sj0);
+                    const uint32_t joff = __umul24(cb[s4], sj0);
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) o.bv[s4][q] = *(const float4 *)((const uint8_t *)X.p0 + (size_t)(joff + nbyte[q]));
                 }
@@ -689,7 +696,7 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
             for (int i = 0; i < 4; ++i)      // (a column the block lacks reads its last one: finite, times a zero)
 #pragma unroll
                 for (int q = 0; q < NQ; ++q)
-                    o.xv[i][q] = *(const uint2 *)((const uint8_t *)X.p0 + (size_t)((__umul24(cb[i], X.sj0) >> 1) + nbyte[q]));
+                    o.xv[i][q] = *(const uint2 *)((const uint8_t *)X.p0 + (size_t)((__umul24(cb[i], sj0) >> 1) + nbyte[q]));
         };
         auto multiply16 = [&](const RegOps16<NH, NQ> &o) {
 #pragma unroll

@@ -63,3 +63,25 @@ def test_batched_products_use_no_scratch(code_objects):
     scratch = {k: s for k, s in _notes(code_objects).items() if k.startswith("spmm_")}
     assert sum(k.startswith("spmm_reg_multi_kernel<true, 16, 2") for k in scratch) == 3      # the widest two-source forms
     assert {k: s for k, s in scratch.items() if s} == {}
+
+
+def _vector_loads(paths, kernels):
+    """{kernel: number of vector memory loads in its code}"""
+    found = {}
+    for p in paths:
+        text = subprocess.run([LLVM + "llvm-objdump", "-d", "--no-show-raw-insn", p], text=True, stdout=subprocess.PIPE, check=True).stdout
+        parts = re.split(r"\n[0-9a-f]+ <(\S+)>:\n", text)
+        for name, body in zip(_demangled(parts[1::2]), parts[2::2]):
+            if re.match(kernels, name):
+                found[name] = len(re.findall(r"\t(?:global|flat|buffer)_load_", body))
+    return found
+
+
+def test_several_products_per_launch_load_no_arguments_per_lane(code_objects):
+    """The kernels that take several products find a product's pointers and strides among their
+    arguments; a lane that chooses between two sources must choose between registers.  Their loads
+    are those of the kernel that takes one product."""
+    loads = _vector_loads(code_objects, r"spmm_(reg_)?(multi_)?kernel<")
+    multi = [k for k in loads if "multi_" in k]
+    assert len(multi) == len(loads) - len(multi) == 48              # 12 of the general form, 36 of the register form
+    assert {k: loads[k] for k in multi if loads[k] != loads[k.replace("multi_", "")]} == {}
