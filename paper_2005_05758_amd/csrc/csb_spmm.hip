@@ -31,6 +31,10 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 // per step: two GRU layers of 1024 in 16-row blocks 32.6 -> 25.4, two LSTM layers in 32-row blocks 23.0 -> 20.0.)
 __device__ __forceinline__ uint32_t uni_(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
+// Product of two 24-bit numbers, modulo 2^32.  (__umul24's result is a signed int: the byte offset of an input
+// row 2 GiB and more into X must not be extended with its sign.)
+__device__ __forceinline__ uint32_t mul24_(uint32_t a, uint32_t b) { return (uint32_t)__umul24(a, b); }
+
 // First record segment of the rank-th row tile.  Where every tile's records fit one segment it is the rank
 // itself: one dependent trip to memory less before a launch of a few microseconds has any work.
 __device__ __forceinline__ uint32_t first_segment(const DevMat &m, uint32_t rank) { return m.one_seg ? rank : m.tile_seg0[rank]; }
@@ -168,7 +172,7 @@ __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float 
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 const bool first = !TWO || cb[s] < split4;
-                const uint8_t *src = (first ? x0 : x1) + (size_t)__umul24(cb[s], first ? sj0 : sj1);
+                const uint8_t *src = (first ? x0 : x1) + (size_t)mul24_(cb[s], first ? sj0 : sj1);
                 o.bv[s] = *(const vec_u *)src;
             }
         };
@@ -369,7 +373,7 @@ __global__ __launch_bounds__(NW * 64) void spmm_bf16_kernel(const DevMat m, cons
                 for (int i = 0; i < 4; ++i) {
                     const uint32_t jj = j0 + (uint32_t)i;
                     const uint32_t cb = colp[jj < p.c ? jj : 0u];  // 4 * column
-                    x[i] = *(const uint2 *)((const uint8_t *)Xb + (__umul24(cb, ldx) >> 1) + noff);
+                    x[i] = *(const uint2 *)((const uint8_t *)Xb + (mul24_(cb, ldx) >> 1) + noff);
                 }
                 // x[i] = right-hand sides 0..3 at column i; tile t wants columns 0..3 at right-hand side t
                 o.b[s][0] = make_uint2((x[0].x & 0xffffu) | (x[1].x << 16), (x[2].x & 0xffffu) | (x[3].x << 16));
@@ -646,11 +650,11 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
                     }
                 if constexpr (TWO) {
                     const bool first = cb[s4] < split4;
-                    const uint8_t *src = first ? x0 + __umul24(cb[s4], sj0) : x1 + __umul24(cb[s4] - split4, sj1);
+                    const uint8_t *src = first ? x0 + mul24_(cb[s4], sj0) : x1 + mul24_(cb[s4] - split4, sj1);
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) o.bv[s4][q] = *(const float4 *)(src + (int)(nbyte[q] - nbyte[0]));
                 } else {
-                    const uint32_t joff = __umul24(cb[s4], sj0);
+                    const uint32_t joff = mul24_(cb[s4], sj0);
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) o.bv[s4][q] = *(const float4 *)((const uint8_t *)X.p0 + (size_t)(joff + nbyte[q]));
                 }
@@ -696,7 +700,7 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
             for (int i = 0; i < 4; ++i)      // (a column the block lacks reads its last one: finite, times a zero)
 #pragma unroll
                 for (int q = 0; q < NQ; ++q)
-                    o.xv[i][q] = *(const uint2 *)((const uint8_t *)X.p0 + (size_t)((__umul24(cb[i], sj0) >> 1) + nbyte[q]));
+                    o.xv[i][q] = *(const uint2 *)((const uint8_t *)X.p0 + (size_t)((mul24_(cb[i], sj0) >> 1) + nbyte[q]));
         };
         auto multiply16 = [&](const RegOps16<NH, NQ> &o) {
 #pragma unroll

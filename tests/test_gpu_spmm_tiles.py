@@ -76,3 +76,33 @@ def test_spmm_infinite_input(batch):
     hit = m.A[:, col] != 0
     assert np.all(np.isinf(got[hit])) and np.all(np.sign(got[hit]) == np.sign(m.A[hit, col])[:, None])
     assert np.all(np.isfinite(got[~hit]))
+
+
+# Rows of X beyond 2 GiB (float32) and beyond 1 GiB (16-bit): offsets of more than 31 bits.  Few
+# right-hand sides in rows far apart; the general forms and, from 256 row tiles on, the register forms.
+@pytest.mark.parametrize("R,br,batch", [(70, 64, 5), (4096, 16, 64), (4096, 16, 68)])
+@pytest.mark.parametrize("fmt,name", [(None, "f32")] + FORMATS)
+def test_spmm_input_rows_far_apart(fmt, name, R, br, batch):
+    C, ld = 16380, 33400
+    first = 16192                                                   # entries in the last columns only
+    assert C * ld < 2 ** 30 and first * ld * (4 if fmt is None else 2) > 2 ** (31 if fmt is None else 30)
+    batch = batch if fmt is None else (batch + 3) // 4 * 4
+    m = csb_inputs.small_matrix(R + batch, R, C - first, br, 32, rate=4.0)
+    A = np.zeros((R, C), np.float32)
+    A[:, first:] = m.A
+    X = csb_inputs.make_vectors(batch, C - first, batch).reshape(C - first, batch)
+    if fmt is None:
+        M = CsbMatrix(A, br, 32)
+        M.plan()
+        M.upload()
+    else:
+        M = packed(A, br, 32, fmt)
+    A, X = (m.A, X) if fmt is None else (oracle.round_weights(m.A, name), oracle.round_weights(X, name).astype(np.float32))
+    wide = torch.empty((C, ld), dtype={"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[name], device="cuda")
+    wide[:, 4:4 + batch] = 0.0
+    wide[first:, 4:4 + batch] = torch.from_numpy(X).cuda()
+    Y = {"f32": M.spmm, "f16": M.spmm_half, "bf16": M.spmm_bfloat}[name](wide[:, 4:4 + batch])
+    torch.cuda.synchronize()
+    k = np.maximum(np.count_nonzero(A, axis=1)[:, None], 1)
+    err = np.abs(Y.cpu().numpy().astype(np.float64) - oracle.matmat(A, X))
+    assert np.all(err <= 2.0 * k * 2.0 ** -24 * oracle.matmat(np.abs(A), np.abs(X)) + 1e-30)

@@ -65,23 +65,40 @@ def test_batched_products_use_no_scratch(code_objects):
     assert {k: s for k, s in scratch.items() if s} == {}
 
 
-def _vector_loads(paths, kernels):
-    """{kernel: number of vector memory loads in its code}"""
+@pytest.fixture(scope="module")
+def code(code_objects):
+    """{kernel: its instructions}"""
     found = {}
-    for p in paths:
+    for p in code_objects:
         text = subprocess.run([LLVM + "llvm-objdump", "-d", "--no-show-raw-insn", p], text=True, stdout=subprocess.PIPE, check=True).stdout
         parts = re.split(r"\n[0-9a-f]+ <(\S+)>:\n", text)
-        for name, body in zip(_demangled(parts[1::2]), parts[2::2]):
-            if re.match(kernels, name):
-                found[name] = len(re.findall(r"\t(?:global|flat|buffer)_load_", body))
+        found.update(zip(_demangled(parts[1::2]), parts[2::2]))
     return found
 
 
-def test_several_products_per_launch_load_no_arguments_per_lane(code_objects):
+def test_several_products_per_launch_load_no_arguments_per_lane(code):
     """The kernels that take several products find a product's pointers and strides among their
     arguments; a lane that chooses between two sources must choose between registers.  Their loads
     are those of the kernel that takes one product."""
-    loads = _vector_loads(code_objects, r"spmm_(reg_)?(multi_)?kernel<")
+    loads = {k: len(re.findall(r"\t(?:global|flat|buffer)_load_", c)) for k, c in code.items() if re.match(r"spmm_(reg_)?(multi_)?kernel<", k)}
     multi = [k for k in loads if "multi_" in k]
     assert len(multi) == len(loads) - len(multi) == 48              # 12 of the general form, 36 of the register form
     assert {k: loads[k] for k in multi if loads[k] != loads[k.replace("multi_", "")]} == {}
+
+
+def test_input_offsets_are_unsigned(code):
+    """A batched product's input may be 4 GiB long: the byte offset of a row, a 24-bit product, is
+    neither extended with its sign nor shifted as a signed number."""
+    wrong = {}
+    for k, c in code.items():
+        if not k.startswith("spmm_"):
+            continue
+        products = set()
+        for line in c.split("\n"):
+            arith = re.match(r"\tv_ashrrev_i32\w* v\d+, \d+, (v\d+)", line)
+            if arith and arith.group(1) in products:
+                wrong[k] = wrong.get(k, 0) + 1
+            written = re.match(r"\t(?:v|global|buffer|ds)_\w+ (v\d+),", line)
+            if written:
+                (products.add if line.startswith("\tv_mul_u32_u24") else products.discard)(written.group(1))
+    assert sum(k.startswith("spmm_") for k in code) > 90 and wrong == {}
