@@ -56,7 +56,7 @@ template <> struct RhsVec<1> { typedef float type __attribute__((ext_vector_type
 template <> struct RhsVec<2> { typedef float type __attribute__((ext_vector_type(2))); };
 template <> struct RhsVec<4> { typedef float type __attribute__((ext_vector_type(4))); };
 
-// One pass: 16 columns (4 MFMA k-steps) of one 16-row slice of one virtual block.
+// One pass: up to 4 KS columns (KS MFMA k-steps) of one 16-row slice of one virtual block.
 struct Pass {
     uint32_t k;           // virtual block, counted inside the segment
     uint32_t m0, kc;      // first row of the slice, first column of the pass
@@ -69,22 +69,24 @@ struct Pass {
 
 template <int NT>
 struct Operands {
-    uint32_t av[4];                          // kernel values as stored
-    typename RhsVec<NT>::type bv[4];         // NT right-hand sides of the lane's column
+    static constexpr int KS = NT == 4 ? 4 : 8;    // k-steps (4 columns each) a pass has room for
+    uint32_t av[KS];                         // kernel values as stored
+    typename RhsVec<NT>::type bv[KS];        // NT right-hand sides of the lane's column
 };
 
-// What bounds it: vector instructions.  The products of a pruned gate matrix are tiny (13 x 13
-// kernels out of 64 x 64 blocks) and a wavefront has two or three passes of at most 16 NT MFMAs, so
-// a pass is written to cost few instructions: a lane reads its NT neighbouring right-hand sides
-// with one load (tile t of the MFMA holds the right-hand sides NT n + t; the loads are aligned to a
-// word, and lanes past the batch are moved back to its last NT right-hand sides, so any batch and
-// stride will do), what a block lacks repeats its last row or column instead of being branched
-// around, operands are masked in a block's last, partial k-step only, rows a slice lacks go to a
-// spare row of the accumulator instead of being predicated, and a pass always issues the same
-// loads, so that counted waits let those of the next two passes fly.
-// Measured against the form with a branch per k-step, value format and slice and masked operands (about
-// 480 instructions per pass): two LSTM layers of 1024 at batch 64 17.2 -> 16.2 us per step, two
-// Li-GRU layers of 512 at batch 33 12.3 -> 11.1.
+// What bounds it: instructions and load issue, not the matrix cores.  The products of a pruned gate matrix are
+// tiny (13 x 13 kernels out of 64 x 64 blocks, 7 x 7 out of 32 x 32), so a pass is written to cost little: a lane
+// reads its NT neighbouring right-hand sides with one load (tile t of the MFMA holds the right-hand sides
+// NT n + t; the loads are aligned to a word, and lanes past the batch are moved back to its last NT right-hand
+// sides, so any batch and stride will do), rows and columns a block lacks repeat its last ones instead of being
+// branched around, operands are masked in a block's last, partial k-step only, and rows a slice lacks go
+// to a spare row of the accumulator instead of being predicated.  K-steps a block lacks are not loaded, though:
+// their loads cost as much as those of the ones it has, and 16 wavefronts per workgroup hide what
+// conservative waits at the branches cost.  The room of a pass is 32 columns (16 at NT = 4, whose operands take
+// the registers): with 16, fuller blocks need another pass.  Nothing is loaded past a wavefront's last pass.
+// Measured on 8192 x 2048 at batch 16 / 3000 x 3000 in 64 x 64 blocks at batch 64 / two LSTM layers of 1024 at
+// batch 64, us: 8.8 / 15.1 / 14.5; four k-steps always loaded, two passes ahead, 16 columns: 10.8 / 17.1 / 15.6;
+// branches per k-step, value format and slice, masked operands throughout: 8.9 / 15.6 / 17.7.
 template <int NT, bool TWO, int NW>
 __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float *__restrict__ Y, const int64_t ldy,
                                           const uint32_t batch, const uint32_t block_x, const uint32_t block_y) {
@@ -92,6 +94,8 @@ __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float 
     typedef typename RhsVec<NT>::type vec;
     typedef vec vec_u __attribute__((aligned(4)));
     constexpr uint32_t NB = 16 * NT;               // batch columns per workgroup
+    constexpr int KS = Operands<NT>::KS;
+    constexpr uint32_t PC = 4 * KS;                // columns per pass
     constexpr uint32_t NTHR = NW * 64;             // NW wavefronts
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = uni_(tid >> 6);
     const uint32_t bt0 = block_y * NB;
@@ -145,36 +149,38 @@ __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float 
             p.desc = ioff + (uni_(v.z) - idx0);
             p.list = ioff + (uni_(v.w) - idx0);
         };
-        // The pass after p.  Past the wavefront's last one the fields stay (its loads are issued again
-        // and dropped) and only `valid` goes off.
+        // The pass after p; past the wavefront's last one only `valid` means anything.
         auto next_pass = [&](const Pass &p) -> Pass {
-            const bool cols = p.kc + 16u < p.c, rows = p.m0 + 16u < p.r, more = p.k + NW < nvbs;
+            const bool cols = p.kc + PC < p.c, rows = p.m0 + 16u < p.r, more = p.k + NW < nvbs;
             Pass q;
             open_vb(cols || rows || !more ? p.k : p.k + NW, q);
-            q.valid = p.valid && (cols || rows || more);
-            q.kc = cols ? p.kc + 16u : rows || more ? 0u : p.kc;
-            q.m0 = cols ? p.m0 : rows ? p.m0 + 16u : more ? 0u : p.m0;
+            q.valid = cols || rows || more;
+            q.kc = cols ? p.kc + PC : 0u;
+            q.m0 = cols ? p.m0 : rows ? p.m0 + 16u : 0u;
             return q;
         };
-        // Eight loads, always.  Rows and columns the block lacks repeat its last ones.
-        auto load_pass = [&](const Pass &p, Operands<NT> &o) {
+        // The loads of the k-steps the block has; those of the first two are issued in any case.  Rows and
+        // columns the block lacks repeat its last ones.
+        auto load_pass = [&](const Pass &p) -> Operands<NT> {
+            Operands<NT> o;                                        // (k-steps the block lacks stay undefined and unused)
             const uint32_t *gv = (const uint32_t *)m.vals + (vf == CSB_VAL_F32 ? p.val_off : p.val_off >> 1);
             const uint32_t arow = p.lane0 + min(p.m0 + mrow, p.r - 1u);
             const uint32_t half = vf == CSB_VAL_F32 ? 0u : 1u;     // 16-bit: a word per lane and PAIR of columns
-            uint32_t jc[4], cb[4];
+            uint32_t jc[KS], cb[KS];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < KS; ++s) {
                 jc[s] = min(p.kc + 4u * s + kq, p.c - 1u);
                 cb[s] = *(const uint16_t *)(meta + p.list + 2u * jc[s]);                   // 4 * column
             }
 #pragma unroll
-            for (int s = 0; s < 4; ++s) o.av[s] = gv[(jc[s] >> half) * (uint32_t)kWave + arow];
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < KS; ++s) {
+                if (s >= 2 && p.kc + 4u * s >= p.c) break;         // (uniform)
+                o.av[s] = gv[(jc[s] >> half) * (uint32_t)kWave + arow];
                 const bool first = !TWO || cb[s] < split4;
                 const uint8_t *src = (first ? x0 : x1) + (size_t)mul24_(cb[s], first ? sj0 : sj1);
                 o.bv[s] = *(const vec_u *)src;
             }
+            return o;
         };
         floatx4 D[NT];
         auto mult_pass = [&](const Pass &p, const Operands<NT> &o) {
@@ -184,7 +190,7 @@ __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float 
             }
             const uint32_t left = p.c - p.kc;                      // columns from here on
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < KS; ++s) {
                 if (4u * s >= left) break;                         // (uniform) k-steps the block does not have
                 uint32_t w = o.av[s];
                 vec b = o.bv[s];
@@ -202,7 +208,7 @@ __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float 
                 for (int nt = 0; nt < NT; ++nt)
                     D[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w), b[nt], D[nt], 0, 0, 0);
             }
-            if (left > 16u) return;                                // the slice has more columns
+            if (left > PC) return;                                 // the slice has more columns
             // lane holds rows 4 kq + i, right-hand sides NT mrow + t of each result; the rows of a slice
             // are distinct, so no two lanes meet in the accumulator (but in its spare row, which nobody
             // reads): all reads, then all writes
@@ -223,23 +229,18 @@ __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float 
                 *(vec *)(myacc + at[i]) = old[i];
             }
         };
-        Operands<NT> oa, ob, oc;                                   // three passes in flight
-        Pass pa, pb, pc;
+        Pass pa, pb;
         open_vb(wave, pa);
         pa.m0 = pa.kc = 0;
-        pa.valid = true;
-        load_pass(pa, oa);
-        pb = next_pass(pa);
-        load_pass(pb, ob);
-        while (true) {
-            pc = next_pass(pb); load_pass(pc, oc);
+        Operands<NT> oa = load_pass(pa), ob;
+        while (true) {                                             // the next pass's loads fly while one multiplies
+            pb = next_pass(pa);
+            if (pb.valid) ob = load_pass(pb);
             mult_pass(pa, oa);
             if (!pb.valid) break;
-            pa = next_pass(pc); load_pass(pa, oa);
+            pa = next_pass(pb);
+            if (pa.valid) oa = load_pass(pa);
             mult_pass(pb, ob);
-            if (!pc.valid) break;
-            pb = next_pass(pa); load_pass(pb, ob);
-            mult_pass(pc, oc);
             if (!pa.valid) break;
         }
     }
