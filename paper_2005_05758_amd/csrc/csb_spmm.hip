@@ -562,11 +562,12 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
         uint32_t irow4[NH];                                        // byte offset of this lane's kernel row in the current block's values, per part (bit 31: none)
         uint32_t parts = 0;
         // A block's data in LDS is four dependent reads deep (record, row slots, map, input offsets), as long as
-        // its products; so records are read two blocks ahead and row slots one, and a block opens with
-        // one wait: the map's.  (8192 x 8192 x 128 float32 63.4 -> 62.7 us, x 512 bfloat16 121.1 -> 118.6.)
-        // One source only: the two-source kernels have not the registers for it (16 wavefronts, 32 rows and 16-bit
-        // values went to scratch), and a recurrent step's wavefronts open too few blocks to gain by it.
-        constexpr bool kAhead = !TWO;
+        // its products.  With 128 right-hand sides of one source, records are read two blocks ahead and row
+        // slots one, and a block opens with one wait: the map's (8192 x 8192 x 128 float32 63.4 -> 62.7 us, x 512
+        // bfloat16 121.1 -> 118.6).  What that holds costs 10 to 20 registers, which the others have not got: two
+        // sources with 32 rows and 16-bit values went to scratch, and the 16-bit form of 16 rows and 64
+        // right-hand sides no longer had two workgroups on a CU (8192 x 2048 x 64 18.6 us, 16.0 without).
+        constexpr bool kAhead = !TWO && NQ == 2;
         auto read_rec = [&](uint32_t k) { return *(const uint4 *)(meta + min(k, nvbs - 1u) * (uint32_t)sizeof(VbRec)); };
         auto decode = [&](const uint4 v, uint32_t k) -> RegPass {
             RegPass p;
@@ -579,12 +580,13 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
             return p;
         };
         auto read_slot = [&](const RegPass &p) -> uint32_t { return meta[p.desc + 4u * (p.lane0 + (lane < p.r ? lane : 0u))]; };
-        uint32_t cb[4];                                            // 4 * column of this lane's columns of the pass opened last
-        auto read_cols = [&](const RegPass &p) {
+        // 4 * column of this lane's columns of pass p
+        auto read_cols = [&](const RegPass &p, uint32_t (&c)[4]) {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                cb[i] = *(const uint16_t *)(meta + p.list + 2u * min(p.kc + (X16 ? 4u * kq + i : 4u * i + kq), p.c - 1u));
+                c[i] = *(const uint16_t *)(meta + p.list + 2u * min(p.kc + (X16 ? 4u * kq + i : 4u * i + kq), p.c - 1u));
         };
+        uint32_t cb_ahead[4];                                      // (kAhead: of the pass opened last)
         // The map of block p: cleared, then every kernel row of the block enters itself at its tile row (the
         // wavefront's LDS operations execute in order).
         auto map_rows = [&](const RegPass &p, const uint32_t slot) {
@@ -600,41 +602,54 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
                 parts |= __ballot(ir != 0xffu) != 0ull ? 1u << h : 0u;
             }
         };
-        RegPass ahead = decode(read_rec(wave), wave);              // the next block ...
-        uint32_t ahead_slot = 0;                                   // ... its rows' places
-        uint4 after = make_uint4(0u, 0u, 0u, 0u);                  // the record of the one after it
+        RegPass ahead;                                             // the next block ...
+        uint32_t ahead_slot;                                       // ... its rows' places
+        uint4 after;                                               // the record of the one after it
         if constexpr (kAhead) {
+            ahead = decode(read_rec(wave), wave);
             ahead_slot = read_slot(ahead);
             after = read_rec(wave + NW);
         }
-        auto open_next = [&]() -> RegPass {
-            const RegPass p = ahead;
-            const uint32_t slot = kAhead ? ahead_slot : read_slot(p);
-            read_cols(p);
+        auto open = [&](uint32_t k) -> RegPass {                   // block k of the segment; blocks are opened in order
+            RegPass p;
+            uint32_t slot;
             if constexpr (kAhead) {
-                ahead = decode(after, p.k + NW);
+                p = ahead;
+                slot = ahead_slot;
+                read_cols(p, cb_ahead);
+                ahead = decode(after, k + NW);
                 ahead_slot = read_slot(ahead);
-                after = read_rec(p.k + 2u * NW);
+                after = read_rec(k + 2u * NW);
             } else {
-                ahead = decode(read_rec(p.k + NW), p.k + NW);
+                p = decode(read_rec(k), k);
+                slot = read_slot(p);
             }
             map_rows(p, slot);
             return p;
         };
-        // The pass after p.  (Only LDS is read on the way: both sides of the branch leave the count of the
-        // global loads in flight alone, so the compiler's counted waits stay exact.)  Past the
-        // wavefront's last pass some block of the segment is opened again: its loads are dropped.
+        // The pass after p.  Only LDS is read on the way, so the count of the global loads in flight is the same
+        // on every path and the compiler's counted waits stay exact.  Past the wavefront's last pass some
+        // block of the segment is opened again: its loads are dropped.  (Without the read-ahead a block
+        // is opened again for its further passes, too: a branch around that takes registers.)
         auto advance = [&](const RegPass &p) -> RegPass {
-            if (p.kc + 16u >= p.c) return open_next();             // (uniform)
+            const bool same = p.kc + 16u < p.c;                    // (uniform)
             RegPass q = p;
-            q.kc = p.kc + 16u;
-            read_cols(q);
+            if constexpr (kAhead) {
+                if (!same) return open(p.k + NW);
+                q.kc = p.kc + 16u;
+                read_cols(q, cb_ahead);
+            } else {
+                q = open(same ? p.k : p.k + NW);
+                q.kc = same ? p.kc + 16u : 0u;
+            }
             return q;
         };
         // 4 NH + 4 NQ loads, always.  (Uses irow4 / parts of the block opened last: p's.)
         auto issue = [&](const RegPass &p, RegOps<NH, NQ> &o) {
             uint32_t ja[4];
             o.parts = parts;
+            uint32_t cb[4];
+            if constexpr (kAhead) { for (int i = 0; i < 4; ++i) cb[i] = cb_ahead[i]; } else read_cols(p, cb);
 #pragma unroll
             for (int s4 = 0; s4 < 4; ++s4) {
                 const uint32_t jj = p.kc + 4u * s4 + kq;
@@ -689,6 +704,8 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
         // 2 NH + 4 NQ loads, always, and one 16-column MFMA per part and tile.
         auto issue16 = [&](const RegPass &p, RegOps16<NH, NQ> &o) {
             o.parts = parts;
+            uint32_t cb[4];
+            if constexpr (kAhead) { for (int i = 0; i < 4; ++i) cb[i] = cb_ahead[i]; } else read_cols(p, cb);
             const uint32_t j0 = p.kc + 4u * kq;                                  // this lane's four columns
             const uint32_t w0 = j0 < p.c ? (j0 >> 1) * 256u : 0x3fffff00u;       // words of the pairs (j0, j0 + 1), (j0 + 2, j0 + 3);
             const uint32_t w1 = j0 + 2u < p.c ? (j0 >> 1) * 256u + 256u : 0x3fffff00u;   // a pair the block lacks: past the stream
@@ -725,7 +742,7 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
         };
         if constexpr (X16) {
             RegOps16<NH, NQ> oa, ob;
-            RegPass pa = open_next(), pb;
+            RegPass pa = open(wave), pb;
             issue16(pa, oa);
             while (true) {
                 pb = advance(pa);
@@ -740,7 +757,7 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
             continue;                                              // (the next segment)
         }
         RegOps<NH, NQ> oa, ob;
-        RegPass pa = open_next(), pb;
+        RegPass pa = open(wave), pb;
         issue(pa, oa);
         while (true) {
             pb = advance(pa);

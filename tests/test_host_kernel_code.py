@@ -46,23 +46,30 @@ def _demangled(names):
 
 
 def _notes(paths):
-    """{kernel: bytes of scratch per lane}"""
+    """{kernel: (bytes of scratch per lane, vector registers)}"""
     found = []
     for p in paths:
         text = subprocess.run([LLVM + "llvm-readelf", "--notes", p], text=True, stdout=subprocess.PIPE, check=True).stdout
         for entry in re.split(r"\n  - \.", text)[1:]:
             name = re.search(r"\.?name: +(_Z\S+)", entry)
-            scratch = re.search(r"\.private_segment_fixed_size: +(\d+)", entry)
-            if name and scratch:
-                found.append((name.group(1), int(scratch.group(1))))
-    return dict(zip(_demangled([n for n, _ in found]), [s for _, s in found]))
+            numbers = [re.search(r"\." + k + r": +(\d+)", entry) for k in ("private_segment_fixed_size", "vgpr_count")]
+            if name and all(numbers):
+                found.append((name.group(1), tuple(int(n.group(1)) for n in numbers)))
+    return dict(zip(_demangled([n for n, _ in found]), [v for _, v in found]))
 
 
 def test_batched_products_use_no_scratch(code_objects):
     """The loops of the batched products count the loads in flight: a spilled register is one more."""
-    scratch = {k: s for k, s in _notes(code_objects).items() if k.startswith("spmm_")}
+    scratch = {k: v[0] for k, v in _notes(code_objects).items() if k.startswith("spmm_")}
     assert sum(k.startswith("spmm_reg_multi_kernel<true, 16, 2") for k in scratch) == 3      # the widest two-source forms
     assert {k: s for k, s in scratch.items() if s} == {}
+
+
+def test_16_row_products_of_16_bit_leave_room_for_two_workgroups(code_objects):
+    """Two workgroups of 16 wavefronts share a CU where a wavefront takes at most 64 of the 512 registers
+    of a lane: the products of 16 rows by 64 right-hand sides in 16 bits."""
+    registers = {k: v[1] for k, v in _notes(code_objects).items() if re.match(r"spmm_reg16_kernel<16, 1, [12], 1>", k)}
+    assert len(registers) == 2 and all(v <= 64 for v in registers.values()), registers
 
 
 @pytest.fixture(scope="module")
