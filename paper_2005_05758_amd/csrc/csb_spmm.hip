@@ -67,9 +67,8 @@ struct Pass {
     bool valid;
 };
 
-template <int NT>
-struct Operands {
-    static constexpr int KS = NT == 4 ? 4 : 8;    // k-steps (4 columns each) a pass has room for
+template <int NT, int KS>
+struct Operands {                            // of up to KS k-steps of 4 columns each
     uint32_t av[KS];                         // kernel values as stored
     typename RhsVec<NT>::type bv[KS];        // NT right-hand sides of the lane's column
 };
@@ -82,20 +81,22 @@ struct Operands {
 // branched around, operands are masked in a block's last, partial k-step only, and rows a slice lacks go
 // to a spare row of the accumulator instead of being predicated.  K-steps a block lacks are not loaded, though:
 // their loads cost as much as those of the ones it has, and 16 wavefronts per workgroup hide what
-// conservative waits at the branches cost.  The room of a pass is 32 columns (16 at NT = 4, whose operands take
-// the registers): with 16, fuller blocks need another pass.  Nothing is loaded past a wavefront's last pass.
+// conservative waits at the branches cost.  The 8 of the 64-column form on tall tiles (NT = 4) do not: there a pass
+// always issues the same loads and the waits are counted (8192 x 8192 in 64 x 64 blocks at batch 256: 111 -> 102 us).
+// The room of a pass is 32 columns (16 at NT = 4, whose operands take the registers, and where blocks are no
+// wider): with 16, fuller blocks need another pass.  Nothing is loaded past a wavefront's last pass.
 // Measured on 8192 x 2048 at batch 16 / 3000 x 3000 in 64 x 64 blocks at batch 64 / two LSTM layers of 1024 at
 // batch 64, us: 8.8 / 15.1 / 14.5; four k-steps always loaded, two passes ahead, 16 columns: 10.8 / 17.1 / 15.6;
 // branches per k-step, value format and slice, masked operands throughout: 8.9 / 15.6 / 17.7.
-template <int NT, bool TWO, int NW>
+template <int NT, bool TWO, int NW, int KS>
 __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float *__restrict__ Y, const int64_t ldy,
                                           const uint32_t batch, const uint32_t block_x, const uint32_t block_y) {
     extern __shared__ float4 smem4[];
     typedef typename RhsVec<NT>::type vec;
     typedef vec vec_u __attribute__((aligned(4)));
     constexpr uint32_t NB = 16 * NT;               // batch columns per workgroup
-    constexpr int KS = Operands<NT>::KS;
     constexpr uint32_t PC = 4 * KS;                // columns per pass
+    constexpr bool kCounted = NT == 4 && NW == 8;  // every pass issues the same loads
     constexpr uint32_t NTHR = NW * 64;             // NW wavefronts
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = uni_(tid >> 6);
     const uint32_t bt0 = block_y * NB;
@@ -159,10 +160,10 @@ __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float 
             q.m0 = cols ? p.m0 : rows ? p.m0 + 16u : 0u;
             return q;
         };
-        // The loads of the k-steps the block has; those of the first two are issued in any case.  Rows and
-        // columns the block lacks repeat its last ones.
-        auto load_pass = [&](const Pass &p) -> Operands<NT> {
-            Operands<NT> o;                                        // (k-steps the block lacks stay undefined and unused)
+        // The loads of the k-steps the block has; those of the first two (kCounted: of all) are issued in any
+        // case.  Rows and columns the block lacks repeat its last ones.
+        auto load_pass = [&](const Pass &p) -> Operands<NT, KS> {
+            Operands<NT, KS> o;                                        // (k-steps the block lacks stay undefined and unused)
             const uint32_t *gv = (const uint32_t *)m.vals + (vf == CSB_VAL_F32 ? p.val_off : p.val_off >> 1);
             const uint32_t arow = p.lane0 + min(p.m0 + mrow, p.r - 1u);
             const uint32_t half = vf == CSB_VAL_F32 ? 0u : 1u;     // 16-bit: a word per lane and PAIR of columns
@@ -174,7 +175,7 @@ __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float 
             }
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
-                if (s >= 2 && p.kc + 4u * s >= p.c) break;         // (uniform)
+                if (s >= (kCounted ? KS : 2) && p.kc + 4u * s >= p.c) break;         // (uniform)
                 o.av[s] = gv[(jc[s] >> half) * (uint32_t)kWave + arow];
                 const bool first = !TWO || cb[s] < split4;
                 const uint8_t *src = (first ? x0 : x1) + (size_t)mul24_(cb[s], first ? sj0 : sj1);
@@ -183,7 +184,7 @@ __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float 
             return o;
         };
         floatx4 D[NT];
-        auto mult_pass = [&](const Pass &p, const Operands<NT> &o) {
+        auto mult_pass = [&](const Pass &p, const Operands<NT, KS> &o) {
             if (p.kc == 0) {                                       // (uniform) a new slice
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) D[nt] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -232,16 +233,29 @@ __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float 
         Pass pa, pb;
         open_vb(wave, pa);
         pa.m0 = pa.kc = 0;
-        Operands<NT> oa = load_pass(pa), ob;
-        while (true) {                                             // the next pass's loads fly while one multiplies
-            pb = next_pass(pa);
-            if (pb.valid) ob = load_pass(pb);
-            mult_pass(pa, oa);
-            if (!pb.valid) break;
-            pa = next_pass(pb);
-            if (pa.valid) oa = load_pass(pa);
-            mult_pass(pb, ob);
-            if (!pa.valid) break;
+        Operands<NT, KS> oa = load_pass(pa), ob;
+        if constexpr (kCounted) {
+            while (true) {                                         // (loads outside of branches: the waits are counted)
+                pb = next_pass(pa);
+                if (!pb.valid) { mult_pass(pa, oa); break; }
+                ob = load_pass(pb);
+                mult_pass(pa, oa);
+                pa = next_pass(pb);
+                if (!pa.valid) { mult_pass(pb, ob); break; }
+                oa = load_pass(pa);
+                mult_pass(pb, ob);
+            }
+        } else {
+            while (true) {                                         // the next pass's loads fly while one multiplies
+                pb = next_pass(pa);
+                if (pb.valid) ob = load_pass(pb);
+                mult_pass(pa, oa);
+                if (!pb.valid) break;
+                pa = next_pass(pb);
+                if (pa.valid) oa = load_pass(pa);
+                mult_pass(pb, ob);
+                if (!pa.valid) break;
+            }
         }
     }
     __syncthreads();
@@ -259,10 +273,10 @@ __device__ __forceinline__ void spmm_body(const DevMat &m, const XSrc &X, float 
     }
 }
 
-template <int NT, bool TWO, int NW>
+template <int NT, bool TWO, int NW, int KS>
 __global__ __launch_bounds__(NW * 64) void spmm_kernel(const DevMat m, const XSrc X, float *__restrict__ Y,
                                                              const int64_t ldy, const uint32_t batch) {
-    spmm_body<NT, TWO, NW>(m, X, Y, ldy, batch, blockIdx.x, blockIdx.y);
+    spmm_body<NT, TWO, NW, KS>(m, X, Y, ldy, batch, blockIdx.x, blockIdx.y);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -812,11 +826,11 @@ struct SpmmJobs {
     float *Y[kMaxJobsPerLaunch];
     int64_t ldy[kMaxJobsPerLaunch];
 };
-template <int NT, bool TWO, int NW>
+template <int NT, bool TWO, int NW, int KS>
 __global__ __launch_bounds__(NW * 64) void spmm_multi_kernel(const SpmmJobs J, const uint32_t batch) {
     const uint32_t j = blockIdx.z;
     if (blockIdx.x >= J.m[j].n_nz_tiles + J.m[j].n_zero_tiles) return;      // the grid is as wide as the widest product
-    spmm_body<NT, TWO, NW>(J.m[j], J.X[j], J.Y[j], J.ldy[j], batch, blockIdx.x, blockIdx.y);
+    spmm_body<NT, TWO, NW, KS>(J.m[j], J.X[j], J.Y[j], J.ldy[j], batch, blockIdx.x, blockIdx.y);
 }
 
 template <bool TWO, int NW, int NH, int VF, int NQ>
@@ -829,6 +843,9 @@ __global__ __launch_bounds__(NW * 64) void spmm_reg_multi_kernel(const SpmmJobs 
 // Launch shape of one product: batch columns per workgroup (16 nt), wavefronts per workgroup.
 struct SpmmShape {
     int nt, nw;
+    int ks;                 // k-steps a pass of the general form has room for: 8 (32 columns), or 4 at NT = 4 and where
+                            // blocks are no wider than 16: half the registers, more workgroups on a CU (6727 x 4661 in
+                            // 16 x 16 blocks at batch 6: 34.0 -> 27.0 us)
     bool two;
     int reg_parts;          // 64 columns, row tiles of 16 or 32 rows: the kernel that keeps the results in
                             // registers, with this many 16-row parts (else 0; four parts do not fit the
@@ -870,6 +887,7 @@ static int spmm_shape(const SpmmCall &c, int32_t batch, size_t launch_wgs_factor
     if (batch >= 48 && wgs(4) * launch_wgs_factor >= 256 && acc_lds(4, 8) <= (size_t)kLdsBudget) nt = 4;
     const bool fits16 = acc_lds(nt, 16) <= (size_t)kLdsBudget;
     const int nw = fits16 && (nt == 4 || wgs(nt) * launch_wgs_factor < 2 * 256) ? 16 : 8;
+    const int ks = nt == 4 || h.bc <= 16 ? 4 : 8;
     // The register-accumulating kernels: row tiles of 16 or 32 rows, 16-byte aligned rows of the input, batch in
     // fours (their 32-bit byte offsets into the value stream must stay below the out-of-range marker).
     const bool aligned = ((uintptr_t)c.p0 % 16 == 0) && c.sj0 % 4 == 0 && (!two || (((uintptr_t)c.p1 % 16 == 0) && c.sj1 % 4 == 0));
@@ -878,17 +896,17 @@ static int spmm_shape(const SpmmCall &c, int32_t batch, size_t launch_wgs_factor
     const int reg_parts = (nt == 4 && aligned && batch % 4 == 0 && (h.br == 16 || h.br == 32) && h.n_vals * 4 < 0x7fffff00ull &&
                            (size_t)h.seg_meta + (size_t)nwr * reg_wave <= (size_t)160 * 1024) ? (int)h.br / 16 : 0;
     if (reg_parts)
-        *out = SpmmShape{nt, nwr, two, reg_parts, nq, (int)h.val_fmt, (size_t)h.seg_meta + (size_t)nwr * reg_wave, (unsigned)tiles,
+        *out = SpmmShape{nt, nwr, ks, two, reg_parts, nq, (int)h.val_fmt, (size_t)h.seg_meta + (size_t)nwr * reg_wave, (unsigned)tiles,
                          (unsigned)((batch + 64 * nq - 1) / (64 * nq))};
     else
-        *out = SpmmShape{nt, nw, two, 0, 1, (int)h.val_fmt, acc_lds(nt, nw), (unsigned)tiles, (unsigned)((batch + 16 * nt - 1) / (16 * nt))};
+        *out = SpmmShape{nt, nw, ks, two, 0, 1, (int)h.val_fmt, acc_lds(nt, nw), (unsigned)tiles, (unsigned)((batch + 16 * nt - 1) / (16 * nt))};
     return CSB_OK;
 }
 
 // The kernel instantiation for a launch shape (one product per launch, or several).
 template <bool MULTI>
 static const void *spmm_kernel_for(const SpmmShape &sh) {
-#define CSB_SPMM_K(NT, TWO, NW) (MULTI ? (const void *)spmm_multi_kernel<NT, TWO, NW> : (const void *)spmm_kernel<NT, TWO, NW>)
+#define CSB_SPMM_K(NT, TWO, NW, KS) (MULTI ? (const void *)spmm_multi_kernel<NT, TWO, NW, KS> : (const void *)spmm_kernel<NT, TWO, NW, KS>)
     if (sh.reg_parts) {
 #define CSB_SPMM_RV(TWO, NW, NH, VF, NQ) (MULTI ? (const void *)spmm_reg_multi_kernel<TWO, NW, NH, VF, NQ> : (const void *)spmm_reg_kernel<TWO, NW, NH, VF, NQ>)
 #define CSB_SPMM_R(TWO, NW, NH, NQ) (sh.vf == CSB_VAL_F16 ? CSB_SPMM_RV(TWO, NW, NH, CSB_VAL_F16, NQ) : sh.vf == CSB_VAL_BF16 ? CSB_SPMM_RV(TWO, NW, NH, CSB_VAL_BF16, NQ) : CSB_SPMM_RV(TWO, NW, NH, CSB_VAL_F32, NQ))
@@ -902,12 +920,14 @@ static const void *spmm_kernel_for(const SpmmShape &sh) {
 #undef CSB_SPMM_R
 #undef CSB_SPMM_RV
     }
-#define CSB_SPMM_KN(NT) \
-    if (sh.nw == 16) return sh.two ? CSB_SPMM_K(NT, true, 16) : CSB_SPMM_K(NT, false, 16); \
-    return sh.two ? CSB_SPMM_K(NT, true, 8) : CSB_SPMM_K(NT, false, 8);
-    if (sh.nt == 4) { CSB_SPMM_KN(4) }
-    if (sh.nt == 2) { CSB_SPMM_KN(2) }
-    CSB_SPMM_KN(1)
+#define CSB_SPMM_KN(NT, KS) \
+    if (sh.nw == 16) return sh.two ? CSB_SPMM_K(NT, true, 16, KS) : CSB_SPMM_K(NT, false, 16, KS); \
+    return sh.two ? CSB_SPMM_K(NT, true, 8, KS) : CSB_SPMM_K(NT, false, 8, KS);
+    if (sh.nt == 4) { CSB_SPMM_KN(4, 4) }
+    if (sh.nt == 2 && sh.ks == 4) { CSB_SPMM_KN(2, 4) }
+    if (sh.nt == 2) { CSB_SPMM_KN(2, 8) }
+    if (sh.ks == 4) { CSB_SPMM_KN(1, 4) }
+    CSB_SPMM_KN(1, 8)
 #undef CSB_SPMM_KN
 #undef CSB_SPMM_K
 }
@@ -944,7 +964,7 @@ int spmm_strided_multi(const SpmmCall *calls, int n, int32_t batch, void *stream
         for (int i = 0; i < n; ++i) {
             int rc = spmm_shape(calls[i], batch, (size_t)n, &sh[i], &J.X[i]);
             if (rc != CSB_OK) return rc;
-            same = same && sh[i].nt == sh[0].nt && sh[i].nw == sh[0].nw && sh[i].two == sh[0].two && sh[i].reg_parts == sh[0].reg_parts && sh[i].nq == sh[0].nq && sh[i].vf == sh[0].vf;
+            same = same && sh[i].nt == sh[0].nt && sh[i].nw == sh[0].nw && sh[i].ks == sh[0].ks && sh[i].two == sh[0].two && sh[i].reg_parts == sh[0].reg_parts && sh[i].nq == sh[0].nq && sh[i].vf == sh[0].vf;
             lds = std::max(lds, sh[i].lds);
             tiles = std::max(tiles, sh[i].tiles);
             J.m[i] = dev_mat(calls[i].mat);

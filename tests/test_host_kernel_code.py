@@ -89,7 +89,7 @@ def test_several_products_per_launch_load_no_arguments_per_lane(code):
     are those of the kernel that takes one product."""
     loads = {k: len(re.findall(r"\t(?:global|flat|buffer)_load_", c)) for k, c in code.items() if re.match(r"spmm_(reg_)?(multi_)?kernel<", k)}
     multi = [k for k in loads if "multi_" in k]
-    assert len(multi) == len(loads) - len(multi) == 48              # 12 of the general form, 36 of the register form
+    assert len(multi) == len(loads) - len(multi) == 56              # 20 of the general form, 36 of the register form
     assert {k: loads[k] for k in multi if loads[k] != loads[k.replace("multi_", "")]} == {}
 
 
