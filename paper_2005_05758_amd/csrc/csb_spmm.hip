@@ -861,9 +861,16 @@ struct SpmmShape {
 // the launch at 128 columns each).
 static int reg_columns(size_t wgs128, int32_t batch) { return batch > 64 && wgs128 >= 256 ? 2 : 1; }
 
+// Row tiles with many blocks (of the n products that share a launch, on average): 12 and more for each of 8 wavefronts.
+static bool long_tiles(const SpmmCall *calls, int n) {
+    uint64_t blocks = 0, tiles = 0;
+    for (int i = 0; i < n; ++i) { blocks += calls[i].mat->plan.hdr.n_vbs; tiles += calls[i].mat->plan.hdr.n_nz_tiles; }
+    return blocks >= 96 * tiles;
+}
+
 // Checks one product's operands and chooses its launch shape; `launch_wgs_factor` products of
 // this size share the launch, which counts when the launch is sized against the GPU's 256 CUs.
-static int spmm_shape(const SpmmCall &c, int32_t batch, size_t launch_wgs_factor, SpmmShape *out, XSrc *X) {
+static int spmm_shape(const SpmmCall &c, int32_t batch, size_t launch_wgs_factor, bool long_tiles, SpmmShape *out, XSrc *X) {
     const csb_matrix *mat = c.mat;
     if (!mat->plan.valid || !mat->uploaded || !mat->d_buf) { set_error("csb_spmm: matrix not planned and uploaded"); return CSB_ESTATE; }
     const DevHeader &h = mat->plan.hdr;
@@ -878,13 +885,17 @@ static int spmm_shape(const SpmmCall &c, int32_t batch, size_t launch_wgs_factor
     const bool two = c.n0 < (uint32_t)h.cols;
     // batch columns per workgroup: the widest form whose launch still gives every CU (256) a workgroup;
     // 16 wavefronts share a tile's blocks when their accumulator tiles fit LDS and the launch alone would
-    // not give every CU two workgroups (64 columns: always when they fit), else 8
+    // not give every CU two workgroups (64 columns: always when they fit), else 8.  64 columns by 8 wavefronts
+    // (tiles of more than 36 rows) read a tile's blocks half as often as 32 do, and their merge is twice as long: they
+    // pay where a wavefront has many blocks.  us at 32 / 64 columns, 64 x 64 blocks, 5 blocks per wavefront:
+    // 8192 x 300 x 97 in blocks of 48 11.7 / 14.3, 8192 x 2048 x 129 39.0 / 48.1, two GRU layers of 2048 at batch 64
+    // 38.6 / 41.4; 16 per wavefront: 8192 x 8192 x 128 75 / 52; 12: 8192 x 4000 x 128 in blocks of 40 55.1 / 54.3.
     const size_t tiles = (size_t)h.n_nz_tiles + h.n_zero_tiles;
     auto wgs = [&](int n) { return tiles * (size_t)((batch + 16 * n - 1) / (16 * n)); };
     auto acc_lds = [&](int n, int waves) { return (size_t)h.seg_meta + (size_t)waves * (h.br + 1) * 16 * n * sizeof(float); };
     int nt = 1;
     if (h.br <= 128 && batch > 16 && wgs(2) * launch_wgs_factor >= 256) nt = 2;
-    if (batch >= 48 && wgs(4) * launch_wgs_factor >= 256 && acc_lds(4, 8) <= (size_t)kLdsBudget) nt = 4;
+    if (batch >= 48 && wgs(4) * launch_wgs_factor >= 256 && acc_lds(4, long_tiles || h.br <= 32 ? 8 : 16) <= (size_t)kLdsBudget) nt = 4;
     const bool fits16 = acc_lds(nt, 16) <= (size_t)kLdsBudget;
     const int nw = fits16 && (nt == 4 || wgs(nt) * launch_wgs_factor < 2 * 256) ? 16 : 8;
     const int ks = nt == 4 || h.bc <= 16 ? 4 : 8;
@@ -937,7 +948,7 @@ int spmm_strided(const csb_matrix *mat, const float *p0, uint32_t n0, int64_t sj
     const SpmmCall c{mat, p0, n0, sj0, p1, sj1, d_Y, ldy};
     SpmmShape sh;
     XSrc X;
-    int rc = spmm_shape(c, batch, 1, &sh, &X);
+    int rc = spmm_shape(c, batch, 1, long_tiles(&c, 1), &sh, &X);
     if (rc != CSB_OK) return rc;
     DevMat dm = dev_mat(mat);
     uint32_t b = (uint32_t)batch;
@@ -961,11 +972,13 @@ int spmm_strided_multi(const SpmmCall *calls, int n, int32_t batch, void *stream
     if (same) {
         size_t lds = 0;
         unsigned tiles = 0;
+        const bool many = long_tiles(calls, n);
         for (int i = 0; i < n; ++i) {
-            int rc = spmm_shape(calls[i], batch, (size_t)n, &sh[i], &J.X[i]);
+            int rc = spmm_shape(calls[i], batch, (size_t)n, many, &sh[i], &J.X[i]);
             if (rc != CSB_OK) return rc;
-            same = same && sh[i].nt == sh[0].nt && sh[i].nw == sh[0].nw && sh[i].ks == sh[0].ks && sh[i].two == sh[0].two && sh[i].reg_parts == sh[0].reg_parts && sh[i].nq == sh[0].nq && sh[i].vf == sh[0].vf;
+            same = same && sh[i].nt == sh[0].nt && sh[i].nw == sh[0].nw && sh[i].two == sh[0].two && sh[i].reg_parts == sh[0].reg_parts && sh[i].nq == sh[0].nq && sh[i].vf == sh[0].vf;
             lds = std::max(lds, sh[i].lds);
+            sh[0].ks = std::max(sh[0].ks, sh[i].ks);               // (the wider pass takes any block)
             tiles = std::max(tiles, sh[i].tiles);
             J.m[i] = dev_mat(calls[i].mat);
             J.Y[i] = calls[i].Y;
