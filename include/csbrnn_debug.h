@@ -36,6 +36,13 @@ int csb_debug_spmv_stamps(const csb_matrix *m, const float *d_x, float *d_y, voi
 size_t csb_debug_stream_read_out_floats(void);
 int csb_debug_stream_read(const void *d_buf, size_t bytes, float *d_out, void *stream);
 
+/*
+ * Right-hand sides per workgroup (64 or 128) that csb_spmm (bits16 = 0) and csb_spmm_bfloat / csb_spmm_half
+ * (bits16 = 1) choose on a plan of `row_tiles` row tiles of 16 or 32 rows, where the form that keeps
+ * its results in registers runs.  Host only.
+ */
+int csb_debug_spmm_columns(int64_t row_tiles, int32_t rows_per_tile, int32_t batch, int32_t bits16);
+
 #ifdef __cplusplus
 }
 #endif

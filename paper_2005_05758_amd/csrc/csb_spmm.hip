@@ -18,6 +18,7 @@
 
 #include "csb_internal.hpp"
 #include "csb_kernels.hpp"
+#include "csbrnn_debug.h"
 
 namespace csb {
 
@@ -856,10 +857,21 @@ struct SpmmShape {
     unsigned tiles, batch_tiles;
 };
 
-// How many times 64 right-hand sides a workgroup of the register-accumulating kernels takes: 128 when
-// the batch has them and every one of the 256 CUs still gets a workgroup (`wgs128`: workgroups of
-// the launch at 128 columns each).
-static int reg_columns(size_t wgs128, int32_t batch) { return batch > 64 && wgs128 >= 256 ? 2 : 1; }
+// How many times 64 right-hand sides a workgroup of the register-accumulating kernels takes, for `tiles` row tiles
+// of `rows` rows in the launch and right-hand sides of 32 or 16 bits.  128 halve what is done per block, and
+// where every one of the 256 CUs has a workgroup of them, what counts is the number of turns the workgroups take
+// over the CUs (a CU holds one of either kind, or two, which then share its units): the last turn may be
+// nearly empty, and so may the last 64 right-hand sides, whose products are computed all the same.  A turn
+// at 128 takes 1.6 to 1.75 times as long as at 64 (32-row tiles, float32), 1.3 to 1.45 (16-bit right-hand sides), 1.55
+// to 1.65 (16-row tiles).  us at 64 / 128: 8192 x 8192 float32 x 128 72 / 63, x 132 106 / 123, x 256 140 / 124, x 260 174 /
+// 183; bfloat16 x 132 65 / 61; 8224 x 4096 float32 x 128 55.6 / 61.7, x 452 165 / 157; 4096 x 2048 x 260 34.8 / 37.5; 4300 x
+// 2048 in 16-row tiles x 132 42 / 47, x 196 54 / 48.
+static int reg_columns(size_t tiles, uint32_t rows, int32_t batch, bool bits16) {
+    const size_t wgs64 = tiles * (size_t)((batch + 63) / 64), wgs128 = tiles * (size_t)((batch + 127) / 128);
+    if (batch <= 64 || wgs128 < 256) return 1;
+    const size_t turn128 = rows <= 16 ? 16 : bits16 ? 14 : 17;                // ten times a turn's length against 64
+    return (wgs128 + 255) / 256 * turn128 < (wgs64 + 255) / 256 * 10 ? 2 : 1;
+}
 
 // Row tiles with many blocks (of the n products that share a launch, on average): 12 and more for each of 8 wavefronts.
 static bool long_tiles(const SpmmCall *calls, int n) {
@@ -903,7 +915,7 @@ static int spmm_shape(const SpmmCall &c, int32_t batch, size_t launch_wgs_factor
     // fours (their 32-bit byte offsets into the value stream must stay below the out-of-range marker).
     const bool aligned = ((uintptr_t)c.p0 % 16 == 0) && c.sj0 % 4 == 0 && (!two || (((uintptr_t)c.p1 % 16 == 0) && c.sj1 % 4 == 0));
     const size_t reg_wave = (size_t)h.br * 64 * sizeof(float) + 64;
-    const int nq = reg_columns(wgs(8) * launch_wgs_factor, batch), nwr = nq > 1 ? 8 : nw;
+    const int nq = reg_columns(tiles * launch_wgs_factor, h.br, batch, false), nwr = nq > 1 ? 8 : nw;
     const int reg_parts = (nt == 4 && aligned && batch % 4 == 0 && (h.br == 16 || h.br == 32) && h.n_vals * 4 < 0x7fffff00ull &&
                            (size_t)h.seg_meta + (size_t)nwr * reg_wave <= (size_t)160 * 1024) ? (int)h.br / 16 : 0;
     if (reg_parts)
@@ -1038,7 +1050,7 @@ static int spmm_16bit(const char *who, int fmt, const csb_matrix *m, const uint1
     const bool half = fmt == CSB_VAL_F16;
     // row tiles of 16 or 32 rows: the kernel that keeps its results in registers
     const size_t tiles = (size_t)h.n_nz_tiles + h.n_zero_tiles;
-    const int nq = reg_columns(tiles * (size_t)((batch + 127) / 128), batch), nwr = nq > 1 ? 8 : nw;
+    const int nq = reg_columns(tiles, h.br, batch, true), nwr = nq > 1 ? 8 : nw;
     const size_t lds_reg = (size_t)h.seg_meta + (size_t)nwr * acc_per_wave + (size_t)nwr * 64;
     if ((h.br == 16 || h.br == 32) && h.n_vals * 4 < 0x7fffff00ull && lds_reg <= (size_t)160 * 1024) {
         XSrc X{(const float *)d_X, (uint32_t)h.cols, ld, (const float *)d_X, ld};
@@ -1086,4 +1098,8 @@ extern "C" int csb_spmm(const csb_matrix *m, const float *d_X, int64_t ldx, floa
     if (batch <= 0 || ldx < batch || ldy < batch) { csb::set_error("csb_spmm: batch <= 0 or a leading dimension below batch"); return CSB_EINVAL; }
     if (m->plan.valid && m->plan.split.active()) { csb::set_error("csb_spmm: matrix is planned for a GRU step"); return CSB_ESTATE; }
     return csb::spmm_strided(m, d_X, (uint32_t)m->cols, ldx, d_X, ldx, d_Y, ldy, batch, stream);
+}
+
+extern "C" int csb_debug_spmm_columns(int64_t row_tiles, int32_t rows_per_tile, int32_t batch, int32_t bits16) {
+    return 64 * csb::reg_columns((size_t)row_tiles, (uint32_t)rows_per_tile, batch, bits16 != 0);
 }
