@@ -139,28 +139,32 @@ __global__ __launch_bounds__(256) void row_segment_keys_vec_kernel(const float *
 
 // keys[bi * C + c] for column segment (bi, c) of the row-pruned matrix: thread per segment,
 // c fastest (every row of the segment is read coalesced).  Any shape.  What bounds it: latency, so the
-// flags of 16 rows are read together, then the rows that survive among them; a row past the segment's
-// end counts as pruned, and a pruned row adds +0, which leaves the sum as it is.
+// flags of G rows are read together, then the rows that survive among them; a row past the segment's
+// end counts as pruned, and a pruned row adds +0, which leaves the sum as it is.  G is 16, or the power of two that
+// holds a shorter segment: with 16 flags for one or two rows, loads of flags are all the kernel does.
 // Measured with masked_copy_kernel below, whole projection: 8001 x 7777, blocks of 32, 357 -> 208 us;
 // 1023 x 777, blocks of 16, 37 -> 25 us (one row at a time, and four columns of a row per thread, before).
+// Whole projection, 2048 x 2048 in blocks of 1 / 2, 2000 x 2001 in blocks of 6, us: 153 / 76 / 45; with 16 throughout 249 / 122 / 49 (this
+// kernel alone 114 / 59 / 10.9; one row at a time 19 / 13 / 9.4).
+template <uint32_t G>
 __global__ __launch_bounds__(256) void col_segment_keys_kernel(const float *__restrict__ W, const int64_t ld,
                                                                  const uint32_t R, const uint32_t C, const uint32_t BR,
                                                                  const uint32_t BC, const uint8_t *__restrict__ keep_r,
                                                                  uint32_t *__restrict__ keys) {
-    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x, bi = blockIdx.y;
+    const uint32_t c = blockIdx.x * 256u + threadIdx.x, bi = blockIdx.y;
     if (c >= C) return;
     const uint32_t r0 = bi * BR, r1 = min(R, r0 + BR);
     const uint8_t *kr = keep_r + (size_t)(c / BC) * R;
     float s = 0.0f;
-    for (uint32_t i = r0; i < r1; i += 16) {
-        uint8_t f[16];
-        float v[16];
+    for (uint32_t i = r0; i < r1; i += G) {
+        uint8_t f[G];
+        float v[G];
 #pragma unroll
-        for (uint32_t q = 0; q < 16; ++q) f[q] = kr[min(i + q, r1 - 1u)];
+        for (uint32_t q = 0; q < G; ++q) f[q] = kr[min(i + q, r1 - 1u)];
 #pragma unroll
-        for (uint32_t q = 0; q < 16; ++q) v[q] = f[q] && i + q < r1 ? W[(size_t)(i + q) * ld + c] : 0.0f;
+        for (uint32_t q = 0; q < G; ++q) v[q] = f[q] && i + q < r1 ? W[(size_t)(i + q) * ld + c] : 0.0f;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) s = fmaf(v[q], v[q], s);
+        for (uint32_t q = 0; q < G; ++q) s = fmaf(v[q], v[q], s);
     }
     keys[(size_t)bi * C + c] = rank_key(s);
 }
@@ -488,8 +492,14 @@ extern "C" int csb_project(const float *d_W, int64_t rows, int64_t cols, int64_t
         launch_select(NBC, st, keys_r, keep_r, R, prune_count(rows, rate));
         if (rows8)
             hipLaunchKernelGGL(col_segment_keys_vec_kernel, dim3((C + 255) / 256, NBR), dim3(256), 0, st, d_W, ld, R, C, BR, BC, keep_r, keys_c);
-        else
-            hipLaunchKernelGGL(col_segment_keys_kernel, dim3((C + 255) / 256, NBR), dim3(256), 0, st, d_W, ld, R, C, BR, BC, keep_r, keys_c);
+        else {
+            const dim3 grid_c((C + 255) / 256, NBR);
+            if (BR > 8) hipLaunchKernelGGL(col_segment_keys_kernel<16>, grid_c, dim3(256), 0, st, d_W, ld, R, C, BR, BC, keep_r, keys_c);
+            else if (BR > 4) hipLaunchKernelGGL(col_segment_keys_kernel<8>, grid_c, dim3(256), 0, st, d_W, ld, R, C, BR, BC, keep_r, keys_c);
+            else if (BR > 2) hipLaunchKernelGGL(col_segment_keys_kernel<4>, grid_c, dim3(256), 0, st, d_W, ld, R, C, BR, BC, keep_r, keys_c);
+            else if (BR > 1) hipLaunchKernelGGL(col_segment_keys_kernel<2>, grid_c, dim3(256), 0, st, d_W, ld, R, C, BR, BC, keep_r, keys_c);
+            else hipLaunchKernelGGL(col_segment_keys_kernel<1>, grid_c, dim3(256), 0, st, d_W, ld, R, C, BR, BC, keep_r, keys_c);
+        }
         launch_select(NBR, st, keys_c, keep_c, C, prune_count(cols, rate));
         if (vec4 && rows8 && BC % 4 == 0)
             hipLaunchKernelGGL(masked_copy_vec_kernel, dim3((C + 1023) / 1024, R / 8), dim3(256), 0, st,

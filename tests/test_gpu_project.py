@@ -44,7 +44,10 @@ def check_project(W, br, bc, rate, tag="", f64_too=False):
     # the 16-byte forms of the kernels: whole blocks of 16 / 32 / 64 columns, with a ragged last
     # group of rows, more than 256 blocks in a row, and row counts that are no multiple of 8
     (100, 128, 16, 32, 5.0), (72, 320, 8, 64, 9.0), (40, 9600, 8, 32, 12.0), (24, 4800, 8, 16, 7.0),
-    (264, 544, 24, 32, 10.0)])
+    (264, 544, 24, 32, 10.0),
+    # column segments of 1 to 17 rows, ragged last ones
+    (33, 70, 1, 3, 3.0), (37, 41, 2, 2, 4.0), (50, 300, 3, 5, 6.0), (61, 90, 5, 9, 5.0), (52, 60, 9, 4, 8.0), (77, 66, 15, 16, 4.0),
+    (70, 130, 17, 32, 6.0)])
 def test_project_small_shapes(R, C, br, bc, rate):
     rng = np.random.default_rng(R * 7 + C)
     check_project(rng.normal(0, 0.05, (R, C)).astype(np.float32), br, bc, rate, tag="gauss", f64_too=True)

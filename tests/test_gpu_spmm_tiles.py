@@ -19,14 +19,16 @@ from test_gpu_val16 import FORMATS, packed      # noqa: E402
 # 256 row tiles and more: every compute unit gets a workgroup of 128 columns.  Batches one step
 # below, at and above a tile; 16- and 32-row tiles; blocks of one and of several column passes.
 @pytest.mark.parametrize("R,C,br,bc,batch", [(8192, 70, 32, 16, 68), (8192, 40, 32, 40, 128), (8190, 33, 32, 32, 132),
-                                             (4100, 130, 16, 32, 124), (2060, 60, 16, 64, 260)])
+                                             (4100, 130, 16, 32, 124), (2060, 60, 16, 64, 260), (8190, 33, 32, 32, 196),
+                                             (4100, 130, 16, 32, 196)])
 def test_spmm_128_columns(R, C, br, bc, batch):
     m = csb_inputs.small_matrix(R + C + batch, R, C, br, bc, rate=4.0)
     check_spmm(m.A, br, bc, csb_inputs.make_vectors(batch, C, batch), tag="128-columns")
 
 
 @pytest.mark.parametrize("fmt,name", FORMATS)
-@pytest.mark.parametrize("R,C,br,bc,batch", [(8192, 70, 32, 16, 68), (8190, 33, 32, 32, 132), (4100, 130, 16, 32, 128)])
+@pytest.mark.parametrize("R,C,br,bc,batch", [(8192, 70, 32, 16, 68), (8190, 33, 32, 32, 132), (4100, 130, 16, 32, 128),
+                                             (4100, 130, 16, 32, 196)])
 def test_spmm_16bit_128_columns(fmt, name, R, C, br, bc, batch):
     m = csb_inputs.small_matrix(R + C + batch, R, C, br, bc, rate=4.0)
     X = csb_inputs.make_vectors(batch, C, batch).reshape(C, batch)
@@ -106,3 +108,60 @@ def test_spmm_input_rows_far_apart(fmt, name, R, br, batch):
     k = np.maximum(np.count_nonzero(A, axis=1)[:, None], 1)
     err = np.abs(Y.cpu().numpy().astype(np.float64) - oracle.matmat(A, X))
     assert np.all(err <= 2.0 * k * 2.0 ** -24 * oracle.matmat(np.abs(A), np.abs(X)) + 1e-30)
+
+
+# Row tiles of 750 blocks, whose records take several segments, among empty ones up to 256 tiles: the register
+# forms of 64 and 128 right-hand sides, whose wavefronts open block after block and start again in every segment.
+@pytest.mark.parametrize("R,br", [(8192, 32), (4096, 16)])
+@pytest.mark.parametrize("fmt,name", [(None, "f32")] + FORMATS)
+def test_spmm_long_row_tiles(fmt, name, R, br):
+    C, rows = 12000, 2 * br
+    m = csb_inputs.small_matrix(21, rows, C, br, 16, rate=2.0)
+    A = np.zeros((R, C), np.float32)
+    A[br:br + rows] = m.A
+    if fmt is None:
+        M = CsbMatrix(A, br, 16)
+        M.plan()
+        M.upload()
+    else:
+        M = packed(A, br, 16, fmt)
+    Aq = m.A if fmt is None else oracle.round_weights(m.A, name)
+    k = np.maximum(np.count_nonzero(m.A, axis=1)[:, None], 1)
+    for batch in (64, 128):
+        X = csb_inputs.make_vectors(batch, C, batch).reshape(C, batch)
+        if fmt is not None:
+            X = oracle.round_weights(X, name).astype(np.float32)
+        Xd = torch.from_numpy(X).cuda()
+        Y = M.spmm(Xd) if fmt is None else M.spmm_bfloat(Xd.to(torch.bfloat16)) if name == "bf16" else M.spmm_half(Xd.to(torch.float16))
+        torch.cuda.synchronize()
+        got = Y.cpu().numpy().astype(np.float64)
+        ref, absr = oracle.matmat(Aq, X), oracle.matmat(np.abs(Aq), np.abs(X))
+        assert np.all(np.abs(got[br:br + rows] - ref) <= 2.0 * k * 2.0 ** -24 * absr + 1e-30)
+        assert not got[:br].any() and not got[br + rows:].any()
+
+
+# Two sources (x_t and h_{t-1}), one layer and two per launch: batches that take 64 columns without being
+# multiples of four, and the register forms of 64 and 128.  256 row tiles of 16 rows, or 128 of 32 and two layers.
+@pytest.mark.parametrize("block", [16, 32])
+@pytest.mark.parametrize("batch", [50, 63, 64, 68, 128, 132])
+@pytest.mark.parametrize("fmt,name", [(None, "f32"), FORMATS[0]])
+def test_rnn_batch_tiles(fmt, name, block, batch):
+    from paper_2005_05758_amd import CsbRnn
+    T, H = 3, 1024
+    wl = csb_inputs.make_rnn(csb_inputs.RnnConfig("t", csb_inputs.LSTM, 2, 40, H, block, 12.0, "binomial", 0.05, batch, T, 90 + batch))
+    Ws = [CsbMatrix(w.A, w.br, w.bc) for w in wl.W]
+    if fmt is not None:
+        for w in Ws:
+            w.set_value_format(fmt)
+    rnn = CsbRnn(csb_inputs.LSTM, 40, H, Ws, [torch.from_numpy(b).cuda() for b in wl.bias])
+    for w in Ws:
+        w.upload()
+    rng = np.random.default_rng(batch)
+    h0, c0 = (rng.uniform(-0.5, 0.5, (2, batch, H)).astype(np.float32) for _ in range(2))
+    W = [w.A if fmt is None else oracle.round_weights(w.A, name) for w in wl.W]
+    ref = oracle.rnn_forward(csb_inputs.LSTM, W, wl.bias, wl.x, 40, H, h0=h0, c0=c0)
+    got = rnn.forward(torch.from_numpy(wl.x).cuda(), torch.from_numpy(h0).cuda(), torch.from_numpy(c0).cuda())
+    torch.cuda.synchronize()
+    err = [float(np.max(np.abs(g.cpu().numpy() - r))) for g, r in zip(got, ref)]
+    print(f"[tiles] rnn block {block} batch {batch} {name}: {err}", flush=True)
+    assert max(err) <= 1e-4
