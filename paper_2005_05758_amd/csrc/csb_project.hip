@@ -339,9 +339,10 @@ static void launch_select(uint32_t groups, hipStream_t st, const uint32_t *keys,
 // whatever the alignment; the flags of all its rows come first, then what survives is read together.
 // Measured on 8191 x 8192, blocks of 32, where only the row flags are unaligned: 245 -> 198 us for the whole
 // projection (a thread took four columns of one row, 16 bytes at a time, before).
-// NT: stores that do not stay behind in the caches, where every row of Z starts on a cache line (128 bytes):
-// 8191 x 8192 198 -> 152 us.  A line that two wavefronts share is better merged in the cache: 8192 x 8191
-// 200 -> 209 us with NT.
+// NT: stores that do not stay behind in the caches, where every row of Z starts on a cache line (128 bytes) and Z is
+// half of the memory-side cache (256 MB) or more: 8191 x 8192 184 -> 141 us.  A line that two wavefronts share is better merged
+// in the cache: 8192 x 8191 200 -> 209 us with NT.  A smaller Z is what the next kernel reads: 4095 x 4096 and a kernel that
+// doubles Z 81 us with NT, 75 without (the projection alone 55 and 56), 3001 x 4096 62 and 58.
 constexpr int kMaskedCopyRows = 8;
 template <bool NT>
 __global__ __launch_bounds__(256) void masked_copy_kernel(const float *W, const int64_t ld, float *Z,
@@ -506,7 +507,7 @@ extern "C" int csb_project(const float *d_W, int64_t rows, int64_t cols, int64_t
                                d_W, ld, d_Z, ldz, R, C, BR, BC, keep_r, keep_c);
         else {
             const dim3 grid_m((C + 255) / 256, (R + kMaskedCopyRows - 1) / kMaskedCopyRows);
-            const bool lines = ldz % 32 == 0 && (uintptr_t)d_Z % 128 == 0;
+            const bool lines = ldz % 32 == 0 && (uintptr_t)d_Z % 128 == 0 && (uint64_t)R * C * sizeof(float) >= 128u << 20;
             if (lines) hipLaunchKernelGGL(masked_copy_kernel<true>, grid_m, dim3(256), 0, st, d_W, ld, d_Z, ldz, R, C, BR, BC, keep_r, keep_c);
             else hipLaunchKernelGGL(masked_copy_kernel<false>, grid_m, dim3(256), 0, st, d_W, ld, d_Z, ldz, R, C, BR, BC, keep_r, keep_c);
         }
