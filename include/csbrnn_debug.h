@@ -43,6 +43,12 @@ int csb_debug_stream_read(const void *d_buf, size_t bytes, float *d_out, void *s
  */
 int csb_debug_spmm_columns(int64_t row_tiles, int32_t rows_per_tile, int32_t batch, int32_t bits16);
 
+/*
+ * Whether csb_rnn_forward runs a batch on the resident kernel (1) or on the batched products (0) when the layouts
+ * of both are uploaded.  Host only.
+ */
+int csb_debug_rnn_prefers_resident(const csb_rnn *rnn, int32_t batch);
+
 #ifdef __cplusplus
 }
 #endif

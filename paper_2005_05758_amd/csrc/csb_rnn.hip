@@ -25,6 +25,7 @@
 
 #include "csb_internal.hpp"
 #include "csb_kernels.hpp"
+#include "csbrnn_debug.h"
 
 namespace csb {
 
@@ -1157,8 +1158,11 @@ static int forward_resident_batch(const csb_rnn *r, const float *d_x, const floa
 // slot, 1700 for the exchange of h_t between workgroups, 6 per workgroup; the forms above 32 slots spill and cost
 // half as much again) times 1.3, plus 0.12 us per further XCD an instance spans, twice for the
 // cells with two dependent products per step; the batch runs in rounds of as many sequences
-// as instances fit.  Batched MFMA path: its launches per diagonal, plus the products at about
-// 12 TFLOP/s.
+// as instances fit.  Batched MFMA path: a product and a cell launch for every kMaxJobsPerLaunch layers of a
+// diagonal, 8 to 9 us as the host enqueues them, about 1 more per layer, 1.8 times that for the cells with two
+// products, plus the products at about 25 TFLOP/s.  us per step, resident / batched: LSTM 153 -> 512 (10x) at batch 32
+// 5.9 / 8.9, 64 11.8 / 9.0; GRU 256 -> 1024 (16x) 16 6.7 / 9.2, 32 13.3 / 9.6; two LSTM layers of 1024 (25x) 8 8.0 / 12.9, 16
+// 16.0 / 11.7; LSTM 512 -> 1024 (12x) 8 6.9 / 9.9, 16 13.9 / 10.2; LSTMP 153 -> 512 -> 256 32 11.6 / 16.7, 64 23.0 / 16.3.
 static double resident_batch_us(const csb_rnn *r, int32_t batch) {
     const bool two = r->cell == CSB_CELL_LSTMP || r->cell == CSB_CELL_GRU_RB;
     const int R = resident_instances(r, batch);
@@ -1169,7 +1173,8 @@ static double resident_batch_us(const csb_rnn *r, int32_t batch) {
 }
 static double batched_us(const csb_rnn *r, int32_t batch) {
     const bool two = r->cell == CSB_CELL_LSTMP || r->cell == CSB_CELL_GRU_RB;
-    return (10.0 + 4.0 * r->n_layers) * (two ? 1.25 : 1.0) + 2.0 * (double)r->plan.total_nnz * batch / 12e6;
+    const int groups = (r->n_layers + kMaxJobsPerLaunch - 1) / kMaxJobsPerLaunch;
+    return (7.5 * groups + r->n_layers) * (two ? 1.8 : 1.0) + 2.0 * (double)r->plan.total_nnz * batch / 25e6;
 }
 static bool batch_prefers_resident(const csb_rnn *r, int32_t batch) {
     if (r->knob_batch_path == 1) return true;
@@ -1178,6 +1183,10 @@ static bool batch_prefers_resident(const csb_rnn *r, int32_t batch) {
 }
 
 }  // namespace csb
+
+extern "C" int csb_debug_rnn_prefers_resident(const csb_rnn *r, int32_t batch) {
+    return r && r->plan.valid && csb::batch_prefers_resident(r, batch) ? 1 : 0;
+}
 
 extern "C" int csb_rnn_create(int32_t cell, int32_t n_layers, int32_t input, int32_t hidden,
                               csb_matrix *const *W, const float *const *d_bias, csb_rnn **out) {
