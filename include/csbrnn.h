@@ -267,6 +267,9 @@ int csb_spmv_static(const csb_matrix *m, const float *d_x, float *d_y, void *str
  * (j,k) at d_X[j*ldx + k], ldx >= batch), d_Y is [rows][ldy] (ldy >= batch).
  * d_ws: csb_workspace_bytes(m, batch) (may be NULL when that is 0).  Runs on the matrix
  * cores (fp32 MFMA); the result does not depend on timing (fixed summation order).
+ * An entry (j,k) of X that is not finite makes column k of Y infinite or NaN in every row that holds an
+ * entry of column j of A, and may make it NaN in the other rows of their row tiles (br rows each): whether
+ * it does depends on sizes, batch and alignment.  Nothing else of Y is touched by it.
  * Errors: NULL / batch <= 0 / a leading dimension below batch -> CSB_EINVAL; not planned
  * or uploaded, or planned for a GRU step -> CSB_ESTATE; cols * ldx beyond 2^30 elements
  * or ldx >= 2^24 (the kernel uses 32-bit element offsets) -> CSB_EUNSUPPORTED; launch
@@ -281,7 +284,8 @@ int csb_spmm(const csb_matrix *m, const float *d_X, int64_t ldx, float *d_Y, int
  * (csb_set_value_format(CSB_VAL_BF16) before csb_plan) and the right-hand sides arrive as
  * bfloat16 bit patterns, d_Xb [cols][ldx] (device, entry (j,k) at d_Xb[j*ldx + k]); the
  * products are exact in binary32 and are accumulated in binary32 into d_Y [rows][ldy] float.
- * Y equals A X for the rounded operands to the float32 dot-product bound of csb_spmm.
+ * Y equals A X for the rounded operands to the float32 dot-product bound of csb_spmm; inputs that are not
+ * finite do what they do there.
  * Errors: NULL / batch <= 0 / a leading dimension below batch -> CSB_EINVAL; matrix not
  * planned and uploaded, planned for a GRU step, or not storing bfloat16 -> CSB_ESTATE; batch or
  * ldx not a multiple of 4, d_Xb not 8-byte aligned, block rows too tall for the accumulator

@@ -383,7 +383,7 @@ __global__ __launch_bounds__(NW * 64) void spmm_bf16_kernel(const DevMat m, cons
                 const uint32_t w0 = gv16[((ok0 ? j0 : 0u) >> 1) * (uint32_t)kWave + arow];
                 const uint32_t w1 = gv16[((ok1 ? j0 + 2u : 0u) >> 1) * (uint32_t)kWave + arow];
                 o.a[s] = make_uint2(ok0 && row_ok ? w0 : 0u, ok1 && row_ok ? w1 : 0u);
-                // (a lane without a column reads the block's first one: finite, times a zero)
+                // (a lane without a column reads the block's first one, times a zero)
                 uint2 x[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -480,6 +480,9 @@ __global__ __launch_bounds__(NW * 64) void spmm_bf16_kernel(const DevMat m, cons
 // slots.  A pass ALWAYS issues 4 NH kernel-value loads and four 16-byte input loads (k-steps and
 // parts a block does not have repeat a valid address and are not multiplied), so the loads of
 // the NEXT pass are in flight while this pass multiplies and the compiler's counted waits hold.
+// A row the block does not keep is a zero times the inputs of its columns: an input that is not finite makes NaN of
+// the rows of the tile (the header says so; checking the results for it and computing such rows again, entry
+// by entry, cost 0.1 to 0.7 us per launch on finite inputs: 8192 x 8192 x 512 bfloat16 119.2 -> 122.2 us).
 // Same records, same value layout, same merge of the wavefronts' tiles as the general kernel.
 //
 // NQ: how many times 64 right-hand sides a workgroup takes.  What a pass costs besides its
@@ -730,7 +733,7 @@ __device__ __forceinline__ void spmm_reg_body(const DevMat &m, const XSrc &X, fl
                 o.aw[h][1] = __builtin_amdgcn_raw_buffer_load_b32(vrsrc, (int)(w1 + irow4[h]), 0, 0);
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i)      // (a column the block lacks reads its last one: finite, times a zero)
+            for (int i = 0; i < 4; ++i)      // (a column the block lacks reads its last one, times a zero)
 #pragma unroll
                 for (int q = 0; q < NQ; ++q)
                     o.xv[i][q] = *(const uint2 *)((const uint8_t *)X.p0 + (size_t)((mul24_(cb[i], sj0) >> 1) + nbyte[q]));

@@ -64,20 +64,47 @@ def test_spmm_any_batch(R, C, br, bc, batch):
     assert np.all(np.abs(out[:, 1:1 + batch].cpu().numpy().astype(np.float64) - ref) <= bound)
 
 
-@pytest.mark.parametrize("batch", [5, 33, 70])
-def test_spmm_infinite_input(batch):
-    """An infinite input reaches the rows that hold an entry of its column, and no others."""
-    m = csb_inputs.small_matrix(5, 96, 64, 32, 32, rate=6.0)
+# What an input that is not finite does, in every form: the general one at 16, 32 and 64 columns, the register ones of
+# 64 and 128 right-hand sides, 16 and 32 rows (from 256 row tiles on), and the 16-bit ones.
+@pytest.mark.parametrize("R,br,batch", [(96, 32, 5), (96, 32, 33), (96, 32, 70), (8200, 32, 63), (8200, 64, 64), (8192, 32, 64),
+                                        (8192, 32, 128), (4100, 16, 64), (4100, 16, 196)])
+@pytest.mark.parametrize("fmt,name", [(None, "f32")] + FORMATS)
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_spmm_infinite_input(value, fmt, name, R, br, batch):
+    """The rows that hold an entry of its column are not finite.  In the general float32 form no others are touched
+    (and an infinity stays one, with its sign); in the others no rows outside of the row tiles that hold the
+    column.  Other right-hand sides are what they are."""
+    C = 70
+    m = csb_inputs.small_matrix(5, R, C, br, 32, rate=6.0)
     col = int(np.flatnonzero(np.count_nonzero(m.A, axis=0))[-1])
-    X = csb_inputs.make_vectors(batch, 64, batch).reshape(64, batch)
-    X[col] = np.inf
-    M = CsbMatrix(m.A, 32, 32)
-    M.plan()
-    M.upload()
-    got = M.spmm(torch.from_numpy(X).cuda()).cpu().numpy()
-    hit = m.A[:, col] != 0
-    assert np.all(np.isinf(got[hit])) and np.all(np.sign(got[hit]) == np.sign(m.A[hit, col])[:, None])
-    assert np.all(np.isfinite(got[~hit]))
+    batch = batch if fmt is None else (batch + 3) // 4 * 4
+    general = fmt is None and (br == 64 or R == 96 or batch % 4 != 0)
+    X = csb_inputs.make_vectors(batch, C, batch).reshape(C, batch)
+    X[col] = value
+    X[col, 1::3] = 1.0                                             # (some right-hand sides are finite throughout)
+    A = m.A
+    if fmt is None:
+        M = CsbMatrix(A, br, 32)
+        M.plan()
+        M.upload()
+    else:
+        M, A = packed(A, br, 32, fmt), oracle.round_weights(m.A, name)
+        X = oracle.round_weights(X, name).astype(np.float32)
+    Xd = torch.from_numpy(X).cuda()
+    Y = M.spmm(Xd) if fmt is None else M.spmm_bfloat(Xd.to(torch.bfloat16)) if name == "bf16" else M.spmm_half(Xd.to(torch.float16))
+    got = Y.cpu().numpy().astype(np.float64)
+    hit, odd = m.A[:, col] != 0, ~np.isfinite(X[col])
+    at = np.ix_(hit, odd)
+    assert not np.any(np.isfinite(got[at]))
+    if general and np.isinf(value):
+        assert np.all(np.isinf(got[at])) and np.all(np.sign(got[at]) == np.sign(m.A[hit, col])[:, None])
+    apart = ~hit if general else ~np.isin(np.arange(R) // br, np.unique(np.flatnonzero(hit) // br))
+    X[col, odd] = 0.0
+    ref, absr = oracle.matmat(A, X), oracle.matmat(np.abs(A), np.abs(X))
+    bound = 2.0 * np.maximum(np.count_nonzero(m.A, axis=1)[:, None], 1) * 2.0 ** -24 * absr + 1e-30
+    for rows, cols in ((apart, odd), (np.ones(R, bool), ~odd)):
+        at = np.ix_(rows, cols)
+        assert np.all(np.abs(got[at] - ref[at]) <= bound[at])
 
 
 # Rows of X beyond 2 GiB (float32) and beyond 1 GiB (16-bit): offsets of more than 31 bits.  Few
