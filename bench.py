@@ -437,46 +437,46 @@ def resident_batches_leg(torch, np, csb_inputs, CsbMatrix, CsbRnn):
     import os
     res = {}
     old = os.environ.get("CSB_RNN_BATCH_PATH")
+
+    def handle(cfg, Ws, bias, path):
+        """A handle whose batches take `path` (None: the one the library picks); it reads the name once, when it is created."""
+        os.environ.pop("CSB_RNN_BATCH_PATH", None)
+        if path is not None:
+            os.environ["CSB_RNN_BATCH_PATH"] = path
+        return CsbRnn(cfg.cell, cfg.input, cfg.hidden, Ws, bias)
+
+    def timed(rnn, cfg, B):
+        xd = torch.from_numpy(np.random.default_rng(B).uniform(-1, 1, (cfg.T, B, cfg.input)).astype(np.float32)).cuda()
+        for _ in range(3):
+            rnn.forward(xd, want_hseq=True)
+        n = 10
+        ms = time_region(lambda: rnn.forward(xd, want_hseq=True), n, torch) / n
+        return {"ms_per_batch": round(ms, 4), "us_per_timestep": round(ms * 1e3 / cfg.T, 3), "sequences_per_s": round(B / (ms * 1e-3))}
+
     try:
         for name in ("cfg1", "cfg2", "cfg3", "cfg4"):
             cfg = csb_inputs.CONFIGS[name]
             wl = csb_inputs.make_rnn(cfg, batch=1)
             Ws = [CsbMatrix(m.A, m.br, m.bc) for m in wl.W]
-            rnn = CsbRnn(cfg.cell, cfg.input, cfg.hidden, Ws, [torch.from_numpy(b).cuda() for b in wl.bias])
-            rnn.upload()
-            for w in Ws:
-                w.upload()
-            entry = {"workgroups_per_instance": rnn.stats()["n_workgroups"], "T": cfg.T}
-            for B in (8, 64):
-                xd = torch.from_numpy(np.random.default_rng(B).uniform(-1, 1, (cfg.T, B, cfg.input)).astype(np.float32)).cuda()
-                row = {}
-                for path in ("resident", "batched", None):
-                    if path is None:
-                        os.environ.pop("CSB_RNN_BATCH_PATH", None)
-                    else:
-                        os.environ["CSB_RNN_BATCH_PATH"] = path
-                    for _ in range(3):
-                        rnn.forward(xd, want_hseq=True)
-                    n = 10
-                    ms = time_region(lambda: rnn.forward(xd, want_hseq=True), n, torch) / n
-                    row[path or "picked"] = {"ms_per_batch": round(ms, 4), "us_per_timestep": round(ms * 1e3 / cfg.T, 3),
-                                             "sequences_per_s": round(B / (ms * 1e-3))}
-                entry[f"batch{B}"] = row
+            bias = [torch.from_numpy(b).cuda() for b in wl.bias]
+            entry = {"T": cfg.T, "batch8": {}, "batch64": {}}
+            for path in ("resident", "batched", None):
+                rnn = handle(cfg, Ws, bias, path)
+                rnn.upload()
+                for w in Ws:
+                    w.upload()
+                entry["workgroups_per_instance"] = rnn.stats()["n_workgroups"]
+                for B in (8, 64):
+                    entry[f"batch{B}"][path or "picked"] = timed(rnn, cfg, B)
+                del rnn
             # the resident layout planned for the batch (csb_rnn_plan_resident): smaller instances, fewer rounds
-            os.environ["CSB_RNN_BATCH_PATH"] = "resident"
+            rnn = handle(cfg, Ws, bias, "resident")
             for B in (8, 64):
                 rnn.plan_resident(B)
                 rnn.upload()
                 st = rnn.stats()
-                xd = torch.from_numpy(np.random.default_rng(B).uniform(-1, 1, (cfg.T, B, cfg.input)).astype(np.float32)).cuda()
-                for _ in range(3):
-                    rnn.forward(xd, want_hseq=True)
-                n = 10
-                ms = time_region(lambda: rnn.forward(xd, want_hseq=True), n, torch) / n
-                entry[f"batch{B}"]["resident_planned_for_batch"] = {
-                    "workgroups_per_instance": st["n_workgroups"], "slots_per_lane": st["slots_per_lane"],
-                    "ms_per_batch": round(ms, 4), "us_per_timestep": round(ms * 1e3 / cfg.T, 3),
-                    "sequences_per_s": round(B / (ms * 1e-3))}
+                entry[f"batch{B}"]["resident_planned_for_batch"] = dict(
+                    workgroups_per_instance=st["n_workgroups"], slots_per_lane=st["slots_per_lane"], **timed(rnn, cfg, B))
             res[name] = entry
             del rnn
     finally:

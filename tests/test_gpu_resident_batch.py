@@ -4,7 +4,6 @@ depends on its own past only), so they run as instances of the one-sequence kern
 Against the float64 oracle to 1e-4 like every other path, and bit for bit against the same
 handle run one sequence at a time; several rounds, ragged last rounds, all cells, models that
 span one and several XCDs, calls of different T, batch and path in turn on one workspace."""
-import os
 import sys
 
 import numpy as np
@@ -121,34 +120,36 @@ def test_against_oracle_and_one_sequence_at_a_time(kind, L, I, H, proj, block, r
     assert s2 is None and torch.equal(h1, h2)
 
 
-def test_both_batch_paths_agree_and_share_a_workspace():
+def test_both_batch_paths_agree_and_share_a_workspace(monkeypatch):
     """With the matrices uploaded too the library picks a path by its cost estimate;
-    CSB_RNN_BATCH_PATH names one.  Calls of different T, batch and path follow each other on one
-    handle (one workspace): every one must still match the oracle."""
+    CSB_RNN_BATCH_PATH, read when a handle is created, names one.  Calls of different T, batch and path
+    follow each other on one workspace: every one must still match the oracle."""
     kind, L, I, H, block = "lstm", 2, 40, 96, 16
-    wl, rnn, mats, ref = make(kind, L, I, H, 0, block, 3.0, 40, 8, seed=5)
-    rnn.upload()
-    for m in mats:
-        m.upload()
-    old = os.environ.get("CSB_RNN_BATCH_PATH")
-    try:
-        plan = [("resident", 40, 8), ("batched", 40, 8), ("resident", 5, 8), ("resident", 40, 8), (None, 40, 1),
-                ("resident", 17, 3), ("batched", 17, 3), ("resident", 40, 8), (None, 9, 1), (None, 40, 8)]
-        for path, T, B in plan:
-            if path is None:
-                os.environ.pop("CSB_RNN_BATCH_PATH", None)
-            else:
-                os.environ["CSB_RNN_BATCH_PATH"] = path
-            x = np.ascontiguousarray(wl.x[:T, :B])
-            h0, c0 = states(kind, L, B, H, 0, T + B)
-            got = rnn.forward(dev(x), dev(h0), dev(c0))
-            torch.cuda.synchronize()
-            check(got, ref(x, h0, c0), f"path={path} T={T} B={B}")
-    finally:
-        if old is None:
-            os.environ.pop("CSB_RNN_BATCH_PATH", None)
+    handles = {}
+    for path in ("resident", "batched", None):
+        if path is None:
+            monkeypatch.delenv("CSB_RNN_BATCH_PATH", raising=False)
         else:
-            os.environ["CSB_RNN_BATCH_PATH"] = old
+            monkeypatch.setenv("CSB_RNN_BATCH_PATH", path)
+        wl, rnn, mats, ref = make(kind, L, I, H, 0, block, 3.0, 40, 8, seed=5)
+        rnn.upload()
+        for m in mats:
+            m.upload()
+        handles[path] = rnn
+    prefers = P.load_library().csb_debug_rnn_prefers_resident
+    assert prefers(handles["resident"]._h, 8) == 1 and prefers(handles["batched"]._h, 8) == 0
+    ws = torch.empty(max(h.workspace_bytes(8, 40) for h in handles.values()) // 4 + 64, dtype=torch.float32, device="cuda")
+    for h in handles.values():
+        h._ws = ws
+    plan = [("resident", 40, 8), ("batched", 40, 8), ("resident", 5, 8), ("resident", 40, 8), (None, 40, 1),
+            ("resident", 17, 3), ("batched", 17, 3), ("resident", 40, 8), (None, 9, 1), (None, 40, 8)]
+    for path, T, B in plan:
+        x = np.ascontiguousarray(wl.x[:T, :B])
+        h0, c0 = states(kind, L, B, H, 0, T + B)
+        got = handles[path].forward(dev(x), dev(h0), dev(c0))
+        torch.cuda.synchronize()
+        check(got, ref(x, h0, c0), f"path={path} T={T} B={B}")
+        assert handles[path]._ws is ws
 
 
 def test_headline_model_batch_of_eight():
