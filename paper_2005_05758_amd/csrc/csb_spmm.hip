@@ -6,7 +6,7 @@
 // (virtual blocks, lane descriptors, input-offset lists) are staged in LDS one segment at a
 // time; the wavefronts take the segment's virtual blocks round-robin, each as 16-row
 // slices: per 4 columns one A operand (16 x 4 of the kernel) feeds one MFMA per 16 batch
-// columns.  The operands of the next pass are loaded while the current one multiplies.
+// columns.
 // The 16 x 16 results are added at the block's row indices into a per-wavefront
 // accumulator tile in LDS (the role of NeuronAccumBuffer, Sec. 4.3.1); the wavefronts'
 // tiles are summed in wavefront order, so the result does not depend on timing.  The
@@ -464,20 +464,18 @@ __global__ __launch_bounds__(NW * 64) void spmm_bf16_kernel(const DevMat m, cons
 // ---------------------------------------------------------------------------------------
 // The wide form for row tiles of 16 or 32 rows, with the results kept in registers (VF: storage
 // format of the kernel values; 16-bit values come as one word per row and pair of columns and
-// are unpacked to binary32 on their way into the MFMA).  Counters of the general kernel above on the 8192 x 8192 matrix with 128
-// right-hand sides show what its launch time is made of: vector instructions other than MFMA
-// keep every SIMD busy for 38 % of the launch (about 480 instructions per pass of at most 16
-// MFMAs, among them the accumulate of every 16-row slice's 16 x 64 results into the wavefront's
-// LDS tile: four 16-byte reads and four writes per lane), the matrix pipe a quarter, and
-// pointing every gather at ONE row of X makes it only 7 % faster -- the gather is not the
-// bound.  Here the kernel operand of an MFMA is not the block's kernel matrix but its
+// are unpacked to binary32 on their way into the MFMA).  What bounds the kernel-row form above on long tiles is
+// instructions, not the gather: on the 8192 x 8192 matrix with 128 right-hand sides, in its first version, vector
+// instructions other than MFMA kept every SIMD busy for 38 % of the launch (among them the accumulate of every
+// 16-row slice's 16 x 64 results into the wavefront's LDS tile: four 16-byte reads and four writes per lane), the matrix
+// pipe a quarter, and pointing every gather at ONE row of X made it only 7 % faster.  Here the kernel operand of an MFMA is not the block's kernel matrix but its
 // rows ALREADY SCATTERED to their places in the row tile: for each 16-row part of the tile, lane
 // (row, k) holds the block's value at that tile row, or zero if the block does not keep the
 // row.  The 16 x 64 results of a part then add up in the SAME registers over all blocks the
 // wavefront works on, and go to LDS once, at the end.  The price is matrix-pipe work for parts
 // a block has few rows in (parts it has none in are skipped).  Which kernel row sits at a tile
 // row comes from a 64-byte map per wavefront in LDS that the block's lanes fill from their row
-// slots.  A pass ALWAYS issues 4 NH kernel-value loads and four 16-byte input loads (k-steps and
+// slots.  A pass ALWAYS issues 4 NH kernel-value loads and 4 NQ 16-byte input loads (k-steps and
 // parts a block does not have repeat a valid address and are not multiplied), so the loads of
 // the NEXT pass are in flight while this pass multiplies and the compiler's counted waits hold.
 // A row the block does not keep is a zero times the inputs of its columns: an input that is not finite makes NaN of
@@ -852,8 +850,8 @@ struct SpmmShape {
                             // 16 x 16 blocks at batch 6: 34.0 -> 27.0 us)
     bool two;
     int reg_parts;          // 64 columns, row tiles of 16 or 32 rows: the kernel that keeps the results in
-                            // registers, with this many 16-row parts (else 0; four parts do not fit the
-                            // registers of a 16-wavefront workgroup)
+                            // registers, with this many 16-row parts (else 0; 64-row tiles' four parts do not fit the registers
+                            // of a 16-wavefront workgroup; for one of 8 there is no such kernel)
     int nq;                 // ... and this many times 64 right-hand sides per workgroup
     int vf;                 // storage format of the kernel values
     size_t lds;
