@@ -1,7 +1,5 @@
 """The rule by which batched products choose 64 or 128 right-hand sides per workgroup, at sizes where
 both were measured (us on MI355X): it takes the faster one.  No GPU."""
-import ctypes
-
 import pytest
 
 from paper_2005_05758_amd import load_library
@@ -18,10 +16,10 @@ from paper_2005_05758_amd import load_library
     (4096, 32, 260, 1, 23.1, 20.1), (8192, 16, 68, 1, 29.8, 25.2), (8192, 16, 132, 1, 42.3, 43.6), (8192, 16, 260, 1, 67.1, 62.9),
     (4300, 16, 68, 1, 23.1, 24.5), (4300, 16, 132, 1, 29.1, 33.2), (4300, 16, 452, 1, 60.9, 53.3)])
 def test_the_faster_width(rows, br, batch, bits16, us64, us128):
-    got = load_library().csb_debug_spmm_columns(ctypes.c_int64(-(-rows // br)), br, batch, bits16)
+    got = load_library().csb_debug_spmm_columns(-(-rows // br), br, batch, bits16)
     assert got == (64 if us64 < us128 else 128)
 
 
 @pytest.mark.parametrize("tiles,batch", [(1, 512), (100, 128), (300, 64), (300, 4), (255, 128)])
 def test_128_needs_a_workgroup_for_every_cu(tiles, batch):
-    assert load_library().csb_debug_spmm_columns(ctypes.c_int64(tiles), 32, batch, 0) == 64
+    assert load_library().csb_debug_spmm_columns(tiles, 32, batch, 0) == 64
