@@ -230,6 +230,51 @@ struct StreamPlan {
     uint64_t off = 0, bytes = 0;   // the section inside the image
 };
 
+// ---- quad section (batched products) -------------------------------------------------------
+// The batched kernels multiply four kernel rows by one input row of 16 to 64 right-hand sides per
+// instruction (csb_spmm_quad.hip).  Output rows are cut into tiles of `tile_rows` (16 or 32); the part of a CSB
+// block that lands in a tile is cut into PASSES of at most 8 columns and all of its rows there.  A
+// pass is one record and one run of values, and the passes of a tile are dealt to kQuadLists
+// lists of equal work, in column order: a wavefront walks one list (or several in a row) and finds everything
+// it needs in the record, which comes in over the scalar path.
+//   table   [n_tiles][kQuadLists] first pass of every list, and one entry more for the end of the last
+//   records [passes + kQuadSpareRecs]
+//   values  binary32: per pass [column][4 rows][quad]; 16-bit formats: [4 columns][4 rows][quad][4 columns]; columns in
+//           fours, zeros where the pass has no such row or column; kQuadPad bytes of zeros behind the last
+// With `seg_rows` > 0 tiles do not cross multiples of it (the gates of a recurrent cell, seg_rows units each);
+// with `split_col` > 0 no pass crosses that column (the border between the two sources of a step's
+// input), and columns of the second part are counted from it.
+constexpr int kQuadRows = 32;
+constexpr int kQuadLists = 16;
+constexpr int kQuadCols = 8;             // columns of a pass
+constexpr int kQuadSpareRecs = 3;        // a wavefront reads the records, and asks for the operands, of passes behind its last one
+constexpr int kQuadPad = 4096;           // a pass's loads may run past its values by less than this
+constexpr uint16_t kQuadNoCol = 0xffff;  // (times a row's bytes: past the end of the input)
+
+struct QuadRec {
+    // what the loads need
+    uint32_t val;                        // byte offset of the pass's values
+    uint16_t stride;                     // bytes from one column (16-bit formats: four columns) to the next
+    uint8_t quads;                       // kernel rows in fours
+    uint8_t flags;                       // kQuadWide: more than 4 columns; kQuadSecond: columns of the second source
+    uint16_t col[kQuadCols];             // input rows; kQuadNoCol where the pass has fewer
+    uint32_t pad[2];
+    // what the row sums need
+    uint8_t slot[kQuadRows];             // the rows' places in the tile; kQuadRows (a spare one) where there is none
+};
+constexpr uint8_t kQuadWide = 1, kQuadSecond = 2;
+static_assert(sizeof(QuadRec) == 64, "QuadRec layout");
+
+struct QuadPlan {
+    bool valid = false;
+    uint32_t n_tiles = 0, tile_rows = 0, seg_rows = 0, tiles_per_seg = 0;
+    uint32_t split_col = 0;
+    uint32_t val_fmt = 0;
+    uint64_t off_table = 0, off_recs = 0, off_vals = 0;
+    uint64_t n_passes = 0, vals_bytes = 0;   // (vals_bytes with the padding)
+    uint32_t tile_row0(uint32_t t) const { return t / tiles_per_seg * seg_rows + t % tiles_per_seg * tile_rows; }
+};
+
 struct Plan {
     bool valid = false;
     SplitSpec split;              // stays when the plan becomes invalid: csb_plan keeps the row layout of a matrix a GRU handle planned
@@ -237,6 +282,7 @@ struct Plan {
     std::vector<uint8_t> image;   // host staging copy of the device image
     DevHeader hdr{};
     StreamPlan stream;            // valid: csb_spmv reads this section instead of the sections above
+    QuadPlan quad;                // valid: batched products read this section instead of the tile-based ones
     csb_plan_stats stats{};
 };
 
@@ -268,6 +314,7 @@ struct csb_matrix {
     int32_t stream_cell_gates = 0;   // > 0: the rows are `gates` stacked groups of rows/gates units each, and a workgroup of
                                      // the row-owned plan is to own all gate rows of its units (set by an RNN handle, whose
                                      // mat-vec launches then finish their cells themselves; csb_plan* ask for plain ranges)
+    int32_t quad_units = 0, quad_split = 0;   // seg_rows and split_col of the quad section (set by an RNN handle)
     csb::Plan plan;
     void *d_buf = nullptr;        // caller-owned device image, set by csb_upload
     bool uploaded = false;
@@ -283,5 +330,7 @@ int plan_matrix(csb_matrix *m, int32_t n_chunks, int32_t waves_per_chunk, const 
 int validate_plan(const csb_matrix *m);
 int plan_stream(csb_matrix *m, int32_t n_wg_req, int32_t rounds_min, csb_plan_stats *stats);
 int validate_stream(const csb_matrix *m);
+int plan_quad(csb_matrix *m);
+int validate_quad(const csb_matrix *m);
 DevMat dev_mat(const csb_matrix *m);
 }  // namespace csb

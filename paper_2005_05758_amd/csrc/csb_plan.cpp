@@ -44,7 +44,7 @@ int plan_matrix(csb_matrix *m, int32_t n_chunks_req, int32_t waves_per_chunk, co
     if (n_chunks_req < 0) { set_error("csb_plan: n_chunks < 0"); return CSB_EINVAL; }
     // mode 4 (internal): as mode 0 but without the row-owned section (the caller builds it itself)
     if (mode < 0 || mode > 4 || mode == 3) { set_error("csb_plan: mode must be 0 (auto), 1 (whole tiles) or 2 (equal split)"); return CSB_EINVAL; }
-    const bool with_rows = mode == 0;
+    const bool with_rows = mode == 0, internal_rows = mode == 4;
     if (mode == 4) mode = 0;
     if (waves_per_chunk != 16) {
         set_error("csb_plan: waves_per_chunk must be 16");
@@ -642,8 +642,13 @@ int plan_matrix(csb_matrix *m, int32_t n_chunks_req, int32_t waves_per_chunk, co
         pl.stream = StreamPlan{};
         if (stats_out) *stats_out = st;
         // the row-owned section for csb_spmv, when the matrix fits it
-        if (with_rows) return plan_stream(m, n_chunks_req, 0, stats_out);
-        return CSB_OK;
+        if (with_rows) {
+            const int rc = plan_stream(m, n_chunks_req, 0, stats_out);
+            if (rc != CSB_OK) return rc;
+        }
+        // ... and the one of the batched products (csb_plan_rows, mode 4, builds its row-owned section first)
+        pl.quad = QuadPlan{};
+        return internal_rows ? (int)CSB_OK : plan_quad(m);
     } catch (const std::bad_alloc &) {
         set_error("csb_plan: out of host memory");
         return CSB_ENOMEM;
@@ -659,7 +664,7 @@ int validate_plan(const csb_matrix *m) {
     const DevHeader &h = pl.hdr;
     const uint8_t *im = pl.image.data();
     auto fail = [&](const char *what) { set_error(std::string("csb_plan_validate: ") + what); return CSB_EINVAL; };
-    if (h.total_bytes > pl.image.size() || (!pl.stream.valid && h.total_bytes != pl.image.size())) return fail("image size");
+    if (h.total_bytes > pl.image.size() || (!pl.stream.valid && !pl.quad.valid && h.total_bytes != pl.image.size())) return fail("image size");
     const auto *chunks = (const ChunkRec *)(im + h.off_chunks);
     const auto *waves = (const WaveRec *)(im + h.off_waves);
     const auto *groups = (const GroupRec *)(im + h.off_groups);
@@ -855,6 +860,10 @@ int validate_plan(const csb_matrix *m) {
     for (uint32_t t = 0; t < n_tiles; ++t) if (!tile_written[t]) return fail("tile never written");
     if (vals_used != m->val.size()) return fail("not every value referenced exactly once");
     if (std::memcmp(expect.data(), got.data(), expect.size() * sizeof(float)) != 0) return fail("image does not decode to the matrix");
+    if (pl.quad.valid) {
+        const int rc = validate_quad(m);
+        if (rc != CSB_OK) return rc;
+    }
     if (pl.stream.valid) return validate_stream(m);
     return CSB_OK;
 }
@@ -866,13 +875,13 @@ int validate_plan(const csb_matrix *m) {
 // (A plan the caller asks for may take all 256 compute units again, whatever share of them an RNN
 // handle had left the matrix.)
 extern "C" int csb_plan(csb_matrix *m, int32_t n_chunks, csb_plan_stats *stats) {
-    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; }
+    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; m->quad_units = 0; m->quad_split = 0; }
     return csb::plan_matrix(m, n_chunks, 16, m ? m->plan.split : csb::SplitSpec{}, stats, 0);
 }
 
 extern "C" int csb_plan_ex(csb_matrix *m, int32_t n_chunks, int32_t mode, csb_plan_stats *stats) {
     if (mode == 3 || mode == 4) { csb::set_error("csb_plan: mode must be 0 (auto), 1 (whole tiles) or 2 (equal split)"); return CSB_EINVAL; }
-    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; }
+    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; m->quad_units = 0; m->quad_split = 0; }
     return csb::plan_matrix(m, n_chunks, 16, m ? m->plan.split : csb::SplitSpec{}, stats, mode);
 }
 
@@ -885,7 +894,7 @@ extern "C" int csb_plan_stats_get(const csb_matrix *m, csb_plan_stats *stats) {
 
 extern "C" int csb_plan_rows(csb_matrix *m, int32_t n_workgroups, int32_t min_rounds, csb_plan_stats *stats) {
     if (n_workgroups < 0 || min_rounds < 0) { csb::set_error("csb_plan_rows: negative parameter"); return CSB_EINVAL; }
-    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; }
+    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; m->quad_units = 0; m->quad_split = 0; }
     int rc = csb::plan_matrix(m, 0, 16, csb::SplitSpec{}, nullptr, 4);
     if (rc != CSB_OK) return rc;
     rc = csb::plan_stream(m, n_workgroups, min_rounds, stats);
@@ -895,7 +904,7 @@ extern "C" int csb_plan_rows(csb_matrix *m, int32_t n_workgroups, int32_t min_ro
         csb::set_error("csb_plan_rows: the matrix does not fit the row-owned layout");
         return CSB_EUNSUPPORTED;
     }
-    return CSB_OK;
+    return csb::plan_quad(m);
 }
 
 extern "C" int csb_plan_validate(const csb_matrix *m) { return csb::validate_plan(m); }

@@ -1,0 +1,277 @@
+// Quad section of the device image (host only): the layout the batched products read (QuadPlan).
+//
+// Role in the method: Sec. 4.3.1 gives a kernel matrix to a PE group in passes of P x Q and Sec. 5.2 asks for equal
+// shares of that uneven work.  Here a pass is at most 8 columns by the (at most 32) kernel rows of one block that
+// land in one row tile, and the passes of a tile are dealt to 16 lists, each pass to the list with the least work so
+// far, in column order: the wavefronts of all workgroups then walk the input at about the same pace,
+// which keeps the rows they gather in the caches.
+#include <algorithm>
+#include <cstring>
+#include <new>
+
+#include "csb_internal.hpp"
+
+namespace csb {
+namespace {
+
+size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+
+struct QPass {
+    uint32_t b;            // CSB block
+    uint16_t a0, q0;       // first kernel row and column
+    uint8_t nrows, ncols;
+    uint8_t shifted;       // 1: summed into row + shift (GRU split)
+};
+
+// Work of a pass, in units of about one instruction of a wavefront: what it costs whatever it multiplies, its input
+// rows, its products and its row sums.
+uint32_t pass_cost(const QPass &p) { return 60u + 4u * kQuadCols + p.ncols * ((p.nrows + 3u) / 4u) * 4u + 3u * p.nrows; }
+
+size_t pass_value_bytes(const QPass &p, bool bits16) {
+    const size_t quads = (p.nrows + 3u) / 4u;
+    return (size_t)((p.ncols + 3u) / 4u) * quads * (bits16 ? 32u : 64u);
+}
+
+// The parts of block b's columns [q0, q1) that are summed together (GRU split) and come from one source.
+struct ColPart { int q0, q1; bool lower, upper, shifted, second; };
+
+template <typename F>
+void for_column_parts(const csb_matrix *m, size_t b, int32_t bj, F f) {
+    const int nc = m->ncols[b];
+    const SplitSpec &sp = m->plan.split;
+    const uint16_t *ci = m->colidx.data() + m->col_off[b];
+    auto pos = [&](int64_t col) {
+        int q = 0;
+        while (q < nc && (int64_t)bj * m->bc + ci[q] < col) ++q;
+        return q;
+    };
+    const int qs = sp.active() ? pos(sp.split_col) : nc, qx = m->quad_split > 0 ? pos(m->quad_split) : nc;
+    auto cut = [&](int q0, int q1, bool lower, bool upper, bool shifted) {   // at the border between the sources
+        const int c = std::min(std::max(qx, q0), q1);
+        if (q0 < c) f(ColPart{q0, c, lower, upper, shifted, false});
+        if (c < q1) f(ColPart{c, q1, lower, upper, shifted, true});
+    };
+    if (!sp.active()) { cut(0, nc, true, true, false); return; }
+    cut(0, nc, true, false, false);
+    cut(0, qs, false, true, false);
+    cut(qs, nc, false, true, true);
+}
+
+// All passes of the matrix: f(tile, pass, second source, slots of the rows).
+template <typename F>
+void for_passes(const csb_matrix *m, const QuadPlan &qp, F f) {
+    const SplitSpec &sp = m->plan.split;
+    uint8_t slot[kQuadRows];
+    for (int32_t bi = 0; bi < m->nbr; ++bi)
+        for (int32_t bj = 0; bj < m->nbc; ++bj) {
+            const size_t b = (size_t)bi * m->nbc + bj;
+            const int nr = m->nrows[b], nc = m->ncols[b];
+            if (nr == 0 || nc == 0) continue;
+            const uint16_t *ri = m->rowidx.data() + m->row_off[b];
+            for_column_parts(m, b, bj, [&](const ColPart &part) {
+                int a = 0;
+                while (a < nr) {
+                    const int64_t gr = (int64_t)bi * m->br + ri[a];
+                    const bool lower = !sp.active() || gr < sp.split_row;
+                    if (lower ? !part.lower : !part.upper) { ++a; continue; }
+                    const int64_t shift = part.shifted ? sp.shift : 0;
+                    const uint32_t seg = (uint32_t)((gr + shift) / qp.seg_rows);
+                    const uint32_t tile = seg * qp.tiles_per_seg + (uint32_t)((gr + shift - (int64_t)seg * qp.seg_rows) / qp.tile_rows);
+                    const int64_t row0 = qp.tile_row0(tile), end = std::min<int64_t>(row0 + qp.tile_rows, (int64_t)(seg + 1) * qp.seg_rows);
+                    int e = a;                           // the kernel rows of this tile
+                    while (e < nr) {
+                        const int64_t orow = (int64_t)bi * m->br + ri[e];
+                        if ((!sp.active() || orow < sp.split_row) != lower || orow + shift >= end) break;
+                        slot[e - a] = (uint8_t)(orow + shift - row0);
+                        ++e;
+                    }
+                    for (int q = part.q0; q < part.q1; q += kQuadCols) {
+                        const QPass p{(uint32_t)b, (uint16_t)a, (uint16_t)q, (uint8_t)(e - a), (uint8_t)std::min(kQuadCols, part.q1 - q),
+                                      (uint8_t)part.shifted};
+                        f(tile, p, part.second, slot);
+                    }
+                    a = e;
+                }
+            });
+        }
+}
+
+}  // namespace
+
+// Builds the section and appends it to the plan's image; leaves plan.quad.valid false where the matrix does not fit
+// it (the batched products then read the tile-based sections).
+int plan_quad(csb_matrix *m) {
+    Plan &pl = m->plan;
+    pl.quad = QuadPlan{};
+    const int64_t rows = m->rows + (pl.split.active() ? pl.split.shift : 0);
+    if (m->cols > kMaxStageCols || rows > 0x7fffffff || rows == 0) return CSB_OK;
+    try {
+        QuadPlan qp{};
+        qp.seg_rows = (uint32_t)(m->quad_units > 0 && rows % m->quad_units == 0 ? m->quad_units : rows);
+        // (tiles of 16 rows where the blocks are no taller and tiles of 32 would not give each of 256 workgroups one: a wavefront then has
+        // half the passes.  Taller blocks would be cut: twice the passes.)
+        qp.tile_rows = m->br <= 16 && rows < 256 * 32 ? 16u : 32u;
+        qp.tiles_per_seg = (qp.seg_rows + qp.tile_rows - 1) / qp.tile_rows;
+        qp.n_tiles = (uint32_t)(rows / qp.seg_rows) * qp.tiles_per_seg;
+        qp.split_col = m->quad_split > 0 ? (uint32_t)m->quad_split : 0u;
+        qp.val_fmt = (uint32_t)m->val_fmt;
+        const bool bits16 = m->val_fmt != CSB_VAL_F32;
+
+        // ---- the passes of every tile, dealt to its lists -------------------------------------
+        struct Entry { QPass p; uint8_t second, list; uint8_t slot[kQuadRows]; };
+        std::vector<std::vector<Entry>> tiles(qp.n_tiles);
+        uint64_t bytes = 0;
+        for_passes(m, qp, [&](uint32_t tile, const QPass &p, bool second, const uint8_t *slot) {
+            Entry e;
+            e.p = p; e.second = second; e.list = 0;
+            std::memset(e.slot, kQuadRows, sizeof(e.slot));
+            std::memcpy(e.slot, slot, p.nrows);
+            tiles[tile].push_back(e);
+            bytes += pass_value_bytes(p, bits16);
+            ++qp.n_passes;
+        });
+        qp.vals_bytes = bytes + kQuadPad;
+        if (qp.vals_bytes >= 0x7fffff00ull || qp.n_passes >= 0x7fffffffull / sizeof(QuadRec)) return CSB_OK;
+        std::vector<uint32_t> table;
+        table.reserve((size_t)qp.n_tiles * kQuadLists + 1);
+        std::vector<const Entry *> order;
+        order.reserve(qp.n_passes);
+        for (auto &t : tiles) {
+            uint64_t work[kQuadLists] = {0};
+            for (Entry &e : t) {
+                int best = 0;
+                for (int l = 1; l < kQuadLists; ++l) if (work[l] < work[best]) best = l;
+                e.list = (uint8_t)best;
+                work[best] += pass_cost(e.p);
+            }
+            for (int l = 0; l < kQuadLists; ++l) {
+                table.push_back((uint32_t)order.size());
+                for (const Entry &e : t) if (e.list == l) order.push_back(&e);
+            }
+        }
+        table.push_back((uint32_t)order.size());
+
+        // ---- image ------------------------------------------------------------------------------
+        qp.off_table = align_up(pl.image.size(), 256);
+        qp.off_recs = align_up(qp.off_table + table.size() * 4, 256);
+        qp.off_vals = align_up(qp.off_recs + (qp.n_passes + kQuadSpareRecs) * sizeof(QuadRec), 256);
+        pl.image.resize(align_up(qp.off_vals + qp.vals_bytes, 256), 0);
+        uint8_t *im = pl.image.data();
+        std::memcpy(im + qp.off_table, table.data(), table.size() * 4);
+        auto *recs = (QuadRec *)(im + qp.off_recs);
+        uint64_t at = 0;
+        for (size_t i = 0; i < order.size(); ++i) {
+            const Entry &e = *order[i];
+            const QPass &p = e.p;
+            const uint32_t quads = (p.nrows + 3u) / 4u;
+            QuadRec &r = recs[i];
+            r.val = (uint32_t)at;
+            r.stride = (uint16_t)(quads * (bits16 ? 32u : 16u));
+            r.quads = (uint8_t)quads;
+            r.flags = (uint8_t)((p.ncols > 4 ? kQuadWide : 0) | (e.second ? kQuadSecond : 0));
+            const uint16_t *ci = m->colidx.data() + m->col_off[p.b];
+            const uint32_t col0 = (uint32_t)(p.b % (uint32_t)m->nbc) * (uint32_t)m->bc - (e.second ? qp.split_col : 0u);
+            for (int j = 0; j < kQuadCols; ++j) r.col[j] = j < p.ncols ? (uint16_t)(col0 + ci[p.q0 + j]) : kQuadNoCol;
+            std::memcpy(r.slot, e.slot, sizeof(r.slot));
+            const int nc = m->ncols[p.b];
+            const float *src = m->val.data() + m->val_off[p.b] + p.q0;
+            uint8_t *dst = im + qp.off_vals + at;
+            for (uint32_t q = 0; q < p.nrows; ++q) {
+                const float *row = src + (size_t)(p.a0 + q) * nc;
+                for (uint32_t j = 0; j < p.ncols; ++j)
+                    if (!bits16) ((float *)dst)[(j * 4u + (q & 3u)) * quads + (q >> 2)] = row[j];
+                    else ((uint16_t *)dst)[(((j >> 2) * 4u + (q & 3u)) * quads + (q >> 2)) * 4u + (j & 3u)] =
+                             m->val_fmt == CSB_VAL_F16 ? f32_to_f16_bits(row[j]) : f32_to_bf16_bits(row[j]);
+            }
+            at += pass_value_bytes(p, bits16);
+        }
+        qp.valid = true;
+        pl.quad = qp;
+        return CSB_OK;
+    } catch (const std::bad_alloc &) {
+        pl.quad = QuadPlan{};
+        pl.valid = false;
+        set_error("csb_plan: out of host memory");
+        return CSB_ENOMEM;
+    }
+}
+
+// Walks the section the way the kernels do, with bounds checks, and compares what it adds up with the matrix: every
+// (output row, input column) must be multiplied once, by its value.
+int validate_quad(const csb_matrix *m) {
+    const Plan &pl = m->plan;
+    const QuadPlan &qp = pl.quad;
+    auto fail = [&](const char *what) { set_error(std::string("csb_plan_validate: quad section: ") + what); return CSB_EINVAL; };
+    if (qp.off_vals + qp.vals_bytes > pl.image.size() || qp.off_recs + (qp.n_passes + kQuadSpareRecs) * sizeof(QuadRec) > qp.off_vals) return fail("section size");
+    const auto *table = (const uint32_t *)(pl.image.data() + qp.off_table);
+    const auto *recs = (const QuadRec *)(pl.image.data() + qp.off_recs);
+    const uint8_t *vals = pl.image.data() + qp.off_vals;
+    const bool bits16 = qp.val_fmt != CSB_VAL_F32;
+    const int64_t rows = m->rows + (pl.split.active() ? pl.split.shift : 0);
+    if (qp.n_tiles != (uint32_t)(rows / qp.seg_rows) * qp.tiles_per_seg || rows % qp.seg_rows) return fail("tiles");
+    // what is expected: (output row, column) -> value, and how often it was seen
+    const size_t cells = (size_t)rows * (size_t)m->cols;
+    std::vector<float> expect(cells, 0.0f), got(cells, 0.0f);
+    std::vector<uint8_t> in(cells, 0);
+    size_t n_expect = 0, n_got = 0;
+    for (int32_t bi = 0; bi < m->nbr; ++bi)
+        for (int32_t bj = 0; bj < m->nbc; ++bj) {
+            const size_t b = (size_t)bi * m->nbc + bj;
+            for (int a = 0; a < m->nrows[b]; ++a)
+                for (int q = 0; q < m->ncols[b]; ++q) {
+                    int64_t row = (int64_t)bi * m->br + m->rowidx[m->row_off[b] + a];
+                    const int64_t col = (int64_t)bj * m->bc + m->colidx[m->col_off[b] + q];
+                    if (pl.split.active() && row >= pl.split.split_row && col >= pl.split.split_col) row += pl.split.shift;
+                    const size_t cell = (size_t)row * (size_t)m->cols + (size_t)col;
+                    expect[cell] = m->val[m->val_off[b] + (int64_t)a * m->ncols[b] + q];
+                    in[cell] = 1;
+                    ++n_expect;
+                }
+        }
+    for (uint32_t t = 0; t < qp.n_tiles; ++t) {
+        const int64_t row0 = qp.tile_row0(t), end = std::min<int64_t>(row0 + qp.tile_rows, (int64_t)(t / qp.tiles_per_seg + 1) * qp.seg_rows);
+        for (int l = 0; l < kQuadLists; ++l) {
+            const uint32_t i0 = table[(size_t)t * kQuadLists + l], i1 = table[(size_t)t * kQuadLists + l + 1];
+            if (i0 > i1 || i1 > qp.n_passes) return fail("list");
+            for (uint32_t i = i0; i < i1; ++i) {
+                const QuadRec &r = recs[i];
+                uint32_t ncols = 0, nrows = 0;
+                while (ncols < (uint32_t)kQuadCols && r.col[ncols] != kQuadNoCol) ++ncols;
+                while (nrows < (uint32_t)kQuadRows && r.slot[nrows] != kQuadRows) ++nrows;
+                const bool second = (r.flags & kQuadSecond) != 0;
+                if (!ncols || !nrows || r.quads != (nrows + 3u) / 4u || r.stride != r.quads * (bits16 ? 32u : 16u) ||
+                    ((r.flags & kQuadWide) != 0) != (ncols > 4) || (second && !qp.split_col)) return fail("pass size");
+                const size_t bytes = pass_value_bytes(QPass{0, 0, 0, (uint8_t)nrows, (uint8_t)ncols, 0}, bits16);
+                if ((uint64_t)r.val + bytes + kQuadPad > qp.vals_bytes) return fail("values");
+                for (uint32_t j = ncols; j < (uint32_t)kQuadCols; ++j) if (r.col[j] != kQuadNoCol) return fail("gap in the columns");
+                for (uint32_t q = nrows; q < (uint32_t)kQuadRows; ++q) if (r.slot[q] != kQuadRows) return fail("gap in the rows");
+                for (uint32_t q = 0; q < r.quads * 4u; ++q)
+                    for (uint32_t j = 0; j < (ncols + 3u) / 4u * 4u; ++j) {
+                        float v;
+                        if (!bits16) v = ((const float *)(vals + r.val))[(j * 4u + (q & 3u)) * r.quads + (q >> 2)];
+                        else {
+                            const uint16_t bits = ((const uint16_t *)(vals + r.val))[(((j >> 2) * 4u + (q & 3u)) * r.quads + (q >> 2)) * 4u + (j & 3u)];
+                            v = qp.val_fmt == CSB_VAL_F16 ? f16_bits_to_f32(bits) : bf16_bits_to_f32(bits);
+                        }
+                        if (q >= nrows || j >= ncols) {
+                            if (v != 0.0f) return fail("value without an entry");
+                            continue;
+                        }
+                        const int64_t row = row0 + r.slot[q], col = (int64_t)r.col[j] + (second ? qp.split_col : 0);
+                        if (row >= end) return fail("row outside of its tile");
+                        if (col >= m->cols || (qp.split_col && (col >= (int64_t)qp.split_col) != second)) return fail("column");
+                        const size_t cell = (size_t)row * (size_t)m->cols + (size_t)col;
+                        if (in[cell] != 1) return fail(in[cell] ? "entry multiplied twice" : "entry that the matrix does not have");
+                        in[cell] = 2;
+                        ++n_got;
+                        got[cell] = v;
+                    }
+            }
+        }
+    }
+    if (n_got != n_expect) return fail("entry missing");
+    if (std::memcmp(expect.data(), got.data(), cells * sizeof(float)) != 0) return fail("values do not decode to the matrix");
+    return CSB_OK;
+}
+
+}  // namespace csb

@@ -18,38 +18,10 @@
 
 #include "csb_internal.hpp"
 #include "csb_kernels.hpp"
+#include "csb_spmm.hpp"
 #include "csbrnn_debug.h"
 
 namespace csb {
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-
-// A value that is the same in every lane, in a scalar register.  Two kernel arguments between which a lane
-// chooses (the strides of two sources) go through it: the compiler turns a choice between two arguments
-// into a per-lane load of the chosen one, a trip to memory in front of every load that needs it.
-// (24 of those per pair of passes in the kernels that take several products; without them, batch 64, us
-// per step: two GRU layers of 1024 in 16-row blocks 32.6 -> 25.4, two LSTM layers in 32-row blocks 23.0 -> 20.0.)
-__device__ __forceinline__ uint32_t uni_(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-
-// Product of two 24-bit numbers, modulo 2^32.  (__umul24's result is a signed int: the byte offset of an input
-// row 2 GiB and more into X must not be extended with its sign.)
-__device__ __forceinline__ uint32_t mul24_(uint32_t a, uint32_t b) { return (uint32_t)__umul24(a, b); }
-
-// First record segment of the rank-th row tile.  Where every tile's records fit one segment it is the rank
-// itself: one dependent trip to memory less before a launch of a few microseconds has any work.
-__device__ __forceinline__ uint32_t first_segment(const DevMat &m, uint32_t rank) { return m.one_seg ? rank : m.tile_seg0[rank]; }
-
-// Element (column j of A, right-hand side n) of the input, from one of two sources; the right-hand
-// sides of a column are contiguous.  Byte offsets fit 32 bits and the strides over j fit 24 bits
-// (checked on the host).
-struct XSrc {
-    const float *p0;
-    uint32_t n0;          // columns j < n0 come from p0, the rest from p1
-    uint32_t sj0;         // stride over j
-    const float *p1;
-    uint32_t sj1;
-};
 
 // NT neighbouring right-hand sides (a load of NT words, aligned to one word).
 template <int NT> struct RhsVec;
@@ -820,14 +792,6 @@ __global__ __launch_bounds__(NW * 64) void spmm_reg16_kernel(const DevMat m, con
     spmm_reg_body<false, NW, NH, VF, NQ, true>(m, X, Y, ldy, batch, blockIdx.x, blockIdx.y);
 }
 
-// Several independent products in one launch (blockIdx.z picks the product): the per-step
-// products of different layers of a batched recurrent model, each too small to fill the GPU.
-struct SpmmJobs {
-    DevMat m[kMaxJobsPerLaunch];
-    XSrc X[kMaxJobsPerLaunch];
-    float *Y[kMaxJobsPerLaunch];
-    int64_t ldy[kMaxJobsPerLaunch];
-};
 template <int NT, bool TWO, int NW, int KS>
 __global__ __launch_bounds__(NW * 64) void spmm_multi_kernel(const SpmmJobs J, const uint32_t batch) {
     const uint32_t j = blockIdx.z;
@@ -963,14 +927,26 @@ int spmm_strided(const csb_matrix *mat, const float *p0, uint32_t n0, int64_t sj
     XSrc X;
     int rc = spmm_shape(c, batch, 1, long_tiles(&c, 1), &sh, &X);
     if (rc != CSB_OK) return rc;
-    DevMat dm = dev_mat(mat);
     uint32_t b = (uint32_t)batch;
     int64_t ld = ldy;
-    void *args[] = {&dm, &X, &d_Y, &ld, &b};
-    const void *kern = spmm_kernel_for<false>(sh);
-    hipError_t e = ensure_dynamic_lds(kern, sh.lds);
-    if (e == hipSuccess)
-        e = hipLaunchKernel(kern, dim3(sh.tiles, sh.batch_tiles), dim3(sh.nw * 64), args, sh.lds, (hipStream_t)stream);
+    QuadShape qs;
+    XSrc QX;
+    hipError_t e;
+    if (quad_shape(c, batch, 1, &qs, &QX)) {
+        QuadMat qm = quad_mat(mat);
+        void *args[] = {&qm, &QX, &d_Y, &ld, &b};
+        const void *kern = quad_kernel(qs, false);
+        e = ensure_dynamic_lds(kern, qs.lds);
+        if (e == hipSuccess)
+            e = hipLaunchKernel(kern, dim3(qs.tiles, qs.batch_tiles), dim3(qs.nw * 64), args, qs.lds, (hipStream_t)stream);
+    } else {
+        DevMat dm = dev_mat(mat);
+        void *args[] = {&dm, &X, &d_Y, &ld, &b};
+        const void *kern = spmm_kernel_for<false>(sh);
+        e = ensure_dynamic_lds(kern, sh.lds);
+        if (e == hipSuccess)
+            e = hipLaunchKernel(kern, dim3(sh.tiles, sh.batch_tiles), dim3(sh.nw * 64), args, sh.lds, (hipStream_t)stream);
+    }
     if (e != hipSuccess) { set_error(std::string("csb_spmm: ") + hipGetErrorString(e)); return CSB_EDEVICE; }
     return CSB_OK;
 }
@@ -996,6 +972,26 @@ int spmm_strided_multi(const SpmmCall *calls, int n, int32_t batch, void *stream
             J.m[i] = dev_mat(calls[i].mat);
             J.Y[i] = calls[i].Y;
             J.ldy[i] = calls[i].ldy;
+        }
+        QuadShape qs[kMaxJobsPerLaunch];
+        QuadJobs QJ{};
+        bool quad = true;
+        for (int i = 0; i < n && quad; ++i) {
+            quad = quad_shape(calls[i], batch, (size_t)n, &qs[i], &QJ.X[i]) && qs[i] == qs[0];
+            QJ.m[i] = quad_mat(calls[i].mat);
+            QJ.Y[i] = calls[i].Y;
+            QJ.ldy[i] = calls[i].ldy;
+            qs[0].tiles = std::max(qs[0].tiles, qs[i].tiles);
+        }
+        if (quad) {
+            uint32_t b = (uint32_t)batch;
+            void *args[] = {&QJ, &b};
+            const void *kern = quad_kernel(qs[0], true);
+            hipError_t e = ensure_dynamic_lds(kern, qs[0].lds);
+            if (e == hipSuccess)
+                e = hipLaunchKernel(kern, dim3(qs[0].tiles, qs[0].batch_tiles, (unsigned)n), dim3(qs[0].nw * 64), args, qs[0].lds, (hipStream_t)stream);
+            if (e != hipSuccess) { set_error(std::string("csb_spmm: ") + hipGetErrorString(e)); return CSB_EDEVICE; }
+            return CSB_OK;
         }
         if (same) {
             uint32_t b = (uint32_t)batch;

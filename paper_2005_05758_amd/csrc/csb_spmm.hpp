@@ -1,0 +1,76 @@
+// Device helpers that the batched products share.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "csb_internal.hpp"
+#include "csb_kernels.hpp"
+
+namespace csb {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// A value that is the same in every lane, in a scalar register.  Two kernel arguments between which a lane
+// chooses (the strides of two sources) go through it: the compiler turns a choice between two arguments
+// into a per-lane load of the chosen one, a trip to memory in front of every load that needs it.
+// (24 of those per pair of passes in the kernels that take several products; without them, batch 64, us
+// per step: two GRU layers of 1024 in 16-row blocks 32.6 -> 25.4, two LSTM layers in 32-row blocks 23.0 -> 20.0.)
+__device__ __forceinline__ uint32_t uni_(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Product of two 24-bit numbers, modulo 2^32.  (__umul24's result is a signed int: the byte offset of an input
+// row 2 GiB and more into X must not be extended with its sign.)
+__device__ __forceinline__ uint32_t mul24_(uint32_t a, uint32_t b) { return (uint32_t)__umul24(a, b); }
+
+// First record segment of the rank-th row tile.  Where every tile's records fit one segment it is the rank
+// itself: one dependent trip to memory less before a launch of a few microseconds has any work.
+__device__ __forceinline__ uint32_t first_segment(const DevMat &m, uint32_t rank) { return m.one_seg ? rank : m.tile_seg0[rank]; }
+
+// Element (column j of A, right-hand side n) of the input, from one of two sources; the right-hand
+// sides of a column are contiguous.  Byte offsets fit 32 bits and the strides over j fit 24 bits
+// (checked on the host).
+struct XSrc {
+    const float *p0;
+    uint32_t n0;          // columns j < n0 come from p0, the rest from p1
+    uint32_t sj0;         // stride over j
+    const float *p1;
+    uint32_t sj1;
+};
+
+// Several independent products in one launch (blockIdx.z picks the product): the per-step
+// products of different layers of a batched recurrent model, each too small to fill the GPU.
+struct SpmmJobs {
+    DevMat m[kMaxJobsPerLaunch];
+    XSrc X[kMaxJobsPerLaunch];
+    float *Y[kMaxJobsPerLaunch];
+    int64_t ldy[kMaxJobsPerLaunch];
+};
+
+// ---- products from the quad section (csb_spmm_quad.hip) -------------------------------------------------------
+constexpr uint32_t kQuadMaxStride = 16383;               // right-hand sides from one column to the next (kQuadNoCol times that, in bytes, fits 32 bits)
+struct QuadMat {
+    const uint32_t *table;
+    const void *recs;
+    const uint8_t *vals;
+    uint32_t vals_bytes, n_tiles, tile_rows, seg_rows, tiles_per_seg, val_fmt, cols;
+};
+struct QuadJobs {
+    QuadMat m[kMaxJobsPerLaunch];
+    XSrc X[kMaxJobsPerLaunch];
+    float *Y[kMaxJobsPerLaunch];
+    int64_t ldy[kMaxJobsPerLaunch];
+};
+struct QuadShape {
+    int columns;            // right-hand sides per workgroup: 32, 64 or 128
+    int nw;                 // wavefronts per workgroup
+    bool two;               // two sources
+    size_t lds;
+    unsigned tiles, batch_tiles;
+    bool operator==(const QuadShape &o) const { return columns == o.columns && nw == o.nw && two == o.two; }
+};
+QuadMat quad_mat(const csb_matrix *m);
+// The launch shape of one product (checked by the caller), `launch_products` of whose size share the launch; false:
+// the product is not for these kernels.
+bool quad_shape(const SpmmCall &c, int32_t batch, size_t launch_products, QuadShape *out, XSrc *X);
+const void *quad_kernel(const QuadShape &sh, bool multi);
+
+}  // namespace csb

@@ -1,0 +1,309 @@
+// Batched CSB-MVM for gfx950 from the quad section of the image: Y = A X in steps of FOUR kernel rows.
+//
+// v_mfma_f32_4x4x1_16b_f32 is sixteen 4 x 4 outer products side by side, as fast per multiply-add as the 16 x 16
+// forms (measured, clocks per SIMD: 9.8 for 256 multiply-adds; 34 for the 1024 of the 16 x 16 x 4 form).  With the right-hand
+// sides of one input row spread over its sixteen blocks (lane = right-hand side) and its A operand taken from ONE
+// block (CBSZ broadcasts, ABID names the block), an instruction multiplies four kernel rows by one input row of 64
+// right-hand sides: a 7 x 7 kernel costs 14 of them per 64 right-hand sides, where 16-row instructions, rows
+// scattered over a 32-row tile, spend as long as 56.  One register of A serves many instructions, and a result
+// register IS an output row (lane = right-hand side): it is added to the wavefront's accumulator of that row, a
+// register picked by the row's place in the tile (VGPR indexing), so results pass through LDS once, at
+// the end, when the wavefronts' tiles are summed in wavefront order.
+// What it all hangs on is in a pass's record (QuadRec), which comes in over the scalar path: no record is staged, nothing is
+// looked up per lane.  An input row that is not finite reaches the rows that use it and no others.
+//
+// What bounds it: the pipe that MFMA and vector instructions share (with every load hitting the caches it is no faster;
+// without the products 8192 x 8192 x 128 takes 16 us instead of 35): products of 4 x 4 granularity, 1.45 times those of the
+// matrix, the row sums (a vector instruction per row and 64 right-hand sides), about 30 others per pass.  Scalar instructions
+// run beside it.  8192 x 8192 at 12x in 32 x 32 blocks, us, records and 16-row instructions from the tile sections / here: 128
+// right-hand sides 63.2 / 35.5 (40 TFLOP/s of products the matrix has), 64 36.9 / 25.4, 16 24.7 / 21.7, 512 242 / 116;
+// 4096 x 4096 in 16-row blocks x 128 29.2 / 15.8, in 64-row blocks 17.0 / 11.0; two LSTM layers of 1024 at batch 64 14.6 / 12.1
+// per step.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "csb_spmm.hpp"
+
+namespace csb {
+
+typedef float floatx32 __attribute__((ext_vector_type(32)));
+
+// ---- the accumulators: registers with fixed numbers, so that one of them can be picked by an index ----------
+// NT tiles of 32 rows from v60 on; behind each a spare one (index 32) for the rows a quad lacks.
+template <int NT>
+struct QuadAcc {
+    floatx32 v[NT];
+};
+
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"      // (M0 is named as clobbered: nothing here keeps a value in it)
+// Rows s of the accumulators += d, s four places of a byte each.  The wait in front covers an MFMA that wrote d; the index
+// is the low byte of the scalar.
+__device__ __forceinline__ void add_rows(QuadAcc<1> &acc, const floatx4 (&d)[1], const uint32_t s) {
+    asm volatile("s_nop 7\n\ts_set_gpr_idx_on %[s0], 0x9\n\tv_add_f32 v60, v60, %[d0]\n\ts_set_gpr_idx_idx %[s1]\n\tv_add_f32 v60, v60, %[d1]\n\t"
+                 "s_set_gpr_idx_idx %[s2]\n\tv_add_f32 v60, v60, %[d2]\n\ts_set_gpr_idx_idx %[s3]\n\tv_add_f32 v60, v60, %[d3]\n\ts_set_gpr_idx_off"
+                 : "+{v[60:91]}"(acc.v[0])
+                 : [d0] "v"(d[0][0]), [d1] "v"(d[0][1]), [d2] "v"(d[0][2]), [d3] "v"(d[0][3]), [s0] "s"(s), [s1] "s"(s >> 8), [s2] "s"(s >> 16),
+                   [s3] "s"(s >> 24)
+                 : "v92", "m0");
+}
+#define CSB_ROW2(I) "v_add_f32 v60, v60, %[d" #I "]\n\tv_add_f32 v94, v94, %[e" #I "]\n\t"
+__device__ __forceinline__ void add_rows(QuadAcc<2> &acc, const floatx4 (&d)[2], const uint32_t s) {
+    asm volatile("s_nop 7\n\ts_set_gpr_idx_on %[s0], 0x9\n\t" CSB_ROW2(0) "s_set_gpr_idx_idx %[s1]\n\t" CSB_ROW2(1) "s_set_gpr_idx_idx %[s2]\n\t" CSB_ROW2(2)
+                 "s_set_gpr_idx_idx %[s3]\n\t" CSB_ROW2(3) "s_set_gpr_idx_off"
+                 : "+{v[60:91]}"(acc.v[0]), "+{v[94:125]}"(acc.v[1])
+                 : [d0] "v"(d[0][0]), [d1] "v"(d[0][1]), [d2] "v"(d[0][2]), [d3] "v"(d[0][3]), [e0] "v"(d[1][0]), [e1] "v"(d[1][1]),
+                   [e2] "v"(d[1][2]), [e3] "v"(d[1][3]), [s0] "s"(s), [s1] "s"(s >> 8), [s2] "s"(s >> 16), [s3] "s"(s >> 24)
+                 : "v92", "v126", "m0");
+}
+#undef CSB_ROW2
+#pragma clang diagnostic pop
+
+// NT times 64 / G right-hand sides, in G groups of 64 / G lanes that take every G-th column of a pass (each
+// group holds partial sums; they meet with the wavefronts' at the end).  G = 1 or 2: four groups of 16 right-hand sides
+// are never faster than two of 32 with half the lanes idle (8192 x 8192 x 16: 21.7 and 21.2 us; 8192 x 2048 x 16
+// in 64 x 64 blocks 7.2 and 6.6): a pass's instructions are the same.
+template <int NT, int G>
+struct QuadForm {
+    static_assert(G == 1 || G == 2, "one or two groups");
+    static constexpr uint32_t lanes = 64 / G;            // lanes of a group
+    static constexpr uint32_t columns = lanes * NT;      // right-hand sides per workgroup
+    static constexpr int steps = kQuadCols / G;          // input loads, and instructions per four rows, of a pass
+    static constexpr int cbsz = G == 1 ? 4 : 3;
+};
+
+// The two halves of a pass's record, in scalar registers: the kernels read them through the constant address space.
+typedef uint32_t uint32x8 __attribute__((ext_vector_type(8)));
+#define CSB_CONST_AS __attribute__((address_space(4)))
+
+template <int NT, int G>
+struct QuadOps {
+    uint32_t a[4];                                       // register j: rows of the quads j and 4 + j by 8 columns
+    uint32_t x[kQuadCols / G][NT];                       // a lane's right-hand sides of G columns
+};
+
+template <int S, int S1, int Q, int NT, int G>
+__device__ __forceinline__ void quad_steps(const QuadOps<NT, G> &o, floatx4 (&D)[NT]) {
+    if constexpr (S < S1) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+            D[t] = __builtin_amdgcn_mfma_f32_4x4x1f32(__uint_as_float(o.a[Q & 3]), __uint_as_float(o.x[S][t]), D[t], QuadForm<NT, G>::cbsz, 2 * S + (Q >> 2), 0);
+        quad_steps<S + 1, S1, Q>(o, D);
+    }
+}
+
+// One wavefront's share of a tile's products: the passes [first, last), added into `acc`.  bt0: first right-hand side
+// of the workgroup.
+template <int NT, int G, bool TWO>
+__device__ __forceinline__ void quad_passes(const QuadMat &m, const XSrc &X, const uint32_t first, const uint32_t last, const uint32_t bt0,
+                                            const uint32_t batch, QuadAcc<NT> &acc) {
+    using F = QuadForm<NT, G>;
+    const uint32_t lane = threadIdx.x & 63u, group = lane / F::lanes;
+    // the lane's place in an A register: row of its quad, which of the two quads, column of the pass
+    const uint32_t blk = (lane >> 2) % (16u / G);
+    const uint32_t arow = lane & 3u, ahalf = (blk & 1u) * 16u, acol = G * (blk >> 1) + group;
+    const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc((void *)m.vals, 0, (int)m.vals_bytes, 0x00020000);
+    // The range of a source ends with the batch of its last column: a lane past the batch reads its neighbours (nothing is
+    // made of them) or a zero, a column that a pass does not have is a zero and no traffic.
+    const uint32_t xlane = (lane % F::lanes) * 4u;
+    const uint32_t sj0 = uni_(X.sj0), sj1 = uni_(X.sj1), n0 = TWO ? uni_(X.n0) : m.cols;
+    const uint64_t p0 = (uint64_t)(uintptr_t)(X.p0 + bt0), p1 = (uint64_t)(uintptr_t)(X.p1 + bt0);
+    const uint32_t end0 = ((n0 - 1u) * sj0 + batch - bt0) * 4u, end1 = TWO ? ((m.cols - n0 - 1u) * sj1 + batch - bt0) * 4u : 0u;
+    const uint8_t CSB_CONST_AS *rec = (const uint8_t CSB_CONST_AS *)(uintptr_t)m.recs + (size_t)first * sizeof(QuadRec);
+    auto read_loads = [&](int i) { return *(const uint32x8 CSB_CONST_AS *)(rec + i * (int)sizeof(QuadRec)); };
+    auto read_slots = [&](int i) { return *(const uint32x8 CSB_CONST_AS *)(rec + i * (int)sizeof(QuadRec) + 32); };
+
+    auto issue = [&](const uint32x8 &r, QuadOps<NT, G> &o) {         // 1 + NT * steps loads
+        const uint32_t stride = r[1] & 0xffffu;
+        const bool second = TWO && ((r[1] >> 24) & kQuadSecond) != 0u;
+        uint32_t row = (second ? sj1 : sj0) * 4u;        // bytes from one column's right-hand sides to the next's
+        asm("" : "+v"(row));                             // (in a vector register: then a column's offset is one instruction)
+        const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(uintptr_t)(second ? p1 : p0), 0, (int)(second ? end1 : end0), 0x00020000);
+#pragma unroll
+        for (int s = 0; s < F::steps; ++s) {
+            uint32_t col;
+            if constexpr (G == 1) {
+                col = (s & 1) ? r[2 + s / 2] >> 16 : r[2 + s / 2] & 0xffffu;
+            } else {
+                col = group ? r[2 + s] >> 16 : r[2 + s] & 0xffffu;
+            }
+            const uint32_t off = mul24_(col, row) + xlane;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) o.x[s][t] = __builtin_amdgcn_raw_buffer_load_b32(xrsrc, (int)(off + 256u * t), 0, 0);
+        }
+        // (of quads a pass does not have: what lies there, and no use is made of it)
+        typedef uint32_t vec4 __attribute__((ext_vector_type(4)));
+        const vec4 a = __builtin_bit_cast(vec4, __builtin_amdgcn_raw_buffer_load_b128(vrsrc, (int)(mul24_(acol, stride) + mul24_(arow, stride >> 2) + ahalf + r[0]), 0, 0));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o.a[j] = a[j];
+    };
+    auto multiply = [&](const uint32_t w, const uint32x8 &slots, const QuadOps<NT, G> &o) {
+        // the loads of the next pass may be in flight, this one's are here (one wait; left to itself the compiler
+        // puts one in front of every product)
+        constexpr int kYounger = 1 + NT * F::steps;
+        __builtin_amdgcn_s_waitcnt((kYounger & 15) | (kYounger >> 4) << 14 | 0x0f70);
+        const uint32_t quads = (w >> 16) & 0xffu;
+        auto product = [&](auto qc, floatx4 (&D)[NT]) {
+            constexpr int Q = decltype(qc)::value;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) D[t] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+            quad_steps<0, F::steps / 2, Q>(o, D);
+            if ((w >> 24) & kQuadWide) quad_steps<F::steps / 2, F::steps, Q>(o, D);
+        };
+        auto pair = [&](auto qc) {
+            constexpr int Q = decltype(qc)::value;
+            floatx4 D0[NT], D1[NT];
+            product(qc, D0);
+            if constexpr (NT > 1) add_rows(acc, D0, slots[Q]);            // (registers for one quad's results)
+            if (Q + 1u < quads) product(std::integral_constant<int, Q + 1>{}, D1);   // (uniform)
+            if constexpr (NT == 1) add_rows(acc, D0, slots[Q]);
+            if (Q + 1u < quads) add_rows(acc, D1, slots[Q + 1]);
+        };
+        pair(std::integral_constant<int, 0>{});
+        if (quads <= 2u) return;
+        pair(std::integral_constant<int, 2>{});
+        if (quads <= 4u) return;
+        pair(std::integral_constant<int, 4>{});
+        if (quads <= 6u) return;
+        pair(std::integral_constant<int, 6>{});
+    };
+    // A pass's loads fly while the one before multiplies.  Scalar loads come back in any order, so that waiting for one is
+    // waiting for all: they are asked for behind the only wait of a turn and used in the next one.
+    QuadOps<NT, G> oa, ob;
+    uint32_t left = last - first;
+    uint32x8 r = read_loads(0), sa = read_slots(0), sb;
+    uint32_t wa = r[1], wb;
+    issue(r, oa);
+    r = read_loads(1);
+    while (true) {
+        issue(r, ob);
+        wb = r[1];
+        r = read_loads(2); sb = read_slots(1);
+        multiply(wa, sa, oa);
+        if (--left == 0u) break;
+        issue(r, oa);
+        wa = r[1];
+        r = read_loads(3); sa = read_slots(2);
+        multiply(wb, sb, ob);
+        if (--left == 0u) break;
+        rec += 2 * sizeof(QuadRec);
+    }
+}
+
+template <int NT, int G, bool TWO, int NW>
+__device__ __forceinline__ void spmm_quad_body(const QuadMat &m, const XSrc &X, float *__restrict__ Y, const int64_t ldy, const uint32_t batch,
+                                               const uint32_t tile, const uint32_t block_y) {
+    extern __shared__ float4 smem4[];
+    using F = QuadForm<NT, G>;
+    constexpr uint32_t NTHR = NW * 64;
+    const uint32_t lane = threadIdx.x & 63u, wave = uni_(threadIdx.x >> 6), tid = wave * 64u + lane;
+    const uint32_t bt0 = block_y * F::columns;
+    QuadAcc<NT> acc;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc.v[t] = 0.0f;
+    const uint32_t CSB_CONST_AS *tab = (const uint32_t CSB_CONST_AS *)(uintptr_t)m.table;
+    const uint32_t l0 = tile * kQuadLists + wave * (kQuadLists / NW);
+    const uint32_t first = tab[l0], last = tab[l0 + kQuadLists / NW];
+    if (first < last) quad_passes<NT, G, TWO>(m, X, first, last, bt0, batch, acc);
+
+    // The wavefronts' tiles, RM rows at a time.
+    constexpr int RM = NT == 2 ? 16 : 32;
+    const uint32_t seg = tile / m.tiles_per_seg, in = tile - seg * m.tiles_per_seg;
+    const uint32_t row0 = seg * m.seg_rows + in * m.tile_rows, tile_rows = min(m.tile_rows, m.seg_rows - in * m.tile_rows);
+    float *red = (float *)smem4;                         // [waves][RM][NT][64]
+#pragma unroll
+    for (int r0 = 0; r0 < kQuadRows; r0 += RM) {
+        if ((uint32_t)r0 >= tile_rows) break;            // (uniform)
+        if (r0) __syncthreads();                         // the rows before are done with
+#pragma unroll
+        for (int i = 0; i < RM; ++i)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) red[((wave * RM + i) * NT + t) * 64u + lane] = acc.v[t][r0 + i];
+        __syncthreads();
+        const uint32_t rows = min(tile_rows - r0, (uint32_t)RM);
+        for (uint32_t e = tid; e < rows * F::columns; e += NTHR) {
+            const uint32_t i = e / F::columns, n = e % F::columns;
+            float s = 0.0f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w)
+#pragma unroll
+                for (int g = 0; g < G; ++g) s += red[(w * RM + i) * (64u * NT) + g * F::lanes + n];
+            if (bt0 + n < batch) Y[(size_t)(row0 + r0 + i) * ldy + bt0 + n] = s;
+        }
+    }
+}
+
+template <int NT, int G, bool TWO, int NW>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void spmm_quad_kernel(const QuadMat m, const XSrc X, float *__restrict__ Y,
+                                                                                              const int64_t ldy, const uint32_t batch) {
+    spmm_quad_body<NT, G, TWO, NW>(m, X, Y, ldy, batch, blockIdx.x, blockIdx.y);
+}
+// Several independent products in one launch (blockIdx.z picks the product).
+template <int NT, int G, bool TWO, int NW>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void spmm_quad_multi_kernel(const QuadJobs J, const uint32_t batch) {
+    const uint32_t j = blockIdx.z;
+    if (blockIdx.x >= J.m[j].n_tiles) return;            // the grid is as wide as the widest product
+    spmm_quad_body<NT, G, TWO, NW>(J.m[j], J.X[j], J.Y[j], J.ldy[j], batch, blockIdx.x, blockIdx.y);
+}
+
+// ---- launches ------------------------------------------------------------------------------------------------
+QuadMat quad_mat(const csb_matrix *m) {
+    const QuadPlan &qp = m->plan.quad;
+    uint8_t *b = (uint8_t *)m->d_buf;
+    return QuadMat{(const uint32_t *)(b + qp.off_table), b + qp.off_recs, b + qp.off_vals, (uint32_t)qp.vals_bytes, qp.n_tiles, qp.tile_rows, qp.seg_rows,
+                   qp.tiles_per_seg, qp.val_fmt, (uint32_t)m->plan.hdr.cols};
+}
+
+// Right-hand sides per workgroup and its wavefronts, for `tiles` row tiles in the launch.  What counts is the
+// number of turns the workgroups take over the 256 CUs and how long a turn is: one of 16 wavefronts takes 1.16 times as long
+// with 64 right-hand sides as with 32 and 1.65 times with 128 (8192 x 8192 at 12x, us: 21.7, 25.4, 35); of 8 wavefronts two share
+// a CU, and a turn of 512 of them takes 2.65 (115 / 2 us), of up to 256 1.9 (41.7), so they pay where the
+// launch takes several turns (x 512: 128 us with 16 wavefronts, 115 with 8; x 260: 102.6 and 95.6; 5000 x 300 x 500 in
+// 64 x 64 blocks 17.5 and 12.3).
+static void quad_columns(size_t tiles, int32_t batch, int *columns, int *nw) {
+    double best = 1e300;
+    for (int c : {32, 64, 128}) {
+        const size_t w = tiles * (size_t)((batch + c - 1) / c);
+        const double turn = c == 32 ? 1.0 : c == 64 ? 1.16 : 1.65, cost = (double)((w + 255) / 256) * turn;
+        if (cost < best) { best = cost; *columns = c; *nw = 16; }
+        if (c < 128) continue;
+        const double cost8 = (double)(w / 512) * 2.65 + (w % 512 > 256 ? 2.65 : w % 512 ? 1.9 : 0.0);
+        if (cost8 < best) { best = cost8; *columns = c; *nw = 8; }
+    }
+}
+
+bool quad_shape(const SpmmCall &c, int32_t batch, size_t launch_products, QuadShape *out, XSrc *X) {
+    const QuadPlan &qp = c.mat->plan.quad;
+    const uint64_t cols = c.mat->plan.hdr.cols;
+    if (!qp.valid || qp.val_fmt != CSB_VAL_F32) return false;
+    // a pass takes its columns from one source: two sources need a plan that was cut where they meet; one source
+    // under such a plan is two that follow each other
+    const bool two_given = c.n0 < (uint32_t)cols, two = qp.split_col > 0 && qp.split_col < cols;
+    if (two_given && (!two || qp.split_col != c.n0)) return false;
+    *X = two_given || !two ? XSrc{c.p0, c.n0, (uint32_t)c.sj0, c.p1, (uint32_t)c.sj1}
+                           : XSrc{c.p0, qp.split_col, (uint32_t)c.sj0, c.p0 + (size_t)qp.split_col * c.sj0, (uint32_t)c.sj0};
+    // 32-bit byte offsets, that of kQuadNoCol among them
+    if (X->sj0 > kQuadMaxStride || X->sj1 > kQuadMaxStride) return false;
+    quad_columns((size_t)qp.n_tiles * launch_products, batch, &out->columns, &out->nw);
+    out->two = two;
+    out->lds = (size_t)out->nw * (out->columns == 128 ? 16 * 2 : 32) * 64 * sizeof(float);
+    out->tiles = (unsigned)qp.n_tiles;
+    out->batch_tiles = (unsigned)((batch + out->columns - 1) / out->columns);
+    return true;
+}
+
+const void *quad_kernel(const QuadShape &sh, bool multi) {
+#define CSB_Q(NT, G, TWO, NW) (multi ? (const void *)spmm_quad_multi_kernel<NT, G, TWO, NW> : (const void *)spmm_quad_kernel<NT, G, TWO, NW>)
+#define CSB_QV(NT, G, NW) return sh.two ? CSB_Q(NT, G, true, NW) : CSB_Q(NT, G, false, NW);
+    if (sh.columns == 128) {
+        if (sh.nw == 8) { CSB_QV(2, 1, 8) }
+        CSB_QV(2, 1, 16)
+    }
+    if (sh.columns == 64) { CSB_QV(1, 1, 16) }
+    CSB_QV(1, 2, 16)
+#undef CSB_QV
+#undef CSB_Q
+}
+
+}  // namespace csb

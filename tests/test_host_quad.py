@@ -1,0 +1,43 @@
+"""The section of the device image that the batched products read: csb_plan_validate walks it the way
+the kernels do and rebuilds the matrix from it.  No GPU."""
+import numpy as np
+import pytest
+
+import csb_inputs
+from paper_2005_05758_amd import CsbMatrix, CsbRnn
+from paper_2005_05758_amd import binding as csb
+
+
+# Blocks lower and taller than a row tile (16 or 32 rows), passes of 1 to 8 columns, kernel rows in fours and not,
+# rows and columns that end inside a tile, a block, a pass.
+@pytest.mark.parametrize("R,C,br,bc", [(1, 1, 1, 1), (33, 70, 1, 9), (37, 53, 8, 8), (64, 65, 16, 16), (150, 77, 33, 40), (200, 90, 64, 64),
+                                       (130, 100, 128, 128), (8200, 33, 16, 32), (300, 17, 256, 8)])
+@pytest.mark.parametrize("fmt", [csb.VAL_F32, csb.VAL_F16, csb.VAL_BF16])
+def test_section_holds_the_matrix(fmt, R, C, br, bc):
+    for rate in (1.0, 3.0) if R < 1000 else (3.0,):
+        M = CsbMatrix(csb_inputs.small_matrix(R + C, R, C, br, bc, rate=rate).A, br, bc)
+        M.set_value_format(fmt)
+        for mode in (0, 1, 2) if R < 1000 else (0,):
+            M.plan(mode=mode)
+            M.validate()
+        M.plan_rows()
+        M.validate()
+
+
+# A recurrent handle's matrices: tiles end with a gate, passes end where the input's two sources meet, the GRU's
+# candidate rows are summed in two parts.
+@pytest.mark.parametrize("cell,gates", [(csb.CELL_LSTM, 4), (csb.CELL_GRU, 3), (csb.CELL_LIGRU, 2), (csb.CELL_LSTMP, 4), (csb.CELL_GRU_RB, 3)])
+@pytest.mark.parametrize("inputs,hidden,block", [(5, 40, 16), (39, 33, 32), (64, 100, 64)])
+def test_section_of_a_recurrent_handle(cell, gates, inputs, hidden, block):
+    state = 24 if cell == csb.CELL_LSTMP else hidden
+    A = csb_inputs.small_matrix(7, gates * hidden, inputs + state, block, block, rate=3.0).A.copy()
+    second = []
+    if cell == csb.CELL_GRU_RB:
+        A[2 * hidden:, inputs:] = 0.0
+        second = [CsbMatrix(csb_inputs.small_matrix(8, hidden, hidden, block, block, rate=3.0).A, block, block)]
+    if cell == csb.CELL_LSTMP:
+        second = [CsbMatrix(csb_inputs.small_matrix(8, state, hidden, block, block, rate=3.0).A, block, block)]
+    W = CsbMatrix(A, block, block)
+    CsbRnn(cell, inputs, hidden, [W], proj=state if cell == csb.CELL_LSTMP else 0, Wp=second or None)
+    for m in [W] + second:
+        m.validate()
