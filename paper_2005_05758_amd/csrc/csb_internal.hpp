@@ -239,8 +239,9 @@ struct StreamPlan {
 // it needs in the record, which comes in over the scalar path.
 //   table   [n_tiles][kQuadLists] first pass of every list, and one entry more for the end of the last
 //   records [passes + kQuadSpareRecs]
-//   values  binary32: per pass [column][4 rows][quad]; 16-bit formats: [4 columns][4 rows][quad][4 columns]; columns in
-//           fours, zeros where the pass has no such row or column; kQuadPad bytes of zeros behind the last
+//   values  binary32: per pass [column][4 rows][quad]; 16-bit formats: [4 columns][4 rows][quad][4 columns], and with more
+//           than four quads [4 columns][4 rows][quad % 4][quad / 4][4 columns], eight of them; columns in fours,
+//           zeros where the pass has no such row or column; kQuadPad bytes of zeros behind the last
 // With `seg_rows` > 0 tiles do not cross multiples of it (the gates of a recurrent cell, seg_rows units each);
 // with `split_col` > 0 no pass crosses that column (the border between the two sources of a step's
 // input), and columns of the second part are counted from it.
@@ -257,7 +258,7 @@ struct QuadRec {
     uint16_t stride;                     // bytes from one column (16-bit formats: four columns) to the next
     uint8_t quads;                       // kernel rows in fours
     uint8_t flags;                       // kQuadWide: more than 4 columns; kQuadSecond: columns of the second source
-    uint16_t col[kQuadCols];             // input rows; kQuadNoCol where the pass has fewer
+    uint16_t col[kQuadCols];                 // input rows; kQuadNoCol where the pass has fewer
     uint32_t pad[2];
     // what the row sums need
     uint8_t slot[kQuadRows];             // the rows' places in the tile; kQuadRows (a spare one) where there is none

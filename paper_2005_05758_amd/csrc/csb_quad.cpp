@@ -25,11 +25,18 @@ struct QPass {
 
 // Work of a pass, in units of about one instruction of a wavefront: what it costs whatever it multiplies, its input
 // rows, its products and its row sums.
-uint32_t pass_cost(const QPass &p) { return 60u + 4u * kQuadCols + p.ncols * ((p.nrows + 3u) / 4u) * 4u + 3u * p.nrows; }
+uint32_t pass_cost(const QPass &p) { return 90u + p.ncols * ((p.nrows + 3u) / 4u) * 4u + 3u * p.nrows; }
 
-size_t pass_value_bytes(const QPass &p, bool bits16) {
-    const size_t quads = (p.nrows + 3u) / 4u;
-    return (size_t)((p.ncols + 3u) / 4u) * quads * (bits16 ? 32u : 64u);
+size_t pass_value_bytes(uint32_t nrows, uint32_t ncols, bool bits16) {
+    const size_t quads = (nrows + 3u) / 4u, fours = (ncols + 3u) / 4u;
+    return bits16 ? fours * (quads > 4 ? 8 : quads) * 32u : fours * quads * 64u;
+}
+uint32_t pass_stride(uint32_t quads, bool bits16) { return bits16 ? (quads > 4 ? 8 : quads) * 32u : quads * 16u; }
+// Position of the value at (row q, column j) among a pass's values.
+size_t value_at(uint32_t quads, uint32_t q, uint32_t j, bool bits16) {
+    if (!bits16) return (j * 4u + (q & 3u)) * quads + (q >> 2);
+    const size_t quad = quads > 4 ? (q >> 2 & 3u) * 2u + (q >> 4) : q >> 2, room = quads > 4 ? 8 : quads;
+    return (((j >> 2) * 4u + (q & 3u)) * room + quad) * 4u + (j & 3u);
 }
 
 // The parts of block b's columns [q0, q1) that are summed together (GRU split) and come from one source.
@@ -127,7 +134,7 @@ int plan_quad(csb_matrix *m) {
             std::memset(e.slot, kQuadRows, sizeof(e.slot));
             std::memcpy(e.slot, slot, p.nrows);
             tiles[tile].push_back(e);
-            bytes += pass_value_bytes(p, bits16);
+            bytes += pass_value_bytes(p.nrows, p.ncols, bits16);
             ++qp.n_passes;
         });
         qp.vals_bytes = bytes + kQuadPad;
@@ -158,15 +165,15 @@ int plan_quad(csb_matrix *m) {
         pl.image.resize(align_up(qp.off_vals + qp.vals_bytes, 256), 0);
         uint8_t *im = pl.image.data();
         std::memcpy(im + qp.off_table, table.data(), table.size() * 4);
-        auto *recs = (QuadRec *)(im + qp.off_recs);
         uint64_t at = 0;
+        auto *recs = (QuadRec *)(im + qp.off_recs);
         for (size_t i = 0; i < order.size(); ++i) {
             const Entry &e = *order[i];
             const QPass &p = e.p;
             const uint32_t quads = (p.nrows + 3u) / 4u;
             QuadRec &r = recs[i];
             r.val = (uint32_t)at;
-            r.stride = (uint16_t)(quads * (bits16 ? 32u : 16u));
+            r.stride = (uint16_t)pass_stride(quads, bits16);
             r.quads = (uint8_t)quads;
             r.flags = (uint8_t)((p.ncols > 4 ? kQuadWide : 0) | (e.second ? kQuadSecond : 0));
             const uint16_t *ci = m->colidx.data() + m->col_off[p.b];
@@ -179,11 +186,10 @@ int plan_quad(csb_matrix *m) {
             for (uint32_t q = 0; q < p.nrows; ++q) {
                 const float *row = src + (size_t)(p.a0 + q) * nc;
                 for (uint32_t j = 0; j < p.ncols; ++j)
-                    if (!bits16) ((float *)dst)[(j * 4u + (q & 3u)) * quads + (q >> 2)] = row[j];
-                    else ((uint16_t *)dst)[(((j >> 2) * 4u + (q & 3u)) * quads + (q >> 2)) * 4u + (j & 3u)] =
-                             m->val_fmt == CSB_VAL_F16 ? f32_to_f16_bits(row[j]) : f32_to_bf16_bits(row[j]);
+                    if (!bits16) ((float *)dst)[value_at(quads, q, j, false)] = row[j];
+                    else ((uint16_t *)dst)[value_at(quads, q, j, true)] = m->val_fmt == CSB_VAL_F16 ? f32_to_f16_bits(row[j]) : f32_to_bf16_bits(row[j]);
             }
-            at += pass_value_bytes(p, bits16);
+            at += pass_value_bytes(p.nrows, p.ncols, bits16);
         }
         qp.valid = true;
         pl.quad = qp;
@@ -239,18 +245,18 @@ int validate_quad(const csb_matrix *m) {
                 while (ncols < (uint32_t)kQuadCols && r.col[ncols] != kQuadNoCol) ++ncols;
                 while (nrows < (uint32_t)kQuadRows && r.slot[nrows] != kQuadRows) ++nrows;
                 const bool second = (r.flags & kQuadSecond) != 0;
-                if (!ncols || !nrows || r.quads != (nrows + 3u) / 4u || r.stride != r.quads * (bits16 ? 32u : 16u) ||
+                if (!ncols || !nrows || r.quads != (nrows + 3u) / 4u || r.stride != pass_stride(r.quads, bits16) ||
                     ((r.flags & kQuadWide) != 0) != (ncols > 4) || (second && !qp.split_col)) return fail("pass size");
-                const size_t bytes = pass_value_bytes(QPass{0, 0, 0, (uint8_t)nrows, (uint8_t)ncols, 0}, bits16);
+                const size_t bytes = pass_value_bytes(nrows, ncols, bits16);
                 if ((uint64_t)r.val + bytes + kQuadPad > qp.vals_bytes) return fail("values");
                 for (uint32_t j = ncols; j < (uint32_t)kQuadCols; ++j) if (r.col[j] != kQuadNoCol) return fail("gap in the columns");
                 for (uint32_t q = nrows; q < (uint32_t)kQuadRows; ++q) if (r.slot[q] != kQuadRows) return fail("gap in the rows");
                 for (uint32_t q = 0; q < r.quads * 4u; ++q)
                     for (uint32_t j = 0; j < (ncols + 3u) / 4u * 4u; ++j) {
                         float v;
-                        if (!bits16) v = ((const float *)(vals + r.val))[(j * 4u + (q & 3u)) * r.quads + (q >> 2)];
+                        if (!bits16) v = ((const float *)(vals + r.val))[value_at(r.quads, q, j, false)];
                         else {
-                            const uint16_t bits = ((const uint16_t *)(vals + r.val))[(((j >> 2) * 4u + (q & 3u)) * r.quads + (q >> 2)) * 4u + (j & 3u)];
+                            const uint16_t bits = ((const uint16_t *)(vals + r.val))[value_at(r.quads, q, j, true)];
                             v = qp.val_fmt == CSB_VAL_F16 ? f16_bits_to_f32(bits) : bf16_bits_to_f32(bits);
                         }
                         if (q >= nrows || j >= ncols) {

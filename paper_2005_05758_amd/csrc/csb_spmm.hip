@@ -1040,6 +1040,20 @@ static int spmm_16bit(const char *who, int fmt, const csb_matrix *m, const uint1
         set_error(w + ": the block rows are too tall for the accumulator tiles");
         return CSB_EUNSUPPORTED;
     }
+    QuadShape qs;
+    if (quad16_shape(m, ldx, batch, &qs)) {
+        QuadMat qm = quad_mat(m);
+        XSrc X{(const float *)d_X, (uint32_t)h.cols, (uint32_t)ldx, (const float *)d_X, (uint32_t)ldx};
+        uint32_t b = (uint32_t)batch;
+        int64_t ldy_ = ldy;
+        void *args[] = {&qm, &X, &d_Y, &ldy_, &b};
+        const void *kern = quad16_kernel(qs, fmt == CSB_VAL_F16);
+        hipError_t e = ensure_dynamic_lds(kern, qs.lds);
+        if (e == hipSuccess)
+            e = hipLaunchKernel(kern, dim3(qs.tiles, qs.batch_tiles), dim3(qs.nw * 64), args, qs.lds, (hipStream_t)stream);
+        if (e != hipSuccess) { set_error(w + ": " + hipGetErrorString(e)); return CSB_EDEVICE; }
+        return CSB_OK;
+    }
     const int nw = fits16 ? 16 : 8;
     DevMat dm = dev_mat(m);
     uint32_t b = (uint32_t)batch, ld = (uint32_t)ldx;

@@ -72,5 +72,8 @@ QuadMat quad_mat(const csb_matrix *m);
 // the product is not for these kernels.
 bool quad_shape(const SpmmCall &c, int32_t batch, size_t launch_products, QuadShape *out, XSrc *X);
 const void *quad_kernel(const QuadShape &sh, bool multi);
+// The same for 16-bit values times 16-bit right-hand sides (one source, `ldx` elements from one column to the next).
+bool quad16_shape(const csb_matrix *mat, int64_t ldx, int32_t batch, QuadShape *out);
+const void *quad16_kernel(const QuadShape &sh, bool half);
 
 }  // namespace csb

@@ -191,13 +191,132 @@ __device__ __forceinline__ void quad_passes(const QuadMat &m, const XSrc &X, con
     }
 }
 
-template <int NT, int G, bool TWO, int NW>
+// ---- 16-bit values times 16-bit right-hand sides (v_mfma_f32_4x4x4_16b) -----------------------------------------
+// An instruction takes four columns.  With NT = 2 a lane holds two neighbouring right-hand sides of an input row in one
+// register; tile t holds the right-hand sides 2 n + t, its operand the halves t of four rows.
+typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+struct QuadOps16 {
+    uint32_t a[4];                                       // registers 2 j and 2 j + 1: rows of the quads 4 j ... by 4 columns each
+    uint32_t x[kQuadCols];                               // NT right-hand sides of a column
+};
+
+// One product: quad Q by the four columns S.
+template <int S, int Q, int NT, bool HALF>
+__device__ __forceinline__ void quad16_step(const QuadOps16 &o, const uint32_t (&b)[NT][2], floatx4 (&D)[NT]) {
+    constexpr int cbsz = 4, abid = 4 * S + (Q & 3);
+    const uint2 a = make_uint2(o.a[2 * (Q >> 2)], o.a[2 * (Q >> 2) + 1]);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const uint2 x = make_uint2(b[t][0], b[t][1]);
+        if constexpr (HALF) D[t] = __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(f16x4, a), __builtin_bit_cast(f16x4, x), D[t], cbsz, abid, 0);
+        else D[t] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(bf16x4, a), __builtin_bit_cast(bf16x4, x), D[t], cbsz, abid, 0);
+    }
+}
+
+// (X: the rows of 16-bit right-hand sides; its stride counts elements)
+template <int NT, bool HALF>
+__device__ __forceinline__ void quad16_passes(const QuadMat &m, const XSrc &X, const uint32_t first, const uint32_t last, const uint32_t bt0,
+                                              const uint32_t batch, QuadAcc<NT> &acc) {
+    constexpr int steps = 2;                             // of four columns
+    const uint32_t lane = threadIdx.x & 63u;
+    // the lane's place in an A register: (four columns, row of the quad), and quad of four
+    const uint32_t afour = 4u * (lane >> 4) + (lane & 3u), aquad = 8u * ((lane >> 2) & 3u), wide_only = (lane >> 4) == 1u;
+    const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc((void *)m.vals, 0, (int)m.vals_bytes, 0x00020000);
+    const uint32_t xlane = lane * 2u * NT;
+    uint32_t row = uni_(X.sj0) * 2u;
+    const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc((void *)((const uint16_t *)X.p0 + bt0), 0,
+                                                                           (int)(((m.cols - 1u) * uni_(X.sj0) + batch - bt0) * 2u), 0x00020000);
+    asm("" : "+v"(row));                                 // (in a vector register: then a column's offset is one instruction)
+    uint32_t lo = 0x05040100u, hi = 0x07060302u;         // v_perm selectors: the low, the high halves of two registers
+    asm("" : "+v"(lo), "+v"(hi));
+    const uint8_t CSB_CONST_AS *rec = (const uint8_t CSB_CONST_AS *)(uintptr_t)m.recs + (size_t)first * sizeof(QuadRec);
+    auto read_loads = [&](int i) { return *(const uint32x8 CSB_CONST_AS *)(rec + i * (int)sizeof(QuadRec)); };
+    auto read_slots = [&](int i) { return *(const uint32x8 CSB_CONST_AS *)(rec + i * (int)sizeof(QuadRec) + 32); };
+    constexpr int kLoads = 1 + 4 * steps;                // of a pass
+
+    auto issue = [&](const uint32x8 &r, QuadOps16 &o) {
+        const uint32_t stride = r[1] & 0xffffu, quads = (r[1] >> 16) & 0xffu;
+        // (of quads that a pass does not have: what lies there, and no use is made of it; of the second four columns, where it has
+        // none: zeros.  They are multiplied all the same: a branch around that is slower, 8192 x 8192 x 512 70.9 us instead of 66.7)
+        uint32_t at = mul24_(afour, stride >> 2) + (aquad << (quads > 4u ? 1u : 0u)) + r[0];
+        at = wide_only > ((r[1] >> 24) & kQuadWide) ? 0x80000000u : at;
+        typedef uint32_t vec4 __attribute__((ext_vector_type(4)));
+        const vec4 a = __builtin_bit_cast(vec4, __builtin_amdgcn_raw_buffer_load_b128(vrsrc, (int)at, 0, 0));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o.a[j] = a[j];
+        auto cols = [&](int i) { return (i & 1) ? r[2 + i / 2] >> 16 : r[2 + i / 2] & 0xffffu; };
+#pragma unroll
+        for (int i = 0; i < 4 * steps; ++i) {
+            if constexpr (NT == 2) o.x[i] = __builtin_amdgcn_raw_buffer_load_b32(xrsrc, (int)(mul24_(cols(i), row) + xlane), 0, 0);
+            else o.x[i] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(xrsrc, (int)(mul24_(cols(i), row) + xlane), 0, 0);
+        }
+    };
+    auto multiply = [&](const uint32_t w, const uint32x8 &slots, const QuadOps16 &o) {
+        __builtin_amdgcn_s_waitcnt((kLoads & 15) | (kLoads >> 4) << 14 | 0x0f70);      // (see quad_passes)
+        const uint32_t quads = (w >> 16) & 0xffu;
+        uint32_t b[steps][NT][2];                        // [four columns][tile][words of two columns]
+#pragma unroll
+        for (int s = 0; s < steps; ++s)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                b[s][0][h] = __builtin_amdgcn_perm(o.x[4 * s + 2 * h + 1], o.x[4 * s + 2 * h], lo);
+                if constexpr (NT == 2) b[s][1][h] = __builtin_amdgcn_perm(o.x[4 * s + 2 * h + 1], o.x[4 * s + 2 * h], hi);
+            }
+        auto quad = [&](auto qc) {
+            constexpr int Q = decltype(qc)::value;
+            floatx4 D[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) D[t] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+            quad16_step<0, Q, NT, HALF>(o, b[0], D);
+            quad16_step<1, Q, NT, HALF>(o, b[1], D);
+            add_rows(acc, D, slots[Q]);
+        };
+        quad(std::integral_constant<int, 0>{});
+        if (quads <= 1u) return;
+        quad(std::integral_constant<int, 1>{});
+        if (quads <= 2u) return;
+        quad(std::integral_constant<int, 2>{});
+        if (quads <= 3u) return;
+        quad(std::integral_constant<int, 3>{});
+        if (quads <= 4u) return;
+        quad(std::integral_constant<int, 4>{});
+        if (quads <= 5u) return;
+        quad(std::integral_constant<int, 5>{});
+        if (quads <= 6u) return;
+        quad(std::integral_constant<int, 6>{});
+        if (quads <= 7u) return;
+        quad(std::integral_constant<int, 7>{});
+    };
+    QuadOps16 oa, ob;
+    uint32_t left = last - first;
+    uint32x8 r = read_loads(0), sa = read_slots(0), sb;
+    uint32_t wa = r[1], wb;
+    issue(r, oa);
+    r = read_loads(1);
+    while (true) {                                       // (as in quad_passes)
+        issue(r, ob);
+        wb = r[1];
+        r = read_loads(2); sb = read_slots(1);
+        multiply(wa, sa, oa);
+        if (--left == 0u) break;
+        issue(r, oa);
+        wa = r[1];
+        r = read_loads(3); sa = read_slots(2);
+        multiply(wb, sb, ob);
+        if (--left == 0u) break;
+        rec += 2 * sizeof(QuadRec);
+    }
+}
+
+// VF: format of the values and the right-hand sides.
+template <int NT, int G, bool TWO, int NW, int VF = CSB_VAL_F32>
 __device__ __forceinline__ void spmm_quad_body(const QuadMat &m, const XSrc &X, float *__restrict__ Y, const int64_t ldy, const uint32_t batch,
                                                const uint32_t tile, const uint32_t block_y) {
     extern __shared__ float4 smem4[];
     using F = QuadForm<NT, G>;
     constexpr uint32_t NTHR = NW * 64;
-    const uint32_t lane = threadIdx.x & 63u, wave = uni_(threadIdx.x >> 6), tid = wave * 64u + lane;
+    const uint32_t wave = uni_(threadIdx.x >> 6);
     const uint32_t bt0 = block_y * F::columns;
     QuadAcc<NT> acc;
 #pragma unroll
@@ -205,9 +324,15 @@ __device__ __forceinline__ void spmm_quad_body(const QuadMat &m, const XSrc &X, 
     const uint32_t CSB_CONST_AS *tab = (const uint32_t CSB_CONST_AS *)(uintptr_t)m.table;
     const uint32_t l0 = tile * kQuadLists + wave * (kQuadLists / NW);
     const uint32_t first = tab[l0], last = tab[l0 + kQuadLists / NW];
-    if (first < last) quad_passes<NT, G, TWO>(m, X, first, last, bt0, batch, acc);
+    if (first < last) {
+        if constexpr (VF == CSB_VAL_F32) quad_passes<NT, G, TWO>(m, X, first, last, bt0, batch, acc);
+        else quad16_passes<NT, VF == CSB_VAL_F16>(m, X, first, last, bt0, batch, acc);
+    }
 
-    // The wavefronts' tiles, RM rows at a time.
+    // The wavefronts' tiles, RM rows at a time.  (The lane is asked for again: kept over the passes it is a register too many.)
+    uint32_t lane;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+    const uint32_t tid = wave * 64u + lane;
     constexpr int RM = NT == 2 ? 16 : 32;
     const uint32_t seg = tile / m.tiles_per_seg, in = tile - seg * m.tiles_per_seg;
     const uint32_t row0 = seg * m.seg_rows + in * m.tile_rows, tile_rows = min(m.tile_rows, m.seg_rows - in * m.tile_rows);
@@ -224,11 +349,12 @@ __device__ __forceinline__ void spmm_quad_body(const QuadMat &m, const XSrc &X, 
         const uint32_t rows = min(tile_rows - r0, (uint32_t)RM);
         for (uint32_t e = tid; e < rows * F::columns; e += NTHR) {
             const uint32_t i = e / F::columns, n = e % F::columns;
+            const uint32_t at = VF == CSB_VAL_F32 || NT == 1 ? n : n / 2u + 64u * (n & 1u);      // tile t: right-hand sides 64 t + lane, or 2 lane + t
             float s = 0.0f;
 #pragma unroll
             for (int w = 0; w < NW; ++w)
 #pragma unroll
-                for (int g = 0; g < G; ++g) s += red[(w * RM + i) * (64u * NT) + g * F::lanes + n];
+                for (int g = 0; g < G; ++g) s += red[(w * RM + i) * (64u * NT) + g * F::lanes + at];
             if (bt0 + n < batch) Y[(size_t)(row0 + r0 + i) * ldy + bt0 + n] = s;
         }
     }
@@ -247,6 +373,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
     spmm_quad_body<NT, G, TWO, NW>(J.m[j], J.X[j], J.Y[j], J.ldy[j], batch, blockIdx.x, blockIdx.y);
 }
 
+// 16-bit values times 16-bit right-hand sides.
+template <int NT, int NW, int VF>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void spmm_quad16_kernel(const QuadMat m, const XSrc X, float *__restrict__ Y,
+                                                                                                const int64_t ldy, const uint32_t batch) {
+    spmm_quad_body<NT, 1, false, NW, VF>(m, X, Y, ldy, batch, blockIdx.x, blockIdx.y);
+}
+
 // ---- launches ------------------------------------------------------------------------------------------------
 QuadMat quad_mat(const csb_matrix *m) {
     const QuadPlan &qp = m->plan.quad;
@@ -255,21 +388,21 @@ QuadMat quad_mat(const csb_matrix *m) {
                    qp.tiles_per_seg, qp.val_fmt, (uint32_t)m->plan.hdr.cols};
 }
 
-// Right-hand sides per workgroup and its wavefronts, for `tiles` row tiles in the launch.  What counts is the
-// number of turns the workgroups take over the 256 CUs and how long a turn is: one of 16 wavefronts takes 1.16 times as long
-// with 64 right-hand sides as with 32 and 1.65 times with 128 (8192 x 8192 at 12x, us: 21.7, 25.4, 35); of 8 wavefronts two share
-// a CU, and a turn of 512 of them takes 2.65 (115 / 2 us), of up to 256 1.9 (41.7), so they pay where the
-// launch takes several turns (x 512: 128 us with 16 wavefronts, 115 with 8; x 260: 102.6 and 95.6; 5000 x 300 x 500 in
-// 64 x 64 blocks 17.5 and 12.3).
-static void quad_columns(size_t tiles, int32_t batch, int *columns, int *nw) {
+// Right-hand sides per workgroup and its wavefronts, for `tiles` row tiles in the launch.  What counts is the number of
+// turns the workgroups take over the 256 CUs and how long a turn is: of 16 wavefronts a CU holds one workgroup; of 8, two, which
+// overlap one's merge with the other's products but leave the last turn half empty.
+// us on 8192 x 8192 at 12x (256 row tiles), which is where the lengths of the turns are from:
+//   float32   32 right-hand sides 21.7; 64 25.4; 128 35 (a turn of 8 wavefronts 41.7, of twice as many of those 58: x 512 128 us with 16, 115
+//             with 8; x 260 102.6 and 95.6; 5000 x 300 x 500 in 64 x 64 blocks 17.5 and 12.3)
+//   16 bits   64 19.1 (8 wavefronts 28.0, twice as many 29.5); 128 22.9 (31.2, 33.4: x 512 82 us with 16, 67 with 8)
+struct QuadTurn { int columns, nw; double one, two; };   // length of a turn of up to 256 workgroups, of up to 512
+static void quad_columns(const QuadTurn *forms, int n, size_t tiles, int32_t batch, QuadShape *out) {
     double best = 1e300;
-    for (int c : {32, 64, 128}) {
-        const size_t w = tiles * (size_t)((batch + c - 1) / c);
-        const double turn = c == 32 ? 1.0 : c == 64 ? 1.16 : 1.65, cost = (double)((w + 255) / 256) * turn;
-        if (cost < best) { best = cost; *columns = c; *nw = 16; }
-        if (c < 128) continue;
-        const double cost8 = (double)(w / 512) * 2.65 + (w % 512 > 256 ? 2.65 : w % 512 ? 1.9 : 0.0);
-        if (cost8 < best) { best = cost8; *columns = c; *nw = 8; }
+    for (int i = 0; i < n; ++i) {
+        const QuadTurn &f = forms[i];
+        const size_t w = tiles * (size_t)((batch + f.columns - 1) / f.columns), slots = f.nw == 8 ? 512 : 256, rest = w % slots;
+        const double cost = (double)(w / slots) * (f.nw == 8 ? f.two : f.one) + (rest > 256 ? f.two : rest ? f.one : 0.0);
+        if (cost < best) { best = cost; out->columns = f.columns; out->nw = f.nw; }
     }
 }
 
@@ -285,7 +418,8 @@ bool quad_shape(const SpmmCall &c, int32_t batch, size_t launch_products, QuadSh
                            : XSrc{c.p0, qp.split_col, (uint32_t)c.sj0, c.p0 + (size_t)qp.split_col * c.sj0, (uint32_t)c.sj0};
     // 32-bit byte offsets, that of kQuadNoCol among them
     if (X->sj0 > kQuadMaxStride || X->sj1 > kQuadMaxStride) return false;
-    quad_columns((size_t)qp.n_tiles * launch_products, batch, &out->columns, &out->nw);
+    static const QuadTurn forms[] = {{32, 16, 21.7, 0}, {64, 16, 25.4, 0}, {128, 16, 35.8, 0}, {128, 8, 41.7, 57.5}};
+    quad_columns(forms, 4, (size_t)qp.n_tiles * launch_products, batch, out);
     out->two = two;
     out->lds = (size_t)out->nw * (out->columns == 128 ? 16 * 2 : 32) * 64 * sizeof(float);
     out->tiles = (unsigned)qp.n_tiles;
@@ -304,6 +438,26 @@ const void *quad_kernel(const QuadShape &sh, bool multi) {
     CSB_QV(1, 2, 16)
 #undef CSB_QV
 #undef CSB_Q
+}
+
+// One source of 16-bit right-hand sides, `ldx` elements from one column to the next.
+bool quad16_shape(const csb_matrix *mat, int64_t ldx, int32_t batch, QuadShape *out) {
+    const QuadPlan &qp = mat->plan.quad;
+    if (!qp.valid || qp.val_fmt == CSB_VAL_F32 || qp.split_col > 0 || ldx > kQuadMaxStride) return false;
+    static const QuadTurn forms[] = {{64, 16, 19.1, 0}, {64, 8, 28.0, 29.5}, {128, 16, 22.9, 0}, {128, 8, 31.2, 33.4}};
+    quad_columns(forms, 4, (size_t)qp.n_tiles, batch, out);
+    out->two = false;
+    out->lds = (size_t)out->nw * 32 * 64 * sizeof(float);
+    out->tiles = (unsigned)qp.n_tiles;
+    out->batch_tiles = (unsigned)((batch + out->columns - 1) / out->columns);
+    return true;
+}
+
+const void *quad16_kernel(const QuadShape &sh, bool half) {
+#define CSB_Q16(NT, NW) (half ? (const void *)spmm_quad16_kernel<NT, NW, CSB_VAL_F16> : (const void *)spmm_quad16_kernel<NT, NW, CSB_VAL_BF16>)
+    if (sh.columns == 64) return sh.nw == 8 ? CSB_Q16(1, 8) : CSB_Q16(1, 16);
+    return sh.nw == 8 ? CSB_Q16(2, 8) : CSB_Q16(2, 16);
+#undef CSB_Q16
 }
 
 }  // namespace csb
