@@ -237,8 +237,11 @@ struct StreamPlan {
 // pass is one record and one run of values, and the passes of a tile are dealt to kQuadLists
 // lists of equal work, in column order: a wavefront walks one list (or several in a row) and finds everything
 // it needs in the record, which comes in over the scalar path.
-//   table   [n_tiles][kQuadLists] first pass of every list, and one entry more for the end of the last
-//   records [passes + kQuadSpareRecs]
+//   records, list after list.  Lists of about the same length start `list_stride` records apart, and a launch finds its
+//           first record without a table: one dependent trip to memory less before it has any work.  The first record
+//           of a list counts its passes.
+//   table   (list_stride == 0: lists of very different lengths) [n_tiles][kQuadLists] first record of every list, and one
+//           entry more for the end of the last
 //   values  binary32: per pass [column][4 rows][quad]; 16-bit formats: [4 columns][4 rows][quad][4 columns], and with more
 //           than four quads [4 columns][4 rows][quad % 4][quad / 4][4 columns], eight of them; columns in fours,
 //           zeros where the pass has no such row or column; kQuadPad bytes of zeros behind the last
@@ -258,8 +261,9 @@ struct QuadRec {
     uint16_t stride;                     // bytes from one column (16-bit formats: four columns) to the next
     uint8_t quads;                       // kernel rows in fours
     uint8_t flags;                       // kQuadWide: more than 4 columns; kQuadSecond: columns of the second source
-    uint16_t col[kQuadCols];                 // input rows; kQuadNoCol where the pass has fewer
-    uint32_t pad[2];
+    uint16_t col[kQuadCols];             // input rows; kQuadNoCol where the pass has fewer
+    uint32_t list_len;                   // a list's first record: its passes
+    uint32_t pad;
     // what the row sums need
     uint8_t slot[kQuadRows];             // the rows' places in the tile; kQuadRows (a spare one) where there is none
 };
@@ -272,7 +276,8 @@ struct QuadPlan {
     uint32_t split_col = 0;
     uint32_t val_fmt = 0;
     uint64_t off_table = 0, off_recs = 0, off_vals = 0;
-    uint64_t n_passes = 0, vals_bytes = 0;   // (vals_bytes with the padding)
+    uint32_t list_stride = 0;
+    uint64_t n_passes = 0, n_recs = 0, vals_bytes = 0;   // (n_recs with gaps between the lists and kQuadSpareRecs, vals_bytes with the padding)
     uint32_t tile_row0(uint32_t t) const { return t / tiles_per_seg * seg_rows + t % tiles_per_seg * tile_rows; }
 };
 

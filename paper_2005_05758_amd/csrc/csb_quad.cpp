@@ -125,12 +125,12 @@ int plan_quad(csb_matrix *m) {
         const bool bits16 = m->val_fmt != CSB_VAL_F32;
 
         // ---- the passes of every tile, dealt to its lists -------------------------------------
-        struct Entry { QPass p; uint8_t second, list; uint8_t slot[kQuadRows]; };
+        struct Entry { QPass p; uint8_t second; uint8_t slot[kQuadRows]; };
         std::vector<std::vector<Entry>> tiles(qp.n_tiles);
         uint64_t bytes = 0;
         for_passes(m, qp, [&](uint32_t tile, const QPass &p, bool second, const uint8_t *slot) {
             Entry e;
-            e.p = p; e.second = second; e.list = 0;
+            e.p = p; e.second = second;
             std::memset(e.slot, kQuadRows, sizeof(e.slot));
             std::memcpy(e.slot, slot, p.nrows);
             tiles[tile].push_back(e);
@@ -139,39 +139,40 @@ int plan_quad(csb_matrix *m) {
         });
         qp.vals_bytes = bytes + kQuadPad;
         if (qp.vals_bytes >= 0x7fffff00ull || qp.n_passes >= 0x7fffffffull / sizeof(QuadRec)) return CSB_OK;
-        std::vector<uint32_t> table;
-        table.reserve((size_t)qp.n_tiles * kQuadLists + 1);
-        std::vector<const Entry *> order;
-        order.reserve(qp.n_passes);
-        for (auto &t : tiles) {
+        std::vector<std::vector<const Entry *>> lists((size_t)qp.n_tiles * kQuadLists);
+        size_t longest = 0;
+        for (size_t t = 0; t < tiles.size(); ++t) {
             uint64_t work[kQuadLists] = {0};
-            for (Entry &e : t) {
+            for (const Entry &e : tiles[t]) {
                 int best = 0;
                 for (int l = 1; l < kQuadLists; ++l) if (work[l] < work[best]) best = l;
-                e.list = (uint8_t)best;
                 work[best] += pass_cost(e.p);
-            }
-            for (int l = 0; l < kQuadLists; ++l) {
-                table.push_back((uint32_t)order.size());
-                for (const Entry &e : t) if (e.list == l) order.push_back(&e);
+                lists[t * kQuadLists + best].push_back(&e);
+                longest = std::max(longest, lists[t * kQuadLists + best].size());
             }
         }
-        table.push_back((uint32_t)order.size());
+        // (the gaps are never read but for a count: half as many records again, or 4 MB, are worth the trip)
+        if ((uint64_t)longest * lists.size() <= qp.n_passes + std::max<uint64_t>(qp.n_passes / 2, 65536)) qp.list_stride = (uint32_t)std::max<size_t>(longest, 1);
+        std::vector<uint32_t> table(lists.size() + 1, 0);
+        for (size_t l = 0; l < lists.size(); ++l) table[l + 1] = table[l] + (uint32_t)(qp.list_stride ? qp.list_stride : lists[l].size());
+        qp.n_recs = table.back() + kQuadSpareRecs;
 
         // ---- image ------------------------------------------------------------------------------
         qp.off_table = align_up(pl.image.size(), 256);
         qp.off_recs = align_up(qp.off_table + table.size() * 4, 256);
-        qp.off_vals = align_up(qp.off_recs + (qp.n_passes + kQuadSpareRecs) * sizeof(QuadRec), 256);
+        qp.off_vals = align_up(qp.off_recs + qp.n_recs * sizeof(QuadRec), 256);
         pl.image.resize(align_up(qp.off_vals + qp.vals_bytes, 256), 0);
         uint8_t *im = pl.image.data();
         std::memcpy(im + qp.off_table, table.data(), table.size() * 4);
         uint64_t at = 0;
         auto *recs = (QuadRec *)(im + qp.off_recs);
-        for (size_t i = 0; i < order.size(); ++i) {
-            const Entry &e = *order[i];
+        for (size_t l = 0; l < lists.size(); ++l)
+          for (size_t k = 0; k < lists[l].size(); ++k) {
+            const Entry &e = *lists[l][k];
             const QPass &p = e.p;
             const uint32_t quads = (p.nrows + 3u) / 4u;
-            QuadRec &r = recs[i];
+            QuadRec &r = recs[table[l] + k];
+            if (k == 0) r.list_len = (uint32_t)lists[l].size();
             r.val = (uint32_t)at;
             r.stride = (uint16_t)pass_stride(quads, bits16);
             r.quads = (uint8_t)quads;
@@ -208,7 +209,7 @@ int validate_quad(const csb_matrix *m) {
     const Plan &pl = m->plan;
     const QuadPlan &qp = pl.quad;
     auto fail = [&](const char *what) { set_error(std::string("csb_plan_validate: quad section: ") + what); return CSB_EINVAL; };
-    if (qp.off_vals + qp.vals_bytes > pl.image.size() || qp.off_recs + (qp.n_passes + kQuadSpareRecs) * sizeof(QuadRec) > qp.off_vals) return fail("section size");
+    if (qp.off_vals + qp.vals_bytes > pl.image.size() || qp.off_recs + qp.n_recs * sizeof(QuadRec) > qp.off_vals) return fail("section size");
     const auto *table = (const uint32_t *)(pl.image.data() + qp.off_table);
     const auto *recs = (const QuadRec *)(pl.image.data() + qp.off_recs);
     const uint8_t *vals = pl.image.data() + qp.off_vals;
@@ -237,9 +238,13 @@ int validate_quad(const csb_matrix *m) {
     for (uint32_t t = 0; t < qp.n_tiles; ++t) {
         const int64_t row0 = qp.tile_row0(t), end = std::min<int64_t>(row0 + qp.tile_rows, (int64_t)(t / qp.tiles_per_seg + 1) * qp.seg_rows);
         for (int l = 0; l < kQuadLists; ++l) {
-            const uint32_t i0 = table[(size_t)t * kQuadLists + l], i1 = table[(size_t)t * kQuadLists + l + 1];
-            if (i0 > i1 || i1 > qp.n_passes) return fail("list");
-            for (uint32_t i = i0; i < i1; ++i) {
+            const size_t list = (size_t)t * kQuadLists + l;
+            const uint64_t i0 = table[list];
+            if (i0 + kQuadSpareRecs > qp.n_recs || table[list + 1] < i0 || table[list + 1] + kQuadSpareRecs > qp.n_recs) return fail("list");
+            if (qp.list_stride && i0 != list * qp.list_stride) return fail("list stride");
+            const uint64_t i1 = i0 + (qp.list_stride ? recs[i0].list_len : table[list + 1] - i0);
+            if (i1 > table[list + 1] || (i1 > i0 && recs[i0].list_len != i1 - i0)) return fail("list length");
+            for (uint64_t i = i0; i < i1; ++i) {
                 const QuadRec &r = recs[i];
                 uint32_t ncols = 0, nrows = 0;
                 while (ncols < (uint32_t)kQuadCols && r.col[ncols] != kQuadNoCol) ++ncols;

@@ -77,6 +77,15 @@ struct QuadForm {
 typedef uint32_t uint32x8 __attribute__((ext_vector_type(8)));
 #define CSB_CONST_AS __attribute__((address_space(4)))
 
+__device__ __forceinline__ uint32_t first_record(const QuadMat &m, const uint32_t list) {
+    return m.list_stride ? list * m.list_stride : ((const uint32_t CSB_CONST_AS *)(uintptr_t)m.table)[list];
+}
+__device__ __forceinline__ uint32_t list_length(const QuadMat &m, const uint32_t list, const uint32x8 &first) {
+    if (m.list_stride) return first[6];
+    const uint32_t CSB_CONST_AS *t = (const uint32_t CSB_CONST_AS *)(uintptr_t)m.table + list;
+    return t[1] - t[0];
+}
+
 template <int NT, int G>
 struct QuadOps {
     uint32_t a[4];                                       // register j: rows of the quads j and 4 + j by 8 columns
@@ -93,10 +102,10 @@ __device__ __forceinline__ void quad_steps(const QuadOps<NT, G> &o, floatx4 (&D)
     }
 }
 
-// One wavefront's share of a tile's products: the passes [first, last), added into `acc`.  bt0: first right-hand side
+// One list of a tile's passes, added into `acc`.  bt0: first right-hand side
 // of the workgroup.
 template <int NT, int G, bool TWO>
-__device__ __forceinline__ void quad_passes(const QuadMat &m, const XSrc &X, const uint32_t first, const uint32_t last, const uint32_t bt0,
+__device__ __forceinline__ void quad_passes(const QuadMat &m, const XSrc &X, const uint32_t list, const uint32_t bt0,
                                             const uint32_t batch, QuadAcc<NT> &acc) {
     using F = QuadForm<NT, G>;
     const uint32_t lane = threadIdx.x & 63u, group = lane / F::lanes;
@@ -110,7 +119,7 @@ __device__ __forceinline__ void quad_passes(const QuadMat &m, const XSrc &X, con
     const uint32_t sj0 = uni_(X.sj0), sj1 = uni_(X.sj1), n0 = TWO ? uni_(X.n0) : m.cols;
     const uint64_t p0 = (uint64_t)(uintptr_t)(X.p0 + bt0), p1 = (uint64_t)(uintptr_t)(X.p1 + bt0);
     const uint32_t end0 = ((n0 - 1u) * sj0 + batch - bt0) * 4u, end1 = TWO ? ((m.cols - n0 - 1u) * sj1 + batch - bt0) * 4u : 0u;
-    const uint8_t CSB_CONST_AS *rec = (const uint8_t CSB_CONST_AS *)(uintptr_t)m.recs + (size_t)first * sizeof(QuadRec);
+    const uint8_t CSB_CONST_AS *rec = (const uint8_t CSB_CONST_AS *)(uintptr_t)m.recs + (size_t)first_record(m, list) * sizeof(QuadRec);
     auto read_loads = [&](int i) { return *(const uint32x8 CSB_CONST_AS *)(rec + i * (int)sizeof(QuadRec)); };
     auto read_slots = [&](int i) { return *(const uint32x8 CSB_CONST_AS *)(rec + i * (int)sizeof(QuadRec) + 32); };
 
@@ -171,9 +180,9 @@ __device__ __forceinline__ void quad_passes(const QuadMat &m, const XSrc &X, con
     // A pass's loads fly while the one before multiplies.  Scalar loads come back in any order, so that waiting for one is
     // waiting for all: they are asked for behind the only wait of a turn and used in the next one.
     QuadOps<NT, G> oa, ob;
-    uint32_t left = last - first;
     uint32x8 r = read_loads(0), sa = read_slots(0), sb;
-    uint32_t wa = r[1], wb;
+    uint32_t left = list_length(m, list, r), wa = r[1], wb;
+    if (left == 0u) return;
     issue(r, oa);
     r = read_loads(1);
     while (true) {
@@ -216,7 +225,7 @@ __device__ __forceinline__ void quad16_step(const QuadOps16 &o, const uint32_t (
 
 // (X: the rows of 16-bit right-hand sides; its stride counts elements)
 template <int NT, bool HALF>
-__device__ __forceinline__ void quad16_passes(const QuadMat &m, const XSrc &X, const uint32_t first, const uint32_t last, const uint32_t bt0,
+__device__ __forceinline__ void quad16_passes(const QuadMat &m, const XSrc &X, const uint32_t list, const uint32_t bt0,
                                               const uint32_t batch, QuadAcc<NT> &acc) {
     constexpr int steps = 2;                             // of four columns
     const uint32_t lane = threadIdx.x & 63u;
@@ -230,7 +239,7 @@ __device__ __forceinline__ void quad16_passes(const QuadMat &m, const XSrc &X, c
     asm("" : "+v"(row));                                 // (in a vector register: then a column's offset is one instruction)
     uint32_t lo = 0x05040100u, hi = 0x07060302u;         // v_perm selectors: the low, the high halves of two registers
     asm("" : "+v"(lo), "+v"(hi));
-    const uint8_t CSB_CONST_AS *rec = (const uint8_t CSB_CONST_AS *)(uintptr_t)m.recs + (size_t)first * sizeof(QuadRec);
+    const uint8_t CSB_CONST_AS *rec = (const uint8_t CSB_CONST_AS *)(uintptr_t)m.recs + (size_t)first_record(m, list) * sizeof(QuadRec);
     auto read_loads = [&](int i) { return *(const uint32x8 CSB_CONST_AS *)(rec + i * (int)sizeof(QuadRec)); };
     auto read_slots = [&](int i) { return *(const uint32x8 CSB_CONST_AS *)(rec + i * (int)sizeof(QuadRec) + 32); };
     constexpr int kLoads = 1 + 4 * steps;                // of a pass
@@ -289,9 +298,9 @@ __device__ __forceinline__ void quad16_passes(const QuadMat &m, const XSrc &X, c
         quad(std::integral_constant<int, 7>{});
     };
     QuadOps16 oa, ob;
-    uint32_t left = last - first;
     uint32x8 r = read_loads(0), sa = read_slots(0), sb;
-    uint32_t wa = r[1], wb;
+    uint32_t left = list_length(m, list, r), wa = r[1], wb;
+    if (left == 0u) return;
     issue(r, oa);
     r = read_loads(1);
     while (true) {                                       // (as in quad_passes)
@@ -321,12 +330,10 @@ __device__ __forceinline__ void spmm_quad_body(const QuadMat &m, const XSrc &X, 
     QuadAcc<NT> acc;
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc.v[t] = 0.0f;
-    const uint32_t CSB_CONST_AS *tab = (const uint32_t CSB_CONST_AS *)(uintptr_t)m.table;
-    const uint32_t l0 = tile * kQuadLists + wave * (kQuadLists / NW);
-    const uint32_t first = tab[l0], last = tab[l0 + kQuadLists / NW];
-    if (first < last) {
-        if constexpr (VF == CSB_VAL_F32) quad_passes<NT, G, TWO>(m, X, first, last, bt0, batch, acc);
-        else quad16_passes<NT, VF == CSB_VAL_F16>(m, X, first, last, bt0, batch, acc);
+    for (uint32_t k = 0; k < (uint32_t)(kQuadLists / NW); ++k) {
+        const uint32_t list = tile * kQuadLists + wave * (kQuadLists / NW) + k;
+        if constexpr (VF == CSB_VAL_F32) quad_passes<NT, G, TWO>(m, X, list, bt0, batch, acc);
+        else quad16_passes<NT, VF == CSB_VAL_F16>(m, X, list, bt0, batch, acc);
     }
 
     // The wavefronts' tiles, RM rows at a time.  (The lane is asked for again: kept over the passes it is a register too many.)
@@ -385,7 +392,7 @@ QuadMat quad_mat(const csb_matrix *m) {
     const QuadPlan &qp = m->plan.quad;
     uint8_t *b = (uint8_t *)m->d_buf;
     return QuadMat{(const uint32_t *)(b + qp.off_table), b + qp.off_recs, b + qp.off_vals, (uint32_t)qp.vals_bytes, qp.n_tiles, qp.tile_rows, qp.seg_rows,
-                   qp.tiles_per_seg, qp.val_fmt, (uint32_t)m->plan.hdr.cols};
+                   qp.tiles_per_seg, qp.val_fmt, (uint32_t)m->plan.hdr.cols, qp.list_stride};
 }
 
 // Right-hand sides per workgroup and its wavefronts, for `tiles` row tiles in the launch.  What counts is the number of
