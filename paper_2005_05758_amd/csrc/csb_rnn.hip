@@ -860,7 +860,8 @@ struct GateJobs {
     const float *bias[kMaxJobsPerLaunch];
     const float *a2[kMaxJobsPerLaunch];   // reset-before GRU, gate part: the second product's sums
     float *c[kMaxJobsPerLaunch];       // LSTM, LSTMP
-    float *h[kMaxJobsPerLaunch];
+    const float *h[kMaxJobsPerLaunch]; // h_(t-1)
+    float *h_out[kMaxJobsPerLaunch];   // h_t (may be h itself)
     float *m[kMaxJobsPerLaunch];       // LSTMP: cell output m_t; reset-before GRU, reset part: q = r h
     float *hseq[kMaxJobsPerLaunch];    // [B][H] of this step, or null
 };
@@ -874,7 +875,7 @@ __global__ void gates_batched_kernel(const GateJobs J, const int cell, const int
     if (e >= H * B) return;
     const int j = blockIdx.y;
     const float *__restrict__ a = J.a[j], *__restrict__ bias = J.bias[j];
-    float *__restrict__ h = J.h[j];
+    const float *h = J.h[j];
     const int k = e / B, n = e - k * B;
     float hn;
     if (cell == kEwRbReset) {
@@ -909,16 +910,8 @@ __global__ void gates_batched_kernel(const GateJobs J, const int cell, const int
         const float z = fast_sigmoid(az);
         hn = z * h[e] + (1.0f - z) * fmaxf(ac, 0.0f);
     }
-    h[e] = hn;
+    J.h_out[j][e] = hn;
     if (J.hseq[j]) J.hseq[j][(size_t)n * H + k] = hn;
-}
-
-// hseq[b][k] = h[k][b] for one step ([W][B] internal -> [B][W] caller's layout)
-__global__ void seq_out_kernel(float *__restrict__ dst, const float *__restrict__ src, int W, int B) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= W * B) return;
-    const int b = e / W, k = e - b * W;
-    dst[e] = src[(size_t)k * B + b];
 }
 
 // [L][B][H] (caller's layout) <-> [L][H][B] (internal); src may be null (zeros).
@@ -929,15 +922,16 @@ __global__ void state_in_kernel(float *__restrict__ dst, const float *__restrict
         dst[i] = src ? src[(l * B + b) * H + k] : 0.0f;
     }
 }
-__global__ void state_out_kernel(float *__restrict__ dst, const float *__restrict__ src, int L, int B, int H) {
+// (`last`: where the last layer's state is, if not with the others in src)
+__global__ void state_out_kernel(float *__restrict__ dst, const float *__restrict__ src, const float *__restrict__ last, int L, int B, int H) {
     const size_t n = (size_t)L * B * H;
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
         const size_t l = i / ((size_t)H * B), rem = i - l * H * B, b = rem / H, k = rem - b * H;
-        dst[i] = src[(l * H + k) * B + b];
+        dst[i] = last && l == (size_t)L - 1 ? last[k * B + b] : src[(l * H + k) * B + b];
     }
 }
 
-// dst[l][k][b] = src[l][b][k] through a 32 x 32 tile in LDS, so that both sides move whole
+// dst[l][k][b] = src[l][b][k] (b < B, k < K) through a 32 x 32 tile in LDS, so that both sides move whole
 // rows of 128 bytes: block (32, 8), grid (ceil(K / 32), ceil(B / 32), L).
 __global__ __launch_bounds__(256) void frames_in_kernel(float *__restrict__ dst, const float *__restrict__ src, int B, int K) {
     __shared__ float tile[32][33];
@@ -977,7 +971,8 @@ static size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 struct RnnWs {
     size_t off_a, off_a2, off_c, off_part, off_biasptr, off_seq, off_hint, off_cint, off_m, off_fa, off_fs, rows_out, part_stride, total;
     size_t off_xt;                     // batched: the input frames of `xt_steps` steps as [input][batch]
-    int32_t xt_steps;
+    size_t off_hs;                     // ... and the last layer's outputs of `hs_steps` steps as [width][batch]
+    int32_t xt_steps, hs_steps;
 };
 
 // XCDs one instance of the resident kernel occupies, and how many instances fit side by side
@@ -1032,6 +1027,11 @@ static RnnWs ws_layout(const csb_rnn *r, int32_t batch, int32_t T) {
         const size_t frame = (size_t)batch * r->input * sizeof(float);
         w.xt_steps = (int32_t)std::max<size_t>(1, std::min<size_t>({(size_t)std::max(T, 1), (size_t)1024, ((size_t)8 << 20) / std::max<size_t>(frame, 1)}));
         w.off_xt = off; off = align256(off + (size_t)w.xt_steps * frame);
+        // the last layer's outputs, kept as the steps leave them and turned over into the caller's sequence a
+        // few steps at a time (8 MB; a step reads the one before, so two at least)
+        const size_t out = (size_t)batch * HS * sizeof(float);
+        w.hs_steps = (int32_t)std::min<size_t>((size_t)std::max(T, 1), std::max<size_t>(2, std::min<size_t>((size_t)1024, ((size_t)8 << 20) / std::max<size_t>(out, 1))));
+        w.off_hs = off; off = align256(off + (size_t)w.hs_steps * out);
     }
     // (LSTMP at batch 1 as well: every layer's m_t, between its gate launch and its projection launch)
     w.off_m = off; off = align256(off + ((r->proj > 0 || two_products) ? (size_t)batch * r->hidden * sizeof(float) * (r->proj > 0 ? (size_t)r->n_layers : per_layer) : 0));
@@ -1509,6 +1509,18 @@ static int rnn_forward_enqueue(const csb_rnn *r, const float *d_x, const float *
         hipLaunchKernelGGL(state_in_kernel, dim3(sblocks), dim3(256), 0, st, hi, d_h0, L, batch, HS);
         if (lstm) hipLaunchKernelGGL(state_in_kernel, dim3(sblocks), dim3(256), 0, st, ci, d_c0, L, batch, H);
         const int gb = (H * batch + 255) / 256;
+        // Where layer l's state of step t lies (t = -1: the initial one): in place, but for the last layer with `ring`: its
+        // outputs stay in a ring of hs_steps steps and are turned over ([width][batch] -> [batch][width]) together.  (A
+        // cell that stores its output in the caller's order stores a word per line, which from about 48 sequences on
+        // costs more than a launch per ring; LSTMP's projection would take a launch per step.  us per step: two LSTM
+        // layers of 1024 at batch 64 12.2 -> 11.9, LSTMP 153 -> 1024 -> 512 at batch 48 18.0 -> 17.2; two Li-GRU layers of
+        // 512 at batch 33 9.8 either way, one LSTM layer of 512 at batch 4 and 20 steps 7.2 -> 7.4.)
+        const bool ring = d_hseq && (lstmp || batch >= 48);
+        float *hs = (float *)((uint8_t *)d_ws + wl.off_hs);
+        auto h_at = [&](int l, int t) -> float * {
+            if (!ring || l != L - 1 || t < 0) return hi + (size_t)l * HS * batch;
+            return hs + (size_t)(t % wl.hs_steps) * HS * batch;
+        };
         // Layer l at step t needs layer l - 1 at step t and itself at step t - 1: everything on
         // the diagonal l + t = d is independent, so a diagonal takes ONE product launch and ONE
         // element-wise launch per phase (for up to kMaxJobsPerLaunch layers each) instead of one per
@@ -1537,9 +1549,10 @@ static int rnn_forward_enqueue(const csb_rnn *r, const float *d_x, const float *
                         J.a2[i] = a2 + (size_t)l * hb;
                         J.bias[i] = r->d_bias[l];
                         J.c[i] = lstm ? ci + (size_t)l * hb : nullptr;
-                        J.h[i] = hi + (size_t)l * HS * batch;
+                        J.h[i] = h_at(l, t - 1);
+                        J.h_out[i] = h_at(l, t);
                         J.m[i] = mb + (size_t)l * hb;
-                        J.hseq[i] = (d_hseq && l == L - 1) ? d_hseq + (size_t)t * batch * HS : nullptr;
+                        J.hseq[i] = (d_hseq && !ring && l == L - 1) ? d_hseq + (size_t)t * batch * HS : nullptr;
                     }
                     hipLaunchKernelGGL(gates_batched_kernel, dim3(gb, n), dim3(256), 0, st, J, mode, H, batch);
                     return (int)CSB_OK;
@@ -1555,19 +1568,28 @@ static int rnn_forward_enqueue(const csb_rnn *r, const float *d_x, const float *
                 SpmmCall calls[kMaxJobsPerLaunch];
                 for (int i = 0; i < n; ++i) {
                     const int l = l0 + i, t = d - l;
-                    float *hl = hi + (size_t)l * HS * batch;
+                    const float *hl = h_at(l, t - 1);
                     if (l == 0)
                         calls[i] = SpmmCall{r->W[l], xt + (size_t)(t % wl.xt_steps) * batch * I, (uint32_t)I, batch, hl, batch,
                                             a + (size_t)l * a_stride, batch};
                     else
-                        calls[i] = SpmmCall{r->W[l], hi + (size_t)(l - 1) * HS * batch, (uint32_t)HS, batch, hl, batch,
+                        calls[i] = SpmmCall{r->W[l], h_at(l - 1, t), (uint32_t)HS, batch, hl, batch,
                                             a + (size_t)l * a_stride, batch};
                 }
                 return spmm_strided_multi(calls, n, batch, st);
             });
             if (rc != CSB_OK) return rc;
+            // the last layer's outputs up to this diagonal's, when their ring is full or the sequence ends
+            auto sequence_out = [&]() {
+                const int t = d - (L - 1);
+                if (!ring || t < 0 || t >= T || ((t + 1) % wl.hs_steps != 0 && t != T - 1)) return;
+                const int t0 = t / wl.hs_steps * wl.hs_steps;
+                hipLaunchKernelGGL(frames_in_kernel, dim3((batch + 31) / 32, (HS + 31) / 32, t - t0 + 1), dim3(32, 8), 0, st,
+                                   d_hseq + (size_t)t0 * batch * HS, hs, HS, batch);
+            };
             if (!two_phase) {
                 ew((int)r->cell);
+                sequence_out();
                 continue;
             }
             ew(lstmp ? kEwLstmpCell : kEwRbReset);               // m_t, or q = r h_(t-1)
@@ -1577,19 +1599,17 @@ static int rnn_forward_enqueue(const csb_rnn *r, const float *d_x, const float *
                 for (int i = 0; i < n; ++i) {
                     const int l = l0 + i;
                     float *ml = mb + (size_t)l * hb;
-                    float *dst = lstmp ? hi + (size_t)l * HS * batch : a2 + (size_t)l * hb;
+                    float *dst = lstmp ? h_at(l, d - l) : a2 + (size_t)l * hb;
                     calls[i] = SpmmCall{r->Wp[l], ml, (uint32_t)H, batch, ml, batch, dst, batch};
                 }
                 return spmm_strided_multi(calls, n, batch, st);
             });
             if (rc != CSB_OK) return rc;
             if (gru_rb) ew(kEwRbGate);
-            else if (d_hseq && d >= L - 1 && d - (L - 1) < T)    // the last layer is on this diagonal
-                hipLaunchKernelGGL(seq_out_kernel, dim3((HS * batch + 255) / 256), dim3(256), 0, st,
-                                   d_hseq + (size_t)(d - (L - 1)) * batch * HS, hi + (size_t)(L - 1) * HS * batch, HS, batch);
+            sequence_out();
         }
-        hipLaunchKernelGGL(state_out_kernel, dim3(sblocks), dim3(256), 0, st, d_hT, hi, L, batch, HS);
-        if (lstm && d_cT) hipLaunchKernelGGL(state_out_kernel, dim3(sblocks), dim3(256), 0, st, d_cT, ci, L, batch, H);
+        hipLaunchKernelGGL(state_out_kernel, dim3(sblocks), dim3(256), 0, st, d_hT, hi, ring ? h_at(L - 1, T - 1) : nullptr, L, batch, HS);
+        if (lstm && d_cT) hipLaunchKernelGGL(state_out_kernel, dim3(sblocks), dim3(256), 0, st, d_cT, ci, (const float *)nullptr, L, batch, H);
         hipError_t eb = hipGetLastError();
         if (eb != hipSuccess) { set_error(std::string("csb_rnn_forward: ") + hipGetErrorString(eb)); return CSB_EDEVICE; }
         return CSB_OK;

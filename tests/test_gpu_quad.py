@@ -45,3 +45,29 @@ def test_product_with_a_recurrent_handles_matrix(inputs, hidden, block, batch):
     Y = M.spmm(torch.from_numpy(X).cuda())
     torch.cuda.synchronize()
     assert np.all(np.abs(Y.cpu().numpy().astype(np.float64) - oracle.matmat(A, X)) <= bound_of(A, X))
+
+
+# The last layer's outputs are turned over a ring of steps at a time: 16 here, so 40 steps fill it twice and a half; on
+# either side of the batch from which on they are (48), and with the projected cell, where they always are.
+@pytest.mark.parametrize("cell,layers,batch,T", [(csb.CELL_LSTM, 2, 2048, 40), (csb.CELL_LSTM, 1, 2048, 16), (csb.CELL_GRU, 1, 2048, 17),
+                                                 (csb.CELL_LIGRU, 2, 47, 3), (csb.CELL_LIGRU, 2, 48, 3), (csb.CELL_LSTMP, 2, 5, 4),
+                                                 (csb.CELL_LSTM, 1, 64, 1), (csb.CELL_LSTMP, 1, 2100, 35)])
+def test_output_sequence_of_a_batch(cell, layers, batch, T):
+    inputs, hidden, state = 10, 64, 40 if cell == csb.CELL_LSTMP else 64
+    gates = {csb.CELL_LSTM: 4, csb.CELL_GRU: 3, csb.CELL_LIGRU: 2, csb.CELL_LSTMP: 4}[cell]
+    A = [csb_inputs.small_matrix(20 + l, gates * hidden, (inputs if l == 0 else state) + state, 16, 16, rate=4.0).A * 0.1 for l in range(layers)]
+    P = [csb_inputs.small_matrix(40 + l, state, hidden, 16, 16, rate=2.0).A * 0.1 for l in range(layers)] if cell == csb.CELL_LSTMP else []
+    W, Wp = [CsbMatrix(a, 16, 16) for a in A], [CsbMatrix(p, 16, 16) for p in P]
+    rnn = CsbRnn(cell, inputs, hidden, W, proj=state if P else 0, Wp=Wp or None)
+    for m in W + Wp:
+        m.upload()
+    x = np.random.default_rng(T).uniform(-1, 1, (T, batch, inputs)).astype(np.float32)
+    ref = oracle.lstmp_forward(A, P, None, x, inputs, hidden, state) if P else oracle.rnn_forward(cell, A, None, x, inputs, hidden)
+    for _ in range(2):                                              # (the second call finds the first one's ring)
+        got = rnn.forward(torch.from_numpy(x).cuda())
+        torch.cuda.synchronize()
+        for g, r in zip(got, ref):
+            if g is not None:
+                assert np.max(np.abs(g.cpu().numpy() - r)) <= 1e-4
+    alone = rnn.forward(torch.from_numpy(x).cuda(), want_hseq=False)  # without the sequence: the state in place
+    assert alone[0] is None and torch.equal(alone[1], got[1])
