@@ -84,7 +84,7 @@ int plan_matrix(csb_matrix *m, int32_t n_chunks_req, int32_t waves_per_chunk, co
                     auto flush = [&]() {
                         if (open && !cur.a.empty()) {
                             by_tile[cur.tile].push_back((uint32_t)vbs.size());
-                            vbs.push_back(cur);
+                            vbs.push_back(std::move(cur));
                         }
                         open = false;
                     };
@@ -99,6 +99,8 @@ int plan_matrix(csb_matrix *m, int32_t n_chunks_req, int32_t waves_per_chunk, co
                             cur = Vb{};
                             cur.tile = tile; cur.b = (uint32_t)b; cur.bj = (uint16_t)bj;
                             cur.q0 = (uint16_t)p.q0; cur.q1 = (uint16_t)p.q1;
+                            cur.a.reserve((size_t)nr);
+                            cur.slot.reserve((size_t)nr);
                             open = true;
                         }
                         cur.a.push_back((uint16_t)a);
@@ -580,6 +582,10 @@ int plan_matrix(csb_matrix *m, int32_t n_chunks_req, int32_t waves_per_chunk, co
         h.n_segs = segs.size();
         h.idx_bytes = idx.size(); h.n_vals = vals_end; h.total_bytes = off;
         Plan &pl = m->plan;
+        // (room for the sections that plan_stream and plan_quad append, up to twice its size each and 1 GB in all: pages that
+        // are not written cost nothing, moving the image twice does: 70 of 490 ms on 8192 x 8192 at 12x)
+        pl.image.clear();
+        pl.image.reserve(off + std::min<size_t>(off * 5, (size_t)1 << 30));
         pl.image.assign(off, 0);
         uint8_t *im = pl.image.data();
         std::memcpy(im, &h, sizeof(h));
