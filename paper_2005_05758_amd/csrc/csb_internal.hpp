@@ -289,6 +289,7 @@ struct Plan {
     DevHeader hdr{};
     StreamPlan stream;            // valid: csb_spmv reads this section instead of the sections above
     QuadPlan quad;                // valid: batched products read this section instead of the tile-based ones
+    QuadPlan quad_low;            // valid: the same matrix in tiles of 16 rows, for launches that these still get through at once
     csb_plan_stats stats{};
 };
 

@@ -653,7 +653,7 @@ int plan_matrix(csb_matrix *m, int32_t n_chunks_req, int32_t waves_per_chunk, co
             if (rc != CSB_OK) return rc;
         }
         // ... and the one of the batched products (csb_plan_rows, mode 4, builds its row-owned section first)
-        pl.quad = QuadPlan{};
+        pl.quad = pl.quad_low = QuadPlan{};
         return internal_rows ? (int)CSB_OK : plan_quad(m);
     } catch (const std::bad_alloc &) {
         set_error("csb_plan: out of host memory");

@@ -105,56 +105,52 @@ void for_passes(const csb_matrix *m, const QuadPlan &qp, F f) {
 
 }  // namespace
 
-// Builds the section and appends it to the plan's image; leaves plan.quad.valid false where the matrix does not fit
-// it (the batched products then read the tile-based sections).
-int plan_quad(csb_matrix *m) {
+// Builds a section of tiles of `tile_rows` rows and appends it to the plan's image; leaves out->valid false where the
+// matrix does not fit it.
+static int build_section(csb_matrix *m, uint32_t tile_rows, QuadPlan *out) {
     Plan &pl = m->plan;
-    pl.quad = QuadPlan{};
+    *out = QuadPlan{};
     const int64_t rows = m->rows + (pl.split.active() ? pl.split.shift : 0);
     if (m->cols > kMaxStageCols || rows > 0x7fffffff || rows == 0) return CSB_OK;
     try {
         QuadPlan qp{};
         qp.seg_rows = (uint32_t)(m->quad_units > 0 && rows % m->quad_units == 0 ? m->quad_units : rows);
-        // (tiles of 16 rows where the blocks are no taller and tiles of 32 would not give each of 256 workgroups one: a wavefront then has
-        // half the passes.  Taller blocks would be cut: twice the passes.)
-        qp.tile_rows = m->br <= 16 && rows < 256 * 32 ? 16u : 32u;
+        qp.tile_rows = tile_rows;
         qp.tiles_per_seg = (qp.seg_rows + qp.tile_rows - 1) / qp.tile_rows;
         qp.n_tiles = (uint32_t)(rows / qp.seg_rows) * qp.tiles_per_seg;
         qp.split_col = m->quad_split > 0 ? (uint32_t)m->quad_split : 0u;
         qp.val_fmt = (uint32_t)m->val_fmt;
         const bool bits16 = m->val_fmt != CSB_VAL_F32;
 
-        // ---- the passes of every tile, dealt to its lists -------------------------------------
-        struct Entry { QPass p; uint8_t second; uint8_t slot[kQuadRows]; };
-        std::vector<std::vector<Entry>> tiles(qp.n_tiles);
+        // ---- the passes, dealt to the lists of their tiles as they come ------------------------
+        struct Entry { QPass p; uint32_t list, pos, val; uint8_t second; uint8_t slot[kQuadRows]; };   // (val: from the list's first value)
+        struct List { uint64_t work; uint32_t passes, bytes; };
+        std::vector<Entry> entries;
+        std::vector<List> lists((size_t)qp.n_tiles * kQuadLists, List{});
         uint64_t bytes = 0;
+        uint32_t longest = 0;
         for_passes(m, qp, [&](uint32_t tile, const QPass &p, bool second, const uint8_t *slot) {
-            Entry e;
+            List *best = &lists[(size_t)tile * kQuadLists];
+            for (List *l = best + 1, *end = best + kQuadLists; l < end; ++l) if (l->work < best->work) best = l;
+            entries.emplace_back();
+            Entry &e = entries.back();
             e.p = p; e.second = second;
+            e.list = (uint32_t)(best - lists.data()); e.pos = best->passes; e.val = best->bytes;
             std::memset(e.slot, kQuadRows, sizeof(e.slot));
             std::memcpy(e.slot, slot, p.nrows);
-            tiles[tile].push_back(e);
-            bytes += pass_value_bytes(p.nrows, p.ncols, bits16);
-            ++qp.n_passes;
+            const size_t n = pass_value_bytes(p.nrows, p.ncols, bits16);
+            best->work += pass_cost(p);
+            best->bytes += (uint32_t)n;
+            longest = std::max(longest, ++best->passes);
+            bytes += n;
         });
+        qp.n_passes = entries.size();
         qp.vals_bytes = bytes + kQuadPad;
         if (qp.vals_bytes >= 0x7fffff00ull || qp.n_passes >= 0x7fffffffull / sizeof(QuadRec)) return CSB_OK;
-        std::vector<std::vector<const Entry *>> lists((size_t)qp.n_tiles * kQuadLists);
-        size_t longest = 0;
-        for (size_t t = 0; t < tiles.size(); ++t) {
-            uint64_t work[kQuadLists] = {0};
-            for (const Entry &e : tiles[t]) {
-                int best = 0;
-                for (int l = 1; l < kQuadLists; ++l) if (work[l] < work[best]) best = l;
-                work[best] += pass_cost(e.p);
-                lists[t * kQuadLists + best].push_back(&e);
-                longest = std::max(longest, lists[t * kQuadLists + best].size());
-            }
-        }
         // (the gaps are never read but for a count: half as many records again, or 4 MB, are worth the trip)
-        if ((uint64_t)longest * lists.size() <= qp.n_passes + std::max<uint64_t>(qp.n_passes / 2, 65536)) qp.list_stride = (uint32_t)std::max<size_t>(longest, 1);
+        if ((uint64_t)longest * lists.size() <= qp.n_passes + std::max<uint64_t>(qp.n_passes / 2, 65536)) qp.list_stride = std::max(longest, 1u);
         std::vector<uint32_t> table(lists.size() + 1, 0);
-        for (size_t l = 0; l < lists.size(); ++l) table[l + 1] = table[l] + (uint32_t)(qp.list_stride ? qp.list_stride : lists[l].size());
+        for (size_t l = 0; l < lists.size(); ++l) table[l + 1] = table[l] + (uint32_t)(qp.list_stride ? qp.list_stride : lists[l].passes);
         qp.n_recs = table.back() + kQuadSpareRecs;
 
         // ---- image ------------------------------------------------------------------------------
@@ -164,16 +160,19 @@ int plan_quad(csb_matrix *m) {
         pl.image.resize(align_up(qp.off_vals + qp.vals_bytes, 256), 0);
         uint8_t *im = pl.image.data();
         std::memcpy(im + qp.off_table, table.data(), table.size() * 4);
-        uint64_t at = 0;
         auto *recs = (QuadRec *)(im + qp.off_recs);
-        for (size_t l = 0; l < lists.size(); ++l)
-          for (size_t k = 0; k < lists[l].size(); ++k) {
-            const Entry &e = *lists[l][k];
+        std::vector<uint32_t> val0(lists.size());            // values lie list after list
+        uint32_t at = 0;
+        for (size_t l = 0; l < lists.size(); ++l) {
+            val0[l] = at;
+            at += lists[l].bytes;
+            if (lists[l].passes) recs[table[l]].list_len = lists[l].passes;
+        }
+        for (const Entry &e : entries) {
             const QPass &p = e.p;
             const uint32_t quads = (p.nrows + 3u) / 4u;
-            QuadRec &r = recs[table[l] + k];
-            if (k == 0) r.list_len = (uint32_t)lists[l].size();
-            r.val = (uint32_t)at;
+            QuadRec &r = recs[table[e.list] + e.pos];
+            r.val = val0[e.list] + e.val;
             r.stride = (uint16_t)pass_stride(quads, bits16);
             r.quads = (uint8_t)quads;
             r.flags = (uint8_t)((p.ncols > 4 ? kQuadWide : 0) | (e.second ? kQuadSecond : 0));
@@ -183,31 +182,45 @@ int plan_quad(csb_matrix *m) {
             std::memcpy(r.slot, e.slot, sizeof(r.slot));
             const int nc = m->ncols[p.b];
             const float *src = m->val.data() + m->val_off[p.b] + p.q0;
-            uint8_t *dst = im + qp.off_vals + at;
+            uint8_t *dst = im + qp.off_vals + r.val;
             for (uint32_t q = 0; q < p.nrows; ++q) {
                 const float *row = src + (size_t)(p.a0 + q) * nc;
-                for (uint32_t j = 0; j < p.ncols; ++j)
-                    if (!bits16) ((float *)dst)[value_at(quads, q, j, false)] = row[j];
-                    else ((uint16_t *)dst)[value_at(quads, q, j, true)] = m->val_fmt == CSB_VAL_F16 ? f32_to_f16_bits(row[j]) : f32_to_bf16_bits(row[j]);
+                if (!bits16)
+                    for (uint32_t j = 0; j < p.ncols; ++j) ((float *)dst)[value_at(quads, q, j, false)] = row[j];
+                else
+                    for (uint32_t j = 0; j < p.ncols; ++j)
+                        ((uint16_t *)dst)[value_at(quads, q, j, true)] = m->val_fmt == CSB_VAL_F16 ? f32_to_f16_bits(row[j]) : f32_to_bf16_bits(row[j]);
             }
-            at += pass_value_bytes(p.nrows, p.ncols, bits16);
         }
         qp.valid = true;
-        pl.quad = qp;
+        *out = qp;
         return CSB_OK;
     } catch (const std::bad_alloc &) {
-        pl.quad = QuadPlan{};
+        *out = QuadPlan{};
         pl.valid = false;
         set_error("csb_plan: out of host memory");
         return CSB_ENOMEM;
     }
 }
 
+// The section, or the two, that the batched products of a matrix read; none where it does not fit (they then read the
+// tile-based sections).  Tiles of 16 rows alone where the blocks are no taller and tiles of 32 would not give each of 256
+// workgroups one: a wavefront then has half the passes.  Taller blocks are cut by tiles of 16 rows, so that all tiles together
+// have about twice the passes, of half the rows: better as long as they still find idle CUs (quad_columns), which they never
+// do beyond 256 tiles.
+int plan_quad(csb_matrix *m) {
+    Plan &pl = m->plan;
+    const int64_t rows = m->rows + (pl.split.active() ? pl.split.shift : 0);
+    pl.quad_low = QuadPlan{};
+    const int rc = build_section(m, m->br <= 16 && rows < 256 * 32 ? 16u : 32u, &pl.quad);
+    if (rc != CSB_OK || !pl.quad.valid || m->br <= 16 || rows > 256 * 16) return rc;
+    return build_section(m, 16u, &pl.quad_low);
+}
+
 // Walks the section the way the kernels do, with bounds checks, and compares what it adds up with the matrix: every
 // (output row, input column) must be multiplied once, by its value.
-int validate_quad(const csb_matrix *m) {
+static int validate_section(const csb_matrix *m, const QuadPlan &qp) {
     const Plan &pl = m->plan;
-    const QuadPlan &qp = pl.quad;
     auto fail = [&](const char *what) { set_error(std::string("csb_plan_validate: quad section: ") + what); return CSB_EINVAL; };
     if (qp.off_vals + qp.vals_bytes > pl.image.size() || qp.off_recs + qp.n_recs * sizeof(QuadRec) > qp.off_vals) return fail("section size");
     const auto *table = (const uint32_t *)(pl.image.data() + qp.off_table);
@@ -283,6 +296,11 @@ int validate_quad(const csb_matrix *m) {
     if (n_got != n_expect) return fail("entry missing");
     if (std::memcmp(expect.data(), got.data(), cells * sizeof(float)) != 0) return fail("values do not decode to the matrix");
     return CSB_OK;
+}
+
+int validate_quad(const csb_matrix *m) {
+    const int rc = validate_section(m, m->plan.quad);
+    return rc == CSB_OK && m->plan.quad_low.valid ? validate_section(m, m->plan.quad_low) : rc;
 }
 
 }  // namespace csb

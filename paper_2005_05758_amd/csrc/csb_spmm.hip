@@ -933,7 +933,7 @@ int spmm_strided(const csb_matrix *mat, const float *p0, uint32_t n0, int64_t sj
     XSrc QX;
     hipError_t e;
     if (quad_shape(c, batch, 1, &qs, &QX)) {
-        QuadMat qm = quad_mat(mat);
+        QuadMat qm = quad_mat(mat, qs.low);
         void *args[] = {&qm, &QX, &d_Y, &ld, &b};
         const void *kern = quad_kernel(qs, false);
         e = ensure_dynamic_lds(kern, qs.lds);
@@ -973,12 +973,12 @@ int spmm_strided_multi(const SpmmCall *calls, int n, int32_t batch, void *stream
             J.Y[i] = calls[i].Y;
             J.ldy[i] = calls[i].ldy;
         }
-        QuadShape qs[kMaxJobsPerLaunch];
+        QuadShape qs[kMaxJobsPerLaunch] = {};
         QuadJobs QJ{};
         bool quad = true;
         for (int i = 0; i < n && quad; ++i) {
             quad = quad_shape(calls[i], batch, (size_t)n, &qs[i], &QJ.X[i]) && qs[i] == qs[0];
-            QJ.m[i] = quad_mat(calls[i].mat);
+            QJ.m[i] = quad_mat(calls[i].mat, qs[i].low);
             QJ.Y[i] = calls[i].Y;
             QJ.ldy[i] = calls[i].ldy;
             qs[0].tiles = std::max(qs[0].tiles, qs[i].tiles);
@@ -1042,7 +1042,7 @@ static int spmm_16bit(const char *who, int fmt, const csb_matrix *m, const uint1
     }
     QuadShape qs;
     if (quad16_shape(m, ldx, batch, &qs)) {
-        QuadMat qm = quad_mat(m);
+        QuadMat qm = quad_mat(m, qs.low);
         XSrc X{(const float *)d_X, (uint32_t)h.cols, (uint32_t)ldx, (const float *)d_X, (uint32_t)ldx};
         uint32_t b = (uint32_t)batch;
         int64_t ldy_ = ldy;

@@ -63,11 +63,12 @@ struct QuadShape {
     int columns;            // right-hand sides per workgroup: 32, 64 or 128
     int nw;                 // wavefronts per workgroup
     bool two;               // two sources
+    bool low;               // the section of 16-row tiles
     size_t lds;
     unsigned tiles, batch_tiles;
-    bool operator==(const QuadShape &o) const { return columns == o.columns && nw == o.nw && two == o.two; }
+    bool operator==(const QuadShape &o) const { return columns == o.columns && nw == o.nw && two == o.two && low == o.low; }
 };
-QuadMat quad_mat(const csb_matrix *m);
+QuadMat quad_mat(const csb_matrix *m, bool low);
 // The launch shape of one product (checked by the caller), `launch_products` of whose size share the launch; false:
 // the product is not for these kernels.
 bool quad_shape(const SpmmCall &c, int32_t batch, size_t launch_products, QuadShape *out, XSrc *X);

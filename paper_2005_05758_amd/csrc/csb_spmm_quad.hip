@@ -16,8 +16,8 @@
 // without the products 8192 x 8192 x 128 takes 16 us instead of 35): products of 4 x 4 granularity, 1.45 times those of the
 // matrix, the row sums (a vector instruction per row and 64 right-hand sides), about 30 others per pass.  Scalar instructions
 // run beside it.  8192 x 8192 at 12x in 32 x 32 blocks, us, records and 16-row instructions from the tile sections / here: 128
-// right-hand sides 63.2 / 35.5 (40 TFLOP/s of products the matrix has), 64 36.9 / 25.4, 16 24.7 / 21.7, 512 242 / 116;
-// 4096 x 4096 in 16-row blocks x 128 29.2 / 15.8, in 64-row blocks 17.0 / 11.0; two LSTM layers of 1024 at batch 64 14.6 / 12.1
+// right-hand sides 63.0 / 34.8 (41 TFLOP/s of products the matrix has), 64 36.9 / 25.0, 16 24.7 / 21.7, 512 242 / 116;
+// 4096 x 4096 in 16-row blocks x 128 29.2 / 15.8, in 64-row blocks 17.0 / 11.0; two LSTM layers of 1024 at batch 64 13.7 / 11.2
 // per step.
 #include <hip/hip_runtime.h>
 
@@ -349,9 +349,11 @@ __device__ __forceinline__ void spmm_quad_body(const QuadMat &m, const XSrc &X, 
         if ((uint32_t)r0 >= tile_rows) break;            // (uniform)
         if (r0) __syncthreads();                         // the rows before are done with
 #pragma unroll
-        for (int i = 0; i < RM; ++i)
+        for (int i = 0; i < RM; ++i) {
+            if (i == 16 && tile_rows <= 16u) break;      // (uniform)
 #pragma unroll
             for (int t = 0; t < NT; ++t) red[((wave * RM + i) * NT + t) * 64u + lane] = acc.v[t][r0 + i];
+        }
         __syncthreads();
         const uint32_t rows = min(tile_rows - r0, (uint32_t)RM);
         for (uint32_t e = tid; e < rows * F::columns; e += NTHR) {
@@ -388,8 +390,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
 }
 
 // ---- launches ------------------------------------------------------------------------------------------------
-QuadMat quad_mat(const csb_matrix *m) {
-    const QuadPlan &qp = m->plan.quad;
+QuadMat quad_mat(const csb_matrix *m, bool low) {
+    const QuadPlan &qp = low ? m->plan.quad_low : m->plan.quad;
     uint8_t *b = (uint8_t *)m->d_buf;
     return QuadMat{(const uint32_t *)(b + qp.off_table), b + qp.off_recs, b + qp.off_vals, (uint32_t)qp.vals_bytes, qp.n_tiles, qp.tile_rows, qp.seg_rows,
                    qp.tiles_per_seg, qp.val_fmt, (uint32_t)m->plan.hdr.cols, qp.list_stride};
@@ -403,14 +405,23 @@ QuadMat quad_mat(const csb_matrix *m) {
 //             with 8; x 260 102.6 and 95.6; 5000 x 300 x 500 in 64 x 64 blocks 17.5 and 12.3)
 //   16 bits   64 19.1 (8 wavefronts 28.0, twice as many 29.5); 128 22.9 (31.2, 33.4: x 512 82 us with 16, 67 with 8)
 struct QuadTurn { int columns, nw; double one, two; };   // length of a turn of up to 256 workgroups, of up to 512
-static void quad_columns(const QuadTurn *forms, int n, size_t tiles, int32_t batch, QuadShape *out) {
+// Where the matrix has a section of 16-row tiles as well, a turn over those takes 0.82 of the time: half the merge and half the
+// products of a pass, the same passes.  us, 32-row / 16-row tiles: 2048 x 2048 x 64 in 32-row blocks 7.4 / 6.0, 1024 x 551 x 33 4.9 / 4.0,
+// 4096 x 2048 x 64 in 64-row blocks 5.7 / 5.2, 4096 x 4096 x 64 12.0 / 10.9; with a turn more, or wider workgroups to avoid it,
+// 4096 x 2048 x 128 6.3 / 6.8, 4096 x 4096 x 256 19.9 / 23.4.
+constexpr double kLowTurn = 0.82;
+static void quad_columns(const QuadTurn *forms, int n, const Plan &pl, size_t launch_products, int32_t batch, QuadShape *out) {
     double best = 1e300;
-    for (int i = 0; i < n; ++i) {
-        const QuadTurn &f = forms[i];
-        const size_t w = tiles * (size_t)((batch + f.columns - 1) / f.columns), slots = f.nw == 8 ? 512 : 256, rest = w % slots;
-        const double cost = (double)(w / slots) * (f.nw == 8 ? f.two : f.one) + (rest > 256 ? f.two : rest ? f.one : 0.0);
-        if (cost < best) { best = cost; out->columns = f.columns; out->nw = f.nw; }
-    }
+    for (int low = 0; low < (pl.quad_low.valid ? 2 : 1); ++low)
+        for (int i = 0; i < n; ++i) {
+            const QuadTurn &f = forms[i];
+            const size_t tiles = (size_t)(low ? pl.quad_low : pl.quad).n_tiles * launch_products;
+            const size_t w = tiles * (size_t)((batch + f.columns - 1) / f.columns), slots = f.nw == 8 ? 512 : 256, rest = w % slots;
+            const double cost = ((double)(w / slots) * (f.nw == 8 ? f.two : f.one) + (rest > 256 ? f.two : rest ? f.one : 0.0)) * (low ? kLowTurn : 1.0);
+            if (cost < best) { best = cost; out->columns = f.columns; out->nw = f.nw; out->low = low != 0; }
+        }
+    out->tiles = (unsigned)(out->low ? pl.quad_low : pl.quad).n_tiles;
+    out->batch_tiles = (unsigned)((batch + out->columns - 1) / out->columns);
 }
 
 bool quad_shape(const SpmmCall &c, int32_t batch, size_t launch_products, QuadShape *out, XSrc *X) {
@@ -426,11 +437,9 @@ bool quad_shape(const SpmmCall &c, int32_t batch, size_t launch_products, QuadSh
     // 32-bit byte offsets, that of kQuadNoCol among them
     if (X->sj0 > kQuadMaxStride || X->sj1 > kQuadMaxStride) return false;
     static const QuadTurn forms[] = {{32, 16, 21.7, 0}, {64, 16, 25.4, 0}, {128, 16, 35.8, 0}, {128, 8, 41.7, 57.5}};
-    quad_columns(forms, 4, (size_t)qp.n_tiles * launch_products, batch, out);
+    quad_columns(forms, 4, c.mat->plan, launch_products, batch, out);
     out->two = two;
     out->lds = (size_t)out->nw * (out->columns == 128 ? 16 * 2 : 32) * 64 * sizeof(float);
-    out->tiles = (unsigned)qp.n_tiles;
-    out->batch_tiles = (unsigned)((batch + out->columns - 1) / out->columns);
     return true;
 }
 
@@ -452,11 +461,9 @@ bool quad16_shape(const csb_matrix *mat, int64_t ldx, int32_t batch, QuadShape *
     const QuadPlan &qp = mat->plan.quad;
     if (!qp.valid || qp.val_fmt == CSB_VAL_F32 || qp.split_col > 0 || ldx > kQuadMaxStride) return false;
     static const QuadTurn forms[] = {{64, 16, 19.1, 0}, {64, 8, 28.0, 29.5}, {128, 16, 22.9, 0}, {128, 8, 31.2, 33.4}};
-    quad_columns(forms, 4, (size_t)qp.n_tiles, batch, out);
+    quad_columns(forms, 4, mat->plan, 1, batch, out);
     out->two = false;
     out->lds = (size_t)out->nw * 32 * 64 * sizeof(float);
-    out->tiles = (unsigned)qp.n_tiles;
-    out->batch_tiles = (unsigned)((batch + out->columns - 1) / out->columns);
     return true;
 }
 

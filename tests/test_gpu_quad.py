@@ -34,6 +34,27 @@ def test_strides_on_both_sides_of_the_limit(ldx, batch):
     assert np.all(np.abs(Y.cpu().numpy().astype(np.float64) - oracle.matmat(A, X)) <= bound_of(A, X))
 
 
+# Tiles of 16 rows up to 256 of them, of 32 where those would take another turn over the CUs: 4090 rows at 64 and 65 right-hand
+# sides, one row more than there are such tiles for, blocks that they cut in two, in four and unevenly.
+@pytest.mark.parametrize("R,C,block", [(4090, 70, 32), (4096, 130, 64), (4097, 50, 33), (2050, 90, 24)])
+@pytest.mark.parametrize("batch", [4, 64, 68, 132, 260])
+@pytest.mark.parametrize("fmt", [csb.VAL_F32, csb.VAL_F16, csb.VAL_BF16])
+def test_both_tile_heights(R, C, block, batch, fmt):
+    A = csb_inputs.small_matrix(R + C, R, C, block, block, rate=3.0).A
+    M = CsbMatrix(A, block, block)
+    M.set_value_format(fmt)
+    M.plan()
+    M.validate()
+    M.upload()
+    X = torch.from_numpy(csb_inputs.make_vectors(batch, C, batch).reshape(C, batch))
+    to = {csb.VAL_F32: torch.float32, csb.VAL_F16: torch.float16, csb.VAL_BF16: torch.bfloat16}[fmt]
+    X = X.to(to)
+    Y = {csb.VAL_F32: M.spmm, csb.VAL_F16: M.spmm_half, csb.VAL_BF16: M.spmm_bfloat}[fmt](X.cuda())
+    torch.cuda.synchronize()
+    Ar, Xr = torch.from_numpy(A).to(to).float().numpy(), X.float().numpy()      # (the rounded operands: their products are exact in float32)
+    assert np.all(np.abs(Y.cpu().numpy().astype(np.float64) - oracle.matmat(Ar, Xr)) <= bound_of(Ar, Xr))
+
+
 @pytest.mark.parametrize("inputs,hidden,block", [(39, 33, 32), (64, 100, 64), (5, 520, 16)])
 @pytest.mark.parametrize("batch", [3, 40, 130])
 def test_product_with_a_recurrent_handles_matrix(inputs, hidden, block, batch):
