@@ -206,6 +206,22 @@ __global__ __launch_bounds__(256) void col_segment_keys_vec_kernel(const float *
     keys[(size_t)bi * C + c] = rank_key(s);
 }
 
+// Inclusive scan over a wavefront's lanes by cross-lane moves (sums, or bits put together), and its last lane's value.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false); }
+template <bool SUM>
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+    auto put = [](uint32_t a, uint32_t b) { return SUM ? a + b : a | b; };
+    v = put(v, dpp_<0x111, 0xf>(v));             // one, two, four, eight lanes up inside a row of 16
+    v = put(v, dpp_<0x112, 0xf>(v));
+    v = put(v, dpp_<0x114, 0xf>(v));
+    v = put(v, dpp_<0x118, 0xf>(v));
+    v = put(v, dpp_<0x142, 0xa>(v));             // the last lane of rows 0 and 2 to rows 1 and 3
+    return put(v, dpp_<0x143, 0xc>(v));          // lane 31 to rows 2 and 3
+}
+template <bool SUM>
+__device__ __forceinline__ uint32_t wave_total(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan<SUM>(v), 63); }
+
 // One workgroup ranks the n <= 16384 segments of one block-column (block-row) and marks the k
 // weakest as pruned, "weaker" being the order of (key, position).  No sort: every thread keeps
 // P consecutive keys in registers; the key T of the k-th weakest is found eight bits at a time
@@ -219,7 +235,9 @@ __global__ __launch_bounds__(256) void col_segment_keys_vec_kernel(const float *
 // one another), and every wavefront scans a round's 256 bins for itself, four to a lane: one
 // barrier per round.
 // Measured on 8192 x 8192, the whole projection: 135.3 -> 129.9 us (16 keys a thread, so half of the
-// threads idle, and three barriers a round before).
+// threads idle, and three barriers a round before).  Scans go by cross-lane moves instead of through the LDS, and positions
+// are only ranked where T is the key of segments on both sides: 129.3 -> 127.2, 2048 x 2048 28.2 -> 25.7, 512 x 192 in blocks
+// of 16 22.2 -> 19.5.
 template <int P>
 __global__ __launch_bounds__(1024) void select_kernel(const uint32_t *__restrict__ keys, uint8_t *__restrict__ keep,
                                                        const uint32_t n, const uint32_t k) {
@@ -260,17 +278,16 @@ __global__ __launch_bounds__(1024) void select_kernel(const uint32_t *__restrict
 #pragma unroll
     for (int q = 0; q < P; ++q)
         if (valid[q]) { all_and &= key[q]; all_or |= key[q]; }
-    for (int d = 32; d > 0; d >>= 1) {
-        all_and &= (uint32_t)__shfl_xor((int)all_and, d, 64);
-        all_or |= (uint32_t)__shfl_xor((int)all_or, d, 64);
-    }
+    all_and = ~wave_total<false>(~all_and);
+    all_or = wave_total<false>(all_or);
     if (lane == 0) { wsum[1][wave] = all_and; wsum[2][wave] = all_or; }
     __syncthreads();
+#pragma unroll
     for (int w = 0; w < 16; ++w) { all_and &= wsum[1][w]; all_or |= wsum[2][w]; }
     const uint32_t varying = all_and ^ all_or;
     const int top = varying ? 31 - __builtin_clz(varying) : -1;      // the highest bit on which keys differ
     // the kk-th weakest of the keys that match prefix on mask
-    uint32_t mask = top < 0 ? 0xffffffffu : ~((2u << top) - 1u), prefix = all_and & mask, kk = k;
+    uint32_t mask = top < 0 ? 0xffffffffu : ~((2u << top) - 1u), prefix = all_and & mask, kk = k, equal = n;      // equal: keys that match prefix on mask
     int round = 0;
     for (int hi = top; hi >= 0; hi -= 8, ++round) {
         const int lo = hi >= 7 ? hi - 7 : 0;
@@ -281,37 +298,39 @@ __global__ __launch_bounds__(1024) void select_kernel(const uint32_t *__restrict
         __syncthreads();
         const uint4 h = hist[round][lane];       // bins 4 lane .. + 3
         const uint32_t sum = h.x + h.y + h.z + h.w;
-        uint32_t incl = sum;
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t up = (uint32_t)__shfl_up((int)incl, d, 64);
-            if (lane >= (uint32_t)d) incl += up;
-        }
+        const uint32_t incl = wave_scan<true>(sum);
         uint32_t below = incl - sum, digit = 4u * lane;
         const unsigned long long hit = __ballot(below < kk && kk <= incl);      // the lane whose bins hold the k-th
+        uint32_t bin = h.x;
         if (kk > below + h.x) {
-            below += h.x; ++digit;
+            below += h.x; ++digit; bin = h.y;
             if (kk > below + h.y) {
-                below += h.y; ++digit;
-                if (kk > below + h.z) { below += h.z; ++digit; }
+                below += h.y; ++digit; bin = h.z;
+                if (kk > below + h.z) { below += h.z; ++digit; bin = h.w; }
             }
         }
         const int src = __builtin_ctzll(hit);
         prefix |= (uint32_t)__builtin_amdgcn_readlane((int)digit, src) << lo;
         mask |= dmask << lo;
         kk = (uint32_t)__builtin_amdgcn_readlane((int)(kk - below), src);
+        equal = (uint32_t)__builtin_amdgcn_readlane((int)bin, src);
     }
-    // prefix is T; kk of the keys equal to T are pruned: the first ones by position
-    uint32_t eq_wave = 0, eq_lower = 0;          // equal keys in the wavefront / in its lower lanes
+    // prefix is T; kk of the `equal` keys equal to T are pruned: the first ones by position, all of them where T is one key
+    uint32_t rank = 0;
+    if (kk < equal) {                            // (the same in all wavefronts)
+        uint32_t eq_wave = 0, eq_lower = 0;      // equal keys in the wavefront / in its lower lanes
 #pragma unroll
-    for (int q = 0; q < P; ++q) {
-        const unsigned long long m = __ballot(valid[q] && key[q] == prefix);
-        eq_wave += (uint32_t)__popcll(m);
-        eq_lower += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        for (int q = 0; q < P; ++q) {
+            const unsigned long long m = __ballot(valid[q] && key[q] == prefix);
+            eq_wave += (uint32_t)__popcll(m);
+            eq_lower += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        }
+        if (lane == 0) wsum[0][wave] = eq_wave;
+        __syncthreads();
+        rank = eq_lower;
+#pragma unroll
+        for (uint32_t w = 0; w < 16; ++w) rank += w < wave ? wsum[0][w] : 0u;
     }
-    if (lane == 0) wsum[0][wave] = eq_wave;
-    __syncthreads();
-    uint32_t rank = eq_lower;
-    for (uint32_t w = 0; w < wave; ++w) rank += wsum[0][w];
     uint32_t flags[P / 4] = {};            // keep flags, one byte each
 #pragma unroll
     for (int q = 0; q < P; ++q) {
