@@ -664,10 +664,10 @@ def val16_leg(torch, np, csb_inputs, CsbMatrix, stream_gbps, formats=("f16", "bf
                 bf[f"batch{Bb}"] = {"us": round(us, 2), "tflops_algorithmic": round(tf, 3)}
             tf = bf["batch512"]["tflops_algorithmic"]
             entry["spmm_bfloat"] = dict(bf, roofline={
-                "kernel": "csb::spmm_reg16_kernel<8, 2, 2, 2>", "bound": "mfma", "achieved": tf, "peak": 2500.0, "unit": "TFLOP/s",
+                "kernel": "csb::spmm_quad16_kernel<2, 8, 2>", "bound": "mfma", "achieved": tf, "peak": 2500.0, "unit": "TFLOP/s",
                 "frac": round(tf / 2500.0, 5), "traffic": None,
-                "note": "dense bf16 MFMA peak as the nominal roof; one 16-column MFMA step per block, part and tile of 16 "
-                        "right-hand sides: the launch is bound by its loads and its instruction stream, not by the matrix cores"})
+                "note": "dense bf16 MFMA peak as the nominal roof; 4 x 4 x 4 MFMA steps on kernels of about 9 x 9: the launch is "
+                        "bound by the pipe that those and the vector instructions of a pass share, not by the dense rate"})
         res[f"spmv_cfg5_{name}"] = entry
         del copies, M
     return res
@@ -704,14 +704,13 @@ def batched_leg(torch, np, csb_inputs, CsbMatrix, CsbRnn, cases=(("cfg5", 128), 
         del M
     best = res.get("spmm_cfg5_b128")
     if best:
-        res["roofline"] = {"kernel": "csb::spmm_reg_kernel<false, 8, 2, 0, 2>", "bound": "mfma", "achieved": best["tflops_algorithmic"],
+        res["roofline"] = {"kernel": "csb::spmm_quad_kernel<2, 1, false, 16>", "bound": "mfma", "achieved": best["tflops_algorithmic"],
                            "peak": MFMA_F32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": best["frac_fp32_mfma_peak"],
                            "traffic": TRAFFIC_BYTES.get("spmm_cfg5_b128"),
                            "us_per_launch": best["us"], "flops_per_launch": 2.0 * best["nnz"] * best["batch"],
                            "note": "the matrix cores are the roof; counters (profiles/spmm_cfg5_b128_pmc.txt): the matrix pipe is "
-                                   "busy 56 % of the launch, with 1.65 x the MFMAs of the kernel-row form (rows are "
-                                   "scattered to their tile rows in the operand, which keeps the results in registers); the "
-                                   "gather of X rows is not the bound (64 right-hand sides per workgroup, all gathers pointed at one row: 3 % faster)"}
+                                   "busy 39 % of the launch (4 x 4 x 1 instructions: rows of a pass in fours) and the vector "
+                                   "instructions that share its issue another 24 %"}
     if not with_rnn:
         return res
     cfg = csb_inputs.CONFIGS["cfg4"]
