@@ -645,7 +645,8 @@ int plan_matrix(csb_matrix *m, int32_t n_chunks_req, int32_t waves_per_chunk, co
         }
         st.matvec_bytes = (int64_t)pl.image.size();
         pl.stats = st;
-        pl.stream = StreamPlan{};
+        pl.stream = StreamPlan{};                // sections of the image before: gone with it, also if the next ones cannot be built
+        pl.quad = pl.quad_low = QuadPlan{};
         if (stats_out) *stats_out = st;
         // the row-owned section for csb_spmv, when the matrix fits it
         if (with_rows) {
@@ -653,7 +654,6 @@ int plan_matrix(csb_matrix *m, int32_t n_chunks_req, int32_t waves_per_chunk, co
             if (rc != CSB_OK) return rc;
         }
         // ... and the one of the batched products (csb_plan_rows, mode 4, builds its row-owned section first)
-        pl.quad = pl.quad_low = QuadPlan{};
         return internal_rows ? (int)CSB_OK : plan_quad(m);
     } catch (const std::bad_alloc &) {
         set_error("csb_plan: out of host memory");
