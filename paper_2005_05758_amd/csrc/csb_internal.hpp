@@ -4,6 +4,9 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <cstdlib>
+#include <cstring>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -281,11 +284,41 @@ struct QuadPlan {
     uint32_t tile_row0(uint32_t t) const { return t / tiles_per_seg * seg_rows + t % tiles_per_seg * tile_rows; }
 };
 
+// The host staging copy of the device image.  Sections are appended to it one after another; realloc grows a large one
+// by remapping its pages, so that it is neither moved (with a std::vector 70 of 490 ms of the first plan of 8192 x 8192 at 12x)
+// nor there twice, and no room has to be set aside for what may not fit.  What throws leaves it as it was.
+class ImageBuf {
+public:
+    ImageBuf() = default;
+    ImageBuf(const ImageBuf &) = delete;
+    ImageBuf &operator=(const ImageBuf &) = delete;
+    ~ImageBuf() { std::free(p_); }
+    uint8_t *data() { return p_; }
+    const uint8_t *data() const { return p_; }
+    size_t size() const { return n_; }
+    void resize(size_t n) {                      // new bytes are zero
+        void *p = std::realloc(p_, n ? n : 1);
+        if (!p) throw std::bad_alloc();
+        p_ = (uint8_t *)p;
+        if (n > n_) std::memset(p_ + n_, 0, n - n_);
+        n_ = n;
+    }
+    void assign_zeros(size_t n) {
+        const size_t kept = n < n_ ? n : n_;
+        resize(n);
+        std::memset(p_, 0, kept);
+    }
+
+private:
+    uint8_t *p_ = nullptr;
+    size_t n_ = 0;
+};
+
 struct Plan {
     bool valid = false;
     SplitSpec split;              // stays when the plan becomes invalid: csb_plan keeps the row layout of a matrix a GRU handle planned
     int32_t req_chunks = 0, req_mode = 0;   // what the plan was asked for
-    std::vector<uint8_t> image;   // host staging copy of the device image
+    ImageBuf image;
     DevHeader hdr{};
     StreamPlan stream;            // valid: csb_spmv reads this section instead of the sections above
     QuadPlan quad;                // valid: batched products read this section instead of the tile-based ones

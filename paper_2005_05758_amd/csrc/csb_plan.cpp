@@ -582,11 +582,7 @@ int plan_matrix(csb_matrix *m, int32_t n_chunks_req, int32_t waves_per_chunk, co
         h.n_segs = segs.size();
         h.idx_bytes = idx.size(); h.n_vals = vals_end; h.total_bytes = off;
         Plan &pl = m->plan;
-        // (room for the sections that plan_stream and plan_quad append, up to twice its size each and 1 GB in all: pages that
-        // are not written cost nothing, moving the image twice does: 70 of 490 ms on 8192 x 8192 at 12x)
-        pl.image.clear();
-        pl.image.reserve(off + std::min<size_t>(off * 5, (size_t)1 << 30));
-        pl.image.assign(off, 0);
+        pl.image.assign_zeros(off);              // (until here a plan made before is whole)
         uint8_t *im = pl.image.data();
         std::memcpy(im, &h, sizeof(h));
         auto put = [&](size_t o, const void *p, size_t n) { if (n) std::memcpy(im + o, p, n); };
@@ -604,6 +600,8 @@ int plan_matrix(csb_matrix *m, int32_t n_chunks_req, int32_t waves_per_chunk, co
         put(h.off_tile_seg0, tile_seg0.data(), tile_seg0.size() * 4);
         put(h.off_segs, segs.data(), segs.size() * sizeof(SegRec));
         pl.hdr = h;
+        pl.stream = StreamPlan{};                // sections of the image before: gone with it, also if the next ones cannot be built
+        pl.quad = pl.quad_low = QuadPlan{};
         pl.split = split;
         pl.req_chunks = n_chunks_req;
         pl.req_mode = with_rows ? 0 : (mode == 0 ? 4 : mode);
@@ -645,8 +643,6 @@ int plan_matrix(csb_matrix *m, int32_t n_chunks_req, int32_t waves_per_chunk, co
         }
         st.matvec_bytes = (int64_t)pl.image.size();
         pl.stats = st;
-        pl.stream = StreamPlan{};                // sections of the image before: gone with it, also if the next ones cannot be built
-        pl.quad = pl.quad_low = QuadPlan{};
         if (stats_out) *stats_out = st;
         // the row-owned section for csb_spmv, when the matrix fits it
         if (with_rows) {

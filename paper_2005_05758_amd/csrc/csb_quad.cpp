@@ -157,7 +157,7 @@ static int build_section(csb_matrix *m, uint32_t tile_rows, QuadPlan *out) {
         qp.off_table = align_up(pl.image.size(), 256);
         qp.off_recs = align_up(qp.off_table + table.size() * 4, 256);
         qp.off_vals = align_up(qp.off_recs + qp.n_recs * sizeof(QuadRec), 256);
-        pl.image.resize(align_up(qp.off_vals + qp.vals_bytes, 256), 0);
+        pl.image.resize(align_up(qp.off_vals + qp.vals_bytes, 256));
         uint8_t *im = pl.image.data();
         std::memcpy(im + qp.off_table, table.data(), table.size() * 4);
         auto *recs = (QuadRec *)(im + qp.off_recs);

@@ -475,7 +475,7 @@ int plan_stream(csb_matrix *m, int32_t n_wg_req, int32_t rounds_min, csb_plan_st
         // ---- 5. write the section -----------------------------------------------------------
         const size_t off = align_up(pl.image.size(), 256);
         const size_t bytes = (size_t)sp.n_wg * sp.wg_bytes;
-        pl.image.resize(off + bytes, 0);
+        pl.image.resize(off + bytes);
         sp.off = off; sp.bytes = bytes;
         uint32_t n_groups = 0;
         uint64_t fma_steps = 0, traffic = (uint64_t)nwg * sp.hdr_bytes;
@@ -599,6 +599,7 @@ int plan_stream(csb_matrix *m, int32_t n_wg_req, int32_t rounds_min, csb_plan_st
         return CSB_OK;
     } catch (const std::bad_alloc &) {
         pl.stream = StreamPlan{};
+        if (pl.image.size() > pl.hdr.total_bytes) pl.image.resize(pl.hdr.total_bytes);       // (shrinks)
         set_error("csb_plan: out of host memory");
         return CSB_ENOMEM;
     }

@@ -47,3 +47,10 @@ def test_what_is_left_is_a_whole_plan_or_none(plans):
     assert {p[2] for p in plans} == {OK, ENOMEM}      # both are met
     for first_mode, room, planned, valid, size in plans:
         assert valid in (OK, ESTATE), (first_mode, room, planned)
+
+
+# The tile sections and the row-owned section of this matrix took 34 MB to plan (image 20 MB); what is added to them is
+# room for the rest of the image, 22 MB, and no more.
+def test_no_room_is_set_aside(plans):
+    first = [p for p in plans if p[0] is None and p[2] == OK]
+    assert first[0][1] <= 34 + first[0][4] / 2 ** 20 / 2
