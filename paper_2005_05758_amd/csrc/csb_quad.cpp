@@ -106,12 +106,13 @@ void for_passes(const csb_matrix *m, const QuadPlan &qp, F f) {
 }  // namespace
 
 // Builds a section of tiles of `tile_rows` rows and appends it to the plan's image; leaves out->valid false where the
-// matrix does not fit it.
-static int build_section(csb_matrix *m, uint32_t tile_rows, QuadPlan *out) {
+// matrix does not fit it, or the section the host's memory.
+static void build_section(csb_matrix *m, uint32_t tile_rows, QuadPlan *out) {
     Plan &pl = m->plan;
+    const size_t image_before = pl.image.size();
     *out = QuadPlan{};
     const int64_t rows = m->rows + (pl.split.active() ? pl.split.shift : 0);
-    if (m->cols > kMaxStageCols || rows > 0x7fffffff || rows == 0) return CSB_OK;
+    if (m->cols > kMaxStageCols || rows > 0x7fffffff || rows == 0) return;
     try {
         QuadPlan qp{};
         qp.seg_rows = (uint32_t)(m->quad_units > 0 && rows % m->quad_units == 0 ? m->quad_units : rows);
@@ -146,7 +147,7 @@ static int build_section(csb_matrix *m, uint32_t tile_rows, QuadPlan *out) {
         });
         qp.n_passes = entries.size();
         qp.vals_bytes = bytes + kQuadPad;
-        if (qp.vals_bytes >= 0x7fffff00ull || qp.n_passes >= 0x7fffffffull / sizeof(QuadRec)) return CSB_OK;
+        if (qp.vals_bytes >= 0x7fffff00ull || qp.n_passes >= 0x7fffffffull / sizeof(QuadRec)) return;
         // (the gaps are never read but for a count: half as many records again, or 4 MB, are worth the trip)
         if ((uint64_t)longest * lists.size() <= qp.n_passes + std::max<uint64_t>(qp.n_passes / 2, 65536)) qp.list_stride = std::max(longest, 1u);
         std::vector<uint32_t> table(lists.size() + 1, 0);
@@ -194,12 +195,10 @@ static int build_section(csb_matrix *m, uint32_t tile_rows, QuadPlan *out) {
         }
         qp.valid = true;
         *out = qp;
-        return CSB_OK;
-    } catch (const std::bad_alloc &) {
+    } catch (const std::bad_alloc &) {               // the section is for speed alone: products read the tile-based ones
         *out = QuadPlan{};
-        pl.valid = false;
-        set_error("csb_plan: out of host memory");
-        return CSB_ENOMEM;
+        pl.image.resize(image_before);               // (shrinks)
+        return;
     }
 }
 
@@ -208,13 +207,12 @@ static int build_section(csb_matrix *m, uint32_t tile_rows, QuadPlan *out) {
 // workgroups one: a wavefront then has half the passes.  Taller blocks are cut by tiles of 16 rows, so that all tiles together
 // have about twice the passes, of half the rows: better as long as they still find idle CUs (quad_columns), which they never
 // do beyond 256 tiles.
-int plan_quad(csb_matrix *m) {
+void plan_quad(csb_matrix *m) {
     Plan &pl = m->plan;
     const int64_t rows = m->rows + (pl.split.active() ? pl.split.shift : 0);
     pl.quad_low = QuadPlan{};
-    const int rc = build_section(m, m->br <= 16 && rows < 256 * 32 ? 16u : 32u, &pl.quad);
-    if (rc != CSB_OK || !pl.quad.valid || m->br <= 16 || rows > 256 * 16) return rc;
-    return build_section(m, 16u, &pl.quad_low);
+    build_section(m, m->br <= 16 && rows < 256 * 32 ? 16u : 32u, &pl.quad);
+    if (pl.quad.valid && m->br > 16 && rows <= 256 * 16) build_section(m, 16u, &pl.quad_low);
 }
 
 // Walks the section the way the kernels do, with bounds checks, and compares what it adds up with the matrix: every

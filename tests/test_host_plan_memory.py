@@ -49,8 +49,9 @@ def test_what_is_left_is_a_whole_plan_or_none(plans):
         assert valid in (OK, ESTATE), (first_mode, room, planned)
 
 
-# The tile sections and the row-owned section of this matrix took 34 MB to plan (image 20 MB); what is added to them is
-# room for the rest of the image, 22 MB, and no more.
-def test_no_room_is_set_aside(plans):
-    first = [p for p in plans if p[0] is None and p[2] == OK]
-    assert first[0][1] <= 34 + first[0][4] / 2 ** 20 / 2
+# 34 MB is what the tile sections and the row-owned section of this matrix take to plan.  No room is set aside for the section
+# of the batched products, which is there for speed alone: where it does not fit, the plan is made without it.
+def test_plan_without_the_batched_section(plans):
+    by_room = {room: (planned, size) for first_mode, room, planned, valid, size in plans if first_mode is None}
+    assert all(planned == OK for room, (planned, size) in by_room.items() if room >= 36)
+    assert by_room[36][1] < by_room[76][1]
