@@ -201,7 +201,8 @@ int csb_plan_rows(csb_matrix *m, int32_t n_workgroups, int32_t min_rounds, csb_p
 int csb_plan_stats_get(const csb_matrix *m, csb_plan_stats *stats);
 
 /* Integer self-check of the planned device image: every offset in bounds, every kernel
- * value referenced exactly once, image decodes to the packed matrix.  Host only. */
+ * value referenced exactly once, image decodes to the packed matrix (which it keeps dense, twice:
+ * CSB_ENOMEM without the memory for that).  Host only. */
 int csb_plan_validate(const csb_matrix *m);
 
 /* Bytes of device memory the planned matrix needs (0 if not planned). */

@@ -911,7 +911,14 @@ extern "C" int csb_plan_rows(csb_matrix *m, int32_t n_workgroups, int32_t min_ro
     return CSB_OK;
 }
 
-extern "C" int csb_plan_validate(const csb_matrix *m) { return csb::validate_plan(m); }
+extern "C" int csb_plan_validate(const csb_matrix *m) {
+    try {
+        return csb::validate_plan(m);
+    } catch (const std::bad_alloc &) {
+        csb::set_error("csb_plan_validate: out of host memory");
+        return CSB_ENOMEM;
+    }
+}
 
 extern "C" size_t csb_device_bytes(const csb_matrix *m) {
     return (m && m->plan.valid) ? m->plan.image.size() : 0;
