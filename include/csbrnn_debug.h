@@ -44,6 +44,12 @@ int csb_debug_stream_read(const void *d_buf, size_t bytes, float *d_out, void *s
 int csb_debug_spmm_columns(int64_t row_tiles, int32_t rows_per_tile, int32_t batch, int32_t bits16);
 
 /*
+ * Passes (at most 8 columns by the rows of one block in one row tile) of the section that the batched products read, in row
+ * tiles of 16 or 32 rows; 0 where the plan has no such section.  Host only.
+ */
+int64_t csb_debug_quad_passes(const csb_matrix *m, int32_t rows_per_tile);
+
+/*
  * Whether csb_rnn_forward runs a batch on the resident kernel (1) or on the batched products (0) when the layouts
  * of both are uploaded.  Host only.
  */

@@ -248,8 +248,7 @@ struct StreamPlan {
 //   values  binary32: per pass [column][4 rows][quad]; 16-bit formats: [4 columns][4 rows][quad][4 columns], and with more
 //           than four quads [4 columns][4 rows][quad % 4][quad / 4][4 columns], eight of them; columns in fours,
 //           zeros where the pass has no such row or column; kQuadPad bytes of zeros behind the last
-// With `seg_rows` > 0 tiles do not cross multiples of it (the gates of a recurrent cell, seg_rows units each);
-// with `split_col` > 0 no pass crosses that column (the border between the two sources of a step's
+// With `split_col` > 0 no pass crosses that column (the border between the two sources of a step's
 // input), and columns of the second part are counted from it.
 constexpr int kQuadRows = 32;
 constexpr int kQuadLists = 16;
@@ -275,13 +274,12 @@ static_assert(sizeof(QuadRec) == 64, "QuadRec layout");
 
 struct QuadPlan {
     bool valid = false;
-    uint32_t n_tiles = 0, tile_rows = 0, seg_rows = 0, tiles_per_seg = 0;
+    uint32_t rows = 0, n_tiles = 0, tile_rows = 0;
     uint32_t split_col = 0;
     uint32_t val_fmt = 0;
     uint64_t off_table = 0, off_recs = 0, off_vals = 0;
     uint32_t list_stride = 0;
     uint64_t n_passes = 0, n_recs = 0, vals_bytes = 0;   // (n_recs with gaps between the lists and kQuadSpareRecs, vals_bytes with the padding)
-    uint32_t tile_row0(uint32_t t) const { return t / tiles_per_seg * seg_rows + t % tiles_per_seg * tile_rows; }
 };
 
 // The host staging copy of the device image.  Sections are appended to it one after another; realloc grows a large one
@@ -354,7 +352,7 @@ struct csb_matrix {
     int32_t stream_cell_gates = 0;   // > 0: the rows are `gates` stacked groups of rows/gates units each, and a workgroup of
                                      // the row-owned plan is to own all gate rows of its units (set by an RNN handle, whose
                                      // mat-vec launches then finish their cells themselves; csb_plan* ask for plain ranges)
-    int32_t quad_units = 0, quad_split = 0;   // seg_rows and split_col of the quad section (set by an RNN handle)
+    int32_t quad_split = 0;       // split_col of the quad section (set by an RNN handle)
     csb::Plan plan;
     void *d_buf = nullptr;        // caller-owned device image, set by csb_upload
     bool uploaded = false;

@@ -10,6 +10,7 @@
 #include <numeric>
 
 #include "csb_internal.hpp"
+#include "csbrnn_debug.h"
 
 namespace csb {
 namespace {
@@ -878,13 +879,13 @@ int validate_plan(const csb_matrix *m) {
 // (A plan the caller asks for may take all 256 compute units again, whatever share of them an RNN
 // handle had left the matrix.)
 extern "C" int csb_plan(csb_matrix *m, int32_t n_chunks, csb_plan_stats *stats) {
-    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; m->quad_units = 0; m->quad_split = 0; }
+    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; m->quad_split = 0; }
     return csb::plan_matrix(m, n_chunks, 16, m ? m->plan.split : csb::SplitSpec{}, stats, 0);
 }
 
 extern "C" int csb_plan_ex(csb_matrix *m, int32_t n_chunks, int32_t mode, csb_plan_stats *stats) {
     if (mode == 3 || mode == 4) { csb::set_error("csb_plan: mode must be 0 (auto), 1 (whole tiles) or 2 (equal split)"); return CSB_EINVAL; }
-    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; m->quad_units = 0; m->quad_split = 0; }
+    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; m->quad_split = 0; }
     return csb::plan_matrix(m, n_chunks, 16, m ? m->plan.split : csb::SplitSpec{}, stats, mode);
 }
 
@@ -897,7 +898,7 @@ extern "C" int csb_plan_stats_get(const csb_matrix *m, csb_plan_stats *stats) {
 
 extern "C" int csb_plan_rows(csb_matrix *m, int32_t n_workgroups, int32_t min_rounds, csb_plan_stats *stats) {
     if (n_workgroups < 0 || min_rounds < 0) { csb::set_error("csb_plan_rows: negative parameter"); return CSB_EINVAL; }
-    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; m->quad_units = 0; m->quad_split = 0; }
+    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; m->quad_split = 0; }
     int rc = csb::plan_matrix(m, 0, 16, csb::SplitSpec{}, nullptr, 4);
     if (rc != CSB_OK) return rc;
     rc = csb::plan_stream(m, n_workgroups, min_rounds, stats);
@@ -909,6 +910,13 @@ extern "C" int csb_plan_rows(csb_matrix *m, int32_t n_workgroups, int32_t min_ro
     }
     csb::plan_quad(m);
     return CSB_OK;
+}
+
+extern "C" int64_t csb_debug_quad_passes(const csb_matrix *m, int32_t rows_per_tile) {
+    if (!m || !m->plan.valid) return 0;
+    for (const csb::QuadPlan *qp : {&m->plan.quad, &m->plan.quad_low})
+        if (qp->valid && (int32_t)qp->tile_rows == rows_per_tile) return (int64_t)qp->n_passes;
+    return 0;
 }
 
 extern "C" int csb_plan_validate(const csb_matrix *m) {

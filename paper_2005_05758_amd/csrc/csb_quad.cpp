@@ -82,9 +82,8 @@ void for_passes(const csb_matrix *m, const QuadPlan &qp, F f) {
                     const bool lower = !sp.active() || gr < sp.split_row;
                     if (lower ? !part.lower : !part.upper) { ++a; continue; }
                     const int64_t shift = part.shifted ? sp.shift : 0;
-                    const uint32_t seg = (uint32_t)((gr + shift) / qp.seg_rows);
-                    const uint32_t tile = seg * qp.tiles_per_seg + (uint32_t)((gr + shift - (int64_t)seg * qp.seg_rows) / qp.tile_rows);
-                    const int64_t row0 = qp.tile_row0(tile), end = std::min<int64_t>(row0 + qp.tile_rows, (int64_t)(seg + 1) * qp.seg_rows);
+                    const uint32_t tile = (uint32_t)((gr + shift) / qp.tile_rows);
+                    const int64_t row0 = (int64_t)tile * qp.tile_rows, end = row0 + qp.tile_rows;
                     int e = a;                           // the kernel rows of this tile
                     while (e < nr) {
                         const int64_t orow = (int64_t)bi * m->br + ri[e];
@@ -115,10 +114,9 @@ static void build_section(csb_matrix *m, uint32_t tile_rows, QuadPlan *out) {
     if (m->cols > kMaxStageCols || rows > 0x7fffffff || rows == 0) return;
     try {
         QuadPlan qp{};
-        qp.seg_rows = (uint32_t)(m->quad_units > 0 && rows % m->quad_units == 0 ? m->quad_units : rows);
+        qp.rows = (uint32_t)rows;
         qp.tile_rows = tile_rows;
-        qp.tiles_per_seg = (qp.seg_rows + qp.tile_rows - 1) / qp.tile_rows;
-        qp.n_tiles = (uint32_t)(rows / qp.seg_rows) * qp.tiles_per_seg;
+        qp.n_tiles = (qp.rows + qp.tile_rows - 1) / qp.tile_rows;
         qp.split_col = m->quad_split > 0 ? (uint32_t)m->quad_split : 0u;
         qp.val_fmt = (uint32_t)m->val_fmt;
         const bool bits16 = m->val_fmt != CSB_VAL_F32;
@@ -226,7 +224,7 @@ static int validate_section(const csb_matrix *m, const QuadPlan &qp) {
     const uint8_t *vals = pl.image.data() + qp.off_vals;
     const bool bits16 = qp.val_fmt != CSB_VAL_F32;
     const int64_t rows = m->rows + (pl.split.active() ? pl.split.shift : 0);
-    if (qp.n_tiles != (uint32_t)(rows / qp.seg_rows) * qp.tiles_per_seg || rows % qp.seg_rows) return fail("tiles");
+    if (qp.rows != (uint64_t)rows || qp.n_tiles != (rows + qp.tile_rows - 1) / qp.tile_rows) return fail("tiles");
     // what is expected: (output row, column) -> value, and how often it was seen
     const size_t cells = (size_t)rows * (size_t)m->cols;
     std::vector<float> expect(cells, 0.0f), got(cells, 0.0f);
@@ -247,7 +245,7 @@ static int validate_section(const csb_matrix *m, const QuadPlan &qp) {
                 }
         }
     for (uint32_t t = 0; t < qp.n_tiles; ++t) {
-        const int64_t row0 = qp.tile_row0(t), end = std::min<int64_t>(row0 + qp.tile_rows, (int64_t)(t / qp.tiles_per_seg + 1) * qp.seg_rows);
+        const int64_t row0 = (int64_t)t * qp.tile_rows, end = std::min<int64_t>(row0 + qp.tile_rows, rows);
         for (int l = 0; l < kQuadLists; ++l) {
             const size_t list = (size_t)t * kQuadLists + l;
             const uint64_t i0 = table[list];

@@ -1227,7 +1227,7 @@ extern "C" int csb_rnn_create(int32_t cell, int32_t n_layers, int32_t input, int
                 // stacked layers, where a cell has two consumers, 12-17 % apart.  (Enqueued from the host
                 // one call at a time, single layers were the other way round: 5.06 / 5.68 for 153->512.)
                 W[l]->stream_cell_gates = cell == CSB_CELL_LIGRU ? 2 : 4;
-                W[l]->quad_units = hidden; W[l]->quad_split = l == 0 ? input : hidden;
+                W[l]->quad_split = l == 0 ? input : hidden;
                 int rc = plan_matrix(W[l], had ? W[l]->plan.req_chunks : 0, 16, sp, nullptr, had ? W[l]->plan.req_mode : 0);
                 if (rc != CSB_OK) { delete r; return rc; }
             }
@@ -1270,7 +1270,7 @@ extern "C" int csb_rnn_create_lstmp(int32_t n_layers, int32_t input, int32_t hid
                     // 153 -> 1024 -> 512 shape in a loop over the same buffers, us per frame, consumer-side /
                     // whole units: one layer 7.71 / 7.24)
                     m->stream_cell_gates = m == W[l] ? 4 : 0;
-                    m->quad_units = m == W[l] ? hidden : proj; m->quad_split = m == W[l] ? (l == 0 ? input : proj) : 0;
+                    m->quad_split = m == W[l] ? (l == 0 ? input : proj) : 0;
                     int rc = plan_matrix(m, 0, 16, SplitSpec{}, nullptr, 0);
                     if (rc != CSB_OK) { delete r; return rc; }
                 }
@@ -1330,7 +1330,7 @@ extern "C" int csb_rnn_create_gru_rb(int32_t n_layers, int32_t input, int32_t hi
                     // also with one layer: measured, us per step, consumer-side / whole units: 39 -> 1024
                     // 8.43 / 7.52, 153 -> 512 7.91 / 7.11, 64 -> 256 7.39 / 7.12)
                     m->stream_cell_gates = m == Wa[l] ? 3 : 1;
-                    m->quad_units = hidden; m->quad_split = m == Wa[l] ? (l == 0 ? input : hidden) : 0;
+                    m->quad_split = m == Wa[l] ? (l == 0 ? input : hidden) : 0;
                     int rc = plan_matrix(m, 0, 16, SplitSpec{}, nullptr, 0);
                     if (rc != CSB_OK) { delete r; return rc; }
                 }

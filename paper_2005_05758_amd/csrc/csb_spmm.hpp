@@ -51,7 +51,7 @@ struct QuadMat {
     const uint32_t *table;
     const void *recs;
     const uint8_t *vals;
-    uint32_t vals_bytes, n_tiles, tile_rows, seg_rows, tiles_per_seg, val_fmt, cols, list_stride;
+    uint32_t vals_bytes, n_tiles, tile_rows, rows, cols, list_stride;
 };
 struct QuadJobs {
     QuadMat m[kMaxJobsPerLaunch];

@@ -341,8 +341,7 @@ __device__ __forceinline__ void spmm_quad_body(const QuadMat &m, const XSrc &X, 
     asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
     const uint32_t tid = wave * 64u + lane;
     constexpr int RM = NT == 2 ? 16 : 32;
-    const uint32_t seg = tile / m.tiles_per_seg, in = tile - seg * m.tiles_per_seg;
-    const uint32_t row0 = seg * m.seg_rows + in * m.tile_rows, tile_rows = min(m.tile_rows, m.seg_rows - in * m.tile_rows);
+    const uint32_t row0 = tile * m.tile_rows, tile_rows = min(m.tile_rows, m.rows - row0);
     float *red = (float *)smem4;                         // [waves][RM][NT][64]
 #pragma unroll
     for (int r0 = 0; r0 < kQuadRows; r0 += RM) {
@@ -393,8 +392,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
 QuadMat quad_mat(const csb_matrix *m, bool low) {
     const QuadPlan &qp = low ? m->plan.quad_low : m->plan.quad;
     uint8_t *b = (uint8_t *)m->d_buf;
-    return QuadMat{(const uint32_t *)(b + qp.off_table), b + qp.off_recs, b + qp.off_vals, (uint32_t)qp.vals_bytes, qp.n_tiles, qp.tile_rows, qp.seg_rows,
-                   qp.tiles_per_seg, qp.val_fmt, (uint32_t)m->plan.hdr.cols, qp.list_stride};
+    return QuadMat{(const uint32_t *)(b + qp.off_table), b + qp.off_recs, b + qp.off_vals, (uint32_t)qp.vals_bytes, qp.n_tiles, qp.tile_rows, qp.rows,
+                   (uint32_t)m->plan.hdr.cols, qp.list_stride};
 }
 
 // Right-hand sides per workgroup and its wavefronts, for `tiles` row tiles in the launch.  What counts is the number of

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import csb_inputs
-from paper_2005_05758_amd import CsbMatrix, CsbRnn
+from paper_2005_05758_amd import CsbMatrix, CsbRnn, load_library
 from paper_2005_05758_amd import binding as csb
 
 
@@ -24,8 +24,8 @@ def test_section_holds_the_matrix(fmt, R, C, br, bc):
         M.validate()
 
 
-# A recurrent handle's matrices: tiles end with a gate, passes end where the input's two sources meet, the GRU's
-# candidate rows are summed in two parts.
+# A recurrent handle's matrices: passes end where the input's two sources meet, the GRU's candidate rows are
+# summed in two parts.
 @pytest.mark.parametrize("cell,gates", [(csb.CELL_LSTM, 4), (csb.CELL_GRU, 3), (csb.CELL_LIGRU, 2), (csb.CELL_LSTMP, 4), (csb.CELL_GRU_RB, 3)])
 @pytest.mark.parametrize("inputs,hidden,block", [(5, 40, 16), (39, 33, 32), (64, 100, 64)])
 def test_section_of_a_recurrent_handle(cell, gates, inputs, hidden, block):
@@ -41,3 +41,17 @@ def test_section_of_a_recurrent_handle(cell, gates, inputs, hidden, block):
     CsbRnn(cell, inputs, hidden, [W], proj=state if cell == csb.CELL_LSTMP else 0, Wp=second or None)
     for m in [W] + second:
         m.validate()
+
+
+# The handle's plan cuts no pass where a gate ends: with an input that ends with a block it has those of a plain plan.
+@pytest.mark.parametrize("hidden,block", [(100, 32), (301, 32), (500, 64), (77, 16)])
+def test_gates_do_not_cut_tiles(hidden, block):
+    inputs = 2 * block
+    A = csb_inputs.small_matrix(5, 4 * hidden, inputs + hidden, block, block, rate=3.0).A
+    plain, W = CsbMatrix(A, block, block), CsbMatrix(A, block, block)
+    plain.plan()
+    CsbRnn(csb.CELL_LSTM, inputs, hidden, [W])
+    for rows in (16, 32):
+        passes = [load_library().csb_debug_quad_passes(m._h, rows) for m in (plain, W)]
+        assert passes[0] == passes[1]
+    assert any(load_library().csb_debug_quad_passes(W._h, rows) for rows in (16, 32))
