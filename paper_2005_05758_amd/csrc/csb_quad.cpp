@@ -205,8 +205,12 @@ static void build_section(csb_matrix *m, uint32_t tile_rows, QuadPlan *out) {
 // workgroups one: a wavefront then has half the passes.  Taller blocks are cut by tiles of 16 rows, so that all tiles together
 // have about twice the passes, of half the rows: better as long as they still find idle CUs (quad_columns), which they never
 // do beyond 256 tiles.
+// None for the 16-bit values of a recurrent handle's gate matrix: its steps multiply float32 right-hand sides, and the
+// products of 16-bit ones take passes from one source alone (LSTM 1024 -> 1024 at 12x in binary16: 15.8 MB of image, without
+// them 8.5).
 void plan_quad(csb_matrix *m) {
     Plan &pl = m->plan;
+    if (m->val_fmt != CSB_VAL_F32 && m->quad_split > 0) return;
     const int64_t rows = m->rows + (pl.split.active() ? pl.split.shift : 0);
     pl.quad_low = QuadPlan{};
     build_section(m, m->br <= 16 && rows < 256 * 32 ? 16u : 32u, &pl.quad);

@@ -55,3 +55,18 @@ def test_gates_do_not_cut_tiles(hidden, block):
         passes = [load_library().csb_debug_quad_passes(m._h, rows) for m in (plain, W)]
         assert passes[0] == passes[1]
     assert any(load_library().csb_debug_quad_passes(W._h, rows) for rows in (16, 32))
+
+
+# What a 16-bit gate matrix of a handle holds for products of right-hand sides: the tile-based sections.
+@pytest.mark.parametrize("fmt", [csb.VAL_F16, csb.VAL_BF16])
+@pytest.mark.parametrize("cell,gates", [(csb.CELL_LSTM, 4), (csb.CELL_GRU, 3)])
+def test_no_section_that_nothing_reads(cell, gates, fmt):
+    A = csb_inputs.small_matrix(5, gates * 64, 96, 32, 32, rate=3.0).A
+    W, plain = CsbMatrix(A, 32, 32), CsbMatrix(A, 32, 32)
+    for m in (W, plain):
+        m.set_value_format(fmt)
+    plain.plan()
+    CsbRnn(cell, 32, 64, [W])
+    W.validate()
+    passes = [[load_library().csb_debug_quad_passes(m._h, rows) for rows in (16, 32)] for m in (W, plain)]
+    assert passes[0] == [0, 0] and all(passes[1])
