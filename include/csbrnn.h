@@ -205,7 +205,8 @@ int csb_plan_stats_get(const csb_matrix *m, csb_plan_stats *stats);
  * CSB_ENOMEM without the memory for that).  Host only. */
 int csb_plan_validate(const csb_matrix *m);
 
-/* Bytes of device memory the planned matrix needs (0 if not planned). */
+/* Bytes of device memory the planned matrix needs (0 if not planned).  A csb_rnn_create* call on a matrix that is planned and
+ * not uploaded lays out anew what its batched steps read; a buffer of the size asked for before that call is still enough. */
 size_t csb_device_bytes(const csb_matrix *m);
 
 /*

@@ -321,6 +321,8 @@ struct Plan {
     StreamPlan stream;            // valid: csb_spmv reads this section instead of the sections above
     QuadPlan quad;                // valid: batched products read this section instead of the tile-based ones
     QuadPlan quad_low;            // valid: the same matrix in tiles of 16 rows, for launches that these still get through at once
+    uint64_t before_quad = 0;     // bytes of the image in front of the batched products' sections
+    uint64_t bytes_told = 0;      // > 0: what csb_device_bytes said before a handle cut those sections anew
     csb_plan_stats stats{};
 };
 
@@ -369,6 +371,8 @@ int validate_plan(const csb_matrix *m);
 int plan_stream(csb_matrix *m, int32_t n_wg_req, int32_t rounds_min, csb_plan_stats *stats);
 int validate_stream(const csb_matrix *m);
 void plan_quad(csb_matrix *m);
+void cut_quad(csb_matrix *m, int64_t split_col);
+void drop_quad(csb_matrix *m);
 int validate_quad(const csb_matrix *m);
 DevMat dev_mat(const csb_matrix *m);
 }  // namespace csb

@@ -603,6 +603,7 @@ int plan_matrix(csb_matrix *m, int32_t n_chunks_req, int32_t waves_per_chunk, co
         pl.hdr = h;
         pl.stream = StreamPlan{};                // sections of the image before: gone with it, also if the next ones cannot be built
         pl.quad = pl.quad_low = QuadPlan{};
+        pl.before_quad = off; pl.bytes_told = 0;
         pl.split = split;
         pl.req_chunks = n_chunks_req;
         pl.req_mode = with_rows ? 0 : (mode == 0 ? 4 : mode);
@@ -877,15 +878,15 @@ int validate_plan(const csb_matrix *m) {
 // A matrix that a GRU handle has planned keeps that row layout when it is planned again (also after
 // csb_set_value_format made the plan invalid): the handle's step kernels depend on it.
 // (A plan the caller asks for may take all 256 compute units again, whatever share of them an RNN
-// handle had left the matrix.)
+// handle had left the matrix.  The border between the sources of a step's input stays where the handle set it.)
 extern "C" int csb_plan(csb_matrix *m, int32_t n_chunks, csb_plan_stats *stats) {
-    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; m->quad_split = 0; }
+    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; }
     return csb::plan_matrix(m, n_chunks, 16, m ? m->plan.split : csb::SplitSpec{}, stats, 0);
 }
 
 extern "C" int csb_plan_ex(csb_matrix *m, int32_t n_chunks, int32_t mode, csb_plan_stats *stats) {
     if (mode == 3 || mode == 4) { csb::set_error("csb_plan: mode must be 0 (auto), 1 (whole tiles) or 2 (equal split)"); return CSB_EINVAL; }
-    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; m->quad_split = 0; }
+    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; }
     return csb::plan_matrix(m, n_chunks, 16, m ? m->plan.split : csb::SplitSpec{}, stats, mode);
 }
 
@@ -898,7 +899,7 @@ extern "C" int csb_plan_stats_get(const csb_matrix *m, csb_plan_stats *stats) {
 
 extern "C" int csb_plan_rows(csb_matrix *m, int32_t n_workgroups, int32_t min_rounds, csb_plan_stats *stats) {
     if (n_workgroups < 0 || min_rounds < 0) { csb::set_error("csb_plan_rows: negative parameter"); return CSB_EINVAL; }
-    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; m->quad_split = 0; }
+    if (m) { m->stream_wg_limit = 256; m->stream_cell_gates = 0; }
     int rc = csb::plan_matrix(m, 0, 16, csb::SplitSpec{}, nullptr, 4);
     if (rc != CSB_OK) return rc;
     rc = csb::plan_stream(m, n_workgroups, min_rounds, stats);

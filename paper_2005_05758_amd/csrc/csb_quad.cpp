@@ -210,11 +210,30 @@ static void build_section(csb_matrix *m, uint32_t tile_rows, QuadPlan *out) {
 // them 8.5).
 void plan_quad(csb_matrix *m) {
     Plan &pl = m->plan;
+    pl.before_quad = pl.image.size();
     if (m->val_fmt != CSB_VAL_F32 && m->quad_split > 0) return;
     const int64_t rows = m->rows + (pl.split.active() ? pl.split.shift : 0);
     pl.quad_low = QuadPlan{};
     build_section(m, m->br <= 16 && rows < 256 * 32 ? 16u : 32u, &pl.quad);
     if (pl.quad.valid && m->br > 16 && rows <= 256 * 16) build_section(m, 16u, &pl.quad_low);
+}
+
+void drop_quad(csb_matrix *m) {
+    m->plan.quad = m->plan.quad_low = QuadPlan{};
+    m->plan.image.resize(m->plan.before_quad);           // (shrinks)
+}
+
+// The matrix belongs to a handle whose steps bring its columns from `split_col` on from a second source.  A plan that the
+// caller made before knows nothing of that border: its sections are cut anew, as long as they are on the host alone (an image
+// that is uploaded stays as it is, and its batched steps read the tile-based sections).
+void cut_quad(csb_matrix *m, int64_t split_col) {
+    m->quad_split = (int32_t)split_col;
+    Plan &pl = m->plan;
+    if (!pl.valid || m->uploaded || pl.quad.split_col == (uint32_t)split_col) return;
+    const uint64_t told = std::max<uint64_t>(pl.bytes_told, pl.image.size());
+    drop_quad(m);
+    plan_quad(m);
+    pl.bytes_told = told;
 }
 
 // Walks the section the way the kernels do, with bounds checks, and compares what it adds up with the matrix: every

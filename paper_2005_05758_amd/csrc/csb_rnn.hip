@@ -1230,7 +1230,8 @@ extern "C" int csb_rnn_create(int32_t cell, int32_t n_layers, int32_t input, int
                 W[l]->quad_split = l == 0 ? input : hidden;
                 int rc = plan_matrix(W[l], had ? W[l]->plan.req_chunks : 0, 16, sp, nullptr, had ? W[l]->plan.req_mode : 0);
                 if (rc != CSB_OK) { delete r; return rc; }
-            }
+                if (!W[l]->plan.quad.valid) plan_quad(W[l]);              // (a plan that csb_plan_rows made builds its sections one by one)
+            } else cut_quad(W[l], l == 0 ? input : hidden);
             r->W.push_back(W[l]);
             r->d_bias.push_back(d_bias ? d_bias[l] : nullptr);
         }
@@ -1273,7 +1274,7 @@ extern "C" int csb_rnn_create_lstmp(int32_t n_layers, int32_t input, int32_t hid
                     m->quad_split = m == W[l] ? (l == 0 ? input : proj) : 0;
                     int rc = plan_matrix(m, 0, 16, SplitSpec{}, nullptr, 0);
                     if (rc != CSB_OK) { delete r; return rc; }
-                }
+                } else cut_quad(m, m == W[l] ? (l == 0 ? input : proj) : 0);
             r->W.push_back(W[l]);
             r->Wp.push_back(Wp[l]);
             r->d_bias.push_back(d_bias ? d_bias[l] : nullptr);
@@ -1333,7 +1334,7 @@ extern "C" int csb_rnn_create_gru_rb(int32_t n_layers, int32_t input, int32_t hi
                     m->quad_split = m == Wa[l] ? (l == 0 ? input : hidden) : 0;
                     int rc = plan_matrix(m, 0, 16, SplitSpec{}, nullptr, 0);
                     if (rc != CSB_OK) { delete r; return rc; }
-                }
+                } else cut_quad(m, m == Wa[l] ? (l == 0 ? input : hidden) : 0);
             r->W.push_back(Wa[l]);
             r->Wp.push_back(Un[l]);
             r->d_bias.push_back(d_bias ? d_bias[l] : nullptr);

@@ -618,6 +618,8 @@ int commit_gates(const GateSrc &s, void *stream) {
 extern "C" int csb_upload(csb_matrix *m, void *d_buf, size_t bytes, void *stream) {
     if (!m || !d_buf) { csb::set_error("csb_upload: NULL pointer"); return CSB_EINVAL; }
     if (!m->plan.valid) { csb::set_error("csb_upload: matrix not planned"); return CSB_ESTATE; }
+    // (a buffer of the size that was asked for before a handle cut the batched products' sections anew holds the image without them)
+    if (bytes < m->plan.image.size() && m->plan.bytes_told && bytes >= m->plan.bytes_told) csb::drop_quad(m);
     if (bytes < m->plan.image.size()) { csb::set_error("csb_upload: device buffer too small"); return CSB_ENOMEM; }
     if ((uintptr_t)d_buf % 256) { csb::set_error("csb_upload: device buffer not 256-byte aligned"); return CSB_EINVAL; }
     hipError_t e = hipMemcpyAsync(d_buf, m->plan.image.data(), m->plan.image.size(), hipMemcpyHostToDevice,

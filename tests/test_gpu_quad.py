@@ -92,3 +92,36 @@ def test_output_sequence_of_a_batch(cell, layers, batch, T):
                 assert np.max(np.abs(g.cpu().numpy() - r)) <= 1e-4
     alone = rnn.forward(torch.from_numpy(x).cuda(), want_hseq=False)  # without the sequence: the state in place
     assert alone[0] is None and torch.equal(alone[1], got[1])
+
+
+# Matrices that their caller planned before the handle was created: not uploaded yet (their section is cut anew), uploaded (they
+# keep the image on the GPU), and uploaded after into a buffer of the size that was asked for before.
+# (A GRU handle plans its matrices itself: an upload before it is void, and so is a size that was asked for before.)
+@pytest.mark.parametrize("cell,gates,upload", [(csb.CELL_LSTM, 4, "after"), (csb.CELL_LSTM, 4, "before"), (csb.CELL_LSTM, 4, "told"),
+                                               (csb.CELL_LIGRU, 2, "told"), (csb.CELL_GRU, 3, "after")])
+@pytest.mark.parametrize("batch", [3, 70])
+def test_batch_with_matrices_planned_by_the_caller(cell, gates, upload, batch):
+    inputs, hidden = 39, 100
+    A = [csb_inputs.small_matrix(20 + l, gates * hidden, (inputs, hidden)[l] + hidden, 32, 32, rate=4.0).A * 0.1 for l in range(2)]
+    W = [CsbMatrix(a, 32, 32) for a in A]
+    for m in W:
+        m.plan()
+    told = [m.device_bytes() for m in W]
+    if upload == "before":
+        for m in W:
+            m.upload()
+    rnn = CsbRnn(cell, inputs, hidden, W)
+    bufs = [torch.zeros(n, dtype=torch.uint8, device="cuda") for n in told]
+    for m, n, buf in zip(W, told, bufs):
+        if upload == "after":
+            m.upload()
+        elif upload == "told":
+            assert csb.lib().csb_upload(m._h, buf.data_ptr(), n - 1, None) == -2      # CSB_ENOMEM
+            assert csb.lib().csb_upload(m._h, buf.data_ptr(), n, None) == 0
+            m.validate()
+    x = np.random.default_rng(batch).uniform(-1, 1, (5, batch, inputs)).astype(np.float32)
+    got, ref = rnn.forward(torch.from_numpy(x).cuda()), oracle.rnn_forward(cell, A, None, x, inputs, hidden)
+    torch.cuda.synchronize()
+    for g, r in zip(got, ref):
+        if g is not None:
+            assert np.max(np.abs(g.cpu().numpy() - r)) <= 1e-4

@@ -70,3 +70,33 @@ def test_no_section_that_nothing_reads(cell, gates, fmt):
     W.validate()
     passes = [[load_library().csb_debug_quad_passes(m._h, rows) for rows in (16, 32)] for m in (W, plain)]
     assert passes[0] == [0, 0] and all(passes[1])
+
+
+# A matrix that was planned before its handle was created, or is planned again after, has the section that a handle's own
+# plan has: cut where the input's two sources meet, inside a block here.
+@pytest.mark.parametrize("plan", ["plan", "mode1", "mode2", "rows"])
+@pytest.mark.parametrize("cell,gates", [(csb.CELL_LSTM, 4), (csb.CELL_GRU, 3), (csb.CELL_LIGRU, 2), (csb.CELL_LSTMP, 4), (csb.CELL_GRU_RB, 3)])
+def test_section_of_a_matrix_planned_by_its_caller(cell, gates, plan):
+    inputs, hidden, state = 39, 64, 48 if cell == csb.CELL_LSTMP else 64
+    A = csb_inputs.small_matrix(7, gates * hidden, inputs + state, 32, 32, rate=2.0).A.copy()
+    B = csb_inputs.small_matrix(8, state, hidden, 32, 32, rate=2.0).A
+    if cell == csb.CELL_GRU_RB:
+        A[2 * hidden:, inputs:] = 0.0
+
+    def handle(before, after):
+        W = CsbMatrix(A, 32, 32)
+        second = [CsbMatrix(B, 32, 32)] if cell in (csb.CELL_GRU_RB, csb.CELL_LSTMP) else []
+        call = {"plan": W.plan, "mode1": lambda: W.plan(mode=1), "mode2": lambda: W.plan(mode=2), "rows": W.plan_rows}[plan]
+        if before:
+            call()
+        CsbRnn(cell, inputs, hidden, [W], proj=state if cell == csb.CELL_LSTMP else 0, Wp=second or None)
+        if after:
+            call()
+        for m in [W] + second:
+            m.validate()
+        return [load_library().csb_debug_quad_passes(W._h, rows) for rows in (16, 32)]
+
+    own = handle(False, False)
+    assert handle(True, False) == own and all(own)
+    if not (cell == csb.CELL_GRU and plan == "rows"):                     # (the rows of a GRU step are laid out by its handle alone)
+        assert handle(False, True) == own
