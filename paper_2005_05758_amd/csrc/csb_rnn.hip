@@ -990,6 +990,17 @@ static int resident_instances(const csb_rnn *r, int32_t batch) {
     return (int)std::min<uint32_t>(8u / xcds * share, (uint32_t)batch);
 }
 
+// Whether the last layer's outputs of a batch stay in a ring of steps and are turned over ([width][batch] -> [batch][width])
+// together.  LSTMP's projection would take a launch per step for it.  The other cells store a word per line where their batch
+// is wide; a ring costs a launch, 2.6 us, and room in the caches.  us per call, without / with one: outputs of 64 x 1024, two LSTM
+// layers, 16 steps 196.0 / 188.4, 8 111.3 / 108.5, one GRU layer 16 138.9 / 143.2, 32 269.7 / 271.5; 128 x 1024, GRU, 16 179.3 /
+// 164.8, 4 51.2 / 52.4; 256 x 512, Li-GRU, 4 44.3 / 43.8, 2 26.8 / 27.9; 512 x 1024, GRU, 2 63.3 / 55.8; 64 x 512, Li-GRU,
+// 8 60.7 / 61.9, 32 217 / 231; 256 x 128, LSTM, 16 109.3 / 110.2.
+static bool output_ring(const csb_rnn *r, int32_t batch, int32_t T) {
+    const uint64_t words = (uint64_t)batch * (uint64_t)r->state_width();
+    return r->cell == CSB_CELL_LSTMP || (batch >= 48 && words >= 65536 && words * (uint64_t)std::max(T, 0) >= 450000);
+}
+
 static RnnWs ws_layout(const csb_rnn *r, int32_t batch, int32_t T) {
     RnnWs w{};
     size_t off = 0;
@@ -1028,9 +1039,9 @@ static RnnWs ws_layout(const csb_rnn *r, int32_t batch, int32_t T) {
         w.xt_steps = (int32_t)std::max<size_t>(1, std::min<size_t>({(size_t)std::max(T, 1), (size_t)1024, ((size_t)8 << 20) / std::max<size_t>(frame, 1)}));
         w.off_xt = off; off = align256(off + (size_t)w.xt_steps * frame);
         // the last layer's outputs, kept as the steps leave them and turned over into the caller's sequence a
-        // few steps at a time (8 MB; a step reads the one before, so two at least)
+        // few steps at a time (output_ring; 8 MB; a step reads the one before, so two at least)
         const size_t out = (size_t)batch * HS * sizeof(float);
-        w.hs_steps = (int32_t)std::min<size_t>((size_t)std::max(T, 1), std::max<size_t>(2, std::min<size_t>((size_t)1024, ((size_t)8 << 20) / std::max<size_t>(out, 1))));
+        if (output_ring(r, batch, T)) w.hs_steps = (int32_t)std::min<size_t>((size_t)std::max(T, 1), std::max<size_t>(2, std::min<size_t>((size_t)1024, ((size_t)8 << 20) / std::max<size_t>(out, 1))));
         w.off_hs = off; off = align256(off + (size_t)w.hs_steps * out);
     }
     // (LSTMP at batch 1 as well: every layer's m_t, between its gate launch and its projection launch)
@@ -1510,13 +1521,8 @@ static int rnn_forward_enqueue(const csb_rnn *r, const float *d_x, const float *
         hipLaunchKernelGGL(state_in_kernel, dim3(sblocks), dim3(256), 0, st, hi, d_h0, L, batch, HS);
         if (lstm) hipLaunchKernelGGL(state_in_kernel, dim3(sblocks), dim3(256), 0, st, ci, d_c0, L, batch, H);
         const int gb = (H * batch + 255) / 256;
-        // Where layer l's state of step t lies (t = -1: the initial one): in place, but for the last layer with `ring`: its
-        // outputs stay in a ring of hs_steps steps and are turned over ([width][batch] -> [batch][width]) together.  (A
-        // cell that stores its output in the caller's order stores a word per line, which from about 48 sequences on
-        // costs more than a launch per ring; LSTMP's projection would take a launch per step.  us per step: two LSTM
-        // layers of 1024 at batch 64 12.2 -> 11.9, LSTMP 153 -> 1024 -> 512 at batch 48 18.0 -> 17.2; two Li-GRU layers of
-        // 512 at batch 33 9.8 either way, one LSTM layer of 512 at batch 4 and 20 steps 7.2 -> 7.4.)
-        const bool ring = d_hseq && (lstmp || batch >= 48);
+        // Where layer l's state of step t lies (t = -1: the initial one): in place, but for the last layer with `ring`.
+        const bool ring = d_hseq && output_ring(r, batch, T);
         float *hs = (float *)((uint8_t *)d_ws + wl.off_hs);
         auto h_at = [&](int l, int t) -> float * {
             if (!ring || l != L - 1 || t < 0) return hi + (size_t)l * HS * batch;

@@ -69,10 +69,11 @@ def test_product_with_a_recurrent_handles_matrix(inputs, hidden, block, batch):
 
 
 # The last layer's outputs are turned over a ring of steps at a time: 16 here, so 40 steps fill it twice and a half; on
-# either side of the batch from which on they are (48), and with the projected cell, where they always are.
+# either side of the size from which on they are (65536 words a step, 450000 in all), and with the projected cell, where they always are.
 @pytest.mark.parametrize("cell,layers,batch,T", [(csb.CELL_LSTM, 2, 2048, 40), (csb.CELL_LSTM, 1, 2048, 16), (csb.CELL_GRU, 1, 2048, 17),
                                                  (csb.CELL_LIGRU, 2, 47, 3), (csb.CELL_LIGRU, 2, 48, 3), (csb.CELL_LSTMP, 2, 5, 4),
-                                                 (csb.CELL_LSTM, 1, 64, 1), (csb.CELL_LSTMP, 1, 2100, 35)])
+                                                 (csb.CELL_LSTM, 1, 64, 1), (csb.CELL_LSTMP, 1, 2100, 35), (csb.CELL_LIGRU, 2, 1024, 6),
+                                                 (csb.CELL_LIGRU, 2, 1024, 7), (csb.CELL_GRU, 1, 1023, 9)])
 def test_output_sequence_of_a_batch(cell, layers, batch, T):
     inputs, hidden, state = 10, 64, 40 if cell == csb.CELL_LSTMP else 64
     gates = {csb.CELL_LSTM: 4, csb.CELL_GRU: 3, csb.CELL_LIGRU: 2, csb.CELL_LSTMP: 4}[cell]

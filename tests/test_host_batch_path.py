@@ -30,3 +30,18 @@ def test_the_faster_path(cell, L, I, H, block, rate, law, measured):
     rnn = handle(cell, L, I, H, block, rate, law)
     got = {b: load_library().csb_debug_rnn_prefers_resident(rnn._h, b) for b in measured}
     assert got == {b: int(res < bat) for b, (res, bat) in measured.items()}
+
+
+# The ring of the last layer's outputs is part of the workspace where the call uses it: from about half a million words of output
+# on, and at least 65536 a step.  (A model whose input is too wide for the resident layout: what else grows with the steps
+# are its input frames.)
+@pytest.mark.parametrize("hidden,batch,T,ring", [(16, 4, 64, False), (64, 40, 64, False), (64, 48, 64, False), (1024, 47, 16, False), (1024, 64, 6, False),
+                                                 (1024, 64, 7, True), (1024, 256, 1, False), (1024, 256, 2, True), (1024, 512, 1, True)])
+def test_workspace_of_a_batch(hidden, batch, T, ring):
+    W = CsbMatrix(csb_inputs.small_matrix(3, 4 * hidden, 2100 + hidden, 64, 64, rate=25.0).A, 64, 64)
+    rnn = CsbRnn(CELL_LSTM, 2100, hidden, [W], None)
+    assert rnn.device_bytes() == 0
+    # (gate sums, cell and output states, frames, the merge words of a mat-vec; every part rounded up to 256 bytes)
+    plain = W.workspace_bytes(1) + 4 * batch * (4 * hidden + 3 * hidden + 2100 * min(T, max(1, (8 << 20) // (4 * batch * 2100))))
+    extra = rnn.workspace_bytes(batch, T) - plain
+    assert (extra > 4 * batch * hidden if ring and T > 1 else extra >= 4 * batch * hidden if ring else extra < 8192)
