@@ -272,6 +272,12 @@ struct QuadRec {
 constexpr uint8_t kQuadWide = 1, kQuadSecond = 2;
 static_assert(sizeof(QuadRec) == 64, "QuadRec layout");
 
+// What the passes of a section add up to, for the estimate of a launch's time.
+struct QuadWork {
+    double passes = 0, quads = 0, steps = 0, rows = 0;   // quads: four rows of a pass; steps: those times its columns
+    double uneven = 1;                                   // work of the longest list, against their mean
+};
+
 struct QuadPlan {
     bool valid = false;
     uint32_t rows = 0, n_tiles = 0, tile_rows = 0;
@@ -279,6 +285,7 @@ struct QuadPlan {
     uint32_t val_fmt = 0;
     uint64_t off_table = 0, off_recs = 0, off_vals = 0;
     uint32_t list_stride = 0;
+    QuadWork work;
     uint64_t n_passes = 0, n_recs = 0, vals_bytes = 0;   // (n_recs with gaps between the lists and kQuadSpareRecs, vals_bytes with the padding)
 };
 
@@ -321,6 +328,9 @@ struct Plan {
     StreamPlan stream;            // valid: csb_spmv reads this section instead of the sections above
     QuadPlan quad;                // valid: batched products read this section instead of the tile-based ones
     QuadPlan quad_low;            // valid: the same matrix in tiles of 16 rows, for launches that these still get through at once
+    // (for the estimate of a batched product's time) columns of all block records, their squares, those of records that have
+    // all of their block's, and rows in sixteens
+    double vb_cols = 0, vb_squares = 0, vb_full = 0, vb_slices = 0;
     uint64_t before_quad = 0;     // bytes of the image in front of the batched products' sections
     uint64_t bytes_told = 0;      // > 0: what csb_device_bytes said before a handle cut those sections anew
     csb_plan_stats stats{};
@@ -355,6 +365,7 @@ struct csb_matrix {
                                      // the row-owned plan is to own all gate rows of its units (set by an RNN handle, whose
                                      // mat-vec launches then finish their cells themselves; csb_plan* ask for plain ranges)
     int32_t quad_split = 0;       // split_col of the quad section (set by an RNN handle)
+    int32_t batch_form = 0;       // csb_debug_spmm_force: which sections the batched products read
     csb::Plan plan;
     void *d_buf = nullptr;        // caller-owned device image, set by csb_upload
     bool uploaded = false;

@@ -601,6 +601,13 @@ int plan_matrix(csb_matrix *m, int32_t n_chunks_req, int32_t waves_per_chunk, co
         put(h.off_tile_seg0, tile_seg0.data(), tile_seg0.size() * 4);
         put(h.off_segs, segs.data(), segs.size() * sizeof(SegRec));
         pl.hdr = h;
+        pl.vb_cols = pl.vb_squares = pl.vb_full = pl.vb_slices = 0;
+        for (const VbRec &v : vrecs) {
+            pl.vb_cols += v.c;
+            pl.vb_squares += (double)v.c * v.c;
+            if (v.c == bc) pl.vb_full += v.c;
+            pl.vb_slices += (v.r + 15) / 16;
+        }
         pl.stream = StreamPlan{};                // sections of the image before: gone with it, also if the next ones cannot be built
         pl.quad = pl.quad_low = QuadPlan{};
         pl.before_quad = off; pl.bytes_told = 0;

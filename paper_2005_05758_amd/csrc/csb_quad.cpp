@@ -139,11 +139,17 @@ static void build_section(csb_matrix *m, uint32_t tile_rows, QuadPlan *out) {
             std::memcpy(e.slot, slot, p.nrows);
             const size_t n = pass_value_bytes(p.nrows, p.ncols, bits16);
             best->work += pass_cost(p);
+            const uint32_t quads = (p.nrows + 3u) / 4u;
+            qp.work.quads += quads; qp.work.steps += quads * p.ncols; qp.work.rows += p.nrows;
             best->bytes += (uint32_t)n;
             longest = std::max(longest, ++best->passes);
             bytes += n;
         });
         qp.n_passes = entries.size();
+        qp.work.passes = (double)qp.n_passes;
+        double all = 0, most = 0;
+        for (const List &l : lists) { all += (double)l.work; most = std::max(most, (double)l.work); }
+        if (all > 0) qp.work.uneven = most * (double)lists.size() / all;
         qp.vals_bytes = bytes + kQuadPad;
         if (qp.vals_bytes >= 0x7fffff00ull || qp.n_passes >= 0x7fffffffull / sizeof(QuadRec)) return;
         // (the gaps are never read but for a count: half as many records again, or 4 MB, are worth the trip)

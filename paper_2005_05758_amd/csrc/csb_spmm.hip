@@ -15,6 +15,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "csb_internal.hpp"
 #include "csb_kernels.hpp"
@@ -822,6 +823,80 @@ struct SpmmShape {
     unsigned tiles, batch_tiles;
 };
 
+// ---- estimate of a launch's time from the tile-based sections -----------------------------------------------------
+// The section of four-row steps takes a pass for every 8 columns of a block and a row sum for every row; here a 16-row product
+// takes a block's rows, many or few, and sums them as it goes: faster where blocks are nearly full, and for few right-hand sides of
+// many row tiles.  Constants as in csb_spmm_quad.hip (us per block record and 8 of its columns, `full` where it keeps
+// them all and they are neighbours, `uneven` what the longest share of 16 has more than
+// their mean; general forms: per 16 rows of a block), from the same measurements.  A launch takes these sections where they save 5 % by the estimates; blocks
+// of more than 32 rows were never faster here.  us here / in four-row steps: 4096 x 4096 in 32-row blocks, float32 x 128 unpruned
+// 45.0 / 63.7, at 2x 38.6 / 43.8, 4x 30.6 / 28.0; bfloat16 x 512 52.5 / 76.4, 54.9 / 55.6, 44.8 / 37.6; 2048 x 2048 in 16-row
+// blocks, float32 x 16 at 2x 12.1 / 14.2, 4x 11.0 / 9.9; 4100 x 2048 in 24-row blocks x 4 at 4x 10.7 / 15.7, x 32 18.8 / 15.7.
+struct TileTurn { double base, block, cols, full, uneven; };
+struct TileCost {
+    int form, rows, nw, room;   // general form: 0, 16 nt columns, wavefronts, k-steps; in registers: 1 (16-bit right-hand sides 2),
+                                // 16-row parts, wavefronts, 64 nq columns; 16-bit general form: 3, 0, wavefronts, 0
+    double base, out;
+    TileTurn one, two;
+};
+static const TileCost kTileCost[] = {
+    {3, 0, 16, 0, 2.71, 2.19, {2.02, 0.893, 0.236, 0.214, 0.927}, {}},
+    {0, 1, 16, 4, 3.97, 0.697, {0, 0.589, 0.337, 0.293, 0}, {}},
+    {0, 1, 16, 8, 3.04, 5.08, {0.885, 0.512, 0.404, 0.397, 1.22}, {}},
+    {0, 1, 8, 4, 4.49, 0, {0, 0.371, 0.0379, 0, 0}, {0, 0.475, 0.475, 0.395, 0}},
+    {0, 1, 8, 8, 3.13, 0.0977, {0, 0.288, 0.134, 0.177, 0}, {0.739, 0.329, 0.565, 0.553, 1.52}},
+    {0, 2, 16, 4, 3.08, 2.84, {0.889, 0.763, 0.51, 0.468, 0}, {}},
+    {0, 2, 16, 8, 3.17, 2.34, {1.32, 0.596, 0.565, 0.569, 1.41}, {}},
+    {0, 2, 8, 4, 3.87, 5.45, {0, 0.362, 0.188, 0.216, 0}, {0, 0.618, 0.438, 0.376, 0}},
+    {0, 2, 8, 8, 3.4, 4.13, {0.326, 0.423, 0.312, 0.299, 0.651}, {0.296, 0.548, 0.595, 0.62, 1.7}},
+    {0, 4, 16, 4, 2.64, 2.28, {1.74, 0.73, 0.939, 0.874, 1.32}, {}},
+    {2, 1, 16, 1, 3.23, 0, {1.25, 0.698, 0.0771, 0.0128, 0}, {}},
+    {2, 1, 8, 2, 4.39, 0.0183, {0.798, 0.582, 0.0203, 0, 0.0369}, {2.21, 1.06, 0.0692, 0, 0}},
+    {2, 2, 16, 1, 2.27, 0.694, {2.87, 0.508, 0.518, 0.228, 0.0437}, {}},
+    {2, 2, 8, 2, 2.56, 0.769, {3.45, 0.27, 0.411, 0.263, 0}, {6.76, 0.624, 0.751, 0.45, 0}},
+    {1, 1, 16, 1, 2.33, 3.14, {1.85, 0.716, 0.403, 0.367, 0}, {}},
+    {1, 1, 8, 2, 2.06, 1.33, {3.02, 0.528, 0.46, 0.412, 0.0323}, {5.43, 1.03, 0.926, 0.813, 0}},
+    {1, 2, 16, 1, 2.84, 2.32, {2.61, 0.517, 1.23, 1.02, 0.0987}, {}},
+    {1, 2, 8, 2, 2.8, 1, {3.78, 0.413, 1.09, 0.984, 0.868}, {7.47, 0.809, 2.23, 1.9, 1.19}},
+};
+// Of n products that share a launch of the shape (form, rows, nw, room).
+static double tile_us(int form, int rows, int nw, int room, const csb_matrix *const *mats, int n, int32_t batch, unsigned batch_tiles) {
+    const TileCost *f = nullptr;
+    for (const TileCost &c : kTileCost) if (c.form == form && c.rows == rows && c.nw == nw && c.room == room) f = &c;
+    double tiles = 0, blocks = 0, vbs = 0, cols = 0, full_cols = 0, squares = 0, out_words = 0;
+    for (int i = 0; i < n; ++i) {
+        const Plan &pl = mats[i]->plan;
+        if (pl.hdr.br > 32) f = nullptr;
+        tiles += (double)pl.hdr.n_nz_tiles + pl.hdr.n_zero_tiles;
+        vbs += pl.hdr.n_vbs;
+        blocks += form % 3 == 0 && pl.hdr.br > 16 ? pl.vb_slices : pl.hdr.n_vbs;      // (the general forms take 16 rows at a time)
+        cols += pl.vb_cols - pl.vb_full;
+        full_cols += pl.vb_full;
+        squares += pl.vb_squares;
+        out_words += (double)pl.hdr.rows_out * batch;
+    }
+    if (!f || vbs == 0) return 1e300;
+    const double wgs = tiles * batch_tiles, slots = nw == 8 ? 512 : 256;
+    const double full = (double)(uint64_t)(wgs / slots), rest = wgs - full * slots;
+    double one = full + (rest > 0 ? 1 : 0), two = 0;
+    if (nw == 8) { two = full + (rest > 256 ? 1 : 0); one = rest > 0 && rest <= 256 ? 1 : 0; }
+    const double per_wave = blocks / tiles / nw;
+    const double mean = (cols + full_cols) / vbs, spread = std::sqrt(std::max(squares / vbs - mean * mean, 0.0) * per_wave) / 8;
+    auto turn = [&](const TileTurn &t) {
+        return t.base + per_wave * (t.block + (t.cols * cols + t.full * full_cols) / (8 * vbs)) + t.uneven * spread;
+    };
+    return f->base + f->out * out_words * 1e-6 + one * turn(f->one) + two * turn(f->two);
+}
+// (Two sources: a choice per lane and load.  The steps of two GRU layers of 512 at 3x and batch 256 took 30.9 us with 128 columns
+// in registers, 22.7 in four-row steps, where products of one source are as fast; those of a Li-GRU layer of 1024 at 3x and
+// batch 128, 64 columns, 18.0 and 15.7, at 2x and batch 16, 16 columns, 13.0 and 14.8.)
+static double tile_us(const SpmmShape &sh, const csb_matrix *const *mats, int n, int32_t batch) {
+    const double two = !sh.two || sh.nt == 1 ? 1.0 : sh.nq > 1 ? 1.5 : 1.2;
+    return two * (sh.reg_parts ? tile_us(1, sh.reg_parts, sh.nw, sh.nq, mats, n, batch, sh.batch_tiles)
+                               : tile_us(0, sh.nt, sh.nw, sh.ks, mats, n, batch, sh.batch_tiles));
+}
+static bool prefers_quads(double quads_us, double tiles_us) { return 0.95 * quads_us <= tiles_us; }
+
 // How many times 64 right-hand sides a workgroup of the register-accumulating kernels takes, for `tiles` row tiles
 // of `rows` rows in the launch and right-hand sides of 32 or 16 bits.  128 halve what is done per block, and
 // where every one of the 256 CUs has a workgroup of them, what counts is the number of turns the workgroups take
@@ -845,11 +920,16 @@ static bool long_tiles(const SpmmCall *calls, int n) {
     return blocks >= 96 * tiles;
 }
 
+static int spmm_ready(const csb_matrix *mat) {
+    if (mat->plan.valid && mat->uploaded && mat->d_buf) return CSB_OK;
+    set_error("csb_spmm: matrix not planned and uploaded");
+    return CSB_ESTATE;
+}
+
 // Checks one product's operands and chooses its launch shape; `launch_wgs_factor` products of
 // this size share the launch, which counts when the launch is sized against the GPU's 256 CUs.
 static int spmm_shape(const SpmmCall &c, int32_t batch, size_t launch_wgs_factor, bool long_tiles, SpmmShape *out, XSrc *X) {
     const csb_matrix *mat = c.mat;
-    if (!mat->plan.valid || !mat->uploaded || !mat->d_buf) { set_error("csb_spmm: matrix not planned and uploaded"); return CSB_ESTATE; }
     const DevHeader &h = mat->plan.hdr;
     // 32-bit element offsets, 24-bit multiplies
     const int64_t smax_j = std::max(c.sj0, c.sj1);
@@ -925,17 +1005,20 @@ int spmm_strided(const csb_matrix *mat, const float *p0, uint32_t n0, int64_t sj
     const SpmmCall c{mat, p0, n0, sj0, p1, sj1, d_Y, ldy};
     SpmmShape sh;
     XSrc X;
-    int rc = spmm_shape(c, batch, 1, long_tiles(&c, 1), &sh, &X);
+    int rc = spmm_ready(mat);
+    if (rc == CSB_OK) rc = spmm_shape(c, batch, 1, long_tiles(&c, 1), &sh, &X);
     if (rc != CSB_OK) return rc;
     uint32_t b = (uint32_t)batch;
     int64_t ld = ldy;
-    QuadShape qs;
     XSrc QX;
+    bool two;
     hipError_t e;
-    if (quad_shape(c, batch, 1, &qs, &QX)) {
+    const bool quads = quad_source(c, &QX, &two);
+    const QuadShape qs = quads ? quad_shape(&mat, 1, batch, false) : QuadShape{};
+    if (quads && (mat->batch_form == kFormQuads || prefers_quads(qs.us, tile_us(sh, &mat, 1, batch)))) {
         QuadMat qm = quad_mat(mat, qs.low);
         void *args[] = {&qm, &QX, &d_Y, &ld, &b};
-        const void *kern = quad_kernel(qs, false);
+        const void *kern = quad_kernel(qs, two, false);
         e = ensure_dynamic_lds(kern, qs.lds);
         if (e == hipSuccess)
             e = hipLaunchKernel(kern, dim3(qs.tiles, qs.batch_tiles), dim3(qs.nw * 64), args, qs.lds, (hipStream_t)stream);
@@ -963,7 +1046,8 @@ int spmm_strided_multi(const SpmmCall *calls, int n, int32_t batch, void *stream
         unsigned tiles = 0;
         const bool many = long_tiles(calls, n);
         for (int i = 0; i < n; ++i) {
-            int rc = spmm_shape(calls[i], batch, (size_t)n, many, &sh[i], &J.X[i]);
+            int rc = spmm_ready(calls[i].mat);
+            if (rc == CSB_OK) rc = spmm_shape(calls[i], batch, (size_t)n, many, &sh[i], &J.X[i]);
             if (rc != CSB_OK) return rc;
             same = same && sh[i].nt == sh[0].nt && sh[i].nw == sh[0].nw && sh[i].two == sh[0].two && sh[i].reg_parts == sh[0].reg_parts && sh[i].nq == sh[0].nq && sh[i].vf == sh[0].vf;
             lds = std::max(lds, sh[i].lds);
@@ -973,23 +1057,36 @@ int spmm_strided_multi(const SpmmCall *calls, int n, int32_t batch, void *stream
             J.Y[i] = calls[i].Y;
             J.ldy[i] = calls[i].ldy;
         }
-        QuadShape qs[kMaxJobsPerLaunch] = {};
+        // (tiles of both heights share a launch of the section's: a workgroup asks its product for its rows)
         QuadJobs QJ{};
-        bool quad = true;
-        for (int i = 0; i < n && quad; ++i) {
-            quad = quad_shape(calls[i], batch, (size_t)n, &qs[i], &QJ.X[i]) && qs[i] == qs[0];
-            QJ.m[i] = quad_mat(calls[i].mat, qs[i].low);
-            QJ.Y[i] = calls[i].Y;
-            QJ.ldy[i] = calls[i].ldy;
-            qs[0].tiles = std::max(qs[0].tiles, qs[i].tiles);
+        const csb_matrix *mats[kMaxJobsPerLaunch];
+        bool quads = true, two = false, forced = false;
+        for (int i = 0; i < n; ++i) {
+            bool t = false;
+            mats[i] = calls[i].mat;
+            quads = quads && quad_source(calls[i], &QJ.X[i], &t) && (i == 0 || t == two);
+            two = t;
+            forced = forced || mats[i]->batch_form == kFormQuads;
         }
-        if (quad) {
+        const QuadShape qs = quads ? quad_shape(mats, n, batch, false) : QuadShape{};
+        if (quads && !forced) {
+            double us = 0;
+            if (same) us = tile_us(sh[0], mats, n, batch);
+            else for (int i = 0; i < n; ++i) us += tile_us(sh[i], &mats[i], 1, batch);
+            quads = prefers_quads(qs.us, us);
+        }
+        if (quads) {
+            for (int i = 0; i < n; ++i) {
+                QJ.m[i] = quad_mat(mats[i], qs.low);
+                QJ.Y[i] = calls[i].Y;
+                QJ.ldy[i] = calls[i].ldy;
+            }
             uint32_t b = (uint32_t)batch;
             void *args[] = {&QJ, &b};
-            const void *kern = quad_kernel(qs[0], true);
-            hipError_t e = ensure_dynamic_lds(kern, qs[0].lds);
+            const void *kern = quad_kernel(qs, two, true);
+            hipError_t e = ensure_dynamic_lds(kern, qs.lds);
             if (e == hipSuccess)
-                e = hipLaunchKernel(kern, dim3(qs[0].tiles, qs[0].batch_tiles, (unsigned)n), dim3(qs[0].nw * 64), args, qs[0].lds, (hipStream_t)stream);
+                e = hipLaunchKernel(kern, dim3(qs.tiles, qs.batch_tiles, (unsigned)n), dim3(qs.nw * 64), args, qs.lds, (hipStream_t)stream);
             if (e != hipSuccess) { set_error(std::string("csb_spmm: ") + hipGetErrorString(e)); return CSB_EDEVICE; }
             return CSB_OK;
         }
@@ -1015,6 +1112,31 @@ int spmm_strided_multi(const SpmmCall *calls, int n, int32_t batch, void *stream
 }  // namespace csb
 
 namespace csb {
+// Launch shape of a product of 16-bit values and 16-bit right-hand sides from the tile-based sections.
+struct Spmm16Shape {
+    bool fits, reg;          // row tiles of 16 or 32 rows: the kernel that keeps its results in registers
+    int nw, nq, nwr;         // wavefronts of the general form; 64-column groups and wavefronts of the other
+    size_t lds;
+    unsigned tiles, batch_tiles;
+    double us;
+};
+static Spmm16Shape spmm16_shape(const csb_matrix *m, int32_t batch) {
+    const DevHeader &h = m->plan.hdr;
+    Spmm16Shape s{};
+    const size_t acc_per_wave = (size_t)h.br * 64 * sizeof(float);
+    s.nw = (size_t)h.seg_meta + 16 * acc_per_wave <= (size_t)kLdsBudget ? 16 : 8;
+    s.fits = (size_t)h.seg_meta + 8 * acc_per_wave <= (size_t)kLdsBudget;
+    s.tiles = (unsigned)(h.n_nz_tiles + h.n_zero_tiles);
+    s.nq = reg_columns(s.tiles, h.br, batch, true);
+    s.nwr = s.nq > 1 ? 8 : s.nw;
+    const size_t lds_reg = (size_t)h.seg_meta + (size_t)s.nwr * acc_per_wave + (size_t)s.nwr * 64;
+    s.reg = (h.br == 16 || h.br == 32) && h.n_vals * 4 < 0x7fffff00ull && lds_reg <= (size_t)160 * 1024;
+    s.lds = s.reg ? lds_reg : (size_t)h.seg_meta + (size_t)s.nw * acc_per_wave;
+    s.batch_tiles = (unsigned)(s.reg ? (batch + 64 * s.nq - 1) / (64 * s.nq) : (batch + 63) / 64);
+    s.us = s.reg ? tile_us(2, (int)h.br / 16, s.nwr, s.nq, &m, 1, batch, s.batch_tiles) : tile_us(3, 0, s.nw, 0, &m, 1, batch, s.batch_tiles);
+    return s;
+}
+
 // csb_spmm_bfloat / csb_spmm_half: both operands in the 16-bit format `fmt`
 static int spmm_16bit(const char *who, int fmt, const csb_matrix *m, const uint16_t *d_X, int64_t ldx, float *d_Y, int64_t ldy,
                       int32_t batch, void *stream) {
@@ -1034,14 +1156,14 @@ static int spmm_16bit(const char *who, int fmt, const csb_matrix *m, const uint1
         set_error(w + ": sizes beyond the kernel's 32-bit offsets");
         return CSB_EUNSUPPORTED;
     }
-    const size_t acc_per_wave = (size_t)h.br * 64 * sizeof(float);
-    const bool fits16 = (size_t)h.seg_meta + 16 * acc_per_wave <= (size_t)kLdsBudget;
-    if ((size_t)h.seg_meta + 8 * acc_per_wave > (size_t)kLdsBudget) {
+    const Spmm16Shape sh = spmm16_shape(m, batch);
+    if (!sh.fits) {
         set_error(w + ": the block rows are too tall for the accumulator tiles");
         return CSB_EUNSUPPORTED;
     }
-    QuadShape qs;
-    if (quad16_shape(m, ldx, batch, &qs)) {
+    const bool quads = quad16_source(m, ldx);
+    const QuadShape qs = quads ? quad_shape(&m, 1, batch, true) : QuadShape{};
+    if (quads && (m->batch_form == kFormQuads || prefers_quads(qs.us, sh.us))) {
         QuadMat qm = quad_mat(m, qs.low);
         XSrc X{(const float *)d_X, (uint32_t)h.cols, (uint32_t)ldx, (const float *)d_X, (uint32_t)ldx};
         uint32_t b = (uint32_t)batch;
@@ -1054,38 +1176,32 @@ static int spmm_16bit(const char *who, int fmt, const csb_matrix *m, const uint1
         if (e != hipSuccess) { set_error(w + ": " + hipGetErrorString(e)); return CSB_EDEVICE; }
         return CSB_OK;
     }
-    const int nw = fits16 ? 16 : 8;
     DevMat dm = dev_mat(m);
     uint32_t b = (uint32_t)batch, ld = (uint32_t)ldx;
     int64_t ldy_ = ldy;
     const bool half = fmt == CSB_VAL_F16;
-    // row tiles of 16 or 32 rows: the kernel that keeps its results in registers
-    const size_t tiles = (size_t)h.n_nz_tiles + h.n_zero_tiles;
-    const int nq = reg_columns(tiles, h.br, batch, true), nwr = nq > 1 ? 8 : nw;
-    const size_t lds_reg = (size_t)h.seg_meta + (size_t)nwr * acc_per_wave + (size_t)nwr * 64;
-    if ((h.br == 16 || h.br == 32) && h.n_vals * 4 < 0x7fffff00ull && lds_reg <= (size_t)160 * 1024) {
+    if (sh.reg) {
         XSrc X{(const float *)d_X, (uint32_t)h.cols, ld, (const float *)d_X, ld};
         void *rargs[] = {&dm, &X, &d_Y, &ldy_, &b};
         const void *kern;
 #define CSB_R16(NW, NH, NQ) (half ? (const void *)spmm_reg16_kernel<NW, NH, CSB_VAL_F16, NQ> : (const void *)spmm_reg16_kernel<NW, NH, CSB_VAL_BF16, NQ>)
-        if (nq == 2) kern = h.br == 16 ? CSB_R16(8, 1, 2) : CSB_R16(8, 2, 2);
-        else if (nw == 16) kern = h.br == 16 ? CSB_R16(16, 1, 1) : CSB_R16(16, 2, 1);
+        if (sh.nq == 2) kern = h.br == 16 ? CSB_R16(8, 1, 2) : CSB_R16(8, 2, 2);
+        else if (sh.nw == 16) kern = h.br == 16 ? CSB_R16(16, 1, 1) : CSB_R16(16, 2, 1);
         else kern = h.br == 16 ? CSB_R16(8, 1, 1) : CSB_R16(8, 2, 1);
 #undef CSB_R16
-        hipError_t e = ensure_dynamic_lds(kern, lds_reg);
+        hipError_t e = ensure_dynamic_lds(kern, sh.lds);
         if (e == hipSuccess)
-            e = hipLaunchKernel(kern, dim3((unsigned)tiles, (unsigned)((batch + 64 * nq - 1) / (64 * nq))), dim3(nwr * 64), rargs, lds_reg,
+            e = hipLaunchKernel(kern, dim3(sh.tiles, sh.batch_tiles), dim3(sh.nwr * 64), rargs, sh.lds,
                                 (hipStream_t)stream);
         if (e != hipSuccess) { set_error(w + ": " + hipGetErrorString(e)); return CSB_EDEVICE; }
         return CSB_OK;
     }
-    const size_t lds = (size_t)h.seg_meta + (size_t)nw * acc_per_wave;
     void *args[] = {&dm, &d_X, &ld, &d_Y, &ldy_, &b};
-    const void *kern = nw == 16 ? (half ? (const void *)spmm_bf16_kernel<16, true> : (const void *)spmm_bf16_kernel<16, false>)
+    const void *kern = sh.nw == 16 ? (half ? (const void *)spmm_bf16_kernel<16, true> : (const void *)spmm_bf16_kernel<16, false>)
                                 : (half ? (const void *)spmm_bf16_kernel<8, true> : (const void *)spmm_bf16_kernel<8, false>);
-    hipError_t e = ensure_dynamic_lds(kern, lds);
+    hipError_t e = ensure_dynamic_lds(kern, sh.lds);
     if (e == hipSuccess)
-        e = hipLaunchKernel(kern, dim3((unsigned)(h.n_nz_tiles + h.n_zero_tiles), (unsigned)((batch + 63) / 64)), dim3(nw * 64), args, lds,
+        e = hipLaunchKernel(kern, dim3(sh.tiles, sh.batch_tiles), dim3(sh.nw * 64), args, sh.lds,
                             (hipStream_t)stream);
     if (e != hipSuccess) { set_error(w + ": " + hipGetErrorString(e)); return CSB_EDEVICE; }
     return CSB_OK;
@@ -1109,6 +1225,39 @@ extern "C" int csb_spmm(const csb_matrix *m, const float *d_X, int64_t ldx, floa
     if (batch <= 0 || ldx < batch || ldy < batch) { csb::set_error("csb_spmm: batch <= 0 or a leading dimension below batch"); return CSB_EINVAL; }
     if (m->plan.valid && m->plan.split.active()) { csb::set_error("csb_spmm: matrix is planned for a GRU step"); return CSB_ESTATE; }
     return csb::spmm_strided(m, d_X, (uint32_t)m->cols, ldx, d_X, ldx, d_Y, ldy, batch, stream);
+}
+
+extern "C" int csb_debug_spmm_force(csb_matrix *m, int32_t form) {
+    if (!m || form < csb::kFormAuto || form > csb::kFormQuads) { csb::set_error("csb_debug_spmm_force: NULL pointer or unknown form"); return CSB_EINVAL; }
+    m->batch_form = form;
+    return CSB_OK;
+}
+
+extern "C" int csb_debug_spmm_form(const csb_matrix *m, int32_t batch, int32_t bits16, int32_t *form) {
+    using namespace csb;
+    if (!m || !form || batch <= 0) { set_error("csb_debug_spmm_form: NULL pointer or batch <= 0"); return CSB_EINVAL; }
+    if (!m->plan.valid) { set_error("csb_debug_spmm_form: matrix not planned"); return CSB_ESTATE; }
+    const uint32_t cols = (uint32_t)m->plan.hdr.cols;
+    SpmmCall c{m, nullptr, cols, batch, nullptr, batch, nullptr, batch};
+    XSrc X;
+    bool two, quads = bits16 ? quad16_source(m, batch) : quad_source(c, &X, &two);
+    if (quads && m->batch_form != kFormQuads) {
+        double us;
+        if (bits16) us = spmm16_shape(m, batch).us;
+        else {
+            SpmmShape sh;
+            const int rc = spmm_shape(c, batch, 1, long_tiles(&c, 1), &sh, &X);
+            if (rc != CSB_OK) return rc;
+            us = tile_us(sh, &m, 1, batch);
+        }
+        quads = prefers_quads(quad_shape(&m, 1, batch, bits16 != 0).us, us);
+    }
+    form[0] = form[1] = form[2] = 0;
+    if (quads) {
+        const QuadShape qs = quad_shape(&m, 1, batch, bits16 != 0);
+        form[0] = (int32_t)(qs.low ? m->plan.quad_low : m->plan.quad).tile_rows; form[1] = qs.columns; form[2] = qs.nw;
+    }
+    return CSB_OK;
 }
 
 extern "C" int csb_debug_spmm_columns(int64_t row_tiles, int32_t rows_per_tile, int32_t batch, int32_t bits16) {

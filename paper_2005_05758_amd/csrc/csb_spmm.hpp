@@ -62,19 +62,22 @@ struct QuadJobs {
 struct QuadShape {
     int columns;            // right-hand sides per workgroup: 32, 64 or 128
     int nw;                 // wavefronts per workgroup
-    bool two;               // two sources
-    bool low;               // the section of 16-row tiles
+    bool low;               // the section of 16-row tiles, where a matrix has it
     size_t lds;
     unsigned tiles, batch_tiles;
-    bool operator==(const QuadShape &o) const { return columns == o.columns && nw == o.nw && two == o.two && low == o.low; }
+    double us;              // estimate of the launch's time
 };
 QuadMat quad_mat(const csb_matrix *m, bool low);
-// The launch shape of one product (checked by the caller), `launch_products` of whose size share the launch; false:
-// the product is not for these kernels.
-bool quad_shape(const SpmmCall &c, int32_t batch, size_t launch_products, QuadShape *out, XSrc *X);
-const void *quad_kernel(const QuadShape &sh, bool multi);
+// Whether a product (checked by the caller) is for these kernels; its sources as they read them, and whether there are two.
+bool quad_source(const SpmmCall &c, XSrc *X, bool *two);
 // The same for 16-bit values times 16-bit right-hand sides (one source, `ldx` elements from one column to the next).
-bool quad16_shape(const csb_matrix *mat, int64_t ldx, int32_t batch, QuadShape *out);
+bool quad16_source(const csb_matrix *mat, int64_t ldx);
+// The launch shape of n products that share a launch.
+QuadShape quad_shape(const csb_matrix *const *mats, int n, int32_t batch, bool bits16);
+const void *quad_kernel(const QuadShape &sh, bool two, bool multi);
 const void *quad16_kernel(const QuadShape &sh, bool half);
+
+// csb_debug_spmm_force's choices
+enum { kFormAuto = 0, kFormTiles = 1, kFormQuads = 2 };
 
 }  // namespace csb

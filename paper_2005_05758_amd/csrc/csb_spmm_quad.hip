@@ -390,61 +390,106 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
 
 // ---- launches ------------------------------------------------------------------------------------------------
 QuadMat quad_mat(const csb_matrix *m, bool low) {
-    const QuadPlan &qp = low ? m->plan.quad_low : m->plan.quad;
+    const QuadPlan &qp = low && m->plan.quad_low.valid ? m->plan.quad_low : m->plan.quad;
     uint8_t *b = (uint8_t *)m->d_buf;
     return QuadMat{(const uint32_t *)(b + qp.off_table), b + qp.off_recs, b + qp.off_vals, (uint32_t)qp.vals_bytes, qp.n_tiles, qp.tile_rows, qp.rows,
                    (uint32_t)m->plan.hdr.cols, qp.list_stride};
 }
 
-// Right-hand sides per workgroup and its wavefronts, for `tiles` row tiles in the launch.  What counts is the number of
-// turns the workgroups take over the 256 CUs and how long a turn is: of 16 wavefronts a CU holds one workgroup; of 8, two, which
-// overlap one's merge with the other's products but leave the last turn half empty.
-// us on 8192 x 8192 at 12x (256 row tiles), which is where the lengths of the turns are from:
-//   float32   32 right-hand sides 21.7; 64 25.4; 128 35 (a turn of 8 wavefronts 41.7, of twice as many of those 58: x 512 128 us with 16, 115
-//             with 8; x 260 102.6 and 95.6; 5000 x 300 x 500 in 64 x 64 blocks 17.5 and 12.3)
-//   16 bits   64 19.1 (8 wavefronts 28.0, twice as many 29.5); 128 22.9 (31.2, 33.4: x 512 82 us with 16, 67 with 8)
-struct QuadTurn { int columns, nw; double one, two; };   // length of a turn of up to 256 workgroups, of up to 512
-// Where the matrix has a section of 16-row tiles as well, a turn over those takes 0.82 of the time: half the merge and half the
-// products of a pass, the same passes.  us, 32-row / 16-row tiles: 2048 x 2048 x 64 in 32-row blocks 7.4 / 6.0, 1024 x 551 x 33 4.9 / 4.0,
-// 4096 x 2048 x 64 in 64-row blocks 5.7 / 5.2, 4096 x 4096 x 64 12.0 / 10.9; with a turn more, or wider workgroups to avoid it,
-// 4096 x 2048 x 128 6.3 / 6.8, 4096 x 4096 x 256 19.9 / 23.4.
-constexpr double kLowTurn = 0.82;
-static void quad_columns(const QuadTurn *forms, int n, const Plan &pl, size_t launch_products, int32_t batch, QuadShape *out) {
-    double best = 1e300;
-    for (int low = 0; low < (pl.quad_low.valid ? 2 : 1); ++low)
-        for (int i = 0; i < n; ++i) {
-            const QuadTurn &f = forms[i];
-            const size_t tiles = (size_t)(low ? pl.quad_low : pl.quad).n_tiles * launch_products;
-            const size_t w = tiles * (size_t)((batch + f.columns - 1) / f.columns), slots = f.nw == 8 ? 512 : 256, rest = w % slots;
-            const double cost = ((double)(w / slots) * (f.nw == 8 ? f.two : f.one) + (rest > 256 ? f.two : rest ? f.one : 0.0)) * (low ? kLowTurn : 1.0);
-            if (cost < best) { best = cost; out->columns = f.columns; out->nw = f.nw; out->low = low != 0; }
-        }
-    out->tiles = (unsigned)(out->low ? pl.quad_low : pl.quad).n_tiles;
-    out->batch_tiles = (unsigned)((batch + out->columns - 1) / out->columns);
+// ---- the launch's shape, by an estimate of its time --------------------------------------------------------------
+// What counts is the number of turns the workgroups take over the 256 CUs and how long a turn is: of 16 wavefronts a CU holds
+// one workgroup; of 8, two, which overlap one's merge with the other's products but leave the last turn half empty (`one`: a
+// turn of up to 256 of those, `two`: of up to 512).  A turn takes the merge of the wavefronts' tiles and what the passes of a
+// list take.  Lists are as long as the matrix makes them, so that no line between the forms lies at one size: the constants
+// (us per pass, step and row of a list; 16-bit values: `step` per four rows) are fitted to 400 matrices of 256 x 128 to
+// 40000 x 8192 in blocks of 4 to 128, pruned 1 to 25 times by three laws, at 2 to 512 right-hand sides in every form of
+// both sections: half of the estimates are within 3 % and nine of ten within 10; on matrices that were not fitted the form
+// taken is 0.5 % off the best one on average and 3.5 at the 95th percentile.  (With one length of a turn for all
+// matrices, that of 8192 x 8192 at 12x, and never the tile-based sections: 2.9 and 19.)
+// us on 8192 x 8192 at 12x, 256 tiles, 512 right-hand sides: float32 128 columns by 16 wavefronts 128, by 8 115; 16 bits 82 and 67;
+// x 64: 16 bits by 16 wavefronts 19.1, by 8 28.0.  32-row / 16-row tiles: 2048 x 2048 x 64 in 32-row blocks 7.4 / 6.0, 4096 x
+// 2048 x 128 in 64-row blocks 6.3 / 6.8.
+struct QuadTurn { double merge, pass, step, row; };
+struct QuadCost {
+    int columns, nw;
+    double base, out;                                    // out: per million output words
+    QuadTurn one, two;
+};
+static const QuadCost kQuadCost32[] = {
+    {32, 16, 2.23, 2.91, {1.34, 0.333, 0.00412, 0.026}, {}},
+    {64, 16, 2.24, 2.11, {1.16, 0.351, 0.00845, 0.0321}, {}},
+    {128, 16, 2.1, 1.3, {2.76, 0.44, 0.014, 0.0428}, {}},
+    {128, 8, 2.73, 0.95, {1.63, 0.512, 0.0186, 0.0363}, {1.57, 0.84, 0.0287, 0.0691}},
+};
+static const QuadCost kQuadCost16[] = {
+    {64, 16, 2.42, 1.62, {1.37, 0.342, 0.0649, 0}, {}},
+    {64, 8, 3.08, 1.18, {0.552, 0.376, 0.097, 0}, {0.861, 0.663, 0.114, 0}},
+    {128, 16, 2.41, 1.3, {3.23, 0.296, 0.0965, 0}, {}},
+    {128, 8, 2.8, 0.805, {2.08, 0.356, 0.127, 0}, {2.34, 0.606, 0.17, 0}},
+};
+static double quad_us(const QuadCost &f, const QuadWork &w, double tiles, double mean_rows, double out_words, int32_t batch) {
+    const double wgs = tiles * ((batch + f.columns - 1) / f.columns), slots = f.nw == 8 ? 512 : 256;
+    const double full = (double)(uint64_t)(wgs / slots), rest = wgs - full * slots;
+    double one = full + (rest > 0 ? 1 : 0), two = 0;
+    if (f.nw == 8) { two = full + (rest > 256 ? 1 : 0); one = rest > 0 && rest <= 256 ? 1 : 0; }
+    const double lists = tiles * kQuadLists, longest = 1 + (w.uneven - 1) / std::max(one + two, 1.0);      // (one turn is as long as its longest list)
+    auto turn = [&](const QuadTurn &t) {
+        return t.merge * mean_rows / kQuadRows + longest * (t.pass * w.passes + t.step * w.steps + t.row * w.rows) / lists;
+    };
+    return f.base + f.out * out_words * 1e-6 + one * turn(f.one) + two * turn(f.two);
 }
 
-bool quad_shape(const SpmmCall &c, int32_t batch, size_t launch_products, QuadShape *out, XSrc *X) {
+QuadShape quad_shape(const csb_matrix *const *mats, int n, int32_t batch, bool bits16) {
+    QuadShape best{};
+    best.us = 1e300;
+    bool any_low = false;
+    for (int i = 0; i < n; ++i) any_low = any_low || mats[i]->plan.quad_low.valid;
+    for (int low = 0; low < (any_low ? 2 : 1); ++low) {
+        QuadWork sum{};
+        double tiles = 0, rows = 0, out_rows = 0;
+        unsigned most_tiles = 0;
+        for (int i = 0; i < n; ++i) {
+            const Plan &pl = mats[i]->plan;
+            const QuadPlan &qp = low && pl.quad_low.valid ? pl.quad_low : pl.quad;
+            sum.passes += qp.work.passes; sum.rows += qp.work.rows;
+            sum.steps += bits16 ? qp.work.quads : qp.work.steps;
+            sum.uneven = std::max(sum.uneven, qp.work.uneven);
+            tiles += qp.n_tiles; rows += (double)qp.n_tiles * qp.tile_rows; out_rows += qp.rows;
+            most_tiles = std::max(most_tiles, (unsigned)qp.n_tiles);
+        }
+        for (const QuadCost &f : bits16 ? kQuadCost16 : kQuadCost32) {
+            const double us = quad_us(f, sum, tiles, rows / tiles, out_rows * batch, batch);
+            if (us < best.us)
+                best = QuadShape{f.columns, f.nw, low != 0, (size_t)f.nw * kQuadRows * 64 * sizeof(float), most_tiles,
+                                 (unsigned)((batch + f.columns - 1) / f.columns), us};
+        }
+    }
+    return best;
+}
+
+bool quad_source(const SpmmCall &c, XSrc *X, bool *two) {
     const QuadPlan &qp = c.mat->plan.quad;
     const uint64_t cols = c.mat->plan.hdr.cols;
-    if (!qp.valid || qp.val_fmt != CSB_VAL_F32) return false;
+    if (!qp.valid || qp.val_fmt != CSB_VAL_F32 || c.mat->batch_form == kFormTiles) return false;
     // a pass takes its columns from one source: two sources need a plan that was cut where they meet; one source
     // under such a plan is two that follow each other
-    const bool two_given = c.n0 < (uint32_t)cols, two = qp.split_col > 0 && qp.split_col < cols;
-    if (two_given && (!two || qp.split_col != c.n0)) return false;
-    *X = two_given || !two ? XSrc{c.p0, c.n0, (uint32_t)c.sj0, c.p1, (uint32_t)c.sj1}
-                           : XSrc{c.p0, qp.split_col, (uint32_t)c.sj0, c.p0 + (size_t)qp.split_col * c.sj0, (uint32_t)c.sj0};
+    const bool two_given = c.n0 < (uint32_t)cols;
+    *two = qp.split_col > 0 && qp.split_col < cols;
+    if (two_given && (!*two || qp.split_col != c.n0)) return false;
+    *X = two_given || !*two ? XSrc{c.p0, c.n0, (uint32_t)c.sj0, c.p1, (uint32_t)c.sj1}
+                            : XSrc{c.p0, qp.split_col, (uint32_t)c.sj0, c.p0 + (size_t)qp.split_col * c.sj0, (uint32_t)c.sj0};
     // 32-bit byte offsets, that of kQuadNoCol among them
-    if (X->sj0 > kQuadMaxStride || X->sj1 > kQuadMaxStride) return false;
-    static const QuadTurn forms[] = {{32, 16, 21.7, 0}, {64, 16, 25.4, 0}, {128, 16, 35.8, 0}, {128, 8, 41.7, 57.5}};
-    quad_columns(forms, 4, c.mat->plan, launch_products, batch, out);
-    out->two = two;
-    out->lds = (size_t)out->nw * (out->columns == 128 ? 16 * 2 : 32) * 64 * sizeof(float);
-    return true;
+    return X->sj0 <= kQuadMaxStride && X->sj1 <= kQuadMaxStride;
 }
 
-const void *quad_kernel(const QuadShape &sh, bool multi) {
+bool quad16_source(const csb_matrix *mat, int64_t ldx) {
+    const QuadPlan &qp = mat->plan.quad;
+    return qp.valid && qp.val_fmt != CSB_VAL_F32 && qp.split_col == 0 && ldx <= kQuadMaxStride && mat->batch_form != kFormTiles;
+}
+
+const void *quad_kernel(const QuadShape &sh, bool two, bool multi) {
 #define CSB_Q(NT, G, TWO, NW) (multi ? (const void *)spmm_quad_multi_kernel<NT, G, TWO, NW> : (const void *)spmm_quad_kernel<NT, G, TWO, NW>)
-#define CSB_QV(NT, G, NW) return sh.two ? CSB_Q(NT, G, true, NW) : CSB_Q(NT, G, false, NW);
+#define CSB_QV(NT, G, NW) return two ? CSB_Q(NT, G, true, NW) : CSB_Q(NT, G, false, NW);
     if (sh.columns == 128) {
         if (sh.nw == 8) { CSB_QV(2, 1, 8) }
         CSB_QV(2, 1, 16)
@@ -453,17 +498,6 @@ const void *quad_kernel(const QuadShape &sh, bool multi) {
     CSB_QV(1, 2, 16)
 #undef CSB_QV
 #undef CSB_Q
-}
-
-// One source of 16-bit right-hand sides, `ldx` elements from one column to the next.
-bool quad16_shape(const csb_matrix *mat, int64_t ldx, int32_t batch, QuadShape *out) {
-    const QuadPlan &qp = mat->plan.quad;
-    if (!qp.valid || qp.val_fmt == CSB_VAL_F32 || qp.split_col > 0 || ldx > kQuadMaxStride) return false;
-    static const QuadTurn forms[] = {{64, 16, 19.1, 0}, {64, 8, 28.0, 29.5}, {128, 16, 22.9, 0}, {128, 8, 31.2, 33.4}};
-    quad_columns(forms, 4, mat->plan, 1, batch, out);
-    out->two = false;
-    out->lds = (size_t)out->nw * 32 * 64 * sizeof(float);
-    return true;
 }
 
 const void *quad16_kernel(const QuadShape &sh, bool half) {

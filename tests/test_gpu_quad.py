@@ -126,3 +126,21 @@ def test_batch_with_matrices_planned_by_the_caller(cell, gates, upload, batch):
     for g, r in zip(got, ref):
         if g is not None:
             assert np.max(np.abs(g.cpu().numpy() - r)) <= 1e-4
+
+
+# Layers whose blocks are of different heights: their matrices' tiles have 16 or 32 rows, and share a launch.
+@pytest.mark.parametrize("blocks", [(16, 64), (32, 16), (64, 24)])
+@pytest.mark.parametrize("batch", [3, 33, 130])
+def test_layers_of_different_block_heights(blocks, batch):
+    inputs, hidden = 40, 100
+    A = [csb_inputs.small_matrix(30 + l, 4 * hidden, (inputs, hidden)[l] + hidden, b, b, rate=4.0).A * 0.1 for l, b in enumerate(blocks)]
+    W = [CsbMatrix(a, b, b) for a, b in zip(A, blocks)]
+    rnn = CsbRnn(csb.CELL_LSTM, inputs, hidden, W)
+    for m in W:
+        assert csb.lib().csb_debug_spmm_force(m._h, 2) == 0
+        m.upload()
+    x = np.random.default_rng(batch).uniform(-1, 1, (6, batch, inputs)).astype(np.float32)
+    got, ref = rnn.forward(torch.from_numpy(x).cuda()), oracle.rnn_forward(csb.CELL_LSTM, A, None, x, inputs, hidden)
+    torch.cuda.synchronize()
+    for g, r in zip(got, ref):
+        assert np.max(np.abs(g.cpu().numpy() - r)) <= 1e-4

@@ -1,6 +1,7 @@
-"""Parity of the batched products at the edges of their batch tiles: the forms that take 128
-right-hand sides per workgroup, against the oracle's float64 product, with the float32 dot-product
-bound of tests/test_gpu_spmm.py."""
+"""Parity of the batched products at the edges of their batch tiles, against the oracle's float64 product, with the
+float32 dot-product bound of tests/test_gpu_spmm.py.  Every test runs in both forms, whichever the estimate favours at its
+size: from the tile-based sections (the general form, and the one that keeps its results in registers, at up to 128
+right-hand sides per workgroup) and from the section of four-row steps."""
 import numpy as np
 import pytest
 
@@ -8,12 +9,25 @@ import csb_inputs
 import oracle
 
 from paper_2005_05758_amd import CsbMatrix
+from paper_2005_05758_amd import binding as csb
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 from test_gpu_spmm import check_spmm            # noqa: E402
 from test_gpu_val16 import FORMATS, packed      # noqa: E402
+
+
+@pytest.fixture(autouse=True, params=["tiles", "quads"])
+def form(request, monkeypatch):
+    upload = CsbMatrix.upload
+
+    def forced(M, *args, **kwargs):
+        assert csb.lib().csb_debug_spmm_force(M._h, {"tiles": 1, "quads": 2}[request.param]) == 0
+        return upload(M, *args, **kwargs)
+
+    monkeypatch.setattr(CsbMatrix, "upload", forced)
+    return request.param
 
 
 # 256 row tiles and more: every compute unit gets a workgroup of 128 columns.  Batches one step
@@ -70,15 +84,15 @@ def test_spmm_any_batch(R, C, br, bc, batch):
                                         (8192, 32, 128), (4100, 16, 64), (4100, 16, 196)])
 @pytest.mark.parametrize("fmt,name", [(None, "f32")] + FORMATS)
 @pytest.mark.parametrize("value", [np.inf, np.nan])
-def test_spmm_infinite_input(value, fmt, name, R, br, batch):
-    """The rows that hold an entry of its column are not finite.  In the general float32 form no others are touched
-    (and an infinity stays one, with its sign); in the others no rows outside of the row tiles that hold the
-    column.  Other right-hand sides are what they are."""
+def test_spmm_infinite_input(value, fmt, name, R, br, batch, form):
+    """The rows that hold an entry of its column are not finite.  In the general float32 form and in four-row steps no
+    others are touched (and an infinity stays one, with its sign); in the others no rows outside of the row tiles that hold
+    the column.  Other right-hand sides are what they are."""
     C = 70
     m = csb_inputs.small_matrix(5, R, C, br, 32, rate=6.0)
     col = int(np.flatnonzero(np.count_nonzero(m.A, axis=0))[-1])
     batch = batch if fmt is None else (batch + 3) // 4 * 4
-    general = fmt is None and (br == 64 or R == 96 or batch % 4 != 0)
+    general = form == "quads" or fmt is None and (br == 64 or R == 96 or batch % 4 != 0)
     X = csb_inputs.make_vectors(batch, C, batch).reshape(C, batch)
     X[col] = value
     X[col, 1::3] = 1.0                                             # (some right-hand sides are finite throughout)
