@@ -1170,10 +1170,11 @@ static int forward_resident_batch(const csb_rnn *r, const float *d_x, const floa
 // half as much again) times 1.3, plus 0.12 us per further XCD an instance spans, twice for the
 // cells with two dependent products per step; the batch runs in rounds of as many sequences
 // as instances fit.  Batched MFMA path: a product and a cell launch for every kMaxJobsPerLaunch layers of a
-// diagonal, 8 to 9 us as the host enqueues them, about 1 more per layer, 1.8 times that for the cells with two
-// products, plus the products at about 25 TFLOP/s.  us per step, resident / batched: LSTM 153 -> 512 (10x) at batch 32
-// 5.9 / 8.9, 64 11.8 / 9.0; GRU 256 -> 1024 (16x) 16 6.7 / 9.2, 32 13.3 / 9.6; two LSTM layers of 1024 (25x) 8 8.0 / 12.9, 16
-// 16.0 / 11.7; LSTM 512 -> 1024 (12x) 8 6.9 / 9.9, 16 13.9 / 10.2; LSTMP 153 -> 512 -> 256 32 11.6 / 16.7, 64 23.0 / 16.3.
+// diagonal, 6 us as the host enqueues them, 0.3 more per layer, 1.55 times that for LSTMP and twice for the reset-before GRU (two
+// products a step), 4.5 per million entries (a product's shortest time), and the products at 55 TFLOP/s.  us per step,
+// resident / batched: LSTM 153 -> 512 (10x) at batch 32 5.3 / 7.2, 64 10.5 / 7.6; GRU 256 -> 1024 (16x) 16 6.1 / 7.4, 24 9.1 / 7.6;
+// two LSTM layers of 1024 (25x) 8 7.1 / 9.3, 16 14.0 / 9.4; LSTM 512 -> 1024 (12x) 8 6.3 / 8.4, 16 12.6 / 8.4; LSTMP 153 -> 512
+// -> 256 24 7.5 / 10.3, 48 15.1 / 10.4; reset-before GRU 153 -> 512 (10x) 32 11.6 / 13.3, 64 22.9 / 13.8.
 static double resident_batch_us(const csb_rnn *r, int32_t batch) {
     const bool two = r->cell == CSB_CELL_LSTMP || r->cell == CSB_CELL_GRU_RB;
     const int R = resident_instances(r, batch);
@@ -1185,12 +1186,13 @@ static double resident_batch_us(const csb_rnn *r, int32_t batch) {
 static double batched_us(const csb_rnn *r, int32_t batch) {
     const bool two = r->cell == CSB_CELL_LSTMP || r->cell == CSB_CELL_GRU_RB;
     const int groups = (r->n_layers + kMaxJobsPerLaunch - 1) / kMaxJobsPerLaunch;
-    return (7.5 * groups + r->n_layers) * (two ? 1.8 : 1.0) + 2.0 * (double)r->plan.total_nnz * batch / 25e6;
+    return (6.0 * groups + 0.3 * r->n_layers) * (r->cell == CSB_CELL_LSTMP ? 1.55 : two ? 2.0 : 1.0) +
+           (double)r->plan.total_nnz * (4.5e-6 + 2.0 * batch / 55e6);
 }
 static bool batch_prefers_resident(const csb_rnn *r, int32_t batch) {
     if (r->knob_batch_path == 1) return true;
     if (r->knob_batch_path == 2) return false;
-    return resident_batch_us(r, batch) * 1.1 < batched_us(r, batch);
+    return resident_batch_us(r, batch) < batched_us(r, batch);
 }
 
 }  // namespace csb

@@ -3,7 +3,7 @@ sizes where both were measured (us per step on MI355X): it takes the faster one.
 import pytest
 
 import csb_inputs
-from paper_2005_05758_amd import CELL_GRU, CELL_LSTM, CELL_LSTMP, CsbMatrix, CsbRnn, load_library
+from paper_2005_05758_amd import CELL_GRU, CELL_LIGRU, CELL_LSTM, CELL_LSTMP, CsbMatrix, CsbRnn, load_library
 
 
 def handle(cell, L, I, H, block, rate, law):
@@ -17,15 +17,17 @@ def handle(cell, L, I, H, block, rate, law):
 
 # model, then batch: (us on the resident kernel, us on the batched products)
 @pytest.mark.parametrize("cell,L,I,H,block,rate,law,measured", [
-    (CELL_LSTM, 1, 153, 512, 32, 10.0, "binomial", {8: (1.5, 8.3), 32: (5.9, 8.9), 64: (11.8, 9.0)}),
-    (CELL_GRU, 1, 256, 1024, 32, 16.0, "beta", {8: (3.3, 9.0), 16: (6.7, 9.2), 32: (13.3, 9.6), 64: (26.6, 10.9)}),
-    (CELL_LSTM, 2, 1024, 1024, 64, 25.0, "binomial", {4: (4.0, 11.4), 8: (8.0, 12.9), 16: (16.0, 11.7), 64: (64.8, 14.4)}),
-    (CELL_LSTM, 1, 64, 128, 16, 8.0, "binomial", {2: (1.2, 8.2), 64: (1.2, 8.3)}),
-    (CELL_LSTM, 2, 153, 256, 16, 8.0, "binomial", {16: (5.9, 8.7), 64: (23.4, 9.8)}),
-    (CELL_LSTMP, 1, 153, 512, 32, 13.0, "binomial", {16: (5.8, 16.2), 32: (11.6, 16.7), 64: (23.0, 16.3)}),
-    (CELL_LSTM, 1, 512, 1024, 32, 12.0, "binomial", {4: (3.5, 10.8), 8: (6.9, 9.9), 16: (13.9, 10.2), 64: (55.4, 12.3)}),
-    (CELL_LSTM, 4, 64, 256, 16, 8.0, "binomial", {4: (1.5, 8.4), 64: (24.1, 10.9)}),
-    (CELL_LSTM, 6, 64, 256, 16, 8.0, "binomial", {4: (3.2, 15.9), 64: (51.0, 19.4)})])
+    (CELL_LSTM, 1, 153, 512, 32, 10.0, "binomial", {8: (1.4, 7.1), 32: (5.3, 7.2), 64: (10.5, 7.6)}),
+    (CELL_GRU, 1, 256, 1024, 32, 16.0, "beta", {8: (3.1, 7.5), 16: (6.1, 7.4), 24: (9.1, 7.6), 32: (12.1, 7.8), 64: (24.1, 8.4)}),
+    (CELL_LSTM, 2, 1024, 1024, 64, 25.0, "binomial", {4: (3.6, 9.3), 8: (7.1, 9.3), 16: (14.0, 9.4), 64: (56.1, 10.8)}),
+    (CELL_LSTM, 1, 64, 128, 16, 8.0, "binomial", {2: (0.9, 6.1), 64: (0.9, 6.3)}),
+    (CELL_LSTM, 2, 153, 256, 16, 8.0, "binomial", {16: (5.3, 7.6), 32: (10.5, 7.8), 64: (21.1, 8.0)}),
+    (CELL_LSTMP, 1, 153, 512, 32, 13.0, "binomial", {16: (5.0, 10.1), 24: (7.5, 10.3), 48: (15.1, 10.4), 64: (20.3, 10.5)}),
+    (CELL_LSTM, 1, 512, 1024, 32, 12.0, "binomial", {4: (3.2, 8.4), 8: (6.3, 8.4), 16: (12.6, 8.4), 64: (50.8, 9.5)}),
+    (CELL_LSTM, 4, 64, 256, 16, 8.0, "binomial", {4: (2.9, 7.9), 8: (5.7, 8.0), 16: (11.2, 7.9), 64: (45.3, 8.9)}),
+    (CELL_LSTM, 6, 64, 256, 16, 8.0, "binomial", {4: (3.1, 15.1), 16: (12.2, 15.0), 64: (49.6, 16.3)}),
+    (CELL_GRU, 2, 512, 512, 32, 20.0, "binomial", {8: (2.7, 7.6), 16: (5.4, 7.5), 32: (10.7, 7.9)}),
+    (CELL_LIGRU, 2, 39, 512, 32, 7.1, "binomial", {8: (3.1, 8.3), 16: (6.3, 8.2), 33: (14.8, 8.5)})])
 def test_the_faster_path(cell, L, I, H, block, rate, law, measured):
     rnn = handle(cell, L, I, H, block, rate, law)
     got = {b: load_library().csb_debug_rnn_prefers_resident(rnn._h, b) for b in measured}
