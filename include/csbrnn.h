@@ -187,7 +187,7 @@ int csb_plan_ex(csb_matrix *m, int32_t n_chunks, int32_t mode, csb_plan_stats *s
  * so a launch requests all of its bytes at once from addresses that depend only on the
  * workgroup and wavefront numbers.  Row sums are formed in a fixed order (bitwise
  * reproducible).  csb_spmv and the per-step launches of csb_rnn_forward's streaming path read
- * this section when it exists; csb_spmm keeps reading the tile-based sections.
+ * this section when it exists; csb_spmm reads sections of its own, or the tile-based ones.
  * csb_plan_rows plans like csb_plan with the parameters of this layout spelled out:
  * n_workgroups (0 = default: one per 256 kernel-matrix rows, at most 256, at least
  * rows / 256) and min_rounds (0 or 1 = as few rounds as the LDS allows; more rounds make
