@@ -302,9 +302,8 @@ public:
     const uint8_t *data() const { return p_; }
     size_t size() const { return n_; }
     void resize(size_t n) {                      // new bytes are zero
-        void *p = std::realloc(p_, n ? n : 1);
-        if (!p) throw std::bad_alloc();
-        p_ = (uint8_t *)p;
+        if (void *p = std::realloc(p_, n ? n : 1)) p_ = (uint8_t *)p;
+        else if (n > n_) throw std::bad_alloc();
         if (n > n_) std::memset(p_ + n_, 0, n - n_);
         n_ = n;
     }

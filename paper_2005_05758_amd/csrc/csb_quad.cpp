@@ -209,7 +209,7 @@ static void build_section(csb_matrix *m, uint32_t tile_rows, QuadPlan *out) {
 // The section, or the two, that the batched products of a matrix read; none where it does not fit (they then read the
 // tile-based sections).  Tiles of 16 rows alone where the blocks are no taller and tiles of 32 would not give each of 256
 // workgroups one: a wavefront then has half the passes.  Taller blocks are cut by tiles of 16 rows, so that all tiles together
-// have about twice the passes, of half the rows: better as long as they still find idle CUs (quad_columns), which they never
+// have about twice the passes, of half the rows: better as long as they still find idle CUs (quad_us), which they never
 // do beyond 256 tiles.
 // None for the 16-bit values of a recurrent handle's gate matrix: its steps multiply float32 right-hand sides, and the
 // products of 16-bit ones take passes from one source alone (LSTM 1024 -> 1024 at 12x in binary16: 15.8 MB of image, without
