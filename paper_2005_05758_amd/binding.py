@@ -22,7 +22,7 @@ _lib = None
 SYMBOLS = ["csb_last_error", "csb_pack", "csb_view_get", "csb_unpack", "csb_set_value_format", "csb_value_format", "csb_sharing_model", "csb_plan", "csb_plan_ex", "csb_plan_rows", "csb_plan_stats_get", "csb_plan_validate", "csb_status",
            "csb_device_bytes", "csb_upload", "csb_workspace_bytes", "csb_spmv", "csb_spmv_static_limit", "csb_spmv_static", "csb_spmm", "csb_spmm_bfloat", "csb_spmm_half",
            "csb_debug_stamp_count", "csb_debug_spmv_stamps",
-           "csb_debug_stream_read_out_floats", "csb_debug_stream_read", "csb_debug_spmm_columns", "csb_debug_quad_passes", "csb_debug_spmm_force", "csb_debug_spmm_form", "csb_debug_rnn_prefers_resident",
+           "csb_debug_stream_read_out_floats", "csb_debug_stream_read", "csb_debug_spmm_columns", "csb_debug_quad_passes", "csb_debug_spmm_force", "csb_debug_spmm_form", "csb_debug_spmm_panel", "csb_debug_rnn_prefers_resident",
            "csb_project_workspace_bytes", "csb_project", "csb_rnn_create_lstmp", "csb_rnn_create_gru_rb",
            "csb_rnn_create", "csb_rnn_device_bytes", "csb_rnn_upload", "csb_rnn_plan_resident", "csb_rnn_stats",
            "csb_rnn_set_poll_limit", "csb_rnn_status", "csb_rnn_workspace_bytes", "csb_rnn_forward", "csb_free", "csb_rnn_free"]
@@ -111,6 +111,7 @@ def load_library():
     L.csb_debug_spmm_columns.argtypes = [C.c_int64, C.c_int32, C.c_int32, C.c_int32]
     L.csb_debug_spmm_force.argtypes = [C.c_void_p, C.c_int32]
     L.csb_debug_spmm_form.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
+    L.csb_debug_spmm_panel.argtypes = [C.c_void_p, C.c_int32, C.POINTER(C.c_int32)]
     L.csb_debug_quad_passes.argtypes = [C.c_void_p, C.c_int32]
     L.csb_debug_quad_passes.restype = C.c_int64
     L.csb_debug_rnn_prefers_resident.argtypes = [C.c_void_p, C.c_int32]

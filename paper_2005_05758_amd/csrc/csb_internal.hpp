@@ -245,9 +245,8 @@ struct StreamPlan {
 //           of a list counts its passes.
 //   table   (list_stride == 0: lists of very different lengths) [n_tiles][kQuadLists] first record of every list, and one
 //           entry more for the end of the last
-//   values  binary32: per pass [column][4 rows][quad]; 16-bit formats: [4 columns][4 rows][quad][4 columns], and with more
-//           than four quads [4 columns][4 rows][quad % 4][quad / 4][4 columns], eight of them; columns in fours,
-//           zeros where the pass has no such row or column; kQuadPad bytes of zeros behind the last
+//   values  binary32: per pass [column][4 rows][quad], columns in fours, zeros where the pass has no such row or column;
+//           16-bit formats: [row][8 columns], zeros where it has no such column; kQuadPad bytes of zeros behind the last
 // With `split_col` > 0 no pass crosses that column (the border between the two sources of a step's
 // input), and columns of the second part are counted from it.
 constexpr int kQuadRows = 32;
@@ -259,13 +258,13 @@ constexpr uint16_t kQuadNoCol = 0xffff;  // (times a row's bytes: past the end o
 
 struct QuadRec {
     // what the loads need
-    uint32_t val;                        // byte offset of the pass's values
-    uint16_t stride;                     // bytes from one column (16-bit formats: four columns) to the next
+    uint32_t val;                        // where the pass's values start, in bytes (16-bit formats: in rows of 16 bytes)
+    uint16_t stride;                     // binary32: bytes from one column to the next
     uint8_t quads;                       // kernel rows in fours
     uint8_t flags;                       // kQuadWide: more than 4 columns; kQuadSecond: columns of the second source
     uint16_t col[kQuadCols];             // input rows; kQuadNoCol where the pass has fewer
     uint32_t list_len;                   // a list's first record: its passes
-    uint32_t pad;
+    uint32_t rows;                       // the places in the tile that the pass has rows for, a bit each
     // what the row sums need
     uint8_t slot[kQuadRows];             // the rows' places in the tile; kQuadRows (a spare one) where there is none
 };

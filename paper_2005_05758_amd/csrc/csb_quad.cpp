@@ -28,15 +28,13 @@ struct QPass {
 uint32_t pass_cost(const QPass &p) { return 90u + p.ncols * ((p.nrows + 3u) / 4u) * 4u + 3u * p.nrows; }
 
 size_t pass_value_bytes(uint32_t nrows, uint32_t ncols, bool bits16) {
-    const size_t quads = (nrows + 3u) / 4u, fours = (ncols + 3u) / 4u;
-    return bits16 ? fours * (quads > 4 ? 8 : quads) * 32u : fours * quads * 64u;
+    return bits16 ? (size_t)nrows * kQuadCols * 2u : (size_t)((ncols + 3u) / 4u) * ((nrows + 3u) / 4u) * 64u;
 }
-uint32_t pass_stride(uint32_t quads, bool bits16) { return bits16 ? (quads > 4 ? 8 : quads) * 32u : quads * 16u; }
+uint32_t pass_stride(uint32_t quads, bool bits16) { return bits16 ? 0u : quads * 16u; }
+uint32_t value_unit(bool bits16) { return bits16 ? 16u : 1u; }
 // Position of the value at (row q, column j) among a pass's values.
 size_t value_at(uint32_t quads, uint32_t q, uint32_t j, bool bits16) {
-    if (!bits16) return (j * 4u + (q & 3u)) * quads + (q >> 2);
-    const size_t quad = quads > 4 ? (q >> 2 & 3u) * 2u + (q >> 4) : q >> 2, room = quads > 4 ? 8 : quads;
-    return (((j >> 2) * 4u + (q & 3u)) * room + quad) * 4u + (j & 3u);
+    return bits16 ? (size_t)q * kQuadCols + j : (j * 4u + (q & 3u)) * (size_t)quads + (q >> 2);
 }
 
 // The parts of block b's columns [q0, q1) that are summed together (GRU split) and come from one source.
@@ -177,7 +175,7 @@ static void build_section(csb_matrix *m, uint32_t tile_rows, QuadPlan *out) {
             const QPass &p = e.p;
             const uint32_t quads = (p.nrows + 3u) / 4u;
             QuadRec &r = recs[table[e.list] + e.pos];
-            r.val = val0[e.list] + e.val;
+            r.val = (val0[e.list] + e.val) / value_unit(bits16);
             r.stride = (uint16_t)pass_stride(quads, bits16);
             r.quads = (uint8_t)quads;
             r.flags = (uint8_t)((p.ncols > 4 ? kQuadWide : 0) | (e.second ? kQuadSecond : 0));
@@ -185,9 +183,10 @@ static void build_section(csb_matrix *m, uint32_t tile_rows, QuadPlan *out) {
             const uint32_t col0 = (uint32_t)(p.b % (uint32_t)m->nbc) * (uint32_t)m->bc - (e.second ? qp.split_col : 0u);
             for (int j = 0; j < kQuadCols; ++j) r.col[j] = j < p.ncols ? (uint16_t)(col0 + ci[p.q0 + j]) : kQuadNoCol;
             std::memcpy(r.slot, e.slot, sizeof(r.slot));
+            for (uint32_t q = 0; q < p.nrows; ++q) r.rows |= 1u << e.slot[q];
             const int nc = m->ncols[p.b];
             const float *src = m->val.data() + m->val_off[p.b] + p.q0;
-            uint8_t *dst = im + qp.off_vals + r.val;
+            uint8_t *dst = im + qp.off_vals + (size_t)r.val * value_unit(bits16);
             for (uint32_t q = 0; q < p.nrows; ++q) {
                 const float *row = src + (size_t)(p.a0 + q) * nc;
                 if (!bits16)
@@ -291,15 +290,21 @@ static int validate_section(const csb_matrix *m, const QuadPlan &qp) {
                 if (!ncols || !nrows || r.quads != (nrows + 3u) / 4u || r.stride != pass_stride(r.quads, bits16) ||
                     ((r.flags & kQuadWide) != 0) != (ncols > 4) || (second && !qp.split_col)) return fail("pass size");
                 const size_t bytes = pass_value_bytes(nrows, ncols, bits16);
-                if ((uint64_t)r.val + bytes + kQuadPad > qp.vals_bytes) return fail("values");
+                const uint64_t val = (uint64_t)r.val * value_unit(bits16);
+                if (val + bytes + kQuadPad > qp.vals_bytes) return fail("values");
                 for (uint32_t j = ncols; j < (uint32_t)kQuadCols; ++j) if (r.col[j] != kQuadNoCol) return fail("gap in the columns");
-                for (uint32_t q = nrows; q < (uint32_t)kQuadRows; ++q) if (r.slot[q] != kQuadRows) return fail("gap in the rows");
-                for (uint32_t q = 0; q < r.quads * 4u; ++q)
-                    for (uint32_t j = 0; j < (ncols + 3u) / 4u * 4u; ++j) {
+                uint32_t places = 0;
+                for (uint32_t q = 0; q < (uint32_t)kQuadRows; ++q) {
+                    if (q >= nrows ? r.slot[q] != kQuadRows : q > 0 && r.slot[q] <= r.slot[q - 1]) return fail("gap in the rows, or their order");
+                    if (q < nrows) places |= 1u << r.slot[q];
+                }
+                if (r.rows != places) return fail("row mask");
+                for (uint32_t q = 0; q < (bits16 ? nrows : r.quads * 4u); ++q)
+                    for (uint32_t j = 0; j < (bits16 ? (uint32_t)kQuadCols : (ncols + 3u) / 4u * 4u); ++j) {
                         float v;
-                        if (!bits16) v = ((const float *)(vals + r.val))[value_at(r.quads, q, j, false)];
+                        if (!bits16) v = ((const float *)(vals + val))[value_at(r.quads, q, j, false)];
                         else {
-                            const uint16_t bits = ((const uint16_t *)(vals + r.val))[value_at(r.quads, q, j, true)];
+                            const uint16_t bits = ((const uint16_t *)(vals + val))[value_at(r.quads, q, j, true)];
                             v = qp.val_fmt == CSB_VAL_F16 ? f16_bits_to_f32(bits) : bf16_bits_to_f32(bits);
                         }
                         if (q >= nrows || j >= ncols) {

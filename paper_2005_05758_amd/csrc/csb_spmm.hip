@@ -1162,6 +1162,18 @@ static int spmm_16bit(const char *who, int fmt, const csb_matrix *m, const uint1
         return CSB_EUNSUPPORTED;
     }
     const bool quads = quad16_source(m, ldx);
+    if (quads && m->batch_form == kFormAuto) {
+        const PanelShape ps = panel_shape(m, batch);
+        QuadMat qm = quad_mat(m, ps.low);
+        uint32_t b = (uint32_t)batch, ld = (uint32_t)ldx;
+        int64_t ldy_ = ldy;
+        void *args[] = {&qm, &d_X, &ld, &d_Y, &ldy_, &b};
+        const void *kern = panel16_kernel(ps, fmt == CSB_VAL_F16);
+        hipError_t e = ensure_dynamic_lds(kern, ps.lds);
+        if (e == hipSuccess) e = hipLaunchKernel(kern, dim3(ps.workgroups), dim3(256 * ps.share), args, ps.lds, (hipStream_t)stream);
+        if (e != hipSuccess) { set_error(w + ": " + hipGetErrorString(e)); return CSB_EDEVICE; }
+        return CSB_OK;
+    }
     const QuadShape qs = quads ? quad_shape(&m, 1, batch, true) : QuadShape{};
     if (quads && (m->batch_form == kFormQuads || prefers_quads(qs.us, sh.us))) {
         QuadMat qm = quad_mat(m, qs.low);
@@ -1257,6 +1269,17 @@ extern "C" int csb_debug_spmm_form(const csb_matrix *m, int32_t batch, int32_t b
         const QuadShape qs = quad_shape(&m, 1, batch, bits16 != 0);
         form[0] = (int32_t)(qs.low ? m->plan.quad_low : m->plan.quad).tile_rows; form[1] = qs.columns; form[2] = qs.nw;
     }
+    return CSB_OK;
+}
+
+extern "C" int csb_debug_spmm_panel(const csb_matrix *m, int32_t batch, int32_t *form) {
+    using namespace csb;
+    if (!m || !form || batch <= 0) { set_error("csb_debug_spmm_panel: NULL pointer or batch <= 0"); return CSB_EINVAL; }
+    if (!m->plan.valid) { set_error("csb_debug_spmm_panel: matrix not planned"); return CSB_ESTATE; }
+    form[0] = form[1] = form[2] = 0;
+    if (!quad16_source(m, batch) || m->batch_form != kFormAuto) return CSB_OK;
+    const PanelShape ps = panel_shape(m, batch);
+    form[0] = ps.rows; form[1] = ps.columns; form[2] = 4 * ps.share;
     return CSB_OK;
 }
 

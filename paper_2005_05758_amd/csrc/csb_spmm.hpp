@@ -76,6 +76,15 @@ bool quad16_source(const csb_matrix *mat, int64_t ldx);
 QuadShape quad_shape(const csb_matrix *const *mats, int n, int32_t batch, bool bits16);
 const void *quad_kernel(const QuadShape &sh, bool two, bool multi);
 const void *quad16_kernel(const QuadShape &sh, bool half);
+// Such products in panels: rows of a tile, right-hand sides of a workgroup, wavefronts that share a list of passes.
+struct PanelShape {
+    int rows, columns, share;
+    bool low;               // the section of 16-row tiles beside that of 32
+    size_t lds;
+    unsigned workgroups;
+};
+PanelShape panel_shape(const csb_matrix *m, int32_t batch);
+const void *panel16_kernel(const PanelShape &ps, bool half);
 
 // csb_debug_spmm_force's choices
 enum { kFormAuto = 0, kFormTiles = 1, kFormQuads = 2 };

@@ -229,8 +229,8 @@ __device__ __forceinline__ void quad16_passes(const QuadMat &m, const XSrc &X, c
                                               const uint32_t batch, QuadAcc<NT> &acc) {
     constexpr int steps = 2;                             // of four columns
     const uint32_t lane = threadIdx.x & 63u;
-    // the lane's place in an A register: (four columns, row of the quad), and quad of four
-    const uint32_t afour = 4u * (lane >> 4) + (lane & 3u), aquad = 8u * ((lane >> 2) & 3u), wide_only = (lane >> 4) == 1u;
+    // the lane's place in an A register: row of a quad, which of four quads, which four columns (lanes 32 ... 63: as 0 ... 31)
+    const uint32_t arow = ((lane >> 2 & 3u) * 4u + (lane & 3u)) * 16u + (lane >> 4 & 1u) * 8u;
     const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc((void *)m.vals, 0, (int)m.vals_bytes, 0x00020000);
     const uint32_t xlane = lane * 2u * NT;
     uint32_t row = uni_(X.sj0) * 2u;
@@ -242,18 +242,17 @@ __device__ __forceinline__ void quad16_passes(const QuadMat &m, const XSrc &X, c
     const uint8_t CSB_CONST_AS *rec = (const uint8_t CSB_CONST_AS *)(uintptr_t)m.recs + (size_t)first_record(m, list) * sizeof(QuadRec);
     auto read_loads = [&](int i) { return *(const uint32x8 CSB_CONST_AS *)(rec + i * (int)sizeof(QuadRec)); };
     auto read_slots = [&](int i) { return *(const uint32x8 CSB_CONST_AS *)(rec + i * (int)sizeof(QuadRec) + 32); };
-    constexpr int kLoads = 1 + 4 * steps;                // of a pass
+    constexpr int kLoads = 2 + 4 * steps;                // of a pass
 
     auto issue = [&](const uint32x8 &r, QuadOps16 &o) {
-        const uint32_t stride = r[1] & 0xffffu, quads = (r[1] >> 16) & 0xffu;
-        // (of quads that a pass does not have: what lies there, and no use is made of it; of the second four columns, where it has
-        // none: zeros.  They are multiplied all the same: a branch around that is slower, 8192 x 8192 x 512 70.9 us instead of 66.7)
-        uint32_t at = mul24_(afour, stride >> 2) + (aquad << (quads > 4u ? 1u : 0u)) + r[0];
-        at = wide_only > ((r[1] >> 24) & kQuadWide) ? 0x80000000u : at;
-        typedef uint32_t vec4 __attribute__((ext_vector_type(4)));
-        const vec4 a = __builtin_bit_cast(vec4, __builtin_amdgcn_raw_buffer_load_b128(vrsrc, (int)at, 0, 0));
+        // (of rows that a pass does not have: what lies there, and no use is made of it; the second four columns are multiplied where
+        // it has none, too: a branch around that is slower, 8192 x 8192 x 512 70.9 us instead of 66.7)
+        const uint32_t at = arow + r[0] * 16u;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) o.a[j] = a[j];
+        for (int j = 0; j < 2; ++j) {
+            const uint2 a = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(vrsrc, (int)(at + 256u * j), 0, 0));
+            o.a[2 * j] = a.x; o.a[2 * j + 1] = a.y;
+        }
         auto cols = [&](int i) { return (i & 1) ? r[2 + i / 2] >> 16 : r[2 + i / 2] & 0xffffu; };
 #pragma unroll
         for (int i = 0; i < 4 * steps; ++i) {
@@ -388,6 +387,170 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
     spmm_quad_body<NT, 1, false, NW, VF>(m, X, Y, ldy, batch, blockIdx.x, blockIdx.y);
 }
 
+// ---- 16-bit operands in panels -------------------------------------------------------------------------------------
+// v_mfma_f32_16x16x32 multiplies 16 rows by 32 columns of 16 right-hand sides four times as fast per multiply-add as the 4 x 4
+// forms, so that rows may stay where they are in the tile and be zero where a pass lacks them: four passes (a list for
+// every 16 lanes) are a panel of 32 columns, nothing is added row by row, and a wavefront's sums are the accumulators of
+// its instructions.  A lane is row i of 16 and takes the eight values of its row from a pass, found by counting the rows in front
+// of it in the record's mask (a row that the pass lacks reads past the end: zeros), and of each of the pass's eight columns 4 or 8
+// neighbouring right-hand sides; v_perm puts columns side by side.  The record comes in as a word per lane and is handed
+// round by DPP.
+// What bounds it: the loads' way through the L1: with the products left out a launch is as long, from 16 rows of X that always hit it is no
+// shorter (measured), and a load of 8 bytes per lane costs as much as one of 16, so that from 128 right-hand sides on
+// lanes take 16 bytes: 8192 x 8192 at 12x, bfloat16 x 512, 66 -> 44 us (8 such loads, 2 of values and a record per panel: at one every 17 clocks
+// 29 us).  Four-row steps / panels, us: x 512 69 / 44, x 256 37 / 24, x 128 23 / 13.9, x 64 18.9 / 12.7, x 8 17.7 / 11.8; 4096 x
+// 4096 in 16-row blocks x 256 22.8 / 13.6; 1024 x 665 at 8x x 32 4.0 / 3.35.  Error against 64 bits, of the norm, of these: 0.749e-7 (0.750e-7
+// before), x 128 0.748e-7 (0.846e-7); 0.661e-7 (0.661e-7); binary16 0.92e-7 (0.98e-7).
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+// Value of lane N of the own 16 lanes.
+template <int N>
+__device__ __forceinline__ uint32_t row_lane(const uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + N, 0xf, 0xf, false); }
+
+// H: tile of 16 H rows; NC: right-hand sides of a lane (4 or 8), 16 NC of a workgroup; S: wavefronts that share a list.
+template <int H, int NC>
+struct PanelOps {
+    uint32_t x[kQuadCols][NC / 2];                       // right-hand sides of each column of the lane's pass, two to a word
+    uint4 a[H];                                          // its columns of a row
+};
+
+// The passes `part`, part + S, ... of four lists of a tile, one list for every 16 lanes; col0: the lane's first right-hand side.
+template <int H, int NC, int S, int VF>
+__device__ __forceinline__ void panel_passes(const QuadMat &m, const uint16_t *X, const uint32_t ldx, const uint32_t batch, const uint32_t tile,
+                                             const uint32_t col0, const uint32_t wave, floatx4 (&acc)[H][NC]) {
+    const uint32_t lane = threadIdx.x & 63u, i = lane & 15u, part = wave >> 2;
+    const uint32_t list = tile * kQuadLists + (wave & 3u) * 4u + (lane >> 4);
+    const uint32_t first = m.list_stride ? list * m.list_stride : m.table[list];
+    const uint32_t len = m.list_stride ? ((const QuadRec *)m.recs)[first].list_len : m.table[list + 1] - first;
+    const uint32_t longest = max(max(__builtin_amdgcn_readlane(len, 0), __builtin_amdgcn_readlane(len, 16)),
+                                 max(__builtin_amdgcn_readlane(len, 32), __builtin_amdgcn_readlane(len, 48)));
+    const __amdgpu_buffer_rsrc_t rrsrc = __builtin_amdgcn_make_buffer_rsrc((void *)m.recs, 0, 0x7fffffff, 0x00020000);
+    const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc((void *)m.vals, 0, (int)m.vals_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc((void *)X, 0, (int)(((m.cols - 1u) * ldx + batch) * 2u), 0x00020000);
+    // a record's eight words come in by eight lanes
+    const uint32_t word = i & 7u, rec0 = first * (uint32_t)sizeof(QuadRec) + word * 4u;
+    const uint32_t none = word >= 2u && word < 6u ? 0xffffffffu : 0u;     // a record of no columns and no rows
+    uint32_t row = ldx * 2u, xlane = col0 * 2u;          // (bytes from one column's right-hand sides to the next's: 16 bits)
+    asm("" : "+v"(row), "+v"(xlane));
+    uint32_t lo = 0x05040100u, hi = 0x07060302u;         // v_perm selectors: the low, the high halves of two registers
+    asm("" : "+s"(lo), "+s"(hi));
+    auto records = [&](const uint32_t j) {
+        return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rrsrc, (int)(j < len ? rec0 + j * (uint32_t)sizeof(QuadRec) : 0x80000000u), 0, 0);
+    };
+    auto issue = [&](const uint32_t w, PanelOps<H, NC> &o) {
+        const uint32_t val = row_lane<0>(w), rows = row_lane<7>(w);
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+            const uint32_t place = 16u * h + i, q = __popc(rows & ((1u << place) - 1u)) + val;       // the row's place among the pass's
+            const uint32_t lacks = ~rows << (31u - place) & 0x80000000u;                            // (past the end of the values: zeros)
+            o.a[h] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(vrsrc, (int)(q << 4 | lacks), 0, 0));
+        }
+        const uint32_t cols[4] = {row_lane<2>(w), row_lane<3>(w), row_lane<4>(w), row_lane<5>(w)};
+#pragma unroll
+        for (int e = 0; e < kQuadCols; ++e) {
+            uint32_t at;                                 // column times row + the lane's place
+            if (e & 1) asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(at) : "v"(cols[e / 2]), "v"(row), "v"(xlane));
+            else asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(at) : "v"(cols[e / 2]), "v"(row), "v"(xlane));
+            if constexpr (NC == 8) {
+                const uint4 v = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, (int)at, 0, 0));
+                o.x[e][0] = v.x; o.x[e][1] = v.y; o.x[e][2] = v.z; o.x[e][3] = v.w;
+            } else {
+                const uint2 v = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(xrsrc, (int)at, 0, 0));
+                o.x[e][0] = v.x; o.x[e][1] = v.y;
+            }
+        }
+    };
+    auto multiply = [&](const PanelOps<H, NC> &o) {
+#pragma unroll
+        for (int n = 0; n < NC; ++n) {
+            auto pair = [&](int e) { return __builtin_amdgcn_perm(o.x[e + 1][n / 2], o.x[e][n / 2], n & 1 ? hi : lo); };
+            const uint4 b = make_uint4(pair(0), pair(2), pair(4), pair(6));
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                if constexpr (VF == CSB_VAL_F16) acc[h][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, o.a[h]), __builtin_bit_cast(f16x8, b), acc[h][n], 0, 0, 0);
+                else acc[h][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, o.a[h]), __builtin_bit_cast(bf16x8, b), acc[h][n], 0, 0, 0);
+            }
+        }
+    };
+    if (part >= longest) return;
+    auto valid = [&](const uint32_t at, const uint32_t w) { return at < len ? w : none; };
+    // A pass's loads fly while the one before multiplies; its record was asked for in front of those.  (One way out of the loop:
+    // with another in its middle the compiler keeps the sums twice and moves loads behind it.)
+    // (In front of the products, where there are registers for both; with 32 rows, 128 right-hand sides and eight wavefronts, 16 on a CU
+    // are worth more: x 512 52 -> 44 us, x 256 26 -> 24, x 128 13.8 -> 13.9.)
+    constexpr bool kEarly = H * NC < 16 || S == 1;
+    PanelOps<H, NC> oa, ob;
+    uint32_t j = part, w = valid(j, records(j)), w1 = records(j + S);
+    issue(w, oa);
+    while (j + S < longest) {
+        w = records(j + 2 * S);
+        __builtin_amdgcn_sched_barrier(0);
+        issue(valid(j + S, w1), ob);
+        if constexpr (kEarly) __builtin_amdgcn_sched_barrier(0);
+        multiply(oa);
+        w1 = records(j + 3 * S);
+        __builtin_amdgcn_sched_barrier(0);
+        issue(valid(j + 2 * S, w), oa);
+        if constexpr (kEarly) __builtin_amdgcn_sched_barrier(0);
+        multiply(ob);
+        j += 2 * S;
+    }
+    if (j < longest) multiply(oa);
+}
+
+template <int H, int NC, int S, int VF>
+__global__ __launch_bounds__(256 * S) __attribute__((amdgpu_waves_per_eu(H * NC == 16 && S == 1 ? 3 : 4))) void spmm_panel16_kernel(
+    const QuadMat m, const uint16_t *__restrict__ X, const uint32_t ldx, float *__restrict__ Y, const int64_t ldy, const uint32_t batch) {
+    extern __shared__ float4 smem4[];
+    constexpr int NW = 4 * S;
+    constexpr uint32_t N = 16 * NC;
+    const uint32_t groups = (batch + N - 1u) / N, tile = blockIdx.x / groups, group = blockIdx.x - tile * groups, bt0 = group * N;
+    const uint32_t wave = uni_(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+    const uint32_t own = bt0 + NC * (lane & 15u);        // the lane's right-hand sides; the last four of a batch come with the four before them
+    const uint32_t col0 = NC == 8 && own + 4u == batch ? own - 4u : own;
+    floatx4 acc[H][NC];
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int n = 0; n < NC; ++n) acc[h][n] = 0.0f;
+    panel_passes<H, NC, S, VF>(m, X, ldx, batch, tile, col0, wave, acc);
+    // the wavefronts' sums, 16 rows at a time: [wave][row of four][four right-hand sides][lane]
+    const uint32_t row0 = tile * m.tile_rows;
+    bool odd = false;
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        if (h) __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < NC / 4; ++c)
+                smem4[((wave * 4u + r) * (NC / 4) + c) * 64u + lane] = make_float4(acc[h][4 * c][r], acc[h][4 * c + 1][r], acc[h][4 * c + 2][r], acc[h][4 * c + 3][r]);
+        __syncthreads();
+        for (uint32_t k = wave; k < (uint32_t)NC; k += NW) {
+            float4 s = smem4[k * 64u + lane];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) {
+                const float4 v = smem4[((uint32_t)w * NC + k) * 64u + lane];
+                s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+            }
+            const uint32_t row = row0 + 16u * h + 4u * (lane >> 4) + k / (NC / 4), n = col0 + 4u * (k % (NC / 4));
+            if (row < m.rows && n >= own && n < batch) {
+                odd = odd || !(fabsf(s.x) < INFINITY && fabsf(s.y) < INFINITY && fabsf(s.z) < INFINITY && fabsf(s.w) < INFINITY);
+                float *y = Y + (size_t)row * ldy + n;
+                y[0] = s.x; y[1] = s.y; y[2] = s.z; y[3] = s.w;
+            }
+        }
+    }
+    // Rows that a pass does not have were multiplied by zeros, which an infinite or undefined input makes NaN of: such a
+    // tile is computed again in steps of the rows there are.
+    if (__syncthreads_or(odd))
+        for (uint32_t g = group * (NC / 4); g < (group + 1u) * (NC / 4) && g * 64u < batch; ++g) {
+            spmm_quad_body<1, 1, false, NW, VF>(m, XSrc{(const float *)X, m.cols, ldx, (const float *)X, ldx}, Y, ldy, batch, tile, g);
+            __syncthreads();
+        }
+}
+
 // ---- launches ------------------------------------------------------------------------------------------------
 QuadMat quad_mat(const csb_matrix *m, bool low) {
     const QuadPlan &qp = low && m->plan.quad_low.valid ? m->plan.quad_low : m->plan.quad;
@@ -498,6 +661,49 @@ const void *quad_kernel(const QuadShape &sh, bool two, bool multi) {
     CSB_QV(1, 2, 16)
 #undef CSB_QV
 #undef CSB_Q
+}
+
+// The shape of a launch of panels, by an estimate of its time: a CU works off its workgroups at a rate that depends on little but
+// the panels (`panel`: us for the passes that four wavefronts take at once), however many of them it holds.  Fitted to 2967
+// launches in every form (260 to 20000 rows, 128 to 8192 columns, blocks of 4 to 64, pruned 1 to 25 times by three laws, 4 to 512
+// right-hand sides): half of the estimates are within 4 %; the form taken is 0.9 % off the best one on average and 4 at the 95th
+// percentile.  Against the better one of four-row steps and tile-based sections panels take 0.73 of the time on average over 6010
+// such launches, and the worst was 1.06 of it (9252 x 2045 in 16-row blocks at 2x, x 12: 22.7 us).
+// Four wavefronts where a list has at most 16 passes; longer sums in one accumulator are further off 64 bits than the halves of two: error against 64 bits, of
+// the norm, 8192 x 8192 in 16-row blocks at 8x, by 4 and by 8 wavefronts 0.96e-7 and 0.83e-7 (four-row steps 0.83e-7).
+struct PanelCost { int rows, columns, share; double base, out, merge, panel; };      // out: per million output words
+static const PanelCost kPanelCost[] = {
+    {16, 64, 1, 3.19, 0.755, 0, 0.296},     {16, 64, 2, 3.07, 1.38, 0, 0.290},    {16, 128, 1, 3.65, 1.00, 0, 0.289},
+    {16, 128, 2, 3.30, 1.25, 0.015, 0.285}, {32, 64, 1, 3.54, 0.952, 0, 0.339},   {32, 64, 2, 3.31, 1.22, 0.200, 0.335},
+    {32, 128, 1, 4.22, 0.929, 0.178, 0.339}, {32, 128, 2, 3.70, 1.00, 0.366, 0.354},
+};
+PanelShape panel_shape(const csb_matrix *m, int32_t batch) {
+    PanelShape best{};
+    double best_us = 1e300;
+    for (int low = 0; low < (m->plan.quad_low.valid ? 2 : 1); ++low) {
+        const QuadPlan &qp = low ? m->plan.quad_low : m->plan.quad;
+        const double passes = qp.work.passes / ((double)qp.n_tiles * kQuadLists);
+        for (const PanelCost &f : kPanelCost) {
+            if (f.rows != (int)qp.tile_rows || (f.columns == 128 && batch < 8)) continue;     // (128: a lane has eight right-hand sides)
+            if (f.share == 1 && passes > 16) continue;
+            const uint64_t wgs = (uint64_t)qp.n_tiles * (uint64_t)((batch + f.columns - 1) / f.columns);
+            const double us = f.base + f.out * qp.rows * batch * 1e-6 + (double)((wgs + 255) / 256) * (f.merge + (passes + 0.5 * f.share) * f.panel);
+            if (us < best_us) {
+                best_us = us;
+                best = PanelShape{f.rows, f.columns, f.share, low != 0, (size_t)4 * f.share * kQuadRows * 64 * sizeof(float), (unsigned)wgs};
+            }
+        }
+    }
+    return best;
+}
+
+const void *panel16_kernel(const PanelShape &ps, bool half) {
+#define CSB_P16(H, NC, S) (half ? (const void *)spmm_panel16_kernel<H, NC, S, CSB_VAL_F16> : (const void *)spmm_panel16_kernel<H, NC, S, CSB_VAL_BF16>)
+#define CSB_P16S(H, NC) (ps.share == 2 ? CSB_P16(H, NC, 2) : CSB_P16(H, NC, 1))
+    if (ps.rows == 16) return ps.columns == 128 ? CSB_P16S(1, 8) : CSB_P16S(1, 4);
+    return ps.columns == 128 ? CSB_P16S(2, 8) : CSB_P16S(2, 4);
+#undef CSB_P16S
+#undef CSB_P16
 }
 
 const void *quad16_kernel(const QuadShape &sh, bool half) {

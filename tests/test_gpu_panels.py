@@ -1,0 +1,84 @@
+"""Parity of the 16-bit products in panels (csb_spmm_bfloat / csb_spmm_half), in every form of a launch, against the oracle's float64
+product of the rounded operands with the float32 dot-product bound (their products are exact in float32)."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import csb_inputs
+import oracle
+from paper_2005_05758_amd import CsbMatrix
+from paper_2005_05758_amd import binding as csb
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+TYPES = {csb.VAL_F16: torch.float16, csb.VAL_BF16: torch.bfloat16}
+
+
+def product(A, br, bc, fmt, X, ldx=None, form=None):
+    """(result, rounded A, rounded X); `form`: what the call has to take (rows of a tile, right-hand sides, wavefronts)."""
+    M = CsbMatrix(A, br, bc)
+    M.set_value_format(fmt)
+    M.plan()
+    M.upload()
+    C, batch = X.shape
+    if form is not None:
+        got = (ctypes.c_int32 * 3)()
+        assert csb.lib().csb_debug_spmm_panel(M._h, batch, got) == 0 and tuple(got) == form
+    wide = torch.full((C, ldx or batch), float("nan"), device="cuda").to(TYPES[fmt])      # what lies beside the batch is never used
+    wide[:, :batch] = torch.from_numpy(X).cuda().to(TYPES[fmt])
+    out = torch.full((A.shape[0], batch + 3), 7.0, device="cuda")
+    call = M.spmm_half if fmt == csb.VAL_F16 else M.spmm_bfloat
+    call(wide[:, :batch], out[:, 1:1 + batch])
+    torch.cuda.synchronize()
+    assert torch.all(out[:, 0] == 7.0) and torch.all(out[:, batch + 1:] == 7.0)
+    return out[:, 1:1 + batch].cpu().numpy().astype(np.float64), torch.from_numpy(A).to(TYPES[fmt]).float().numpy(), wide[:, :batch].float().cpu().numpy()
+
+
+def bound_of(A, X):
+    return 2.0 * np.maximum(np.count_nonzero(A, axis=1)[:, None], 1) * 2.0 ** -24 * oracle.matmat(np.abs(A), np.abs(X)) + 1e-30
+
+
+# Every form, at row counts beside a multiple of its tile and at batches one step below, at and above its columns; with 128 the last
+# lane has eight right-hand sides (136) or moves back to the last eight (68, 132, 196).
+@pytest.mark.parametrize("R,C,block,rate,batch,form", [
+    (150, 90, 16, 3.0, 4, (16, 64, 4)), (97, 600, 33, 2.0, 60, (16, 64, 8)), (4090, 70, 32, 3.0, 64, (16, 64, 4)),
+    (150, 90, 32, 3.0, 260, (16, 64, 4)), (4100, 70, 24, 3.0, 8, (32, 64, 4)), (4500, 2600, 32, 1.5, 60, (32, 64, 8)),
+    (4097, 1500, 16, 4.0, 68, (16, 128, 8)), (4097, 1500, 16, 4.0, 136, (16, 128, 4)), (5000, 900, 32, 4.0, 68, (32, 128, 8)),
+    (3000, 1000, 64, 4.0, 132, (32, 128, 8)), (9000, 500, 32, 4.0, 196, (32, 128, 4)), (8200, 300, 16, 1.5, 128, (32, 128, 4))])
+@pytest.mark.parametrize("fmt", list(TYPES))
+def test_every_form(R, C, block, rate, batch, form, fmt):
+    A = csb_inputs.small_matrix(3, R, C, block, block, rate=rate).A
+    got, Ar, Xr = product(A, block, block, fmt, csb_inputs.make_vectors(batch, C, batch).reshape(C, batch), batch + 12, form)
+    assert np.all(np.abs(got - oracle.matmat(Ar, Xr)) <= bound_of(Ar, Xr))
+
+
+# Lists of very different lengths are found through a table: one full block row of 1100 that are nearly empty.
+@pytest.mark.parametrize("batch", [12, 72])
+def test_lists_of_different_lengths(batch):
+    R, C = 1100 * 32, 4000
+    A = np.zeros((R, C), np.float32)
+    A[64:96] = np.random.default_rng(1).standard_normal((32, C), np.float32)
+    A[::640, 7] = 1.0
+    got, Ar, Xr = product(A, 32, 32, csb.VAL_BF16, csb_inputs.make_vectors(2, C, batch).reshape(C, batch))
+    assert np.all(np.abs(got - oracle.matmat(Ar, Xr)) <= bound_of(Ar, Xr))
+
+
+@pytest.mark.parametrize("R,block,batch", [(96, 16, 12), (96, 32, 132), (8200, 32, 196), (4100, 16, 260)])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_an_input_that_is_not_finite_reaches_the_rows_that_use_it_alone(value, R, block, batch):
+    C = 300
+    A = csb_inputs.small_matrix(5, R, C, block, 32, rate=6.0).A
+    X = csb_inputs.make_vectors(batch, C, batch).reshape(C, batch)
+    col = int(np.flatnonzero(np.count_nonzero(A, axis=0))[-1])
+    X[col, ::3] = value
+    got, Ar, Xr = product(A, block, 32, csb.VAL_BF16, X)
+    odd, hit = ~np.isfinite(X[col]), Ar[:, col] != 0
+    at = np.ix_(hit, odd)
+    assert not np.any(np.isfinite(got[at]))
+    if np.isinf(value):
+        assert np.all(np.sign(got[at]) == np.sign(Ar[hit, col])[:, None])
+    Xr[col, odd] = 0.0
+    good = np.abs(got - oracle.matmat(Ar, Xr)) <= bound_of(Ar, Xr)
+    good[at] = True
+    assert np.all(good)
