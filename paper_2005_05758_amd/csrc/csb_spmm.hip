@@ -1114,18 +1114,18 @@ int spmm_strided_multi(const SpmmCall *calls, int n, int32_t batch, void *stream
 namespace csb {
 // Launch shape of a product of 16-bit values and 16-bit right-hand sides from the tile-based sections.
 struct Spmm16Shape {
-    bool fits, reg;          // row tiles of 16 or 32 rows: the kernel that keeps its results in registers
+    bool reg;                // row tiles of 16 or 32 rows: the kernel that keeps its results in registers
     int nw, nq, nwr;         // wavefronts of the general form; 64-column groups and wavefronts of the other
     size_t lds;
     unsigned tiles, batch_tiles;
     double us;
 };
+static bool spmm16_fits(const DevHeader &h) { return (size_t)h.seg_meta + 8 * (size_t)h.br * 64 * sizeof(float) <= (size_t)kLdsBudget; }
 static Spmm16Shape spmm16_shape(const csb_matrix *m, int32_t batch) {
     const DevHeader &h = m->plan.hdr;
     Spmm16Shape s{};
     const size_t acc_per_wave = (size_t)h.br * 64 * sizeof(float);
     s.nw = (size_t)h.seg_meta + 16 * acc_per_wave <= (size_t)kLdsBudget ? 16 : 8;
-    s.fits = (size_t)h.seg_meta + 8 * acc_per_wave <= (size_t)kLdsBudget;
     s.tiles = (unsigned)(h.n_nz_tiles + h.n_zero_tiles);
     s.nq = reg_columns(s.tiles, h.br, batch, true);
     s.nwr = s.nq > 1 ? 8 : s.nw;
@@ -1156,8 +1156,7 @@ static int spmm_16bit(const char *who, int fmt, const csb_matrix *m, const uint1
         set_error(w + ": sizes beyond the kernel's 32-bit offsets");
         return CSB_EUNSUPPORTED;
     }
-    const Spmm16Shape sh = spmm16_shape(m, batch);
-    if (!sh.fits) {
+    if (!spmm16_fits(h)) {
         set_error(w + ": the block rows are too tall for the accumulator tiles");
         return CSB_EUNSUPPORTED;
     }
@@ -1174,6 +1173,7 @@ static int spmm_16bit(const char *who, int fmt, const csb_matrix *m, const uint1
         if (e != hipSuccess) { set_error(w + ": " + hipGetErrorString(e)); return CSB_EDEVICE; }
         return CSB_OK;
     }
+    const Spmm16Shape sh = spmm16_shape(m, batch);
     const QuadShape qs = quads ? quad_shape(&m, 1, batch, true) : QuadShape{};
     if (quads && (m->batch_form == kFormQuads || prefers_quads(qs.us, sh.us))) {
         QuadMat qm = quad_mat(m, qs.low);

@@ -392,13 +392,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
 // forms, so that rows may stay where they are in the tile and be zero where a pass lacks them: four passes (a list for
 // every 16 lanes) are a panel of 32 columns, nothing is added row by row, and a wavefront's sums are the accumulators of
 // its instructions.  A lane is row i of 16 and takes the eight values of its row from a pass, found by counting the rows in front
-// of it in the record's mask (a row that the pass lacks reads past the end: zeros), and of each of the pass's eight columns 4 or 8
-// neighbouring right-hand sides; v_perm puts columns side by side.  The record comes in as a word per lane and is handed
+// of it in the record's mask (a row that the pass lacks reads past the end: zeros), and of each of the pass's eight columns 8
+// neighbouring right-hand sides, or twice 2; v_perm puts columns side by side.  The record comes in as a word per lane and is handed
 // round by DPP.
 // What bounds it: the loads' way through the L1: with the products left out a launch is as long, from 16 rows of X that always hit it is no
-// shorter (measured), and a load of 8 bytes per lane costs as much as one of 16, so that from 128 right-hand sides on
-// lanes take 16 bytes: 8192 x 8192 at 12x, bfloat16 x 512, 66 -> 44 us (8 such loads, 2 of values and a record per panel: at one every 17 clocks
-// 29 us).  Four-row steps / panels, us: x 512 69 / 44, x 256 37 / 24, x 128 23 / 13.9, x 64 18.9 / 12.7, x 8 17.7 / 11.8; 4096 x
+// shorter (measured).  A load of 4 bytes per lane takes it about 4 clocks, of 8 bytes 12, of 16 bytes 13: lanes take 16 where there are
+// 128 right-hand sides, else 4 twice; with 8 bytes 8192 x 8192 at 12x, bfloat16, takes 66 us instead of 44 at 512 right-hand sides, 12.8
+// instead of 10.6 at 64.  Four-row steps / panels, us: x 512 69 / 44, x 256 37 / 24, x 128 23 / 13.9, x 64 18.9 / 10.6, x 8 17.7 / 9.7; 4096 x
 // 4096 in 16-row blocks x 256 22.8 / 13.6; 1024 x 665 at 8x x 32 4.0 / 3.35.  Error against 64 bits, of the norm, of these: 0.749e-7 (0.750e-7
 // before), x 128 0.748e-7 (0.846e-7); 0.661e-7 (0.661e-7); binary16 0.92e-7 (0.98e-7).
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -408,7 +408,7 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 template <int N>
 __device__ __forceinline__ uint32_t row_lane(const uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + N, 0xf, 0xf, false); }
 
-// H: tile of 16 H rows; NC: right-hand sides of a lane (4 or 8), 16 NC of a workgroup; S: wavefronts that share a list.
+// H: tile of 16 H rows; NC: right-hand sides of a lane (4, as two and two, or 8), 16 NC of a workgroup; S: wavefronts that share a list.
 template <int H, int NC>
 struct PanelOps {
     uint32_t x[kQuadCols][NC / 2];                       // right-hand sides of each column of the lane's pass, two to a word
@@ -456,8 +456,8 @@ __device__ __forceinline__ void panel_passes(const QuadMat &m, const uint16_t *X
                 const uint4 v = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, (int)at, 0, 0));
                 o.x[e][0] = v.x; o.x[e][1] = v.y; o.x[e][2] = v.z; o.x[e][3] = v.w;
             } else {
-                const uint2 v = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(xrsrc, (int)at, 0, 0));
-                o.x[e][0] = v.x; o.x[e][1] = v.y;
+                o.x[e][0] = __builtin_amdgcn_raw_buffer_load_b32(xrsrc, (int)at, 0, 0);
+                o.x[e][1] = __builtin_amdgcn_raw_buffer_load_b32(xrsrc, (int)(at + 64u), 0, 0);
             }
         }
     };
@@ -506,15 +506,19 @@ __global__ __launch_bounds__(256 * S) __attribute__((amdgpu_waves_per_eu(H * NC 
     constexpr int NW = 4 * S;
     constexpr uint32_t N = 16 * NC;
     const uint32_t groups = (batch + N - 1u) / N, tile = blockIdx.x / groups, group = blockIdx.x - tile * groups, bt0 = group * N;
-    const uint32_t wave = uni_(threadIdx.x >> 6), lane = threadIdx.x & 63u;
-    const uint32_t own = bt0 + NC * (lane & 15u);        // the lane's right-hand sides; the last four of a batch come with the four before them
-    const uint32_t col0 = NC == 8 && own + 4u == batch ? own - 4u : own;
+    const uint32_t wave = uni_(threadIdx.x >> 6);
+    // a lane's right-hand sides: two and the two 32 further on, or eight; the last four of a batch come with the four before them
+    auto first_of = [&](const uint32_t ln) { return bt0 + (NC == 4 ? 2u : 8u) * (ln & 15u); };
+    auto from = [&](const uint32_t own) { return NC == 8 && own + 4u == batch ? own - 4u : own; };
     floatx4 acc[H][NC];
 #pragma unroll
     for (int h = 0; h < H; ++h)
 #pragma unroll
         for (int n = 0; n < NC; ++n) acc[h][n] = 0.0f;
-    panel_passes<H, NC, S, VF>(m, X, ldx, batch, tile, col0, wave, acc);
+    panel_passes<H, NC, S, VF>(m, X, ldx, batch, tile, from(first_of(threadIdx.x)), wave, acc);
+    uint32_t lane;                                       // (asked for again: kept over the passes it is a register too many)
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+    const uint32_t own = first_of(lane), col0 = from(own);
     // the wavefronts' sums, 16 rows at a time: [wave][row of four][four right-hand sides][lane]
     const uint32_t row0 = tile * m.tile_rows;
     bool odd = false;
@@ -528,14 +532,33 @@ __global__ __launch_bounds__(256 * S) __attribute__((amdgpu_waves_per_eu(H * NC 
                 smem4[((wave * 4u + r) * (NC / 4) + c) * 64u + lane] = make_float4(acc[h][4 * c][r], acc[h][4 * c + 1][r], acc[h][4 * c + 2][r], acc[h][4 * c + 3][r]);
         __syncthreads();
         for (uint32_t k = wave; k < (uint32_t)NC; k += NW) {
-            float4 s = smem4[k * 64u + lane];
+            // (four and four in a row, then those: nearer to 64 bits than all in a row)
+            auto four = [&](const int w0) {
+                float4 v = smem4[((uint32_t)w0 * NC + k) * 64u + lane];
 #pragma unroll
-            for (int w = 1; w < NW; ++w) {
-                const float4 v = smem4[((uint32_t)w * NC + k) * 64u + lane];
+                for (int w = w0 + 1; w < w0 + 4; ++w) {
+                    const float4 p = smem4[((uint32_t)w * NC + k) * 64u + lane];
+                    v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
+                }
+                return v;
+            };
+            float4 s = four(0);
+            if constexpr (NW == 8) {
+                asm volatile("" : "+v"(s.x), "+v"(s.y), "+v"(s.z), "+v"(s.w));      // (not the registers for all eight)
+                const float4 v = four(4);
                 s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
             }
-            const uint32_t row = row0 + 16u * h + 4u * (lane >> 4) + k / (NC / 4), n = col0 + 4u * (k % (NC / 4));
-            if (row < m.rows && n >= own && n < batch) {
+            const uint32_t row = row0 + 16u * h + 4u * (lane >> 4) + k / (NC / 4);
+            auto store = [&](const uint32_t n, const float v0, const float v1) {      // (batches are even, and so is n)
+                if (row >= m.rows || n < own || n >= batch) return;
+                odd = odd || !(fabsf(v0) < INFINITY && fabsf(v1) < INFINITY);
+                float *y = Y + (size_t)row * ldy + n;
+                y[0] = v0; y[1] = v1;
+            };
+            if constexpr (NC == 4) {
+                store(col0, s.x, s.y);
+                store(col0 + 32u, s.z, s.w);
+            } else if (const uint32_t n = col0 + 4u * (k % (NC / 4)); row < m.rows && n >= own && n < batch) {
                 odd = odd || !(fabsf(s.x) < INFINITY && fabsf(s.y) < INFINITY && fabsf(s.z) < INFINITY && fabsf(s.w) < INFINITY);
                 float *y = Y + (size_t)row * ldy + n;
                 y[0] = s.x; y[1] = s.y; y[2] = s.z; y[3] = s.w;
@@ -664,33 +687,37 @@ const void *quad_kernel(const QuadShape &sh, bool two, bool multi) {
 }
 
 // The shape of a launch of panels, by an estimate of its time: a CU works off its workgroups at a rate that depends on little but
-// the panels (`panel`: us for the passes that four wavefronts take at once), however many of them it holds.  Fitted to 2967
+// the panels (`panel`: us for the passes that four wavefronts take at once), however many of them it holds.  Fitted to 1573
 // launches in every form (260 to 20000 rows, 128 to 8192 columns, blocks of 4 to 64, pruned 1 to 25 times by three laws, 4 to 512
-// right-hand sides): half of the estimates are within 4 %; the form taken is 0.9 % off the best one on average and 4 at the 95th
-// percentile.  Against the better one of four-row steps and tile-based sections panels take 0.73 of the time on average over 6010
-// such launches, and the worst was 1.06 of it (9252 x 2045 in 16-row blocks at 2x, x 12: 22.7 us).
+// right-hand sides): half of the estimates are within 4 %; the form taken is 1.0 % off the best one on average and 5 at the 95th
+// percentile (the worst: 8342 x 7541 unpruned x 72, 64.6 us where 128 columns take 46.1).  Against the better one of four-row steps and
+// tile-based sections panels took 0.73 of the time on average over 6010 such launches, and the worst 1.06 of it (9252 x 2045 in
+// 16-row blocks at 2x, x 12), before the forms of 64 columns loaded 4 bytes at a time.
 // Four wavefronts where a list has at most 16 passes; longer sums in one accumulator are further off 64 bits than the halves of two: error against 64 bits, of
 // the norm, 8192 x 8192 in 16-row blocks at 8x, by 4 and by 8 wavefronts 0.96e-7 and 0.83e-7 (four-row steps 0.83e-7).
-struct PanelCost { int rows, columns, share; double base, out, merge, panel; };      // out: per million output words
+struct PanelCost { int rows, columns, share; double base, out, merge, panel; };      // out: per million output words (four forms of 16 rows, four of 32)
 static const PanelCost kPanelCost[] = {
-    {16, 64, 1, 3.19, 0.755, 0, 0.296},     {16, 64, 2, 3.07, 1.38, 0, 0.290},    {16, 128, 1, 3.65, 1.00, 0, 0.289},
-    {16, 128, 2, 3.30, 1.25, 0.015, 0.285}, {32, 64, 1, 3.54, 0.952, 0, 0.339},   {32, 64, 2, 3.31, 1.22, 0.200, 0.335},
-    {32, 128, 1, 4.22, 0.929, 0.178, 0.339}, {32, 128, 2, 3.70, 1.00, 0.366, 0.354},
+    {16, 64, 1, 3.26, 0.748, 0, 0.239},     {16, 64, 2, 3.13, 2.34, 0, 0.195},     {16, 128, 1, 3.69, 1.40, 0.069, 0.289},
+    {16, 128, 2, 3.50, 1.91, 0.006, 0.283}, {32, 64, 1, 3.66, 1.20, 0, 0.249},     {32, 64, 2, 3.40, 1.79, 0.301, 0.227},
+    {32, 128, 1, 4.34, 1.16, 0.343, 0.330}, {32, 128, 2, 3.98, 1.39, 0.572, 0.348},
 };
 PanelShape panel_shape(const csb_matrix *m, int32_t batch) {
     PanelShape best{};
     double best_us = 1e300;
+    // (a small call's kernel is done in 3 us: what is the same for several forms is worked out once)
     for (int low = 0; low < (m->plan.quad_low.valid ? 2 : 1); ++low) {
         const QuadPlan &qp = low ? m->plan.quad_low : m->plan.quad;
-        const double passes = qp.work.passes / ((double)qp.n_tiles * kQuadLists);
-        for (const PanelCost &f : kPanelCost) {
-            if (f.rows != (int)qp.tile_rows || (f.columns == 128 && batch < 8)) continue;     // (128: a lane has eight right-hand sides)
-            if (f.share == 1 && passes > 16) continue;
-            const uint64_t wgs = (uint64_t)qp.n_tiles * (uint64_t)((batch + f.columns - 1) / f.columns);
-            const double us = f.base + f.out * qp.rows * batch * 1e-6 + (double)((wgs + 255) / 256) * (f.merge + (passes + 0.5 * f.share) * f.panel);
+        const double passes = qp.work.passes / ((double)qp.n_tiles * kQuadLists), out = (double)qp.rows * batch * 1e-6;
+        const uint64_t wgs64 = (uint64_t)qp.n_tiles * (((uint32_t)batch + 63u) >> 6), wgs128 = (uint64_t)qp.n_tiles * (((uint32_t)batch + 127u) >> 7);
+        const double turns64 = (double)((wgs64 + 255) >> 8), turns128 = (double)((wgs128 + 255) >> 8);
+        const PanelCost *forms = kPanelCost + (qp.tile_rows == 16 ? 0 : 4);
+        for (const PanelCost *f = forms; f < forms + 4; ++f) {
+            if ((f->columns == 128 && batch < 8) || (f->share == 1 && passes > 16)) continue;     // (128: a lane has eight right-hand sides)
+            const double us = f->base + f->out * out + (f->columns == 128 ? turns128 : turns64) * (f->merge + (passes + 0.5 * f->share) * f->panel);
             if (us < best_us) {
                 best_us = us;
-                best = PanelShape{f.rows, f.columns, f.share, low != 0, (size_t)4 * f.share * kQuadRows * 64 * sizeof(float), (unsigned)wgs};
+                best = PanelShape{f->rows, f->columns, f->share, low != 0, (size_t)4 * f->share * kQuadRows * 64 * sizeof(float),
+                                  (unsigned)(f->columns == 128 ? wgs128 : wgs64)};
             }
         }
     }

@@ -40,12 +40,12 @@ def bound_of(A, X):
 
 
 # Every form, at row counts beside a multiple of its tile and at batches one step below, at and above its columns; with 128 the last
-# lane has eight right-hand sides (136) or moves back to the last eight (68, 132, 196).
+# lane has eight right-hand sides (128) or moves back to the last eight (68, 124, 260, 508).
 @pytest.mark.parametrize("R,C,block,rate,batch,form", [
-    (150, 90, 16, 3.0, 4, (16, 64, 4)), (97, 600, 33, 2.0, 60, (16, 64, 8)), (4090, 70, 32, 3.0, 64, (16, 64, 4)),
-    (150, 90, 32, 3.0, 260, (16, 64, 4)), (4100, 70, 24, 3.0, 8, (32, 64, 4)), (4500, 2600, 32, 1.5, 60, (32, 64, 8)),
-    (4097, 1500, 16, 4.0, 68, (16, 128, 8)), (4097, 1500, 16, 4.0, 136, (16, 128, 4)), (5000, 900, 32, 4.0, 68, (32, 128, 8)),
-    (3000, 1000, 64, 4.0, 132, (32, 128, 8)), (9000, 500, 32, 4.0, 196, (32, 128, 4)), (8200, 300, 16, 1.5, 128, (32, 128, 4))])
+    (150, 90, 16, 3.0, 4, (16, 64, 8)), (97, 600, 33, 2.0, 60, (16, 64, 8)), (4090, 70, 32, 3.0, 64, (16, 64, 4)),
+    (4090, 70, 32, 3.0, 260, (16, 64, 4)), (4100, 70, 24, 3.0, 8, (32, 64, 4)), (4500, 2600, 32, 1.5, 60, (32, 64, 8)),
+    (4097, 2500, 16, 2.0, 124, (16, 128, 8)), (4097, 1500, 16, 4.0, 124, (16, 128, 4)), (4097, 1500, 16, 4.0, 128, (16, 128, 4)),
+    (4500, 2600, 32, 1.5, 68, (32, 128, 8)), (5000, 900, 32, 4.0, 260, (32, 128, 4)), (8200, 300, 16, 1.5, 508, (32, 128, 4))])
 @pytest.mark.parametrize("fmt", list(TYPES))
 def test_every_form(R, C, block, rate, batch, form, fmt):
     A = csb_inputs.small_matrix(3, R, C, block, block, rate=rate).A
