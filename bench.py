@@ -664,7 +664,7 @@ def val16_leg(torch, np, csb_inputs, CsbMatrix, stream_gbps, formats=("f16", "bf
                 bf[f"batch{Bb}"] = {"us": round(us, 2), "tflops_algorithmic": round(tf, 3)}
             tf = bf["batch512"]["tflops_algorithmic"]
             entry["spmm_bfloat"] = dict(bf, roofline={
-                "kernel": "csb::spmm_quad16_kernel<2, 8, 2>", "bound": "mfma", "achieved": tf, "peak": 2500.0, "unit": "TFLOP/s",
+                "kernel": "csb::spmm_panel16_kernel<2, 8, 2, 2>", "bound": "mfma", "achieved": tf, "peak": 2500.0, "unit": "TFLOP/s",
                 "frac": round(tf / 2500.0, 5), "traffic": None,
                 "note": "dense bf16 MFMA peak as the nominal roof; 4 x 4 x 4 MFMA steps on kernels of about 9 x 9: the launch is "
                         "bound by the pipe that those and the vector instructions of a pass share, not by the dense rate"})
