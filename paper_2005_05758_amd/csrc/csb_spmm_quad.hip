@@ -201,7 +201,8 @@ __device__ __forceinline__ void quad_passes(const QuadMat &m, const XSrc &X, con
 }
 
 // ---- 16-bit values times 16-bit right-hand sides (v_mfma_f32_4x4x4_16b) -----------------------------------------
-// An instruction takes four columns.  With NT = 2 a lane holds two neighbouring right-hand sides of an input row in one
+// (Calls take panels, further down; these steps compute the tiles that an input which is not finite reaches, and stand
+// beside the panels for measurements.)  An instruction takes four columns.  With NT = 2 a lane holds two neighbouring right-hand sides of an input row in one
 // register; tile t holds the right-hand sides 2 n + t, its operand the halves t of four rows.
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
