@@ -242,7 +242,7 @@ struct StreamPlan {
 // it needs in the record, which comes in over the scalar path.
 //   records, list after list.  Lists of about the same length start `list_stride` records apart, and a launch finds its
 //           first record without a table: one dependent trip to memory less before it has any work.  The first record
-//           of a list counts its passes.
+//           of a list counts its passes.  All of them, gaps included, may take more than 2 GiB, a tile's never do.
 //   table   (list_stride == 0: lists of very different lengths) [n_tiles][kQuadLists] first record of every list, and one
 //           entry more for the end of the last
 //   values  binary32: per pass [column][4 rows][quad], columns in fours, zeros where the pass has no such row or column;
@@ -270,6 +270,8 @@ struct QuadRec {
 };
 constexpr uint8_t kQuadWide = 1, kQuadSecond = 2;
 static_assert(sizeof(QuadRec) == 64, "QuadRec layout");
+// (a pass holds an entry of the matrix, and a list is no longer than the passes of one tile)
+static_assert(sizeof(QuadRec) * kQuadLists * kQuadRows * kMaxStageCols <= 0x7fffffff, "a tile's records by offsets of 31 bits");
 
 // What the passes of a section add up to, for the estimate of a launch's time.
 struct QuadWork {

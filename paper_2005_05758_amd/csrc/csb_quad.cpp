@@ -281,6 +281,7 @@ static int validate_section(const csb_matrix *m, const QuadPlan &qp) {
             if (qp.list_stride && i0 != list * qp.list_stride) return fail("list stride");
             const uint64_t i1 = i0 + (qp.list_stride ? recs[i0].list_len : table[list + 1] - i0);
             if (i1 > table[list + 1] || (i1 > i0 && recs[i0].list_len != i1 - i0)) return fail("list length");
+            if ((i1 - table[(size_t)t * kQuadLists]) * sizeof(QuadRec) > 0x7fffffffull) return fail("a tile's records");      // (byte offsets of 31 bits)
             for (uint64_t i = i0; i < i1; ++i) {
                 const QuadRec &r = recs[i];
                 uint32_t ncols = 0, nrows = 0;

@@ -421,16 +421,17 @@ template <int H, int NC, int S, int VF>
 __device__ __forceinline__ void panel_passes(const QuadMat &m, const uint16_t *X, const uint32_t ldx, const uint32_t batch, const uint32_t tile,
                                              const uint32_t col0, const uint32_t wave, floatx4 (&acc)[H][NC]) {
     const uint32_t lane = threadIdx.x & 63u, i = lane & 15u, part = wave >> 2;
-    const uint32_t list = tile * kQuadLists + (wave & 3u) * 4u + (lane >> 4);
-    const uint32_t first = m.list_stride ? list * m.list_stride : m.table[list];
+    const uint32_t list0 = tile * kQuadLists, list = list0 + (wave & 3u) * 4u + (lane >> 4);
+    const uint32_t first0 = m.list_stride ? list0 * m.list_stride : m.table[list0], first = m.list_stride ? list * m.list_stride : m.table[list];
     const uint32_t len = m.list_stride ? ((const QuadRec *)m.recs)[first].list_len : m.table[list + 1] - first;
     const uint32_t longest = max(max(__builtin_amdgcn_readlane(len, 0), __builtin_amdgcn_readlane(len, 16)),
                                  max(__builtin_amdgcn_readlane(len, 32), __builtin_amdgcn_readlane(len, 48)));
-    const __amdgpu_buffer_rsrc_t rrsrc = __builtin_amdgcn_make_buffer_rsrc((void *)m.recs, 0, 0x7fffffff, 0x00020000);
+    // (from the tile's first record on: those of a matrix may lie further apart than an offset reaches, those of a tile do not)
+    const __amdgpu_buffer_rsrc_t rrsrc = __builtin_amdgcn_make_buffer_rsrc((void *)((const QuadRec *)m.recs + first0), 0, 0x7fffffff, 0x00020000);
     const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc((void *)m.vals, 0, (int)m.vals_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc((void *)X, 0, (int)(((m.cols - 1u) * ldx + batch) * 2u), 0x00020000);
     // a record's eight words come in by eight lanes
-    const uint32_t word = i & 7u, rec0 = first * (uint32_t)sizeof(QuadRec) + word * 4u;
+    const uint32_t word = i & 7u, rec0 = (first - first0) * (uint32_t)sizeof(QuadRec) + word * 4u;
     const uint32_t none = word >= 2u && word < 6u ? 0xffffffffu : 0u;     // a record of no columns and no rows
     uint32_t row = ldx * 2u, xlane = col0 * 2u;          // (bytes from one column's right-hand sides to the next's: 16 bits)
     asm("" : "+v"(row), "+v"(xlane));

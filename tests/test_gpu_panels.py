@@ -64,6 +64,16 @@ def test_lists_of_different_lengths(batch):
     assert np.all(np.abs(got - oracle.matmat(Ar, Xr)) <= bound_of(Ar, Xr))
 
 
+# Records of more than 2 GiB: 257 tiles of 16 lists, 8400 records of 64 bytes from one list to the next, are 2.21e9 bytes (32390400 passes; the
+# first 32 tiles have half as many as the others).
+def test_records_beyond_2_gib():
+    R, C = 257 * 32, 4200
+    A = np.random.default_rng(1).standard_normal((R, C), np.float32)
+    A[:1024, ::2] = 0.0
+    got, Ar, Xr = product(A, 1, 1, csb.VAL_BF16, csb_inputs.make_vectors(3, C, 4).reshape(C, 4))
+    assert np.all(np.abs(got - oracle.matmat(Ar, Xr)) <= bound_of(Ar, Xr))
+
+
 @pytest.mark.parametrize("R,block,batch", [(96, 16, 12), (96, 32, 132), (8200, 32, 196), (4100, 16, 260)])
 @pytest.mark.parametrize("value", [np.inf, np.nan])
 def test_an_input_that_is_not_finite_reaches_the_rows_that_use_it_alone(value, R, block, batch):
