@@ -1162,15 +1162,21 @@ static int spmm_16bit(const char *who, int fmt, const csb_matrix *m, const uint1
     }
     const bool quads = quad16_source(m, ldx);
     if (quads && m->batch_form == kFormAuto) {
-        const PanelShape ps = panel_shape(m, batch);
-        QuadMat qm = quad_mat(m, ps.low);
-        uint32_t b = (uint32_t)batch, ld = (uint32_t)ldx;
-        int64_t ldy_ = ldy;
-        void *args[] = {&qm, &d_X, &ld, &d_Y, &ldy_, &b};
-        const void *kern = panel16_kernel(ps, fmt == CSB_VAL_F16);
-        hipError_t e = ensure_dynamic_lds(kern, ps.lds);
-        if (e == hipSuccess) e = hipLaunchKernel(kern, dim3(ps.workgroups), dim3(256 * ps.share), args, ps.lds, (hipStream_t)stream);
-        if (e != hipSuccess) { set_error(w + ": " + hipGetErrorString(e)); return CSB_EDEVICE; }
+        int32_t n = 0;
+        for (int32_t n0 = 0; n0 < batch; n0 += n) {
+            const PanelShape ps = panel_shape(m, batch - n0);
+            n = ps.batch;
+            QuadMat qm = quad_mat(m, ps.low);
+            const uint16_t *x = d_X + n0;
+            float *y = d_Y + n0;
+            uint32_t b = (uint32_t)n, ld = (uint32_t)ldx;
+            int64_t ldy_ = ldy;
+            void *args[] = {&qm, &x, &ld, &y, &ldy_, &b};
+            const void *kern = panel16_kernel(ps, fmt == CSB_VAL_F16);
+            hipError_t e = ensure_dynamic_lds(kern, ps.lds);
+            if (e == hipSuccess) e = hipLaunchKernel(kern, dim3(ps.workgroups), dim3(256 * ps.share), args, ps.lds, (hipStream_t)stream);
+            if (e != hipSuccess) { set_error(w + ": " + hipGetErrorString(e)); return CSB_EDEVICE; }
+        }
         return CSB_OK;
     }
     const Spmm16Shape sh = spmm16_shape(m, batch);

@@ -82,6 +82,7 @@ struct PanelShape {
     bool low;               // the section of 16-row tiles beside that of 32
     size_t lds;
     unsigned workgroups;
+    int32_t batch;          // right-hand sides of the launch: all, or as many as a grid has threads for
 };
 PanelShape panel_shape(const csb_matrix *m, int32_t batch);
 const void *panel16_kernel(const PanelShape &ps, bool half);

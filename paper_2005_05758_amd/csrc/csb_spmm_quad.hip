@@ -719,10 +719,13 @@ PanelShape panel_shape(const csb_matrix *m, int32_t batch) {
             if (us < best_us) {
                 best_us = us;
                 best = PanelShape{f->rows, f->columns, f->share, low != 0, (size_t)4 * f->share * kQuadRows * 64 * sizeof(float),
-                                  (unsigned)(f->columns == 128 ? wgs128 : wgs64)};
+                                  (unsigned)(f->columns == 128 ? wgs128 : wgs64), batch};
             }
         }
     }
+    // a grid's row has fewer than 2^32 threads (65536 tiles by 512 threads by 128 workgroups a tile are as many)
+    const uint64_t tiles = (best.low ? m->plan.quad_low : m->plan.quad).n_tiles, groups = std::max<uint64_t>(0xffffffffull / (256u * best.share) / tiles, 1);
+    if (groups * best.columns < (uint64_t)batch) { best.batch = (int32_t)(groups * best.columns); best.workgroups = (unsigned)(groups * tiles); }
     return best;
 }
 

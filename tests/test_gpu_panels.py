@@ -74,6 +74,30 @@ def test_records_beyond_2_gib():
     assert np.all(np.abs(got - oracle.matmat(Ar, Xr)) <= bound_of(Ar, Xr))
 
 
+# 65536 tiles by 128 groups of right-hand sides by 512 threads are 2^32 threads, more than a grid's row has: the last right-hand
+# sides are a launch of their own.  (288 passes a tile: lists of more than 16, for which there are no workgroups of 256 threads.)
+def test_more_threads_than_a_grid_has():
+    R, C, batch = 65536 * 32, 9, 16380
+    if torch.cuda.mem_get_info()[0] < 4 * R * batch + (8 << 30):
+        pytest.skip("no memory for a result of 137 GB")
+    A = np.random.default_rng(1).standard_normal((R, C), np.float32)
+    M = CsbMatrix(A, 1, 1)
+    M.set_value_format(csb.VAL_BF16)
+    M.plan()
+    M.upload()
+    form = (ctypes.c_int32 * 3)()
+    assert csb.lib().csb_debug_spmm_panel(M._h, batch, form) == 0 and form[2] == 8
+    X = torch.from_numpy(csb_inputs.make_vectors(5, C, batch)).cuda().to(torch.bfloat16)
+    Y = M.spmm_bfloat(X)
+    torch.cuda.synchronize()
+    Ad, Xd = torch.from_numpy(A).cuda().to(torch.bfloat16).float(), X.float()
+    for rows in (slice(0, 64), slice(R // 2 - 32, R // 2 + 32), slice(R - 64, R)):
+        ref, absr = Ad[rows].double() @ Xd.double(), Ad[rows].abs().double() @ Xd.abs().double()
+        assert torch.all((Y[rows].double() - ref).abs() <= 2.0 * C * 2.0 ** -24 * absr + 1e-30)
+    del Y
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("R,block,batch", [(96, 16, 12), (96, 32, 132), (8200, 32, 196), (4100, 16, 260)])
 @pytest.mark.parametrize("value", [np.inf, np.nan])
 def test_an_input_that_is_not_finite_reaches_the_rows_that_use_it_alone(value, R, block, batch):
