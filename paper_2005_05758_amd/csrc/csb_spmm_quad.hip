@@ -568,12 +568,18 @@ __global__ __launch_bounds__(256 * S) __attribute__((amdgpu_waves_per_eu(H * NC 
         }
     }
     // Rows that a pass does not have were multiplied by zeros, which an infinite or undefined input makes NaN of: such a
-    // tile is computed again in steps of the rows there are.
-    if (__syncthreads_or(odd))
-        for (uint32_t g = group * (NC / 4); g < (group + 1u) * (NC / 4) && g * 64u < batch; ++g) {
-            spmm_quad_body<1, 1, false, NW, VF>(m, XSrc{(const float *)X, m.cols, ldx, (const float *)X, ldx}, Y, ldy, batch, tile, g);
-            __syncthreads();
-        }
+    // tile is computed again in steps of the rows there are, of 128 right-hand sides only the 64 that need it.  8192 x 8192 at 12x, us, all finite /
+    // an infinite input that 682 rows use / nothing but NaN: x 512 48 / 82 / 109 (110 and 158 with all by 64 and 64), x 128 14.5 / 36 / 41 (53 and 62),
+    // x 64 10.7 / 28 / 30.  (Four-row steps alone: 71, 21.7, 17.9 whatever the inputs.)
+    if (!__syncthreads_or(odd)) return;
+    const XSrc src{(const float *)X, m.cols, ldx, (const float *)X, ldx};
+    if constexpr (NC == 4) {
+        spmm_quad_body<1, 1, false, NW, VF>(m, src, Y, ldy, batch, tile, group);
+    } else {
+        const bool odd0 = __syncthreads_or(odd && (lane & 8u) == 0u), odd1 = __syncthreads_or(odd && (lane & 8u) != 0u);
+        if (odd0 && odd1) spmm_quad_body<2, 1, false, NW, VF>(m, src, Y, ldy, batch, tile, group);
+        else spmm_quad_body<1, 1, false, NW, VF>(m, src, Y, ldy, batch, tile, group * 2u + (odd1 ? 1u : 0u));
+    }
 }
 
 // ---- launches ------------------------------------------------------------------------------------------------

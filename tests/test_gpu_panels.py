@@ -116,3 +116,40 @@ def test_an_input_that_is_not_finite_reaches_the_rows_that_use_it_alone(value, R
     good = np.abs(got - oracle.matmat(Ar, Xr)) <= bound_of(Ar, Xr)
     good[at] = True
     assert np.all(good)
+
+
+# Which right-hand sides are computed again: in workgroups of 128 either 64 of them or all, in binary16 as in bfloat16.  `odd`: the
+# right-hand sides with such an input, in the first, the second or both halves of a workgroup, among the last four of a batch.
+@pytest.mark.parametrize("R,C,block,rate,batch,odd,form", [
+    (96, 300, 32, 6.0, 64, [5], (16, 64, 8)), (5000, 900, 32, 4.0, 260, [7], (32, 128, 4)), (5000, 900, 32, 4.0, 260, [127, 259], (32, 128, 4)),
+    (5000, 900, 32, 4.0, 260, [63, 64, 129], (32, 128, 4)), (4500, 2600, 32, 1.5, 68, [66], (32, 128, 8)), (4500, 2600, 32, 1.5, 68, [0, 67], (32, 128, 8)),
+    (4097, 1500, 16, 4.0, 124, [63, 123], (16, 128, 4)), (4097, 2500, 16, 2.0, 124, [64], (16, 128, 8))])
+@pytest.mark.parametrize("fmt", list(TYPES))
+def test_right_hand_sides_that_are_computed_again(fmt, R, C, block, rate, batch, odd, form):
+    A = csb_inputs.small_matrix(5, R, C, block, block, rate=rate).A
+    X = csb_inputs.make_vectors(batch, C, batch).reshape(C, batch)
+    col = int(np.argmax(np.count_nonzero(A, axis=0)))
+    X[col, odd] = -np.inf
+    got, Ar, Xr = product(A, block, block, fmt, X, form=form)
+    at = np.ix_(Ar[:, col] != 0, odd)
+    assert np.all(got[at] == -np.sign(Ar[Ar[:, col] != 0, col])[:, None] * np.inf)
+    Xr[col, odd] = 0.0
+    good = np.abs(got - oracle.matmat(Ar, Xr)) <= bound_of(Ar, Xr)
+    good[at] = True
+    assert np.all(good)
+
+
+# Weights that are infinite or undefined, and sums beyond float32's range, reach their own rows.
+@pytest.mark.parametrize("R,block,batch", [(96, 32, 64), (4100, 16, 132)])
+def test_results_that_are_not_finite_stay_in_their_rows(R, block, batch):
+    C = 300
+    A = csb_inputs.small_matrix(5, R, C, block, 32, rate=6.0).A
+    rows = [int(r) for r in np.flatnonzero(np.count_nonzero(A, axis=1) > 3)[[0, 7, -1]]]
+    A[rows[0], np.flatnonzero(A[rows[0]])[1]] = np.inf
+    A[rows[1], np.flatnonzero(A[rows[1]])[1]] = np.nan
+    A[rows[2], A[rows[2]] != 0] = 3e38                      # (four times that and more)
+    X = np.abs(csb_inputs.make_vectors(batch, C, batch).reshape(C, batch)) + 1.0
+    got, Ar, Xr = product(A, block, 32, csb.VAL_BF16, X)
+    assert np.all(got[[rows[0], rows[2]]] == np.inf) and np.all(np.isnan(got[rows[1]]))
+    Ar[rows], got[rows] = 0.0, 0.0
+    assert np.all(np.abs(got - oracle.matmat(Ar, Xr)) <= bound_of(Ar, Xr))
