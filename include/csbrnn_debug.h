@@ -50,15 +50,15 @@ int csb_debug_spmm_columns(int64_t row_tiles, int32_t rows_per_tile, int32_t bat
 int64_t csb_debug_quad_passes(const csb_matrix *m, int32_t rows_per_tile);
 
 /*
- * What the batched products of `m` read: 0 (the default): 16-bit values times 16-bit right-hand sides the section of four-row
- * steps, in panels of eight columns, the others what an estimate of the launch's time favours; 1: the tile-based
- * sections; 2: the section of four-row steps, in such steps, wherever it can be read.
+ * What the batched products of `m` read: 0 (the default): what an estimate of the launch's time favours; 1: the tile-based
+ * sections; 2: the section of four-row steps wherever it can be read.  16-bit values times 16-bit right-hand sides read that
+ * section, in panels of eight columns, unless the tile-based ones are asked for.
  */
 int csb_debug_spmm_force(csb_matrix *m, int32_t form);
 
 /*
- * The form that csb_spmm (bits16 = 0) takes for `batch` contiguous right-hand sides, or (bits16 = 1) the better one of these for
- * csb_spmm_bfloat / csb_spmm_half, which take panels wherever there is the section:
+ * The form that csb_spmm (bits16 = 0) or csb_spmm_bfloat / csb_spmm_half (bits16 = 1: csb_debug_spmm_panel's answer) takes for
+ * `batch` contiguous right-hand sides:
  * form[0] = rows of a tile of the section of four-row steps (0: the tile-based sections), form[1] = right-hand sides and
  * form[2] = wavefronts of a workgroup.  Host only.
  */

@@ -275,7 +275,7 @@ static_assert(sizeof(QuadRec) * kQuadLists * kQuadRows * kMaxStageCols <= 0x7fff
 
 // What the passes of a section add up to, for the estimate of a launch's time.
 struct QuadWork {
-    double passes = 0, quads = 0, steps = 0, rows = 0;   // quads: four rows of a pass; steps: those times its columns
+    double passes = 0, steps = 0, rows = 0;              // steps: four rows of a pass times its columns
     double uneven = 1;                                   // work of the longest list, against their mean
 };
 

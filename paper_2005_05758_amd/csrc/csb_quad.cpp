@@ -138,7 +138,7 @@ static void build_section(csb_matrix *m, uint32_t tile_rows, QuadPlan *out) {
             const size_t n = pass_value_bytes(p.nrows, p.ncols, bits16);
             best->work += pass_cost(p);
             const uint32_t quads = (p.nrows + 3u) / 4u;
-            qp.work.quads += quads; qp.work.steps += quads * p.ncols; qp.work.rows += p.nrows;
+            qp.work.steps += quads * p.ncols; qp.work.rows += p.nrows;
             best->bytes += (uint32_t)n;
             longest = std::max(longest, ++best->passes);
             bytes += n;

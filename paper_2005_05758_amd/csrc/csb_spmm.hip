@@ -829,18 +829,16 @@ struct SpmmShape {
 // many row tiles.  Constants as in csb_spmm_quad.hip (us per block record and 8 of its columns, `full` where it keeps
 // them all and they are neighbours, `uneven` what the longest share of 16 has more than
 // their mean; general forms: per 16 rows of a block), from the same measurements.  A launch takes these sections where they save 5 % by the estimates; blocks
-// of more than 32 rows were never faster here.  us here / in four-row steps: 4096 x 4096 in 32-row blocks, float32 x 128 unpruned
-// 45.0 / 63.7, at 2x 38.6 / 43.8, 4x 30.6 / 28.0; bfloat16 x 512 52.5 / 76.4, 54.9 / 55.6, 44.8 / 37.6; 2048 x 2048 in 16-row
-// blocks, float32 x 16 at 2x 12.1 / 14.2, 4x 11.0 / 9.9; 4100 x 2048 in 24-row blocks x 4 at 4x 10.7 / 15.7, x 32 18.8 / 15.7.
+// of more than 32 rows were never faster here.  us here / in four-row steps: 4096 x 4096 in 32-row blocks x 128 unpruned
+// 45.0 / 63.7, at 2x 38.6 / 43.8, 4x 30.6 / 28.0; 2048 x 2048 in 16-row blocks x 16 at 2x 12.1 / 14.2, 4x 11.0 / 9.9; 4100 x 2048
+// in 24-row blocks x 4 at 4x 10.7 / 15.7, x 32 18.8 / 15.7.
 struct TileTurn { double base, block, cols, full, uneven; };
 struct TileCost {
-    int form, rows, nw, room;   // general form: 0, 16 nt columns, wavefronts, k-steps; in registers: 1 (16-bit right-hand sides 2),
-                                // 16-row parts, wavefronts, 64 nq columns; 16-bit general form: 3, 0, wavefronts, 0
+    int form, rows, nw, room;   // general form: 0, 16 nt columns, wavefronts, k-steps; in registers: 1, 16-row parts, wavefronts, 64 nq columns
     double base, out;
     TileTurn one, two;
 };
 static const TileCost kTileCost[] = {
-    {3, 0, 16, 0, 2.71, 2.19, {2.02, 0.893, 0.236, 0.214, 0.927}, {}},
     {0, 1, 16, 4, 3.97, 0.697, {0, 0.589, 0.337, 0.293, 0}, {}},
     {0, 1, 16, 8, 3.04, 5.08, {0.885, 0.512, 0.404, 0.397, 1.22}, {}},
     {0, 1, 8, 4, 4.49, 0, {0, 0.371, 0.0379, 0, 0}, {0, 0.475, 0.475, 0.395, 0}},
@@ -850,10 +848,6 @@ static const TileCost kTileCost[] = {
     {0, 2, 8, 4, 3.87, 5.45, {0, 0.362, 0.188, 0.216, 0}, {0, 0.618, 0.438, 0.376, 0}},
     {0, 2, 8, 8, 3.4, 4.13, {0.326, 0.423, 0.312, 0.299, 0.651}, {0.296, 0.548, 0.595, 0.62, 1.7}},
     {0, 4, 16, 4, 2.64, 2.28, {1.74, 0.73, 0.939, 0.874, 1.32}, {}},
-    {2, 1, 16, 1, 3.23, 0, {1.25, 0.698, 0.0771, 0.0128, 0}, {}},
-    {2, 1, 8, 2, 4.39, 0.0183, {0.798, 0.582, 0.0203, 0, 0.0369}, {2.21, 1.06, 0.0692, 0, 0}},
-    {2, 2, 16, 1, 2.27, 0.694, {2.87, 0.508, 0.518, 0.228, 0.0437}, {}},
-    {2, 2, 8, 2, 2.56, 0.769, {3.45, 0.27, 0.411, 0.263, 0}, {6.76, 0.624, 0.751, 0.45, 0}},
     {1, 1, 16, 1, 2.33, 3.14, {1.85, 0.716, 0.403, 0.367, 0}, {}},
     {1, 1, 8, 2, 2.06, 1.33, {3.02, 0.528, 0.46, 0.412, 0.0323}, {5.43, 1.03, 0.926, 0.813, 0}},
     {1, 2, 16, 1, 2.84, 2.32, {2.61, 0.517, 1.23, 1.02, 0.0987}, {}},
@@ -869,7 +863,7 @@ static double tile_us(int form, int rows, int nw, int room, const csb_matrix *co
         if (pl.hdr.br > 32) f = nullptr;
         tiles += (double)pl.hdr.n_nz_tiles + pl.hdr.n_zero_tiles;
         vbs += pl.hdr.n_vbs;
-        blocks += form % 3 == 0 && pl.hdr.br > 16 ? pl.vb_slices : pl.hdr.n_vbs;      // (the general forms take 16 rows at a time)
+        blocks += form == 0 && pl.hdr.br > 16 ? pl.vb_slices : pl.hdr.n_vbs;      // (the general forms take 16 rows at a time)
         cols += pl.vb_cols - pl.vb_full;
         full_cols += pl.vb_full;
         squares += pl.vb_squares;
@@ -1014,7 +1008,7 @@ int spmm_strided(const csb_matrix *mat, const float *p0, uint32_t n0, int64_t sj
     bool two;
     hipError_t e;
     const bool quads = quad_source(c, &QX, &two);
-    const QuadShape qs = quads ? quad_shape(&mat, 1, batch, false) : QuadShape{};
+    const QuadShape qs = quads ? quad_shape(&mat, 1, batch) : QuadShape{};
     if (quads && (mat->batch_form == kFormQuads || prefers_quads(qs.us, tile_us(sh, &mat, 1, batch)))) {
         QuadMat qm = quad_mat(mat, qs.low);
         void *args[] = {&qm, &QX, &d_Y, &ld, &b};
@@ -1068,7 +1062,7 @@ int spmm_strided_multi(const SpmmCall *calls, int n, int32_t batch, void *stream
             two = t;
             forced = forced || mats[i]->batch_form == kFormQuads;
         }
-        const QuadShape qs = quads ? quad_shape(mats, n, batch, false) : QuadShape{};
+        const QuadShape qs = quads ? quad_shape(mats, n, batch) : QuadShape{};
         if (quads && !forced) {
             double us = 0;
             if (same) us = tile_us(sh[0], mats, n, batch);
@@ -1118,7 +1112,6 @@ struct Spmm16Shape {
     int nw, nq, nwr;         // wavefronts of the general form; 64-column groups and wavefronts of the other
     size_t lds;
     unsigned tiles, batch_tiles;
-    double us;
 };
 static bool spmm16_fits(const DevHeader &h) { return (size_t)h.seg_meta + 8 * (size_t)h.br * 64 * sizeof(float) <= (size_t)kLdsBudget; }
 static Spmm16Shape spmm16_shape(const csb_matrix *m, int32_t batch) {
@@ -1133,7 +1126,6 @@ static Spmm16Shape spmm16_shape(const csb_matrix *m, int32_t batch) {
     s.reg = (h.br == 16 || h.br == 32) && h.n_vals * 4 < 0x7fffff00ull && lds_reg <= (size_t)160 * 1024;
     s.lds = s.reg ? lds_reg : (size_t)h.seg_meta + (size_t)s.nw * acc_per_wave;
     s.batch_tiles = (unsigned)(s.reg ? (batch + 64 * s.nq - 1) / (64 * s.nq) : (batch + 63) / 64);
-    s.us = s.reg ? tile_us(2, (int)h.br / 16, s.nwr, s.nq, &m, 1, batch, s.batch_tiles) : tile_us(3, 0, s.nw, 0, &m, 1, batch, s.batch_tiles);
     return s;
 }
 
@@ -1160,8 +1152,7 @@ static int spmm_16bit(const char *who, int fmt, const csb_matrix *m, const uint1
         set_error(w + ": the block rows are too tall for the accumulator tiles");
         return CSB_EUNSUPPORTED;
     }
-    const bool quads = quad16_source(m, ldx);
-    if (quads && m->batch_form == kFormAuto) {
+    if (quad16_source(m, ldx)) {
         int32_t n = 0;
         for (int32_t n0 = 0; n0 < batch; n0 += n) {
             const PanelShape ps = panel_shape(m, batch - n0);
@@ -1180,20 +1171,6 @@ static int spmm_16bit(const char *who, int fmt, const csb_matrix *m, const uint1
         return CSB_OK;
     }
     const Spmm16Shape sh = spmm16_shape(m, batch);
-    const QuadShape qs = quads ? quad_shape(&m, 1, batch, true) : QuadShape{};
-    if (quads && (m->batch_form == kFormQuads || prefers_quads(qs.us, sh.us))) {
-        QuadMat qm = quad_mat(m, qs.low);
-        XSrc X{(const float *)d_X, (uint32_t)h.cols, (uint32_t)ldx, (const float *)d_X, (uint32_t)ldx};
-        uint32_t b = (uint32_t)batch;
-        int64_t ldy_ = ldy;
-        void *args[] = {&qm, &X, &d_Y, &ldy_, &b};
-        const void *kern = quad16_kernel(qs, fmt == CSB_VAL_F16);
-        hipError_t e = ensure_dynamic_lds(kern, qs.lds);
-        if (e == hipSuccess)
-            e = hipLaunchKernel(kern, dim3(qs.tiles, qs.batch_tiles), dim3(qs.nw * 64), args, qs.lds, (hipStream_t)stream);
-        if (e != hipSuccess) { set_error(w + ": " + hipGetErrorString(e)); return CSB_EDEVICE; }
-        return CSB_OK;
-    }
     DevMat dm = dev_mat(m);
     uint32_t b = (uint32_t)batch, ld = (uint32_t)ldx;
     int64_t ldy_ = ldy;
@@ -1255,24 +1232,20 @@ extern "C" int csb_debug_spmm_form(const csb_matrix *m, int32_t batch, int32_t b
     using namespace csb;
     if (!m || !form || batch <= 0) { set_error("csb_debug_spmm_form: NULL pointer or batch <= 0"); return CSB_EINVAL; }
     if (!m->plan.valid) { set_error("csb_debug_spmm_form: matrix not planned"); return CSB_ESTATE; }
+    if (bits16) return csb_debug_spmm_panel(m, batch, form);
     const uint32_t cols = (uint32_t)m->plan.hdr.cols;
     SpmmCall c{m, nullptr, cols, batch, nullptr, batch, nullptr, batch};
     XSrc X;
-    bool two, quads = bits16 ? quad16_source(m, batch) : quad_source(c, &X, &two);
+    bool two, quads = quad_source(c, &X, &two);
     if (quads && m->batch_form != kFormQuads) {
-        double us;
-        if (bits16) us = spmm16_shape(m, batch).us;
-        else {
-            SpmmShape sh;
-            const int rc = spmm_shape(c, batch, 1, long_tiles(&c, 1), &sh, &X);
-            if (rc != CSB_OK) return rc;
-            us = tile_us(sh, &m, 1, batch);
-        }
-        quads = prefers_quads(quad_shape(&m, 1, batch, bits16 != 0).us, us);
+        SpmmShape sh;
+        const int rc = spmm_shape(c, batch, 1, long_tiles(&c, 1), &sh, &X);
+        if (rc != CSB_OK) return rc;
+        quads = prefers_quads(quad_shape(&m, 1, batch).us, tile_us(sh, &m, 1, batch));
     }
     form[0] = form[1] = form[2] = 0;
     if (quads) {
-        const QuadShape qs = quad_shape(&m, 1, batch, bits16 != 0);
+        const QuadShape qs = quad_shape(&m, 1, batch);
         form[0] = (int32_t)(qs.low ? m->plan.quad_low : m->plan.quad).tile_rows; form[1] = qs.columns; form[2] = qs.nw;
     }
     return CSB_OK;
@@ -1283,7 +1256,7 @@ extern "C" int csb_debug_spmm_panel(const csb_matrix *m, int32_t batch, int32_t 
     if (!m || !form || batch <= 0) { set_error("csb_debug_spmm_panel: NULL pointer or batch <= 0"); return CSB_EINVAL; }
     if (!m->plan.valid) { set_error("csb_debug_spmm_panel: matrix not planned"); return CSB_ESTATE; }
     form[0] = form[1] = form[2] = 0;
-    if (!quad16_source(m, batch) || m->batch_form != kFormAuto) return CSB_OK;
+    if (!quad16_source(m, batch)) return CSB_OK;
     const PanelShape ps = panel_shape(m, batch);
     form[0] = ps.rows; form[1] = ps.columns; form[2] = 4 * ps.share;
     return CSB_OK;

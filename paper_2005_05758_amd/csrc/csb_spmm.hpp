@@ -73,9 +73,8 @@ bool quad_source(const SpmmCall &c, XSrc *X, bool *two);
 // The same for 16-bit values times 16-bit right-hand sides (one source, `ldx` elements from one column to the next).
 bool quad16_source(const csb_matrix *mat, int64_t ldx);
 // The launch shape of n products that share a launch.
-QuadShape quad_shape(const csb_matrix *const *mats, int n, int32_t batch, bool bits16);
+QuadShape quad_shape(const csb_matrix *const *mats, int n, int32_t batch);
 const void *quad_kernel(const QuadShape &sh, bool two, bool multi);
-const void *quad16_kernel(const QuadShape &sh, bool half);
 // Such products in panels: rows of a tile, right-hand sides of a workgroup, wavefronts that share a list of passes.
 struct PanelShape {
     int rows, columns, share;

@@ -201,8 +201,8 @@ __device__ __forceinline__ void quad_passes(const QuadMat &m, const XSrc &X, con
 }
 
 // ---- 16-bit values times 16-bit right-hand sides (v_mfma_f32_4x4x4_16b) -----------------------------------------
-// (Calls take panels, further down; these steps compute the tiles that an input which is not finite reaches, and stand
-// beside the panels for measurements.)  An instruction takes four columns.  With NT = 2 a lane holds two neighbouring right-hand sides of an input row in one
+// (Products run in panels, further down; these steps compute the tiles that an input which is not finite reaches.)
+// An instruction takes four columns.  With NT = 2 a lane holds two neighbouring right-hand sides of an input row in one
 // register; tile t holds the right-hand sides 2 n + t, its operand the halves t of four rows.
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
@@ -379,13 +379,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
     const uint32_t j = blockIdx.z;
     if (blockIdx.x >= J.m[j].n_tiles) return;            // the grid is as wide as the widest product
     spmm_quad_body<NT, G, TWO, NW>(J.m[j], J.X[j], J.Y[j], J.ldy[j], batch, blockIdx.x, blockIdx.y);
-}
-
-// 16-bit values times 16-bit right-hand sides.
-template <int NT, int NW, int VF>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void spmm_quad16_kernel(const QuadMat m, const XSrc X, float *__restrict__ Y,
-                                                                                                const int64_t ldy, const uint32_t batch) {
-    spmm_quad_body<NT, 1, false, NW, VF>(m, X, Y, ldy, batch, blockIdx.x, blockIdx.y);
 }
 
 // ---- 16-bit operands in panels -------------------------------------------------------------------------------------
@@ -595,31 +588,24 @@ QuadMat quad_mat(const csb_matrix *m, bool low) {
 // one workgroup; of 8, two, which overlap one's merge with the other's products but leave the last turn half empty (`one`: a
 // turn of up to 256 of those, `two`: of up to 512).  A turn takes the merge of the wavefronts' tiles and what the passes of a
 // list take.  Lists are as long as the matrix makes them, so that no line between the forms lies at one size: the constants
-// (us per pass, step and row of a list; 16-bit values: `step` per four rows) are fitted to 400 matrices of 256 x 128 to
+// (us per pass, step and row of a list) are fitted to 400 matrices of 256 x 128 to
 // 40000 x 8192 in blocks of 4 to 128, pruned 1 to 25 times by three laws, at 2 to 512 right-hand sides in every form of
 // both sections: half of the estimates are within 3 % and nine of ten within 10; on matrices that were not fitted the form
 // taken is 0.5 % off the best one on average and 3.5 at the 95th percentile.  (With one length of a turn for all
 // matrices, that of 8192 x 8192 at 12x, and never the tile-based sections: 2.9 and 19.)
-// us on 8192 x 8192 at 12x, 256 tiles, 512 right-hand sides: float32 128 columns by 16 wavefronts 128, by 8 115; 16 bits 82 and 67;
-// x 64: 16 bits by 16 wavefronts 19.1, by 8 28.0.  32-row / 16-row tiles: 2048 x 2048 x 64 in 32-row blocks 7.4 / 6.0, 4096 x
-// 2048 x 128 in 64-row blocks 6.3 / 6.8.
+// us on 8192 x 8192 at 12x, 256 tiles, 512 right-hand sides: 128 columns by 16 wavefronts 128, by 8 115.  32-row / 16-row tiles: 2048 x
+// 2048 x 64 in 32-row blocks 7.4 / 6.0, 4096 x 2048 x 128 in 64-row blocks 6.3 / 6.8.
 struct QuadTurn { double merge, pass, step, row; };
 struct QuadCost {
     int columns, nw;
     double base, out;                                    // out: per million output words
     QuadTurn one, two;
 };
-static const QuadCost kQuadCost32[] = {
+static const QuadCost kQuadCost[] = {
     {32, 16, 2.23, 2.91, {1.34, 0.333, 0.00412, 0.026}, {}},
     {64, 16, 2.24, 2.11, {1.16, 0.351, 0.00845, 0.0321}, {}},
     {128, 16, 2.1, 1.3, {2.76, 0.44, 0.014, 0.0428}, {}},
     {128, 8, 2.73, 0.95, {1.63, 0.512, 0.0186, 0.0363}, {1.57, 0.84, 0.0287, 0.0691}},
-};
-static const QuadCost kQuadCost16[] = {
-    {64, 16, 2.42, 1.62, {1.37, 0.342, 0.0649, 0}, {}},
-    {64, 8, 3.08, 1.18, {0.552, 0.376, 0.097, 0}, {0.861, 0.663, 0.114, 0}},
-    {128, 16, 2.41, 1.3, {3.23, 0.296, 0.0965, 0}, {}},
-    {128, 8, 2.8, 0.805, {2.08, 0.356, 0.127, 0}, {2.34, 0.606, 0.17, 0}},
 };
 static double quad_us(const QuadCost &f, const QuadWork &w, double tiles, double mean_rows, double out_words, int32_t batch) {
     const double wgs = tiles * ((batch + f.columns - 1) / f.columns), slots = f.nw == 8 ? 512 : 256;
@@ -633,7 +619,7 @@ static double quad_us(const QuadCost &f, const QuadWork &w, double tiles, double
     return f.base + f.out * out_words * 1e-6 + one * turn(f.one) + two * turn(f.two);
 }
 
-QuadShape quad_shape(const csb_matrix *const *mats, int n, int32_t batch, bool bits16) {
+QuadShape quad_shape(const csb_matrix *const *mats, int n, int32_t batch) {
     QuadShape best{};
     best.us = 1e300;
     bool any_low = false;
@@ -645,13 +631,12 @@ QuadShape quad_shape(const csb_matrix *const *mats, int n, int32_t batch, bool b
         for (int i = 0; i < n; ++i) {
             const Plan &pl = mats[i]->plan;
             const QuadPlan &qp = low && pl.quad_low.valid ? pl.quad_low : pl.quad;
-            sum.passes += qp.work.passes; sum.rows += qp.work.rows;
-            sum.steps += bits16 ? qp.work.quads : qp.work.steps;
+            sum.passes += qp.work.passes; sum.rows += qp.work.rows; sum.steps += qp.work.steps;
             sum.uneven = std::max(sum.uneven, qp.work.uneven);
             tiles += qp.n_tiles; rows += (double)qp.n_tiles * qp.tile_rows; out_rows += qp.rows;
             most_tiles = std::max(most_tiles, (unsigned)qp.n_tiles);
         }
-        for (const QuadCost &f : bits16 ? kQuadCost16 : kQuadCost32) {
+        for (const QuadCost &f : kQuadCost) {
             const double us = quad_us(f, sum, tiles, rows / tiles, out_rows * batch, batch);
             if (us < best.us)
                 best = QuadShape{f.columns, f.nw, low != 0, (size_t)f.nw * kQuadRows * 64 * sizeof(float), most_tiles,
@@ -742,13 +727,6 @@ const void *panel16_kernel(const PanelShape &ps, bool half) {
     return ps.columns == 128 ? CSB_P16S(2, 8) : CSB_P16S(2, 4);
 #undef CSB_P16S
 #undef CSB_P16
-}
-
-const void *quad16_kernel(const QuadShape &sh, bool half) {
-#define CSB_Q16(NT, NW) (half ? (const void *)spmm_quad16_kernel<NT, NW, CSB_VAL_F16> : (const void *)spmm_quad16_kernel<NT, NW, CSB_VAL_BF16>)
-    if (sh.columns == 64) return sh.nw == 8 ? CSB_Q16(1, 8) : CSB_Q16(1, 16);
-    return sh.nw == 8 ? CSB_Q16(2, 8) : CSB_Q16(2, 16);
-#undef CSB_Q16
 }
 
 }  // namespace csb

@@ -1,7 +1,7 @@
 """Parity of the batched products at the edges of their batch tiles, against the oracle's float64 product, with the
 float32 dot-product bound of tests/test_gpu_spmm.py.  Every test runs in both forms, whichever the estimate favours at its
 size: from the tile-based sections (the general form, and the one that keeps its results in registers, at up to 128
-right-hand sides per workgroup) and from the section of four-row steps."""
+right-hand sides per workgroup) and from the section of four-row steps (16-bit operands: in panels)."""
 import numpy as np
 import pytest
 
@@ -85,7 +85,7 @@ def test_spmm_any_batch(R, C, br, bc, batch):
 @pytest.mark.parametrize("fmt,name", [(None, "f32")] + FORMATS)
 @pytest.mark.parametrize("value", [np.inf, np.nan])
 def test_spmm_infinite_input(value, fmt, name, R, br, batch, form):
-    """The rows that hold an entry of its column are not finite.  In the general float32 form and in four-row steps no
+    """The rows that hold an entry of its column are not finite.  In the general float32 form, in four-row steps and in panels no
     others are touched (and an infinity stays one, with its sign); in the others no rows outside of the row tiles that hold
     the column.  Other right-hand sides are what they are."""
     C = 70
