@@ -15,8 +15,9 @@ torch = pytest.importorskip("torch")
 TYPES = {csb.VAL_F16: torch.float16, csb.VAL_BF16: torch.bfloat16}
 
 
-def product(A, br, bc, fmt, X, ldx=None, form=None):
-    """(result, rounded A, rounded X); `form`: what the call has to take (rows of a tile, right-hand sides, wavefronts)."""
+def product(A, br, bc, fmt, X, ldx=None, form=None, first=0):
+    """(result, rounded A, rounded X); `form`: what the call has to take (rows of a tile, right-hand sides, wavefronts); `first`: X's place in
+    its rows."""
     M = CsbMatrix(A, br, bc)
     M.set_value_format(fmt)
     M.plan()
@@ -26,13 +27,13 @@ def product(A, br, bc, fmt, X, ldx=None, form=None):
         got = (ctypes.c_int32 * 3)()
         assert csb.lib().csb_debug_spmm_panel(M._h, batch, got) == 0 and tuple(got) == form
     wide = torch.full((C, ldx or batch), float("nan"), device="cuda").to(TYPES[fmt])      # what lies beside the batch is never used
-    wide[:, :batch] = torch.from_numpy(X).cuda().to(TYPES[fmt])
+    wide[:, first:first + batch] = torch.from_numpy(X).cuda().to(TYPES[fmt])
     out = torch.full((A.shape[0], batch + 3), 7.0, device="cuda")
     call = M.spmm_half if fmt == csb.VAL_F16 else M.spmm_bfloat
-    call(wide[:, :batch], out[:, 1:1 + batch])
+    call(wide[:, first:first + batch], out[:, 1:1 + batch])
     torch.cuda.synchronize()
     assert torch.all(out[:, 0] == 7.0) and torch.all(out[:, batch + 1:] == 7.0)
-    return out[:, 1:1 + batch].cpu().numpy().astype(np.float64), torch.from_numpy(A).to(TYPES[fmt]).float().numpy(), wide[:, :batch].float().cpu().numpy()
+    return out[:, 1:1 + batch].cpu().numpy().astype(np.float64), torch.from_numpy(A).to(TYPES[fmt]).float().numpy(), wide[:, first:first + batch].float().cpu().numpy()
 
 
 def bound_of(A, X):
@@ -50,6 +51,18 @@ def bound_of(A, X):
 def test_every_form(R, C, block, rate, batch, form, fmt):
     A = csb_inputs.small_matrix(3, R, C, block, block, rate=rate).A
     got, Ar, Xr = product(A, block, block, fmt, csb_inputs.make_vectors(batch, C, batch).reshape(C, batch), batch + 12, form)
+    assert np.all(np.abs(got - oracle.matmat(Ar, Xr)) <= bound_of(Ar, Xr))
+
+
+# X at 8 bytes from a multiple of 16, every row of it or every second one, in the forms of 128 right-hand sides (loads of 16 bytes) and of 64.
+@pytest.mark.parametrize("R,C,block,rate,batch,form", [(97, 600, 33, 2.0, 60, (16, 64, 8)), (4097, 2500, 16, 2.0, 124, (16, 128, 8)),
+                                                       (4097, 1500, 16, 4.0, 128, (16, 128, 4)), (4500, 2600, 32, 1.5, 68, (32, 128, 8)),
+                                                       (5000, 900, 32, 4.0, 260, (32, 128, 4))])
+@pytest.mark.parametrize("beside", [8, 12])
+def test_x_aligned_to_8_bytes(R, C, block, rate, batch, form, beside):
+    A = csb_inputs.small_matrix(3, R, C, block, block, rate=rate).A
+    ldx = (batch + 7) // 8 * 8 + beside
+    got, Ar, Xr = product(A, block, block, csb.VAL_BF16, csb_inputs.make_vectors(batch, C, batch).reshape(C, batch), ldx, form, first=4)
     assert np.all(np.abs(got - oracle.matmat(Ar, Xr)) <= bound_of(Ar, Xr))
 
 
