@@ -666,8 +666,8 @@ def val16_leg(torch, np, csb_inputs, CsbMatrix, stream_gbps, formats=("f16", "bf
             entry["spmm_bfloat"] = dict(bf, roofline={
                 "kernel": "csb::spmm_panel16_kernel<2, 8, 2, 2>", "bound": "mfma", "achieved": tf, "peak": 2500.0, "unit": "TFLOP/s",
                 "frac": round(tf / 2500.0, 5), "traffic": None,
-                "note": "dense bf16 MFMA peak as the nominal roof; 4 x 4 x 4 MFMA steps on kernels of about 9 x 9: the launch is "
-                        "bound by the pipe that those and the vector instructions of a pass share, not by the dense rate"})
+                "note": "dense bf16 MFMA peak as the nominal roof; 16 x 16 x 32 MFMA on panels of four passes of up to 8 columns: the "
+                        "launch is bound by the way of the gathered right-hand sides through the L1, not by the dense rate"})
         res[f"spmv_cfg5_{name}"] = entry
         del copies, M
     return res

@@ -235,11 +235,12 @@ struct StreamPlan {
 
 // ---- quad section (batched products) -------------------------------------------------------
 // The batched kernels multiply four kernel rows by one input row of 16 to 64 right-hand sides per
-// instruction (csb_spmm_quad.hip).  Output rows are cut into tiles of `tile_rows` (16 or 32); the part of a CSB
+// instruction, or, 16-bit values by 16-bit right-hand sides, the rows of a tile by four passes (csb_spmm_quad.hip).  Output rows are cut into tiles of `tile_rows` (16 or 32); the part of a CSB
 // block that lands in a tile is cut into PASSES of at most 8 columns and all of its rows there.  A
 // pass is one record and one run of values, and the passes of a tile are dealt to kQuadLists
 // lists of equal work, in column order: a wavefront walks one list (or several in a row) and finds everything
-// it needs in the record, which comes in over the scalar path.
+// it needs in the record, which comes in over the scalar path; with 16-bit operands it walks four lists side by side, 16 lanes each,
+// and the record comes in as a word per lane.
 //   records, list after list.  Lists of about the same length start `list_stride` records apart, and a launch finds its
 //           first record without a table: one dependent trip to memory less before it has any work.  The first record
 //           of a list counts its passes.  All of them, gaps included, may take more than 2 GiB, a tile's never do.

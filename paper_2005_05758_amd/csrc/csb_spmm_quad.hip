@@ -391,10 +391,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
 // round by DPP.
 // What bounds it: the loads' way through the L1: with the products left out a launch is as long, from 16 rows of X that always hit it is no
 // shorter (measured).  A load of 4 bytes per lane takes it about 4 clocks, of 8 bytes 12, of 16 bytes 13: lanes take 16 where there are
-// 128 right-hand sides, else 4 twice; with 8 bytes 8192 x 8192 at 12x, bfloat16, takes 66 us instead of 44 at 512 right-hand sides, 12.8
-// instead of 10.6 at 64.  Four-row steps / panels, us: x 512 69 / 44, x 256 37 / 24, x 128 23 / 13.9, x 64 18.9 / 10.6, x 8 17.7 / 9.7; 4096 x
-// 4096 in 16-row blocks x 256 22.8 / 13.6; 1024 x 665 at 8x x 32 4.0 / 3.35.  Error against 64 bits, of the norm, of these: 0.749e-7 (0.750e-7
-// before), x 128 0.748e-7 (0.846e-7); 0.661e-7 (0.661e-7); binary16 0.92e-7 (0.98e-7).
+// 128 right-hand sides, else 4 twice; with 8 bytes 8192 x 8192 at 12x, bfloat16, took 66 us instead of 44 at 512 right-hand sides, 12.8
+// instead of 10.6 at 64.  Four-row steps / panels, us, launches replayed back to back: x 512 72.7 / 44.9 (a call among others 63.8 / 42), x 128
+// 21.9 / 14.4, x 64 17.5 / 10.5, x 8 17.5 / 9.9; 4096 x 4096 in 16-row blocks x 256 22.6 / 15.5; 1024 x 665 at 8x x 32 4.4 / 3.8.  Error
+// against 64 bits, of the norm, four-row steps / panels: x 512 0.749e-7 / 0.693e-7, x 128 0.845e-7 / 0.692e-7, binary16 x 512 0.979e-7 /
+// 0.876e-7; 4096 x 4096 in 16-row blocks at 12x x 256 0.661e-7 / 0.598e-7.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
@@ -682,12 +683,13 @@ const void *quad_kernel(const QuadShape &sh, bool two, bool multi) {
 // The shape of a launch of panels, by an estimate of its time: a CU works off its workgroups at a rate that depends on little but
 // the panels (`panel`: us for the passes that four wavefronts take at once), however many of them it holds.  Fitted to 1573
 // launches in every form (260 to 20000 rows, 128 to 8192 columns, blocks of 4 to 64, pruned 1 to 25 times by three laws, 4 to 512
-// right-hand sides): half of the estimates are within 4 %; the form taken is 1.0 % off the best one on average and 5 at the 95th
-// percentile (the worst: 8342 x 7541 unpruned x 72, 64.6 us where 128 columns take 46.1).  Against the better one of four-row steps and
-// tile-based sections panels took 0.73 of the time on average over 6010 such launches, and the worst 1.06 of it (9252 x 2045 in
-// 16-row blocks at 2x, x 12), before the forms of 64 columns loaded 4 bytes at a time.
+// right-hand sides): half of the estimates are within 4 %.  Over 2086 others the form taken is 0.9 % off the best one on average and 5 at
+// the 95th percentile; it is furthest off beyond 256 tiles and between 64 and 128 right-hand sides, where 64 columns take twice the workgroups
+// (8342 x 7541 unpruned x 72 64.5 us, 128 columns 48.3; 10856 x 6632 unpruned x 84 63.2 and 46.4).  Against the older forms, four-row steps and
+// tile-based sections as the estimate chose between them, panels took 0.73 of the time on average over 4215 such launches, and the worst
+// 1.07 of it (9880 x 3359 unpruned x 100: 50.9 / 54.6 us); a dozen others, of at most 330 columns, lost up to 0.1 us of 3.3 to 4.1.
 // Four wavefronts where a list has at most 16 passes; longer sums in one accumulator are further off 64 bits than the halves of two: error against 64 bits, of
-// the norm, 8192 x 8192 in 16-row blocks at 8x, by 4 and by 8 wavefronts 0.96e-7 and 0.83e-7 (four-row steps 0.83e-7).
+// the norm, 8192 x 8192 in 16-row blocks at 8x, by 4 and by 8 wavefronts 0.96e-7 and 0.78e-7 (four-row steps 0.83e-7).
 struct PanelCost { int rows, columns, share; double base, out, merge, panel; };      // out: per million output words (four forms of 16 rows, four of 32)
 static const PanelCost kPanelCost[] = {
     {16, 64, 1, 3.26, 0.748, 0, 0.239},     {16, 64, 2, 3.13, 2.34, 0, 0.195},     {16, 128, 1, 3.69, 1.40, 0.069, 0.289},
